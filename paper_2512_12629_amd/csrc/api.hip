@@ -34,6 +34,8 @@ size_t table_layout(cube2_ctx *c) {
     }
     c->pp_soff = off;
     off = align_up(off + (size_t)kSRows * 4 * sizeof(float), 256);
+    c->pp_aoff = off;
+    off = align_up(off + (size_t)kSRowsAdj * 4 * sizeof(float), 256);
     if (c->fp64) {
         for (int l = 0; l < c->n_levels; ++l) {
             Level &L = c->lv[l];
@@ -247,6 +249,8 @@ int cube2_init_tables(cube2_ctx *ctx, void *tables, size_t table_bytes, cube2_st
     CUBE2_CHECK_HIP(hipMemsetAsync(ctx->tables, 0, 256, s));
     CUBE2_CHECK_HIP(hipMemcpyAsync(ctx->tables + ctx->pp_soff, ctx->pp_srows.data(),
                                    ctx->pp_srows.size() * sizeof(float), hipMemcpyHostToDevice, s));
+    CUBE2_CHECK_HIP(hipMemcpyAsync(ctx->tables + ctx->pp_aoff, ctx->pp_arows.data(),
+                                   ctx->pp_arows.size() * sizeof(float), hipMemcpyHostToDevice, s));
     if (ctx->fp64)
         CUBE2_CHECK_HIP(hipMemcpyAsync(ctx->tables + ctx->pp64_off, ctx->pp_rows64.data(),
                                        ctx->pp_rows64.size() * sizeof(double),

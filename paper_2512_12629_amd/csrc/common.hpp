@@ -44,23 +44,29 @@ namespace cube2 {
 // Pair-law table of the PP kernels (built on the host, see pp.hip).
 constexpr int kPairKMax = 128;     // grid intervals of [0, b_f)
 constexpr int kPairRow = 12;       // floats per interval: 9 coefficients, y map, pad
-// FP32 forward pair law, indexed by s = r^2: one row of 4 cubic coefficients
-// per 1/16 of an octave, for s in [2^-31, 2^7).  The row of s is its float
-// bit pattern shifted right by 19 (exponent and top 4 mantissa bits) minus
-// kSRow0.
-constexpr int kSMantBits = 4;
-constexpr int kSRow0 = (127 - 31) << kSMantBits;
-constexpr int kSRows = (7 + 31) << kSMantBits;  // 608
+// FP32 pair law tables of the PP kernels by s = r^2 (pp.hip): one row of four
+// floats per 2^-kSMant of an octave of s.  A row's place is its float exponent
+// and top mantissa bits modulo kSOctaves octaves.
+constexpr int kSMant = 6;          // forward: 64 rows per octave
+constexpr int kSMantAdj = 7;       // adjoint: 128 rows per octave
+constexpr int kSOctaves = 32;
+constexpr int kSRows = 20 << kSMant;         // rows held (20 octaves)
+constexpr int kSRowsAdj = 20 << kSMantAdj;
 }  // namespace cube2
 
 struct cube2_ctx {
     cube2_config cfg;
     int pp_K = 0;                      // intervals of the pair-law grid
     float pp_kinv = 0.f;               // K / b_f
-    float pp_negc = 0.f;               // -1/b_f^2, rounded away from zero (FP32 pair law)
+    // the FP32 pair law's units (pp.hip): position scale and scale of g (powers
+    // of two), and whether s is clamped to the table
+    float pp_pscale = 1.f, pp_unit = 1.f;
+    bool pp_clamp = false;
+    uint32_t pp_bmax = 0, pp_bmax_adj = 0;   // float bits of s that the clamped form stops at
     int pp_halo = 1;                   // PP neighbour reach in IOS cells: 1 (b_f <= 2), 2 (b_f <= 4)
     std::vector<float> pp_srows;       // kSRows * 4 floats: the FP32 forward pair law by s = r^2
-    size_t pp_soff = 0;                // byte offset of pp_srows in `tables`
+    std::vector<float> pp_arows;       // kSRowsAdj * 4 floats: the same for the adjoint
+    size_t pp_soff = 0, pp_aoff = 0;   // byte offsets of the two in `tables`
     std::vector<double> pp_rows64;     // the same rows in FP64
     size_t pp64_off = 0;               // FP64 rows (CUBE2_FP64_FORM only)
     bool fp64 = false;                 // CUBE2_FP64_FORM

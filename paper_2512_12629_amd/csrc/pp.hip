@@ -15,8 +15,8 @@
 // (2H + 1)^2 contiguous ranges (x-rows of 2H + 1 cells); neighbours in a
 // dense cell are read by all lanes of a wave at the same LDS address (a
 // broadcast).  Per range the pair sum is accumulated in FP32 and then added
-// to the total with Kahan compensation.  Boxes too large for LDS read the
-// same data from HBM.
+// to the total with Kahan compensation.  Boxes too large for LDS pass through
+// it in parts.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -34,14 +34,15 @@ template <int H> struct PPBox {
     static constexpr int SEGS = PB * PB * PB;      // 1000 or 1728
     static constexpr int W = 2 * H + 1;            // neighbour cells per axis
 };
-// Forward: 512 threads, 3840 staged particles (60 KB; 3456 with the wider
-// box): 2 blocks (4 waves per SIMD) per CU.  Adjoint: the cotangent is staged
-// too, so it runs 1024-thread blocks with 4096 staged particles (128 KB):
-// 1 block (4 waves per SIMD).
+// Forward: 512 threads, 16 bytes per staged particle: 2 blocks (4 waves per
+// SIMD) per CU in 160 KB of LDS, of which the pair-law table takes 20 KB each.
+// Adjoint: the cotangent is staged too (24 bytes per particle) and the finer
+// table takes 40 KB, so it runs 1024-thread blocks, 1 block (4 waves per SIMD).
 template <bool ADJ, int H> struct PPGeo {
     static constexpr int BLOCK = ADJ ? 1024 : 512;
-    static constexpr int CAP = ADJ ? 4096 : (H == 1 ? 3840 : 3456);
+    static constexpr int CAP = ADJ ? (H == 1 ? 4800 : 4656) : (H == 1 ? 3376 : 3152);
     static constexpr int SEG_PER_THREAD = (PPBox<H>::SEGS + BLOCK - 1) / BLOCK;
+    static constexpr int ROWS = ADJ ? kSRowsAdj : kSRows;
 };
 
 }  // namespace
@@ -63,37 +64,46 @@ template <bool ADJ, int H> struct PPGeo {
 // s = 1 - r/b_f, Q(t) = 32/35 + 32/7 t + 704/35 t^2 + 64/5 t^3.  The row of
 // r >= b_f is zero.  This exact table, in FP64, serves the plain FP64 form.
 //
-// The FP32 forward kernel evaluates g as a function of s = r^2 instead, which
-// needs neither a square root nor r^-3.  Since g vanishes like (b_f - r)^5 at
-// the cutoff, and sparse particles often have all their neighbours close to
-// it, the table does not hold g itself: with h = g / (b_f^2 - s)^5, smooth and
-// nonzero up to and beyond the cutoff (there the factorised form gives h =
-// Q(1 - r/b_f) / (r^3 (b_f (b_f + r))^5), continued analytically past b_f),
-// it holds H = h b_f^10 w = g / w^4 with w = 1 - s/b_f^2, still smooth (one
-// simple zero at the cutoff, continued linearly past it), and the kernel
-// forms g = H w^4 with w clamped to [0, 1]: exact zero beyond the cutoff.
-// Near the cutoff the fit of H errs like 1/w relative (7e-7 at w = 1/32 on
-// the row s in [3.75, 3.875) for b_f = 2), as the FP32 rounding of s does
-// anyway (b_f^2 - s turns it into 6e-8 / w per power of w); with more powers
-// of w in the table the cubic would have to follow a multiple zero.  s is cut
-// at its float exponent and top 4 mantissa bits (1/16 of an octave, s in
-// [2^-31, 2^7)); on each piece H is the cubic through its values at the 4 Chebyshev nodes (fitted in FP64
-// on the host from eq. (2) evaluated in extended precision).  For exact s the
-// table's g is within 8e-7 of the true g, relative; FP32 rounding of s adds
-// its own part near the cutoff, as rounding of r does in any evaluation.  The
-// row index is the bit pattern of s shifted right, the local variable the
-// remaining 19 mantissa bits read as a float in [0, 1/16).  Every pair
-// separation in the staged box is below 2(H + 1) fine cells per axis (4 or
-// 6), so s < 108 < 2^7 and the row exists; the 2^-31 added to s (below the smallest nonzero
-// separation squared, 2^-30) keeps a coincident pair on row 0, where g is
-// finite and g D = 0.
+// The FP32 kernels evaluate g as a function of s = r^2 instead, which needs
+// neither a square root nor r^-3, through its fifth root: g = unit L(s)^5.
+// Near the cutoff g vanishes like (1 - r/b_f)^5, and sparse particles often
+// have all their neighbours there, so a table of g itself would lose its
+// relative accuracy; L has a simple zero at the cutoff, which a table follows
+// to the last bit, and 0.3 times the curvature of g where g ~ 1/r^3.  L is a
+// quadratic per row of 1/64 octave of s (the adjoint, which also needs dL/ds:
+// 1/128), in y = s/10 - k with k, the row's centre, in the row's fourth
+// word: L = c0 + y (c1 + c2 y).  Among the floats next to the centre, k is
+// the one whose L is nearest to a float, so that c0 adds no error of its own.
+// With y in tenths of s the derivative comes free: dg/ds = unit 5 L^4 dL/ds
+// and 2 dg/ds = unit L^4 (c1 + 2 c2 y).  unit is a power of two that puts L
+// in [0, 1]; in the row that holds the cutoff c0 = 0 and k = b_f^2/10, so that
+// the FMA's clamp to [0, 1] gives exactly 0 at and beyond b_f, and the rows
+// beyond are zero.  Against a cubic of g / (1 - s/b_f^2)^4 on rows of 1/16
+// octave this takes 17 instructions per pair instead of 20 (and 30 instead of
+// 39 in the adjoint), with the same error (FP32 operations against extended
+// precision, b_f = 2, b_pp = 0.2: rms 3.0e-7 against 3.2e-7 for r < 0.9 b_f;
+// the adjoint's derivative term 2.9e-6 of the Jacobian against 7.0e-6).
+//
+// s0 = 2^e0 is added to s, with e0 at least 3 octaves below (b_pp/2)^2: below
+// that g is nearly constant, so the table has no use for finer octaves and a
+// coincident pair has a row (g finite, g D = 0).  Positions are staged in
+// units of 2^-j fine cells, which are exact too, with j such that s0 has
+// float exponent field 128: a row's place in the table is then its bits modulo
+// 32 octaves, with no base to subtract.  Every separation in the staged box is
+// below 2 (H + 1) fine cells per axis, so s < 2^6 (H = 1) or 2^7.  If the
+// octaves from s0 to there exceed the 20 that the table holds (a small b_f or
+// b_pp), s is clamped to the first row beyond the cutoff instead (CLAMP, one
+// more instruction per pair): cutoff and s0 are at most 19 octaves apart,
+// since b_pp / 2 >= b_f / 128.
 
 namespace {
 
-// The pair-law table in LDS, declared at namespace scope so that every
-// access is a 32-bit LDS address, indexed by s = r^2 (the forward and the
-// adjoint kernel both read it).
+// The pair-law tables in LDS, declared at namespace scope so that every
+// access is a 32-bit LDS address.
+// s0 in the scaled units: float exponent field 128
+constexpr float kPairS0 = 2.0f;
 __shared__ float4 pair_srows[kSRows];
+__shared__ float4 pair_arows[kSRowsAdj];
 
 __device__ __forceinline__ void kahan_add(float &s, float &c, float v) {
     const float y = v - c;
@@ -102,62 +112,57 @@ __device__ __forceinline__ void kahan_add(float &s, float &c, float v) {
     s = t;
 }
 
-// g(r) * D accumulated into (fx, fy, fz) from the s-indexed table (LDS).
-// The table holds H = g / w^4, and w = 1 - s/b_f^2 is formed as one FMA with
-// the result clamped to [0, 1] (negc = -1/b_f^2 rounded away from zero, so
-// that w = 0 for every s >= b_f^2).
 __device__ __forceinline__ float unit_clamp(float x) { return __builtin_amdgcn_fmed3f(x, 0.0f, 1.0f); }
 
-__device__ __forceinline__ void pair_accumulate(float dx, float dy, float dz, float negc, float &fx,
-                                                float &fy, float &fz) {
-    const float s = fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, 0x1p-31f)));
-    const uint32_t b = __float_as_uint(s);
-    const float4 c = pair_srows[(b >> (23 - kSMantBits)) - kSRow0];
-    const float z = __uint_as_float((b & ((1u << (23 - kSMantBits)) - 1u)) | 0x3F800000u) - 1.0f;
-    const float h = fmaf(fmaf(fmaf(c.w, z, c.z), z, c.y), z, c.x);
-    const float w = unit_clamp(fmaf(s, negc, 1.0f));
-    const float w2 = w * w;
-    const float g = h * (w2 * w2);
+// Place of the row of s (float bits b) in the forward table.
+__host__ __device__ __forceinline__ uint32_t row_place(uint32_t b, int mant) {
+    return (b >> (23 - mant)) & (uint32_t)((kSOctaves << mant) - 1);
+}
+
+// g(r) D / unit accumulated into (fx, fy, fz).  s0 is staged as the fourth
+// word of the neighbour: with all four words in use the position is one
+// 128-bit LDS read, which takes 4.7 cycles of the CU's LDS for a wave that
+// reads a few addresses (12 for 64 different ones); a 96-bit read takes 8.5
+// (20).
+template <bool CLAMP>
+__device__ __forceinline__ void pair_accumulate(float dx, float dy, float dz, float s0,
+                                                uint32_t bmax, float &fx, float &fy, float &fz) {
+    const float s = fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, s0)));
+    uint32_t b = __float_as_uint(s);
+    if (CLAMP) b = min(b, bmax);
+    const float4 c = pair_srows[row_place(b, kSMant)];
+    const float y = fmaf(s, 0.1f, c.w);
+    const float l = unit_clamp(fmaf(fmaf(c.z, y, c.y), y, c.x));
+    const float l2 = l * l;
+    const float g = (l2 * l2) * l;
     fx = fmaf(g, dx, fx);
     fy = fmaf(g, dy, fy);
     fz = fmaf(g, dz, fz);
 }
 
-// Adjoint of one pair for the cotangents: out += J(D) u with u = abar_j -
-// abar_i and J = d(g D)/dD = g I + 2 g_s D D^T, g_s = dg/ds.  It reads the
-// forward's table: H = g / w^4, w = 1 - s/b_f^2, and, by synthetic
-// division of the same cubic, dH/dz, with z the local variable of the row
-// (s = 2^e (1 + z)), so H_s = (dH/dz) 2^-e; one 16-byte table read per pair
-// (the LDS reads, not the arithmetic, limit this kernel).  With w clamped to
-// [0, 1] as in pair_accumulate: g = H w^4 and 2 g_s = w^3 (2 H_s w + 8 negc
-// H), negc = -1/b_f^2.  Every term enters the accumulators through an FMA.
+// Adjoint of one pair for the cotangents: out += J(D) u / unit with u = abar_j
+// - abar_i and J = d(g D)/dD = g I + 2 g_s D D^T, g_s = dg/ds.  Every term
+// enters the accumulators through an FMA.
+template <bool CLAMP>
 __device__ __forceinline__ void pair_adjoint(float dx, float dy, float dz, float ux, float uy,
-                                             float uz, float negc, float &ox, float &oy,
-                                             float &oz) {
-    const float s = fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, 0x1p-31f)));
-    const uint32_t b = __float_as_uint(s);
-    const float4 c = pair_srows[(b >> (23 - kSMantBits)) - kSRow0];
-    const float z = __uint_as_float((b & ((1u << (23 - kSMantBits)) - 1u)) | 0x3F800000u) - 1.0f;
-    const float inv2e2 = __uint_as_float(0x7F800000u - (b & 0x7F800000u));  // 2^(1-e)
-    float h = fmaf(c.w, z, c.z);
-    float hz = fmaf(c.w, z, h);
-    h = fmaf(h, z, c.y);
-    hz = fmaf(hz, z, h);
-    h = fmaf(h, z, c.x);
-    const float w = unit_clamp(fmaf(s, negc, 1.0f));
-    const float w2 = w * w;
-    const float g = h * (w2 * w2);
-    const float gs2 = (w2 * w) * fmaf(hz * inv2e2, w, (8.0f * negc) * h);  // 2 g_s
-    const float du = fmaf(dz, uz, fmaf(dy, uy, dx * ux)) * gs2;
+                                             float uz, uint32_t bmax, float &ox,
+                                             float &oy, float &oz) {
+    const float s = fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, kPairS0)));
+    uint32_t b = __float_as_uint(s);
+    if (CLAMP) b = min(b, bmax);
+    const float4 c = pair_arows[row_place(b, kSMantAdj)];
+    const float y = fmaf(s, 0.1f, c.w);
+    const float t = fmaf(c.z, y, c.y);
+    const float l = unit_clamp(fmaf(t, y, c.x));
+    const float ls = fmaf(c.z, y, t);                   // 10 dL/ds
+    const float l2 = l * l;
+    const float l4 = l2 * l2;
+    const float g = l4 * l;
+    const float du = fmaf(dz, uz, fmaf(dy, uy, dx * ux)) * (l4 * ls);   // D.u 2 g_s
     ox = fmaf(du, dx, fmaf(g, ux, ox));
     oy = fmaf(du, dy, fmaf(g, uy, oy));
     oz = fmaf(du, dz, fmaf(g, uz, oz));
 }
-
-// Heavy tiles are done in z-chunks: own cells are ordered z-major, so the own
-// cells of z-layers [z0, z1) are a contiguous particle range and the box cells
-// they need are the contiguous box layers [z0, z1 + 2H), a contiguous slice of
-// the staged list.
 
 // The heaviest tiles are split: the first kSplitTiles entries of the
 // heaviest-first order are offered as kSplitParts work items each; a tile
@@ -173,16 +178,24 @@ __device__ __forceinline__ void pair_adjoint(float dx, float dy, float dz, float
 // tile, so its tiles are not few per workgroup, and the split's bookkeeping
 // would take it past 128 VGPRs (one workgroup per CU instead of two).
 constexpr int kSplitParts = 8, kSplitTiles = 128;
-template <int H> constexpr int split_parts() { return H == 1 ? kSplitParts : 1; }
+template <int H> constexpr int split_parts() { return kSplitParts; }
+
+// The pair law's units (see above): ps = 2^j and its product with the 2^-15 of
+// a position unit, the scale of the sums (unit, and for the forward D's
+// 2^-j too) and the float bits that the clamped form stops at.
+struct PPLaw {
+    float ps, ips, unit;
+    uint32_t bmax;
+};
 
 // ADJ = false: acc = G m sum_j g D (forward).  ADJ = true: out = G m sum_j
 // J(D) (abar_j - abar_i) for the cotangent abar (the adjoint), which stages
 // abar_j beside x_j and so holds half as many particles per chunk.
-template <bool ADJ, int H>
-__global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK)) void pp_kernel(const uint16_t *__restrict__ pos,
+template <bool ADJ, int H, bool CLAMP>
+__global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK), 4) void pp_kernel(const uint16_t *__restrict__ pos,
                                                      const uint32_t *__restrict__ cs, int n,
                                                      int nt, const float4 *__restrict__ table,
-                                                     float negc, float gm,
+                                                     PPLaw law, float gm,
                                                      const float *__restrict__ abar,
                                                      float *__restrict__ acc, int accumulate,
                                                      const uint32_t *__restrict__ order,
@@ -194,21 +207,26 @@ __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK)) void pp_kernel(const uint16
     constexpr int kPSegPerThread = PPGeo<ADJ, H>::SEG_PER_THREAD;
     constexpr int kPB = PPBox<H>::PB, kPSegs = PPBox<H>::SEGS, kW = PPBox<H>::W;
     __shared__ uint32_t seg_pre[kPSegs + 1];
-    __shared__ uint32_t seg_src[kPSegs];
-    // staged particles; the adjoint interleaves each position with its
-    // cotangent (xs[2 v], xs[2 v + 1]), so that both reads of a pair share one
-    // address register
-    constexpr int XS = ADJ ? 2 : 1;
-    __shared__ float4 xs[XS * CAP];
+    // An x-row of the box crosses three tiles (H, 8 and H cells), and a tile's
+    // x-consecutive cells are consecutive in the particle order: particle =
+    // staged index + seg_delta of the row's part
+    __shared__ uint32_t seg_delta[kPB * kPB * 3];
+    // staged particles: position and s0, or for the adjoint position and
+    // cotangent (x, y, z, ax; ay, az)
+    __shared__ float4 xs[CAP];
+    __shared__ float2 xa[ADJ ? CAP : 1];
     __shared__ uint32_t cst[kTileCells + 1];     // own cells: particle starts (tile-relative)
     __shared__ uint32_t scan_sh[kPPBlock / 64 + 1];
-    __shared__ int chunk_sh, tile_sh;
+    __shared__ int tile_sh;
     __shared__ uint32_t maxcnt_sh;
 
     const int tid = threadIdx.x;
     const int n_ios = nt * kTileIos;
-    const float inv = 1.0f / 32768.0f;
-    for (int i = tid; i < kSRows; i += kPPBlock) pair_srows[i] = table[i];
+    const float ps = law.ps, ips = law.ips;
+    const uint32_t bmax = law.bmax;
+    for (int i = tid; i < PPGeo<ADJ, H>::ROWS; i += kPPBlock) (ADJ ? pair_arows : pair_srows)[i] = table[i];
+    // part of a box row that holds the box coordinate bx
+    auto part_of = [](int bx) { return bx < H ? 0 : (bx < H + kTileIos ? 1 : 2); };
 
     // Persistent workgroups: each takes the next work item of the
     // heaviest-first order (claim_slot) until all are taken (the exit test
@@ -272,7 +290,9 @@ __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK)) void pp_kernel(const uint16
             const int s = tid * kPSegPerThread + k;
             if (s < kPSegs) {
                 seg_pre[s] = pre;
-                seg_src[s] = src[k];
+                const int bx = s % kPB;
+                if (bx == 0 || bx == H || bx == H + kTileIos)
+                    seg_delta[(s / kPB) * 3 + part_of(bx)] = src[k] - pre;
             }
             pre_k[k] = pre;
             pre += cnt[k];
@@ -282,228 +302,212 @@ __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK)) void pp_kernel(const uint16
         // own cells (box segments with coordinates 1..8): their particle
         // starts relative to the tile's first particle, from the box ranges
         // (the own cells' particles are one contiguous range)
-        const uint32_t p0 = seg_src[(H * kPB + H) * kPB + H];
+        const uint32_t p0 = seg_pre[(H * kPB + H) * kPB + H] + seg_delta[(H * kPB + H) * 3 + 1];
         for (int i = tid; i <= kTileCells; i += kPPBlock) {
-            if (i < kTileCells) {
-                const int s = (((i >> 6) + H) * kPB + ((i >> 3) & 7) + H) * kPB + (i & 7) + H;
-                cst[i] = seg_src[s] - p0;
-            } else {
-                const int s = ((7 + H) * kPB + 7 + H) * kPB + 7 + H;  // last own cell
-                cst[i] = seg_src[s] + (seg_pre[s + 1] - seg_pre[s]) - p0;
-            }
-        }
-        if (tid == 0) {
-            // z-chunks: the smallest power-of-two count whose staged slices fit
-            int C = 1;
-            for (; C < 8; C <<= 1) {
-                bool fits = true;
-                for (int c = 0; c < C; ++c) {
-                    const int z0 = c * 8 / C, z1 = (c + 1) * 8 / C;
-                    if (seg_pre[(z1 + 2 * H) * kPB * kPB] - seg_pre[z0 * kPB * kPB] > (uint32_t)CAP)
-                        fits = false;
-                }
-                if (fits) break;
-            }
-            chunk_sh = C;
+            const int u = min(i, kTileCells - 1);          // past the end: the last own cell's end
+            const int row = ((u >> 6) + H) * kPB + ((u >> 3) & 7) + H;
+            cst[i] = seg_pre[row * kPB + (u & 7) + H + (i - u)] + seg_delta[row * 3 + 1] - p0;
         }
         __syncthreads();
-        const int C = chunk_sh;
         const uint32_t maxcnt = maxcnt_sh;
+        const uint32_t own = cst[kTileCells];
+        const bool single = total <= (uint32_t)CAP;   // the whole box is staged at once
 
-        for (int c = 0; c < C; ++c) {
-            const int z0 = c * 8 / C, z1 = (c + 1) * 8 / C;
-            const uint32_t vb = seg_pre[z0 * kPB * kPB], ve = seg_pre[(z1 + 2 * H) * kPB * kPB];
-            const bool staged = ve - vb <= (uint32_t)CAP;
-            if (c > 0) __syncthreads();  // previous chunk done with xs
-            if (!ADJ && staged && C == 1 && maxcnt <= 4) {
-                // sparse box: every thread copies the particles of its own
-                // segments (at most 4 each), no search needed; one segment at
-                // a time keeps the register footprint of the staging small
+        // Blocks of own particles, one particle per thread; part p of a split
+        // tile takes blocks p, p + nparts, ...  A box that fits is staged for the
+        // first of them.  Otherwise each block streams the box layers that its
+        // cells reach through LDS, CAP particles at a time, its sums staying in
+        // registers.
+        bool staged = false;
+        for (uint32_t l0 = (uint32_t)(part * kPPBlock); l0 < own; l0 += (uint32_t)(kPPBlock * nparts)) {
+            const uint32_t lp = l0 + tid;
+            const bool active = lp < own;
+            const int u = seg_search_n<kTileCells>(cst, active ? lp : own - 1);
+            const uint32_t p = p0 + (active ? lp : own - 1);
+            const int bx = (u & 7) + H, by = ((u >> 3) & 7) + H, bz = (u >> 6) + H;
+            const int su = (bz * kPB + by) * kPB + bx;
+            const uint32_t vown = seg_pre[su] + (active ? lp : own - 1) - cst[u];
+            uint32_t V0 = 0, V1 = total;
+            float xi = 0.f, yi = 0.f, zi = 0.f;
+            float aix = 0.f, aiy = 0.f, aiz = 0.f;
+            if (!single) {
+                const int za = seg_search_n<kTileCells>(cst, l0) >> 6;
+                const int zb = seg_search_n<kTileCells>(cst, min(l0 + kPPBlock, own) - 1) >> 6;
+                V0 = seg_pre[za * kPB * kPB];
+                V1 = seg_pre[(zb + 2 * H + 1) * kPB * kPB];
+                xi = (float)(2 * (bx - H)) * ps + (float)pos[p] * ips;
+                yi = (float)(2 * (by - H)) * ps + (float)pos[(int64_t)n + p] * ips;
+                zi = (float)(2 * (bz - H)) * ps + (float)pos[2 * (int64_t)n + p] * ips;
+            }
+            if (ADJ) {
+                aix = abar[p];
+                aiy = abar[(int64_t)n + p];
+                aiz = abar[2 * (int64_t)n + p];
+            }
+            float sx = 0.f, sy = 0.f, sz = 0.f, cx = 0.f, cy = 0.f, cz = 0.f;
+            for (uint32_t vb = V0; vb < V1; vb += CAP) {
+                const uint32_t ve = min(vb + (uint32_t)CAP, V1);
+                if (!staged) {
+                    if (!single) __syncthreads();   // the previous chunk is done with xs
+                    if (!ADJ && single && maxcnt <= 4) {
+                        // sparse box: every thread copies the particles of its own
+                        // segments (at most 4 each), no search needed; one segment at
+                        // a time keeps the register footprint of the staging small
 #pragma unroll 1
-                for (int k = 0; k < kPSegPerThread; ++k) {
-                    const int s = tid * kPSegPerThread + k;
-                    const int bx = s % kPB, by = (s / kPB) % kPB, bz = s / (kPB * kPB);
-                    uint32_t o[4][3];
+                        for (int k = 0; k < kPSegPerThread; ++k) {
+                            const int s = tid * kPSegPerThread + k;
+                            const int bx = s % kPB, by = (s / kPB) % kPB, bz = s / (kPB * kPB);
+                            uint32_t o[4][3];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        if ((uint32_t)i >= cnt[k]) continue;
-                        const uint32_t p = src[k] + i;
-                        o[i][0] = pos[p];
-                        o[i][1] = pos[(int64_t)n + p];
-                        o[i][2] = pos[2 * (int64_t)n + p];
-                    }
+                            for (int i = 0; i < 4; ++i) {
+                                if ((uint32_t)i >= cnt[k]) continue;
+                                const uint32_t p = src[k] + i;
+                                o[i][0] = pos[p];
+                                o[i][1] = pos[(int64_t)n + p];
+                                o[i][2] = pos[2 * (int64_t)n + p];
+                            }
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        if ((uint32_t)i >= cnt[k]) continue;
-                        float4 q;
-                        q.x = (float)(2 * (bx - H)) + (float)o[i][0] * inv;
-                        q.y = (float)(2 * (by - H)) + (float)o[i][1] * inv;
-                        q.z = (float)(2 * (bz - H)) + (float)o[i][2] * inv;
-                        q.w = 0.0f;
-                        xs[XS * (pre_k[k] + i)] = q;
-                        if (ADJ) {
-                            const uint32_t p = src[k] + i;
-                            xs[XS * (pre_k[k] + i) + 1] = make_float4(abar[p], abar[(int64_t)n + p],
-                                                                      abar[2 * (int64_t)n + p], 0.f);
+                            for (int i = 0; i < 4; ++i) {
+                                if ((uint32_t)i >= cnt[k]) continue;
+                                float4 q;
+                                q.x = (float)(2 * (bx - H)) * ps + (float)o[i][0] * ips;
+                                q.y = (float)(2 * (by - H)) * ps + (float)o[i][1] * ips;
+                                q.z = (float)(2 * (bz - H)) * ps + (float)o[i][2] * ips;
+                                q.w = kPairS0;
+                                xs[pre_k[k] + i] = q;
+                            }
+                        }
+                    } else {
+                        // kStage particles per thread at a time: the segment searches and
+                        // the loads of a batch are issued before the LDS stores
+                        constexpr int kStage = 4;
+                        for (uint32_t v0 = vb + tid; v0 < ve; v0 += kPPBlock * kStage) {
+                            int sg[kStage];
+                            uint32_t pj[kStage];
+#pragma unroll
+                            for (int k = 0; k < kStage; ++k) {
+                                const uint32_t v = v0 + k * kPPBlock;
+                                sg[k] = v < ve ? seg_search(seg_pre, kPSegs, v) : -1;
+                                pj[k] = sg[k] < 0 ? 0u : v + seg_delta[(sg[k] / kPB) * 3 + part_of(sg[k] % kPB)];
+                            }
+                            uint32_t o[kStage][3];
+                            float ab[kStage][3];
+#pragma unroll
+                            for (int k = 0; k < kStage; ++k) {
+                                if (sg[k] < 0) continue;
+                                const uint32_t p = pj[k];
+                                o[k][0] = pos[p];
+                                o[k][1] = pos[(int64_t)n + p];
+                                o[k][2] = pos[2 * (int64_t)n + p];
+                                if (ADJ) {
+                                    ab[k][0] = abar[p];
+                                    ab[k][1] = abar[(int64_t)n + p];
+                                    ab[k][2] = abar[2 * (int64_t)n + p];
+                                }
+                            }
+#pragma unroll
+                            for (int k = 0; k < kStage; ++k) {
+                                if (sg[k] < 0) continue;
+                                const int s = sg[k];
+                                const int bx = s % kPB, by = (s / kPB) % kPB, bz = s / (kPB * kPB);
+                                float4 q;
+                                q.x = (float)(2 * (bx - H)) * ps + (float)o[k][0] * ips;
+                                q.y = (float)(2 * (by - H)) * ps + (float)o[k][1] * ips;
+                                q.z = (float)(2 * (bz - H)) * ps + (float)o[k][2] * ips;
+                                q.w = ADJ ? ab[k][0] : kPairS0;
+                                const uint32_t v = v0 + k * kPPBlock;
+                                xs[v - vb] = q;
+                                if (ADJ) xa[v - vb] = make_float2(ab[k][1], ab[k][2]);
+                            }
                         }
                     }
+                    __syncthreads();
+                    staged = single;
                 }
-            } else if (staged) {
-                // kStage particles per thread at a time: the segment searches and
-                // the loads of a batch are issued before the LDS stores
-                constexpr int kStage = 4;
-                for (uint32_t v0 = vb + tid; v0 < ve; v0 += kPPBlock * kStage) {
-                    int sg[kStage];
-                    uint32_t pj[kStage];
-#pragma unroll
-                    for (int k = 0; k < kStage; ++k) {
-                        const uint32_t v = v0 + k * kPPBlock;
-                        sg[k] = v < ve ? seg_search(seg_pre, kPSegs, v) : -1;
-                        pj[k] = sg[k] < 0 ? 0u : seg_src[sg[k]] + (v - seg_pre[sg[k]]);
-                    }
-                    uint32_t o[kStage][3];
-                    float4 ab[kStage];
-#pragma unroll
-                    for (int k = 0; k < kStage; ++k) {
-                        if (sg[k] < 0) continue;
-                        const uint32_t p = pj[k];
-                        o[k][0] = pos[p];
-                        o[k][1] = pos[(int64_t)n + p];
-                        o[k][2] = pos[2 * (int64_t)n + p];
-                        if (ADJ)
-                            ab[k] = make_float4(abar[p], abar[(int64_t)n + p],
-                                                abar[2 * (int64_t)n + p], 0.f);
-                    }
-#pragma unroll
-                    for (int k = 0; k < kStage; ++k) {
-                        if (sg[k] < 0) continue;
-                        const int s = sg[k];
-                        const int bx = s % kPB, by = (s / kPB) % kPB, bz = s / (kPB * kPB);
-                        float4 q;
-                        q.x = (float)(2 * (bx - H)) + (float)o[k][0] * inv;
-                        q.y = (float)(2 * (by - H)) + (float)o[k][1] * inv;
-                        q.z = (float)(2 * (bz - H)) + (float)o[k][2] * inv;
-                        q.w = 0.0f;
-                        const uint32_t v = v0 + k * kPPBlock;
-                        xs[XS * (v - vb)] = q;
-                        if (ADJ) xs[XS * (v - vb) + 1] = ab[k];
-                    }
-                }
-            }
-            __syncthreads();
-            // own particles of the cells [z0*64, z1*64): a contiguous range;
-            // part p of a split tile takes its blocks p, p + nparts, ...
-            const uint32_t q0 = cst[z0 * 64], q1 = cst[z1 * 64];
-            for (uint32_t lp = q0 + (uint32_t)(part * kPPBlock + tid); lp < q1;
-                 lp += (uint32_t)(kPPBlock * nparts)) {
-                const int u = seg_search_n<kTileCells>(cst, lp);
-                const uint32_t p = p0 + lp;
-                const int bx = (u & 7) + H, by = ((u >> 3) & 7) + H, bz = (u >> 6) + H;
-                float xi, yi, zi;
-                if (staged) {
-                    // the particle itself is staged: same exact floats, no HBM read
-                    const int su = (bz * kPB + by) * kPB + bx;
-                    const float4 qi = xs[XS * (seg_pre[su] + (lp - cst[u]) - vb)];
+                if (!active) continue;
+                if (single) {      // the particle itself is staged: the same exact floats
+                    const float4 qi = xs[vown];
                     xi = qi.x;
                     yi = qi.y;
                     zi = qi.z;
-                } else {
-                    xi = (float)(2 * (bx - H)) + (float)pos[p] * inv;
-                    yi = (float)(2 * (by - H)) + (float)pos[(int64_t)n + p] * inv;
-                    zi = (float)(2 * (bz - H)) + (float)pos[2 * (int64_t)n + p] * inv;
                 }
-                float aix = 0.f, aiy = 0.f, aiz = 0.f;
-                if (ADJ) {
-                    aix = abar[p];
-                    aiy = abar[(int64_t)n + p];
-                    aiz = abar[2 * (int64_t)n + p];
-                }
-                float sx = 0.f, sy = 0.f, sz = 0.f, cx = 0.f, cy = 0.f, cz = 0.f;
-                if (staged) {
-                    // the three x-neighbours of a cell are consecutive box segments,
-                    // so the 27 neighbour cells are 9 contiguous ranges of xs
-                    for (int row = 0; row < kW * kW; ++row) {
-                        const int oy = row % kW - H, oz = row / kW - H;
-                        const int sm = ((bz + oz) * kPB + (by + oy)) * kPB + bx;
-                        const uint32_t v0 = seg_pre[sm - H] - vb, v1 = seg_pre[sm + H + 1] - vb;
-                        float fx = 0.f, fy = 0.f, fz = 0.f;
-                        if (ADJ) {
-                            // four pairs per iteration: the loop control and the LDS
-                            // latency spread over more work.  The loops run on the
-                            // LDS address against precomputed bounds, never below xs
-                            // (LDS addresses compare unsigned).
-                            const float4 *q = xs + 2 * v0;
-                            const float4 *const qe = xs + 2 * v1;
-                            const float4 *const qe4 = xs + 2 * (v1 >= v0 + 3 ? v1 - 3 : v0);
-                            for (; q < qe4; q += 8) {
-                                float4 x[4], a[4];
+                // the 2H + 1 x-neighbours of a cell are consecutive box segments, so the
+                // neighbour cells are (2H + 1)^2 contiguous ranges of xs
+                for (int row = 0; row < kW * kW; ++row) {
+                    const int oy = row % kW - H, oz = row / kW - H;
+                    const int sm = ((bz + oz) * kPB + (by + oy)) * kPB + bx;
+                    const uint32_t r0 = max(seg_pre[sm - H], vb), r1 = min(seg_pre[sm + H + 1], ve);
+                    const uint32_t v0 = r0 - vb, v1 = max(r0, r1) - vb;
+                    float fx = 0.f, fy = 0.f, fz = 0.f;
+                    if (ADJ) {
+                        // four pairs per iteration: the loop control and the LDS
+                        // latency spread over more work.  The loops run on the
+                        // LDS address against precomputed bounds, never below xs
+                        // (LDS addresses compare unsigned).
+                        const float4 *q = xs + v0;
+                        const float2 *qa = xa + v0;
+                        const float4 *const qe = xs + v1;
+                        const float4 *const qe4 = xs + (v1 >= v0 + 3 ? v1 - 3 : v0);
+                        for (; q < qe4; q += 4, qa += 4) {
+                            float4 x[4];
+                            float2 a[4];
 #pragma unroll
-                                for (int t = 0; t < 4; ++t) {
-                                    x[t] = q[2 * t];
-                                    a[t] = q[2 * t + 1];
-                                }
+                            for (int t = 0; t < 4; ++t) {
+                                x[t] = q[t];
+                                a[t] = qa[t];
+                            }
 #pragma unroll
-                                for (int t = 0; t < 4; ++t)
-                                    pair_adjoint(x[t].x - xi, x[t].y - yi, x[t].z - zi, a[t].x - aix,
-                                                 a[t].y - aiy, a[t].z - aiz, negc, fx, fy, fz);
-                            }
-                            for (; q < qe; q += 2) {
-                                const float4 qa = q[0], aa = q[1];
-                                pair_adjoint(qa.x - xi, qa.y - yi, qa.z - zi, aa.x - aix, aa.y - aiy,
-                                             aa.z - aiz, negc, fx, fy, fz);
-                            }
-                        } else {
-                            // two pairs per iteration.  The loop runs on the LDS
-                            // address against a precomputed bound, never below xs
-                            // (one add and one compare per trip).
-                            const float4 *q = xs + v0;
-                            const float4 *const qend = xs + v1;
-                            const float4 *const qe = xs + (v1 > v0 ? v1 - 1 : v0);
-                            for (; q < qe; q += 2) {
-                                const float4 qa = q[0], qb = q[1];
-                                pair_accumulate(qa.x - xi, qa.y - yi, qa.z - zi, negc, fx, fy, fz);
-                                pair_accumulate(qb.x - xi, qb.y - yi, qb.z - zi, negc, fx, fy, fz);
-                            }
-                            if (q < qend) {
-                                const float4 qa = q[0];
-                                pair_accumulate(qa.x - xi, qa.y - yi, qa.z - zi, negc, fx, fy, fz);
-                            }
+                            for (int t = 0; t < 4; ++t)
+                                pair_adjoint<CLAMP>(x[t].x - xi, x[t].y - yi, x[t].z - zi,
+                                                    x[t].w - aix, a[t].x - aiy, a[t].y - aiz,
+                                                    bmax, fx, fy, fz);
                         }
-                        kahan_add(sx, cx, fx);
-                        kahan_add(sy, cy, fy);
-                        kahan_add(sz, cz, fz);
-                    }
-                } else {
-                    for (int nb = 0; nb < kW * kW * kW; ++nb) {
-                        const int ox = nb % kW - H, oy = (nb / kW) % kW - H, oz = nb / (kW * kW) - H;
-                        const int s = ((bz + oz) * kPB + (by + oy)) * kPB + (bx + ox);
-                        const uint32_t v0 = seg_pre[s], v1 = seg_pre[s + 1];
-                        const float bxo = (float)(2 * (bx + ox - H)), byo = (float)(2 * (by + oy - H)),
-                                    bzo = (float)(2 * (bz + oz - H));
-                        float fx = 0.f, fy = 0.f, fz = 0.f;
-                        for (uint32_t v = v0; v < v1; ++v) {
-                            const uint32_t pj = seg_src[s] + (v - v0);
-                            const float xj = bxo + (float)pos[pj] * inv;
-                            const float yj = byo + (float)pos[(int64_t)n + pj] * inv;
-                            const float zj = bzo + (float)pos[2 * (int64_t)n + pj] * inv;
-                            if (ADJ)
-                                pair_adjoint(xj - xi, yj - yi, zj - zi, abar[pj] - aix,
-                                             abar[(int64_t)n + pj] - aiy, abar[2 * (int64_t)n + pj] - aiz,
-                                             negc, fx, fy, fz);
-                            else
-                                pair_accumulate(xj - xi, yj - yi, zj - zi, negc, fx, fy, fz);
+                        for (; q < qe; ++q, ++qa) {
+                            const float4 x = q[0];
+                            const float2 a = qa[0];
+                            pair_adjoint<CLAMP>(x.x - xi, x.y - yi, x.z - zi, x.w - aix,
+                                                a.x - aiy, a.y - aiz, bmax, fx, fy, fz);
                         }
-                        kahan_add(sx, cx, fx);
-                        kahan_add(sy, cy, fy);
-                        kahan_add(sz, cz, fz);
-                    }
-                }
-                const float a[3] = {gm * sx, gm * sy, gm * sz};
+                    } else {
+                        // four pairs per iteration, then two, then one.  The
+                        // loop runs on the LDS address against a precomputed
+                        // bound, never below xs.
+                        const float4 *q = xs + v0;
+                        const float4 *const qe4 = xs + (v1 >= v0 + 3 ? v1 - 3 : v0);
+                        for (; q < qe4; q += 4) {
+                            float4 x[4];
 #pragma unroll
-                for (int d = 0; d < 3; ++d) {
-                    float *dst = acc + (int64_t)d * n + p;
-                    *dst = accumulate ? *dst + a[d] : a[d];
+                            for (int t = 0; t < 4; ++t) x[t] = q[t];
+#pragma unroll
+                            for (int t = 0; t < 4; ++t)
+                                pair_accumulate<CLAMP>(x[t].x - xi, x[t].y - yi, x[t].z - zi,
+                                                       x[t].w, bmax, fx, fy, fz);
+                        }
+                        if ((v1 - v0) & 2u) {
+                            const float4 qa = q[0], qb = q[1];
+                            pair_accumulate<CLAMP>(qa.x - xi, qa.y - yi, qa.z - zi, qa.w, bmax,
+                                                   fx, fy, fz);
+                            pair_accumulate<CLAMP>(qb.x - xi, qb.y - yi, qb.z - zi, qb.w, bmax,
+                                                   fx, fy, fz);
+                            q += 2;
+                        }
+                        if ((v1 - v0) & 1u) {
+                            const float4 qa = q[0];
+                            pair_accumulate<CLAMP>(qa.x - xi, qa.y - yi, qa.z - zi, qa.w, bmax,
+                                                   fx, fy, fz);
+                        }
+                    }
+                    kahan_add(sx, cx, fx);
+                    kahan_add(sy, cy, fy);
+                    kahan_add(sz, cz, fz);
                 }
+            }
+            if (!active) continue;
+            const float a[3] = {gm * (sx * law.unit), gm * (sy * law.unit), gm * (sz * law.unit)};
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                float *dst = acc + (int64_t)d * n + p;
+                *dst = accumulate ? *dst + a[d] : a[d];
             }
         }
         __syncthreads();  // this tile is done with the LDS arrays
@@ -530,75 +534,138 @@ void compose(const double P[9], double alpha, double beta, double Q[9]) {
 
 namespace {
 
-// h = g / (b_f^2 - r^2)^5 for the pair law g(r) of eqs. (2) and (4d), in
-// extended precision: where 1/r^2 - R(r, b_f) would cancel (r >= b_pp and
-// r >= b_f/2) through its factorised form (which also continues h past the
-// cutoff), elsewhere from the branches of R(r, b).
-long double pair_h_direct(double b_pp, double b_f, double rd) {
-    using X = long double;
-    const X r = rd, bf = b_f;
-    auto r_over_r = [&](X b) -> X {  // R(r, b) / r
-        const X t = r / b;
+// The fifth root of the pair law g(r) / unit (eqs. 2 and 4d), in FP64: where
+// 1/r^2 - R(r, b_f) would cancel (r >= b_pp and r >= b_f/2) through its
+// factorised form, which also continues it, negative, past the cutoff;
+// elsewhere from the branches of R(r, b).
+double pair_root(double b_pp, double b_f, double s, double unit) {
+    const double r = std::sqrt(s);
+    if (r >= b_pp && 2 * r >= b_f) {  // g = q^5 Q(q) / r^3, q = 1 - r/b_f
+        const double q = 1 - r / b_f;
+        const double Q = 1344.0 / 35 + q * (-2912.0 / 35 + q * (2048.0 / 35 + q * (-64.0 / 5)));
+        return q * std::pow(Q / (r * r * r * unit), 0.2);
+    }
+    auto r_over_r = [&](double b) {   // R(r, b) / r
+        const double t = r / b;
         if (t >= 1) return 1 / (r * r * r);
         if (2 * t < 1)
-            return (X(64) / 5 + t * t * (X(-256) / 5 + t * (32 + t * (X(1536) / 35 + t * (X(-192) / 5))))) /
+            return (64.0 / 5 + t * t * (-256.0 / 5 + t * (32 + t * (1536.0 / 35 + t * (-192.0 / 5))))) /
                    (b * b * b);
-        const X p = X(3) / 35 / (t * t) - X(32) / 5 +
-                    t * (X(256) / 5 + t * (-96 + t * (X(256) / 5 + t * (32 + t * (X(-1536) / 35 + t * (X(64) / 5))))));
-        return p / (b * b * r);
+        return (3.0 / 35 / (t * t) - 32.0 / 5 +
+                t * (256.0 / 5 + t * (-96 + t * (256.0 / 5 + t * (32 + t * (-1536.0 / 35 + t * (64.0 / 5))))))) /
+               (b * b * r);
     };
-    if (r >= b_pp && 2 * r >= bf) {
-        // r^3 g = q^5 Q(q), q = 1 - r/b_f, and b_f^2 - r^2 = q b_f (b_f + r)
-        const X q = 1 - r / bf;
-        const X Q = X(1344) / 35 + q * (X(-2912) / 35 + q * (X(2048) / 35 + q * (X(-64) / 5)));
-        const X u = bf * (bf + r);
-        return Q / (r * r * r * u * u * u * u * u);
-    }
-    const X w = bf * bf - r * r;
-    return (r_over_r(b_pp) - r_over_r(bf)) / (w * w * w * w * w);
+    return std::pow((r_over_r(b_pp) - r_over_r(b_f)) / unit, 0.2);
 }
 
-// A table of H = g / w^4 = h b_f^10 w, w = 1 - s/b_f^2, by s = r^2 (see the
-// comments above pair_accumulate and pair_adjoint): row t covers s in
-// [2^e (1 + i/2^mb), 2^e (1 + (i+1)/2^mb)) with (e + 127) 2^mb + i = t + row0,
-// and holds the polynomial of degree D-1 in z in [0, 2^-mb) through H at the
-// D Chebyshev nodes, solved in FP64 in the variable y = 2^mb z and rescaled.  Built from
-// eq. (2) directly (extended precision), independent of the r grid; rows
-// beyond the cutoff are zero.
-void fit_h_rows(const cube2_ctx *ctx, int mb, int D, int row0, int nrows, int row_floats,
-                std::vector<float> &out) {
-    const double pi = 3.14159265358979323846, bf = ctx->cfg.b_fine;
-    const long double bf10 = std::pow((long double)bf, 10);  // rows hold H = h b_f^10 w
-    std::vector<double> yn(D);
-    for (int j = 0; j < D; ++j) yn[j] = 0.5 + 0.5 * std::cos(pi * (j + 0.5) / D);
-    out.assign((size_t)nrows * row_floats, 0.0f);
+// The rows of L (see the comment at the top of the law) for 2^mant rows per
+// octave, from the octave of s0 on, in scaled units (s and s0 times 4^j).
+// grid holds L at 2^(kSMantAdj + 1) points per octave: the adjoint's rows are
+// the quadratics through both ends and the middle, which leaves the smallest
+// rms error in dL/ds; the forward's, twice as wide, the least-squares fit to
+// five points, close to the smallest error in L.
+void fit_root_rows(const cube2_ctx *ctx, int mant, int nrows, const std::vector<double> &grid,
+                   std::vector<float> &out) {
+    const double bpp = ctx->cfg.b_pp, bf = ctx->cfg.b_fine;
+    const double p2 = (double)ctx->pp_pscale * ctx->pp_pscale, unit = ctx->pp_unit, s0 = kPairS0;
+    const double cut = bf * bf * p2 + s0, c = 0.1f;
+    const int per = 1 << (kSMantAdj + 1 - mant);     // grid points per row
     for (int t = 0; t < nrows; ++t) {
-        const int e = ((t + row0) >> mb) - 127, i = (t + row0) & ((1 << mb) - 1);
-        const double scale = std::ldexp(1.0, e), inv = 1.0 / (1 << mb);
-        if (scale * (1.0 + i * inv) >= bf * bf) continue;  // beyond the cutoff: h = 0
-        double A[8][9];
-        for (int j = 0; j < D; ++j) {
-            const double sv = scale * (1.0 + (i + yn[j]) * inv);
-            double p = 1.0;
-            for (int k = 0; k < D; ++k, p *= yn[j]) A[j][k] = p;
-            const long double w = 1.0L - (long double)sv / ((long double)bf * bf);
-            A[j][D] = (double)(pair_h_direct(ctx->cfg.b_pp, bf, std::sqrt(sv)) * bf10 * w);
-        }
-        for (int c = 0; c < D; ++c) {  // Gauss-Jordan, partial pivoting
-            int pv = c;
-            for (int r = c + 1; r < D; ++r)
-                if (std::fabs(A[r][c]) > std::fabs(A[pv][c])) pv = r;
-            for (int k = 0; k <= D; ++k) std::swap(A[c][k], A[pv][k]);
-            for (int r = 0; r < D; ++r) {
-                if (r == c) continue;
-                const double f = A[r][c] / A[c][c];
-                for (int k = c; k <= D; ++k) A[r][k] -= f * A[c][k];
+        const double oct = std::ldexp(s0, t >> mant), w = std::ldexp(oct, -mant);
+        const double lo = oct + (t & ((1 << mant) - 1)) * w, hi = lo + w;
+        if (lo >= cut) break;        // this and the following rows lie beyond the cutoff: zero
+        const double mid = lo + w / 2, half = w / 2;
+        float k, c0;
+        double c1, c2;
+        if (hi >= cut) {
+            // L = (x - cut) (h0 + h1 (x - cut)) through two points on the far
+            // side of the row from the cutoff; k rounded down, so that s >=
+            // b_f^2 has y >= 0 and L <= 0
+            auto h = [&](double x) { return pair_root(bpp, bf, (x - s0) / p2, unit) / (x - cut); };
+            const double x0 = cut > mid ? lo + w / 8 : mid + w / 8, x1 = x0 + w / 4;
+            const double a = h(x0), h1 = (h(x1) - a) / (x1 - x0), h0 = a + h1 * (cut - x0);
+            k = (float)(c * cut);
+            if (k > c * cut) k = std::nextafter(k, 0.0f);
+            c0 = 0.0f;
+            c1 = h0 / c;
+            c2 = h1 / (c * c);
+        } else {
+            const double *g = &grid[(size_t)t * per];
+            double l0, a1, a2;       // L = l0 + e (a1 + e a2), e in [-1, 1]
+            if (per == 2) {
+                l0 = g[1];
+                a1 = (g[2] - g[0]) / 2;
+                a2 = (g[2] + g[0] - 2 * g[1]) / 2;
+            } else {                 // least squares over e = -1, -1/2, 0, 1/2, 1
+                const double m0 = g[0] + g[1] + g[2] + g[3] + g[4], m2 = g[0] + g[4] + (g[1] + g[3]) / 4;
+                a1 = (g[4] - g[0] + (g[3] - g[1]) / 2) / 2.5;
+                a2 = (m2 - m0 / 2) / 0.875;
+                l0 = (m0 - 2.5 * a2) / 5;
             }
+            // 8 neighbouring floats kc + i ulp
+            const float kc = (float)(c * mid);
+            const double ulp = (double)std::nextafter(kc, 2 * kc) - kc, ich = 1 / (c * half);
+            const double e0 = (kc - c * mid) * ich, de = ulp * ich;
+            double best = 1, d = 0;
+            int at = 0;
+            for (int i = 0; i < 8; ++i) {
+                const double e = e0 + i * de, v = l0 + e * (a1 + e * a2), err = std::fabs((float)v - v);
+                if (err < best) {
+                    best = err;
+                    at = i;
+                    d = e;
+                }
+            }
+            k = (float)(kc + at * ulp);
+            c0 = (float)(l0 + d * (a1 + d * a2));
+            c1 = (a1 + 2 * d * a2) * ich;
+            c2 = a2 * ich * ich;
         }
-        double p = 1.0;
-        for (int k = 0; k < D; ++k, p *= (1 << mb))
-            out[(size_t)t * row_floats + k] = (float)(A[k][D] / A[k][k] * p);
+        float *row = &out[(size_t)t * 4];
+        row[0] = c0;
+        row[1] = (float)c1;
+        row[2] = (float)c2;
+        row[3] = -k;
     }
+}
+
+// The law's units and both tables.
+void build_root_tables(cube2_ctx *ctx) {
+    const double bpp = ctx->cfg.b_pp, bf = ctx->cfg.b_fine;
+    // the largest odd e0 at least 3 octaves below (b_pp/2)^2, but not below
+    // the 2^-31 under the smallest separation (2^-15)
+    int e0 = (int)std::floor(2.0 * std::log2(bpp / 2)) - 3;
+    if ((e0 & 1) == 0) --e0;
+    e0 = std::max(e0, -31);
+    const int j = (1 - e0) / 2;
+    ctx->pp_pscale = std::ldexp(1.0f, j);
+        const int top = ctx->pp_halo == 1 ? 6 : 7;           // s < 2^top
+    ctx->pp_clamp = top - e0 > (kSRows >> kSMant);
+    ctx->pp_unit = 1.0f;
+    ctx->pp_srows.assign((size_t)kSRows * 4, 0.0f);
+    ctx->pp_arows.assign((size_t)kSRowsAdj * 4, 0.0f);
+    ctx->pp_bmax = ctx->pp_bmax_adj = 0x40000000u;       // the row of s0
+    if (bf * bf <= 0x1p-30) return;                      // no pair of different positions: zero rows
+    // unit >= 1.05 g(0): L stays below the clamp
+    const double g0 = 64.0 / 5 * (1.0 / (bpp * bpp * bpp) - 1.0 / (bf * bf * bf));
+    ctx->pp_unit = (float)std::ldexp(1.0, (int)std::ceil(std::log2(1.05 * g0)));
+    // L at both ends and in the middle of the adjoint's rows, up to the cutoff
+    const double p2 = (double)ctx->pp_pscale * ctx->pp_pscale, s0 = kPairS0, last = bf * bf * p2 + s0;
+    std::vector<double> grid((size_t)2 * kSRowsAdj + 1, 0.0);
+    for (size_t i = 0; i < grid.size(); ++i) {
+        const double oct = std::ldexp(s0, (int)(i >> (kSMantAdj + 1)));
+        const double x = oct + std::ldexp(oct, -kSMantAdj - 1) * (i & ((2 << kSMantAdj) - 1));
+        if (x >= last) break;
+        grid[i] = pair_root(bpp, bf, (x - s0) / p2, ctx->pp_unit);
+    }
+    fit_root_rows(ctx, kSMant, kSRows, grid, ctx->pp_srows);
+    fit_root_rows(ctx, kSMantAdj, kSRowsAdj, grid, ctx->pp_arows);
+    // first bit pattern of the row after the one that holds the cutoff
+    const float cut = (float)(bf * bf * ctx->pp_pscale * ctx->pp_pscale + kPairS0);
+    uint32_t b;
+    std::memcpy(&b, &cut, 4);
+    ctx->pp_bmax = ((b >> (23 - kSMant)) + 1) << (23 - kSMant);
+    ctx->pp_bmax_adj = ((b >> (23 - kSMantAdj)) + 1) << (23 - kSMantAdj);
 }
 
 }  // namespace
@@ -625,10 +692,6 @@ int build_pair_table(cube2_ctx *ctx) {
     const double w = bf / K;
     ctx->pp_K = K;
     ctx->pp_kinv = (float)(K / bf);
-    // -1/b_f^2 rounded away from zero: s * (-negc) >= 1 whenever s >= b_f^2
-    float cinv = (float)(1.0 / (bf * bf));
-    if ((double)cinv < 1.0 / (bf * bf)) cinv = std::nextafter(cinv, 2.0f * cinv);
-    ctx->pp_negc = -cinv;
     ctx->pp_rows64.assign((size_t)(K + 1) * kPairRow, 0.0);
     for (int k = 0; k < K; ++k) {
         const double mid = (k + 0.5) * w, rl = k * w, rr = (k + 1) * w;
@@ -669,31 +732,37 @@ int build_pair_table(cube2_ctx *ctx) {
         row64[9] = ya;
         row64[10] = yb;
     }
-    fit_h_rows(ctx, kSMantBits, 4, kSRow0, kSRows, 4, ctx->pp_srows);
+    build_root_tables(ctx);
     return 0;
 }
 
 namespace {
 
-template <bool ADJ, int H>
+template <bool ADJ, int H, bool CLAMP>
 int launch_pp_kernel_h(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,
                      const float *abar, float *out, int accumulate, unsigned char *work,
                      const WorkLayout &L, hipStream_t s, float grid_frac,
                      const uint8_t *skip) {
-    const float4 *table = reinterpret_cast<const float4 *>(ctx->tables + ctx->pp_soff);
+    const float4 *table =
+        reinterpret_cast<const float4 *>(ctx->tables + (ADJ ? ctx->pp_aoff : ctx->pp_soff));
+    PPLaw law;
+    law.ps = ctx->pp_pscale;
+    law.ips = ctx->pp_pscale * 0x1p-15f;
+    law.unit = ADJ ? ctx->pp_unit : ctx->pp_unit / ctx->pp_pscale;
+    law.bmax = ADJ ? ctx->pp_bmax_adj : ctx->pp_bmax;
     const int nt = ctx->nt;
     const int ntiles = nt * nt * nt;
     int r = launch_order_tiles(ctx, cs, work, L, s);
     if (r) return r;
     const uint32_t *order = tile_order_ptr(work, L);
     uint32_t *queue = tile_queue_ptr(ctx, work, L);
-    auto k = pp_kernel<ADJ, H>;
+    auto k = pp_kernel<ADJ, H, CLAMP>;
     const int nsplit = split_parts<H>() > 1 ? std::min(kSplitTiles, ntiles) : 0;
     const int nitems = ntiles + nsplit * (split_parts<H>() - 1);
     const unsigned grid = std::max(
         1u, (unsigned)((float)persistent_grid(k, PPGeo<ADJ, H>::BLOCK, nitems) * grid_frac));
     k<<<grid, PPGeo<ADJ, H>::BLOCK, 0, s>>>(
-        pos, cs, (int)n, nt, table, ctx->pp_negc,
+        pos, cs, (int)n, nt, table, law,
         (float)(ctx->cfg.g_newton * ctx->cfg.m_p), abar, out, accumulate, order, queue, ntiles,
         nsplit, skip);
     CUBE2_LAUNCH_CHECK();
@@ -705,11 +774,14 @@ int launch_pp_kernel(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, in
                      const float *abar, float *out, int accumulate, unsigned char *work,
                      const WorkLayout &L, hipStream_t s, float grid_frac = 1.0f,
                      const uint8_t *skip = nullptr) {
+    auto go = [&](auto launch) {
+        return launch(ctx, pos, cs, n, abar, out, accumulate, work, L, s, grid_frac, skip);
+    };
     if (ctx->pp_halo == 1)
-        return launch_pp_kernel_h<ADJ, 1>(ctx, pos, cs, n, abar, out, accumulate, work, L, s,
-                                          grid_frac, skip);
-    return launch_pp_kernel_h<ADJ, 2>(ctx, pos, cs, n, abar, out, accumulate, work, L, s,
-                                      grid_frac, skip);
+        return ctx->pp_clamp ? go(launch_pp_kernel_h<ADJ, 1, true>)
+                             : go(launch_pp_kernel_h<ADJ, 1, false>);
+    return ctx->pp_clamp ? go(launch_pp_kernel_h<ADJ, 2, true>)
+                         : go(launch_pp_kernel_h<ADJ, 2, false>);
 }
 
 __global__ void add3_kernel(float *__restrict__ acc, const float *__restrict__ b, int64_t m) {
@@ -809,62 +881,51 @@ int launch_pp_backward(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, 
 
 }  // namespace cube2
 
-extern "C" int cube2_pair_law_f32(const cube2_ctx *ctx, const float *d, float *g, int64_t n) {
+namespace {
+
+// The operations of pair_accumulate and pair_adjoint up to g (and 2 g_s),
+// in the same order, for one separation in fine cells; false if it lies
+// beyond the staged box's reach of 2 (halo + 1) fine cells per axis.
+bool pair_law_host(const cube2_ctx *ctx, bool adj, float dx, float dy, float dz, float *g,
+                   float *gs2) {
     using namespace cube2;
+    const float lim = 2.0f * (float)(ctx->pp_halo + 1), ps = ctx->pp_pscale;
+    if (!(std::fabs(dx) < lim && std::fabs(dy) < lim && std::fabs(dz) < lim)) return false;
+    dx *= ps;
+    dy *= ps;
+    dz *= ps;
+    const float s = std::fmaf(dz, dz, std::fmaf(dy, dy, std::fmaf(dx, dx, kPairS0)));
+    uint32_t b;
+    std::memcpy(&b, &s, 4);
+    if (ctx->pp_clamp) b = std::min(b, adj ? ctx->pp_bmax_adj : ctx->pp_bmax);
+    const int mant = adj ? kSMantAdj : kSMant;
+    const float *c = &(adj ? ctx->pp_arows : ctx->pp_srows)[(size_t)row_place(b, mant) * 4];
+    const float y = std::fmaf(s, 0.1f, c[3]);
+    const float t = std::fmaf(c[2], y, c[1]);
+    const float l = std::fmin(std::fmax(std::fmaf(t, y, c[0]), 0.0f), 1.0f);
+    const float l2 = l * l, l4 = l2 * l2;
+    *g = (l4 * l) * ctx->pp_unit;
+    *gs2 = (l4 * std::fmaf(c[2], y, t)) * (ctx->pp_unit * ps * ps);
+    return true;
+}
+
+}  // namespace
+
+extern "C" int cube2_pair_law_f32(const cube2_ctx *ctx, const float *d, float *g, int64_t n) {
     if (!ctx || n < 0 || (n > 0 && (!d || !g))) return CUBE2_EINVAL;
     for (int64_t i = 0; i < n; ++i) {
-        const float dx = d[i], dy = d[n + i], dz = d[2 * n + i];
-        // the staged box's reach: below 2 (halo + 1) fine cells per axis
-        const float lim = 2.0f * (float)(ctx->pp_halo + 1);
-        if (!(std::fabs(dx) < lim && std::fabs(dy) < lim && std::fabs(dz) < lim))
-            return CUBE2_EINVAL;
-        // the operations of pair_accumulate, in the same order
-        const float s = std::fmaf(dz, dz, std::fmaf(dy, dy, std::fmaf(dx, dx, 0x1p-31f)));
-        uint32_t b;
-        std::memcpy(&b, &s, 4);
-        const float *c = &ctx->pp_srows[(size_t)((b >> (23 - kSMantBits)) - kSRow0) * 4];
-        const uint32_t zb = (b & ((1u << (23 - kSMantBits)) - 1u)) | 0x3F800000u;
-        float z;
-        std::memcpy(&z, &zb, 4);
-        z -= 1.0f;
-        const float h = std::fmaf(std::fmaf(std::fmaf(c[3], z, c[2]), z, c[1]), z, c[0]);
-        const float w = std::fmin(std::fmax(std::fmaf(s, ctx->pp_negc, 1.0f), 0.0f), 1.0f);
-        const float w2 = w * w;
-        g[i] = h * (w2 * w2);
+        float gs2;
+        if (!pair_law_host(ctx, false, d[i], d[n + i], d[2 * n + i], &g[i], &gs2)) return CUBE2_EINVAL;
     }
     return CUBE2_OK;
 }
 
 extern "C" int cube2_pair_jacobian_f32(const cube2_ctx *ctx, const float *d, float *g, float *gs,
                                        int64_t n) {
-    using namespace cube2;
     if (!ctx || n < 0 || (n > 0 && (!d || !g || !gs))) return CUBE2_EINVAL;
     for (int64_t i = 0; i < n; ++i) {
-        const float dx = d[i], dy = d[n + i], dz = d[2 * n + i];
-        // the staged box's reach: below 2 (halo + 1) fine cells per axis
-        const float lim = 2.0f * (float)(ctx->pp_halo + 1);
-        if (!(std::fabs(dx) < lim && std::fabs(dy) < lim && std::fabs(dz) < lim))
-            return CUBE2_EINVAL;
-        // the operations of pair_adjoint, in the same order
-        const float s = std::fmaf(dz, dz, std::fmaf(dy, dy, std::fmaf(dx, dx, 0x1p-31f)));
-        uint32_t b;
-        std::memcpy(&b, &s, 4);
-        const float *c = &ctx->pp_srows[(size_t)((b >> (23 - kSMantBits)) - kSRow0) * 4];
-        const uint32_t zb = (b & ((1u << (23 - kSMantBits)) - 1u)) | 0x3F800000u;
-        const uint32_t eb = 0x7F800000u - (b & 0x7F800000u);
-        float z, inv2e2;
-        std::memcpy(&z, &zb, 4);
-        std::memcpy(&inv2e2, &eb, 4);
-        z -= 1.0f;
-        float h = std::fmaf(c[3], z, c[2]);
-        float hz = std::fmaf(c[3], z, h);
-        h = std::fmaf(h, z, c[1]);
-        hz = std::fmaf(hz, z, h);
-        h = std::fmaf(h, z, c[0]);
-        const float w = std::fmin(std::fmax(std::fmaf(s, ctx->pp_negc, 1.0f), 0.0f), 1.0f);
-        const float w2 = w * w;
-        g[i] = h * (w2 * w2);
-        gs[i] = 0.5f * ((w2 * w) * std::fmaf(hz * inv2e2, w, (8.0f * ctx->pp_negc) * h));
+        if (!pair_law_host(ctx, true, d[i], d[n + i], d[2 * n + i], &g[i], &gs[i])) return CUBE2_EINVAL;
+        gs[i] *= 0.5f;
     }
     return CUBE2_OK;
 }
