@@ -52,6 +52,10 @@ constexpr int kSMantAdj = 7;       // adjoint: 128 rows per octave
 constexpr int kSOctaves = 32;
 constexpr int kSRows = 20 << kSMant;         // rows held (20 octaves)
 constexpr int kSRowsAdj = 20 << kSMantAdj;
+// Light tiles of the PP kernels (pp.hip): most z-layers of a tile's cells that
+// a wave takes at once, and how many particles their box may hold.
+constexpr int kPPLightLayers = 2;
+constexpr int kPPLightCap = 520, kPPLightCapAdj = 512;
 }  // namespace cube2
 
 struct cube2_ctx {
@@ -439,8 +443,12 @@ int launch_fx_to_f64(uint64_t *buf, int64_t m, double unit, hipStream_t s);
 int launch_interp(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,
                   const float *phi_f, const float *phi_c, float *acc, int accumulate,
                   hipStream_t s);
+// light_cap > 0: the PP kernels' order, with the light tiles (every box of
+// kPPLightLayers cell layers holds at most light_cap particles) last;
+// *n_heavy receives the device address of the number of the others.
 int launch_order_tiles(cube2_ctx *ctx, const uint32_t *cs, unsigned char *work,
-                       const WorkLayout &L, hipStream_t s);
+                       const WorkLayout &L, hipStream_t s, int light_cap = 0,
+                       const uint32_t **n_heavy = nullptr);
 int launch_reset_tile_queue(cube2_ctx *ctx, unsigned char *work, const WorkLayout &L,
                             hipStream_t s);
 // Device-wide exclusive scan of m uint32 (in may equal out); tmp: the
@@ -466,6 +474,14 @@ inline const uint32_t *tile_order_ptr(unsigned char *work, const WorkLayout &L) 
 }
 inline uint32_t *tile_queue_ptr(const cube2_ctx *ctx, unsigned char *work, const WorkLayout &L) {
     return reinterpret_cast<uint32_t *>(work + L.tile_order) + 4 * (size_t)ctx->nt * ctx->nt * ctx->nt;
+}
+
+// The light tiles' work counters of the PP kernels, 8 of them 128 bytes apart:
+// in the part of the tile order region that the sort no longer needs (the keys
+// and values before it).  Meshes of fewer tiles than kLightQueueWords use none.
+constexpr int kLightQueueWords = 8 * 32;
+inline uint32_t *light_tile_queue_ptr(const cube2_ctx *ctx, unsigned char *work, const WorkLayout &L) {
+    return reinterpret_cast<uint32_t *>(work + L.tile_order) + (size_t)ctx->nt * ctx->nt * ctx->nt;
 }
 
 // Workgroups of `kernel` (block threads, no dynamic LDS) that fit on the

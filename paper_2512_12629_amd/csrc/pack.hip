@@ -257,6 +257,50 @@ __global__ void tile_keys_kernel(const uint32_t *__restrict__ cs, int nt, uint32
     vals[b] = t;
 }
 
+// The same for the PP kernels, one wave per tile: light tiles get the last
+// key, the others 254 less their thousands.  A tile is light if each of its
+// boxes of kPPLightLayers layers of cells and the halo holds at most light_cap
+// particles.
+__global__ void pp_tile_keys_kernel(const uint32_t *__restrict__ cs, int nt, uint32_t light_cap,
+                                    uint32_t *__restrict__ keys, uint32_t *__restrict__ vals) {
+    const int ntiles = nt * nt * nt;
+    const int b = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
+    const int lane = threadIdx.x & 63;
+    if (b >= ntiles) return;
+    int tx, ty, tz;
+    tile_of_block(b, nt, tx, ty, tz);
+    const uint32_t t = (uint32_t)((tz * nt + ty) * nt + tx);
+    const int n_ios = nt * kTileIos;
+    constexpr int NB = kTileIos / kPPLightLayers;
+    uint32_t sum[NB] = {};
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {            // the 100 x-rows of the 10^3 box
+        const int r = lane + 64 * k;
+        if (r >= 100) break;
+        const int by = r % 10, bz = r / 10;
+        const int cy = wrapn(ty * kTileIos + by - 1, n_ios), cz = wrapn(tz * kTileIos + bz - 1, n_ios);
+        const uint32_t a = cell_key(wrapn(tx * kTileIos - 1, n_ios), cy, cz, nt),
+                       m = cell_key(tx * kTileIos, cy, cz, nt),
+                       e = cell_key(wrapn(tx * kTileIos + 8, n_ios), cy, cz, nt);
+        const uint32_t c = (cs[a + 1] - cs[a]) + (cs[m + 8] - cs[m]) + (cs[e + 1] - cs[e]);
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+            if (bz >= i * kPPLightLayers && bz < (i + 1) * kPPLightLayers + 2) sum[i] += c;
+    }
+    uint32_t most = 0;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) sum[i] += (uint32_t)__shfl_xor((int)sum[i], o, 64);
+        most = max(most, sum[i]);
+    }
+    if (lane == 0) {
+        const uint32_t cnt = cs[(t + 1) * kTileCells] - cs[t * kTileCells];
+        keys[b] = most <= light_cap ? 255u : 254u - min(cnt >> 10, 254u);
+        vals[b] = t;
+    }
+}
+
 }  // namespace
 
 int launch_exclusive_scan(const uint32_t *in, uint32_t *out, int64_t m, uint32_t *tmp,
@@ -270,14 +314,18 @@ int launch_exclusive_scan(const uint32_t *in, uint32_t *out, int64_t m, uint32_t
 // XCD-slab order.  The tile indices land in the first ntiles words of the
 // tile_order region; the work counter (tile_queue_ptr) is reset to zero.
 int launch_order_tiles(cube2_ctx *ctx, const uint32_t *cs, unsigned char *work,
-                       const WorkLayout &L, hipStream_t s) {
+                       const WorkLayout &L, hipStream_t s, int light_cap,
+                       const uint32_t **n_heavy) {
     const int nt = ctx->nt;
     const int ntiles = nt * nt * nt;
     uint32_t *base = reinterpret_cast<uint32_t *>(work + L.tile_order);
     uint32_t *order = base, *vin = base + ntiles, *kin = base + 2 * ntiles, *kout = base + 3 * ntiles;
     uint32_t *tmp = reinterpret_cast<uint32_t *>(work + L.scan_tmp);
     uint32_t *ghist = reinterpret_cast<uint32_t *>(work + L.hist);
-    tile_keys_kernel<<<(ntiles + 255) / 256, 256, 0, s>>>(cs, nt, kin, vin);
+    if (light_cap > 0)
+        pp_tile_keys_kernel<<<(ntiles + 3) / 4, 256, 0, s>>>(cs, nt, (uint32_t)light_cap, kin, vin);
+    else
+        tile_keys_kernel<<<(ntiles + 255) / 256, 256, 0, s>>>(cs, nt, kin, vin);
     CUBE2_LAUNCH_CHECK();
     const int nblk = (ntiles + kSortTile - 1) / kSortTile;
     radix_count<<<nblk, kBlock, 0, s>>>(kin, ntiles, 0, nblk, ghist);
@@ -286,6 +334,11 @@ int launch_order_tiles(cube2_ctx *ctx, const uint32_t *cs, unsigned char *work,
     if (r) return r;
     radix_scatter<<<nblk, kBlock, 0, s>>>(kin, vin, kout, order, ntiles, 0, nblk, ghist);
     CUBE2_LAUNCH_CHECK();
+    if (light_cap > 0 && ntiles >= kLightQueueWords) {
+        fill_u32<<<1, kLightQueueWords, 0, s>>>(light_tile_queue_ptr(ctx, work, L), 0u, kLightQueueWords);
+        CUBE2_LAUNCH_CHECK();
+    }
+    if (n_heavy) *n_heavy = ghist + (size_t)255 * nblk;   // start of the last key's first block
     return launch_reset_tile_queue(ctx, work, L, s);
 }
 

@@ -43,6 +43,26 @@ template <bool ADJ, int H> struct PPGeo {
     static constexpr int CAP = ADJ ? (H == 1 ? 4800 : 4656) : (H == 1 ? 3376 : 3152);
     static constexpr int SEG_PER_THREAD = (PPBox<H>::SEGS + BLOCK - 1) / BLOCK;
     static constexpr int ROWS = ADJ ? kSRowsAdj : kSRows;
+    // bytes of the workgroup-wide arrays (LDS offsets of the kernel below)
+    static constexpr int XA = CAP * 16, PRE = XA + (ADJ ? CAP * 8 : 0),
+                         DELTA = PRE + (PPBox<H>::SEGS + 1) * 4,
+                         CST = DELTA + PPBox<H>::PB * PPBox<H>::PB * 3 * 4,
+                         SCAN = CST + (kTileCells + 1) * 4, TILE = SCAN + (BLOCK / 64 + 1) * 4,
+                         BYTES = TILE + 8;
+};
+
+// The light tiles' form (one-cell reach): waves work on their own, each with
+// its own slice of the LDS.  LAYERS z-layers of a tile's cells per item at
+// most, LCAP staged particles (forward: x, y and z in arrays of their own, 12
+// bytes per particle).
+template <bool ADJ> struct PPLight {
+    static constexpr int WAVES = ADJ ? 9 : 8;
+    static constexpr int LAYERS = kPPLightLayers;
+    static constexpr int SEGS = 100 * (LAYERS + 2);
+    static constexpr int LCAP = ADJ ? kPPLightCapAdj : kPPLightCap;
+    static constexpr int XA = LCAP * (ADJ ? 16 : 12), DELTA = LCAP * (ADJ ? 24 : 12),
+                         OWN = DELTA + 30 * (LAYERS + 2) * 4, PRE = OWN + 8 * LAYERS * 4,
+                         BYTES = (int)((PRE + (SEGS + 1) * 2 + 15) / 16 * 16);
 };
 
 }  // namespace
@@ -174,11 +194,7 @@ __device__ __forceinline__ void pair_adjoint(float dx, float dy, float dz, float
 // alone; each particle's sum is still formed by one thread in the same
 // order.  (Splitting four tiles per workgroup was slower: every part
 // stages the box again.)
-// The two-cell reach (b_f > 2) keeps whole tiles: it has ~5x the pairs per
-// tile, so its tiles are not few per workgroup, and the split's bookkeeping
-// would take it past 128 VGPRs (one workgroup per CU instead of two).
 constexpr int kSplitParts = 8, kSplitTiles = 128;
-template <int H> constexpr int split_parts() { return kSplitParts; }
 
 // The pair law's units (see above): ps = 2^j and its product with the 2^-15 of
 // a position unit, the scale of the sums (unit, and for the forward D's
@@ -187,6 +203,253 @@ struct PPLaw {
     float ps, ips, unit;
     uint32_t bmax;
 };
+
+// The pairs of one particle with the staged neighbours [v0, v1): two per trip.
+template <bool ADJ, bool CLAMP>
+__device__ __forceinline__ void light_row(const unsigned char *base, uint32_t v0, uint32_t v1, float xi,
+                                          float yi, float zi, float aix, float aiy, float aiz,
+                                          uint32_t bmax, float &fx, float &fy, float &fz) {
+    using P = PPLight<ADJ>;
+    if constexpr (ADJ) {
+        const float4 *q = reinterpret_cast<const float4 *>(base);
+        const float2 *qa = reinterpret_cast<const float2 *>(base + P::XA);
+        for (; v0 + 1 < v1; v0 += 2) {
+            const float4 x = q[v0], y = q[v0 + 1];
+            const float2 a = qa[v0], b = qa[v0 + 1];
+            pair_adjoint<CLAMP>(x.x - xi, x.y - yi, x.z - zi, x.w - aix, a.x - aiy, a.y - aiz, bmax,
+                                fx, fy, fz);
+            pair_adjoint<CLAMP>(y.x - xi, y.y - yi, y.z - zi, y.w - aix, b.x - aiy, b.y - aiz, bmax,
+                                fx, fy, fz);
+        }
+        if (v0 < v1) {
+            const float4 x = q[v0];
+            const float2 a = qa[v0];
+            pair_adjoint<CLAMP>(x.x - xi, x.y - yi, x.z - zi, x.w - aix, a.x - aiy, a.y - aiz, bmax,
+                                fx, fy, fz);
+        }
+    } else {
+        const float *x = reinterpret_cast<const float *>(base), *y = x + P::LCAP, *z = y + P::LCAP;
+        for (; v0 + 1 < v1; v0 += 2) {
+            const float x0 = x[v0], x1 = x[v0 + 1], y0 = y[v0], y1 = y[v0 + 1], z0 = z[v0], z1 = z[v0 + 1];
+            pair_accumulate<CLAMP>(x0 - xi, y0 - yi, z0 - zi, kPairS0, bmax, fx, fy, fz);
+            pair_accumulate<CLAMP>(x1 - xi, y1 - yi, z1 - zi, kPairS0, bmax, fx, fy, fz);
+        }
+        if (v0 < v1) pair_accumulate<CLAMP>(x[v0] - xi, y[v0] - yi, z[v0] - zi, kPairS0, bmax, fx, fy, fz);
+    }
+}
+
+// LDS stores of this wave are visible to its own later loads (the LDS serves
+// a wave in order; this keeps the compiler from reordering them).
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Light tiles (few particles in every box, see pp_tile_keys_kernel), each wave
+// by itself: `layers` z-layers of a tile's cells per item, 64 own particles at
+// a time, the box of 10 x 10 x (layers + 2) cells staged in the wave's slice
+// of the LDS.  A whole workgroup per such tile spent most of its time waiting:
+// ~500 particles have ~27 candidates each, and between the tile's claim and
+// its first pair lay four dependent memory accesses and seven barriers.  Waves
+// with an item each overlap these chains without a barrier, and the adjoint's
+// 1024-thread workgroup no longer idles half its threads.  What bounds it now
+// is the LDS: the reads of the pair loop, whose lanes are in different cells.
+// Measured without halos: 480^3 particles on 1024^3 5.5 -> 4.6 ms (adjoint
+// 14.3 -> 7.8), 128^3 on 256^3 148 -> 124 us (266 -> 185).  Positions as
+// 16-byte words, with room for 7 waves instead of 8: 4.7 ms and 133 us.
+template <bool ADJ, bool CLAMP>
+__device__ __forceinline__ void light_tiles(unsigned char *lds, const uint16_t *__restrict__ pos,
+                                            const uint32_t *__restrict__ cs, int n, int nt,
+                                            const PPLaw &law, float gm, const float *__restrict__ abar,
+                                            float *__restrict__ acc, int accumulate,
+                                            const uint32_t *__restrict__ order,
+                                            uint32_t *__restrict__ queue, int ntiles, int layers,
+                                            const uint8_t *__restrict__ skip) {
+    using P = PPLight<ADJ>;
+    constexpr int PER = (P::SEGS + 63) / 64;       // box cells per lane
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lane = (int)(threadIdx.x & 63);
+    if (wave >= P::WAVES) return;
+    unsigned char *const base = lds + wave * P::BYTES;
+    float *const x = reinterpret_cast<float *>(base);
+    uint32_t *const delta = reinterpret_cast<uint32_t *>(base + P::DELTA);
+    uint32_t *const ownp = reinterpret_cast<uint32_t *>(base + P::OWN);   // first particle of each own row
+    uint16_t *const pre = reinterpret_cast<uint16_t *>(base + P::PRE);
+    const int n_ios = nt * kTileIos;
+    const float ps = law.ps, ips = law.ips;
+    const int per_tile = kTileIos / layers;
+    const int ncell = 100 * (layers + 2), nown = 8 * layers;
+    auto part_of = [](int bx) { return bx < 1 ? 0 : (bx < 1 + kTileIos ? 1 : 2); };
+    // Workgroups b = g (mod 8) run on one XCD; they take every 8th tile of the
+    // order, which is the XCD's slab of the mesh (tile_of_block).  A wave's
+    // first chunk of items is its number among the group's waves; the next ones
+    // come from the group's counter, or, with up to 4 items per wave, at fixed
+    // strides: one atomic counter serves only some 70 million claims a second
+    // (measured, 14-18 ns each), too few for one claim per item.
+    const int ng = gridDim.x >= 8 ? 8 : 1, g = (int)blockIdx.x % ng;
+    const int gx = ((int)gridDim.x - g + ng - 1) / ng;                // workgroups of the group
+    const int nw = gx * P::WAVES;
+    const int nitems = ntiles > g ? (ntiles - g + ng - 1) / ng * per_tile : 0;
+    const bool fixed = nitems <= 4 * nw || nt * nt * nt < kLightQueueWords;
+    const int chunk = fixed ? 1 : min(nitems / (2 * nw), 64);
+    int next = wave * gx + (int)blockIdx.x / ng, item = 0, end = 0;
+    for (;;) {
+        if (item >= end) {
+            const int c = __builtin_amdgcn_readfirstlane(next);
+            if (c >= (nitems + chunk - 1) / chunk) break;
+            item = c * chunk;
+            end = min(item + chunk, nitems);
+            if (fixed)
+                next = c + nw;
+            else if (lane == 0)
+                next = nw + (int)min(atomicAdd(queue + 32 * g, 1u), 0x3FFFFFFFu);
+        }
+        const int t = (int)order[item / per_tile * ng + g], zp = item % per_tile;
+        ++item;
+        if (skip && skip[t]) continue;
+        const int tx = t % nt, ty = (t / nt) % nt, tz = t / (nt * nt);
+        const int c0x = tx * kTileIos - 1, c0y = ty * kTileIos - 1,
+                  c0z = tz * kTileIos - 1 + zp * layers;
+        wave_fence();       // the previous item's loads come first
+        // particle ranges of the box cells, PER consecutive ones per lane
+        uint32_t src[PER], cnt[PER], sum = 0;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int s = min(lane * PER + k, ncell - 1);
+            const int r = s / 10, bx = s - r * 10, bz = r / 10, by = r - bz * 10;
+            const uint32_t key = cell_key(wrapn(c0x + bx, n_ios), wrapn(c0y + by, n_ios),
+                                          wrapn(c0z + bz, n_ios), nt);
+            src[k] = cs[key];
+            cnt[k] = cs[key + 1];
+        }
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            cnt[k] = lane * PER + k < ncell ? cnt[k] - src[k] : 0u;
+            sum += cnt[k];
+        }
+        uint32_t at = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_up(at, o, 64);
+            if (lane >= o) at += y;
+        }
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)at, 63);
+        at -= sum;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int s = lane * PER + k;
+            if (s < ncell) {
+                const int r = s / 10, bx = s - r * 10;
+                pre[s] = (uint16_t)at;
+                if (bx <= 1 || bx == 9) delta[r * 3 + part_of(bx)] = src[k] - at;
+            }
+            at += cnt[k];
+        }
+        for (int s = ncell + lane; s <= P::SEGS; s += 64) pre[s] = (uint16_t)total;
+        wave_fence();
+        if (lane < nown) {   // own rows: box layers 1..layers, y 1..8, x 1..8
+            const int r = (1 + (lane >> 3)) * 10 + 1 + (lane & 7);
+            ownp[lane] = pre[r * 10 + 1] + delta[r * 3 + 1];
+        }
+        // stage, four particles per lane at a time
+        constexpr int kStage = 4;
+        for (uint32_t v0 = (uint32_t)lane; v0 < total; v0 += 64 * kStage) {
+            int u[kStage];
+            uint32_t p[kStage], o[kStage][3];
+            float ab[kStage][3];
+#pragma unroll
+            for (int k = 0; k < kStage; ++k) {
+                const uint32_t v = min(v0 + 64 * k, total - 1);   // past the end: the last again
+                int lo = 0;
+#pragma unroll
+                for (int step = 256; step > 0; step >>= 1) {
+                    const int c = min(lo + step, P::SEGS);
+                    if (pre[c] <= v && c < P::SEGS) lo = c;
+                }
+                u[k] = lo;
+                const int r = lo / 10;
+                p[k] = v + delta[r * 3 + part_of(lo - r * 10)];
+            }
+#pragma unroll
+            for (int k = 0; k < kStage; ++k) {
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    o[k][d] = pos[(int64_t)d * n + p[k]];
+                    if (ADJ) ab[k][d] = abar[(int64_t)d * n + p[k]];
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < kStage; ++k) {
+                const uint32_t v = min(v0 + 64 * k, total - 1);
+                const int r = u[k] / 10, bx = u[k] - r * 10, bz = r / 10, by = r - bz * 10;
+                const float qx = (float)(2 * (bx - 1)) * ps + (float)o[k][0] * ips,
+                            qy = (float)(2 * (by - 1)) * ps + (float)o[k][1] * ips,
+                            qz = (float)(2 * (bz - 1)) * ps + (float)o[k][2] * ips;
+                if constexpr (ADJ) {
+                    reinterpret_cast<float4 *>(base)[v] = make_float4(qx, qy, qz, ab[k][0]);
+                    reinterpret_cast<float2 *>(base + P::XA)[v] = make_float2(ab[k][1], ab[k][2]);
+                } else {
+                    x[v] = qx;
+                    x[P::LCAP + v] = qy;
+                    x[2 * P::LCAP + v] = qz;
+                }
+            }
+        }
+        wave_fence();
+        const int rl = layers * 10 + 8;      // last own row
+        const uint32_t p1 = pre[rl * 10 + 9] + delta[rl * 3 + 1];
+        for (uint32_t p = ownp[0] + lane; p < p1; p += 64) {
+            int i = 0;
+#pragma unroll
+            for (int step = P::LAYERS * 4; step > 0; step >>= 1)
+                if (i + step < nown && ownp[i + step] <= p) i += step;
+            const int r = (1 + (i >> 3)) * 10 + 1 + (i & 7);
+            const uint32_t v = p - delta[r * 3 + 1];
+            int c = r * 10 + 1;
+#pragma unroll
+            for (int step = 4; step > 0; step >>= 1)
+                if (pre[c + step] <= v) c += step;
+            float xi, yi, zi, aix = 0.f, aiy = 0.f, aiz = 0.f;
+            if constexpr (ADJ) {
+                const float4 q = reinterpret_cast<const float4 *>(base)[v];
+                const float2 a = reinterpret_cast<const float2 *>(base + P::XA)[v];
+                xi = q.x;
+                yi = q.y;
+                zi = q.z;
+                aix = q.w;
+                aiy = a.x;
+                aiz = a.y;
+            } else {
+                xi = x[v];
+                yi = x[P::LCAP + v];
+                zi = x[2 * P::LCAP + v];
+            }
+            uint32_t v0[9], v1[9];
+#pragma unroll
+            for (int row = 0; row < 9; ++row) {
+                const int sm = c + (row / 3 - 1) * 100 + (row % 3 - 1) * 10;
+                v0[row] = pre[sm - 1];
+                v1[row] = pre[sm + 2];
+            }
+            float sx = 0.f, sy = 0.f, sz = 0.f, cx = 0.f, cy = 0.f, cz = 0.f;
+#pragma unroll
+            for (int row = 0; row < 9; ++row) {
+                float fx = 0.f, fy = 0.f, fz = 0.f;
+                light_row<ADJ, CLAMP>(base, v0[row], v1[row], xi, yi, zi, aix, aiy, aiz, law.bmax, fx,
+                                      fy, fz);
+                kahan_add(sx, cx, fx);
+                kahan_add(sy, cy, fy);
+                kahan_add(sz, cz, fz);
+            }
+            const float a[3] = {gm * (sx * law.unit), gm * (sy * law.unit), gm * (sz * law.unit)};
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                float *dst = acc + (int64_t)d * n + p;
+                *dst = accumulate ? *dst + a[d] : a[d];
+            }
+        }
+    }
+}
 
 // ADJ = false: acc = G m sum_j g D (forward).  ADJ = true: out = G m sum_j
 // J(D) (abar_j - abar_i) for the cotangent abar (the adjoint), which stages
@@ -200,25 +463,31 @@ __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK), 4) void pp_kernel(const uin
                                                      float *__restrict__ acc, int accumulate,
                                                      const uint32_t *__restrict__ order,
                                                      uint32_t *__restrict__ queue, int ntiles,
-                                                     int nsplit,
-                                                     const uint8_t *__restrict__ skip) {
+                                                     int nsplit, const uint32_t *__restrict__ n_heavy,
+                                                     uint32_t *__restrict__ light_queue,
+                                                     int layers, const uint8_t *__restrict__ skip) {
+    using G = PPGeo<ADJ, H>;
     constexpr int CAP = PPGeo<ADJ, H>::CAP;
     constexpr int kPPBlock = PPGeo<ADJ, H>::BLOCK;
     constexpr int kPSegPerThread = PPGeo<ADJ, H>::SEG_PER_THREAD;
     constexpr int kPB = PPBox<H>::PB, kPSegs = PPBox<H>::SEGS, kW = PPBox<H>::W;
-    __shared__ uint32_t seg_pre[kPSegs + 1];
+    // one arena: the workgroup's arrays, then the waves' slices of the light tiles
+    constexpr int kArena = H == 1 && PPLight<ADJ>::WAVES * PPLight<ADJ>::BYTES > G::BYTES
+                               ? PPLight<ADJ>::WAVES * PPLight<ADJ>::BYTES : G::BYTES;
+    __shared__ __align__(16) unsigned char lds[kArena];
+    // staged particles: position and s0, or for the adjoint position and
+    // cotangent (x, y, z, ax; ay, az)
+    float4 *const xs = reinterpret_cast<float4 *>(lds);
+    float2 *const xa = reinterpret_cast<float2 *>(lds + G::XA);
+    uint32_t *const seg_pre = reinterpret_cast<uint32_t *>(lds + G::PRE);
     // An x-row of the box crosses three tiles (H, 8 and H cells), and a tile's
     // x-consecutive cells are consecutive in the particle order: particle =
     // staged index + seg_delta of the row's part
-    __shared__ uint32_t seg_delta[kPB * kPB * 3];
-    // staged particles: position and s0, or for the adjoint position and
-    // cotangent (x, y, z, ax; ay, az)
-    __shared__ float4 xs[CAP];
-    __shared__ float2 xa[ADJ ? CAP : 1];
-    __shared__ uint32_t cst[kTileCells + 1];     // own cells: particle starts (tile-relative)
-    __shared__ uint32_t scan_sh[kPPBlock / 64 + 1];
-    __shared__ int tile_sh;
-    __shared__ uint32_t maxcnt_sh;
+    uint32_t *const seg_delta = reinterpret_cast<uint32_t *>(lds + G::DELTA);
+    uint32_t *const cst = reinterpret_cast<uint32_t *>(lds + G::CST);   // own cells: tile-relative starts
+    uint32_t *const scan_sh = reinterpret_cast<uint32_t *>(lds + G::SCAN);
+    int &tile_sh = *reinterpret_cast<int *>(lds + G::TILE);
+    uint32_t &maxcnt_sh = *reinterpret_cast<uint32_t *>(lds + G::TILE + 4);
 
     const int tid = threadIdx.x;
     const int n_ios = nt * kTileIos;
@@ -233,8 +502,10 @@ __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK), 4) void pp_kernel(const uin
     // is block-uniform).  Thread 0 claims the next item while the current
     // one is processed.  Items [0, nsplit kSplitParts) are the parts of the
     // nsplit heaviest tiles, the rest one whole tile each.
-    constexpr int kParts = split_parts<H>();
-    const int nitems = ntiles + nsplit * (kParts - 1);
+    constexpr int kParts = kSplitParts;
+    const int nheavy = H == 1 ? (int)*n_heavy : ntiles;
+    nsplit = min(nsplit, nheavy);
+    const int nitems = nheavy + nsplit * (kParts - 1);
     const int split_items = nsplit * kParts;
     int next = 0;
     if (tid == 0) next = claim_slot(queue, nitems);
@@ -247,7 +518,7 @@ __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK), 4) void pp_kernel(const uin
         const int item = __builtin_amdgcn_readfirstlane(tile_sh);   // block-uniform
         if (item >= nitems) break;
         if (tid == 0) next = claim_slot(queue, nitems);
-        const bool split = kParts > 1 && item < split_items;
+        const bool split = item < split_items;
         const int ti = split ? item / kParts : item - split_items + nsplit;
         const int part = split ? item % kParts : 0;
         const int t = (int)order[ti];
@@ -349,7 +620,7 @@ __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK), 4) void pp_kernel(const uin
                 const uint32_t ve = min(vb + (uint32_t)CAP, V1);
                 if (!staged) {
                     if (!single) __syncthreads();   // the previous chunk is done with xs
-                    if (!ADJ && single && maxcnt <= 4) {
+                    if (!ADJ && H == 2 && single && maxcnt <= 4) {
                         // sparse box: every thread copies the particles of its own
                         // segments (at most 4 each), no search needed; one segment at
                         // a time keeps the register footprint of the staging small
@@ -511,6 +782,11 @@ __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK), 4) void pp_kernel(const uin
             }
         }
         __syncthreads();  // this tile is done with the LDS arrays
+    }
+    if constexpr (H == 1) {
+        __syncthreads();  // every thread has left the queue
+        light_tiles<ADJ, CLAMP>(lds, pos, cs, n, nt, law, gm, abar, acc, accumulate, order + nheavy,
+                                light_queue, ntiles - nheavy, layers, skip);
     }
 }
 
@@ -738,6 +1014,10 @@ int build_pair_table(cube2_ctx *ctx) {
 
 namespace {
 
+// Meshes with at most so many tiles have fewer two-layer items than the chip
+// has waves (256 CUs x 16).
+constexpr int kOneLayerTiles = 1024;
+
 template <bool ADJ, int H, bool CLAMP>
 int launch_pp_kernel_h(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,
                      const float *abar, float *out, int accumulate, unsigned char *work,
@@ -752,19 +1032,25 @@ int launch_pp_kernel_h(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, 
     law.bmax = ADJ ? ctx->pp_bmax_adj : ctx->pp_bmax;
     const int nt = ctx->nt;
     const int ntiles = nt * nt * nt;
-    int r = launch_order_tiles(ctx, cs, work, L, s);
+    // with the one-cell reach the light tiles come last in the order, and the
+    // scanned digit counts say where they begin
+    const int lcap = H == 1 ? PPLight<ADJ>::LCAP : 0;
+    const uint32_t *n_heavy = nullptr;
+    int r = launch_order_tiles(ctx, cs, work, L, s, lcap, &n_heavy);
     if (r) return r;
     const uint32_t *order = tile_order_ptr(work, L);
     uint32_t *queue = tile_queue_ptr(ctx, work, L);
     auto k = pp_kernel<ADJ, H, CLAMP>;
-    const int nsplit = split_parts<H>() > 1 ? std::min(kSplitTiles, ntiles) : 0;
-    const int nitems = ntiles + nsplit * (split_parts<H>() - 1);
+    const int nsplit = std::min(kSplitTiles, ntiles);
+    const int nitems = ntiles + nsplit * (kSplitParts - 1);
+    // one z-layer of cells per light item where there are few of them
+    const int layers = ntiles <= kOneLayerTiles ? 1 : PPLight<ADJ>::LAYERS;
     const unsigned grid = std::max(
         1u, (unsigned)((float)persistent_grid(k, PPGeo<ADJ, H>::BLOCK, nitems) * grid_frac));
     k<<<grid, PPGeo<ADJ, H>::BLOCK, 0, s>>>(
         pos, cs, (int)n, nt, table, law,
         (float)(ctx->cfg.g_newton * ctx->cfg.m_p), abar, out, accumulate, order, queue, ntiles,
-        nsplit, skip);
+        nsplit, n_heavy, light_tile_queue_ptr(ctx, work, L), layers, skip);
     CUBE2_LAUNCH_CHECK();
     return CUBE2_OK;
 }
