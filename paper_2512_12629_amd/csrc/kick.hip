@@ -11,51 +11,408 @@
 // displacement is not finite (a non-finite acceleration or velocity, or a
 // displacement beyond 2^62 units) is not moved, and the status word records
 // it (cube2_status then returns CUBE2_ENONFINITE).
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace cube2 {
 namespace {
 
+// One particle of IOS cell (cx, cy, cz) kicked and drifted: its new cell,
+// offsets and velocity; bad is set if it could not be moved.
+__device__ __forceinline__ void drifted(const uint16_t *__restrict__ pos, const float *__restrict__ vel,
+                                        const float *__restrict__ acc, int n, uint32_t p, int cx, int cy,
+                                        int cz, int n_f, double kick, double drift, int (&c)[3],
+                                        uint16_t (&o)[3], float (&v)[3], bool &bad) {
+#pragma clang fp contract(off)
+    const int64_t mask = ((int64_t)n_f << kFracBits) - 1;   // a power of two less one
+    const int uc[3] = {cx, cy, cz};
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const int64_t i = (int64_t)d * n + p;
+        const double kv = kick * (double)acc[i];
+        const double v1 = (double)vel[i] + kv;
+        double dq = rint((drift * v1) * 32768.0);
+        if (!(fabs(dq) < 0x1p62)) {   // also NaN: the particle stays where it is
+            dq = 0.0;
+            bad = true;
+        }
+        const int64_t q = (((int64_t)uc[d] << 16) + pos[i] + (int64_t)dq) & mask;
+        c[d] = (int)(q >> 16);
+        o[d] = (uint16_t)(q & 0xFFFF);
+        v[d] = (float)v1;
+    }
+}
+
 __global__ __launch_bounds__(kBlock) void kick_drift_kernel(
     const uint16_t *__restrict__ pos, const uint32_t *__restrict__ cs,
     const float *__restrict__ vel, const float *__restrict__ acc, int n, int nt, int n_f,
     double kick, double drift, uint32_t *__restrict__ keys, uint32_t *__restrict__ vals,
-    uint16_t *__restrict__ offs, uint32_t *__restrict__ status) {
-#pragma clang fp contract(off)
+    uint16_t *__restrict__ offs, uint32_t *__restrict__ status,
+    const uint32_t *__restrict__ run) {
     __shared__ uint32_t cst[kTileCells + 1];
-    int tx, ty, tz;
-    tile_of_block(blockIdx.x, nt, tx, ty, tz);
+    if (run && *run == 0u) return;      // the fallback of the local re-sort, not needed
     const int tid = threadIdx.x;
-    const uint32_t key0 = (uint32_t)((tz * nt + ty) * nt + tx) * kTileCells;
-    stage_cell_starts<kBlock>(cst, cs, key0);
-    __syncthreads();
-    const int64_t span = (int64_t)n_f << kFracBits;
-    const int cbase[3] = {tx * kTileIos, ty * kTileIos, tz * kTileIos};
     bool bad = false;
-    for (uint32_t p = cst[0] + tid; p < cst[kTileCells]; p += kBlock) {
-        const int u = seg_search_n<kTileCells>(cst, p);
-        const int uc[3] = {u & 7, (u >> 3) & 7, u >> 6};
-        int c[3];
+    for (int b = blockIdx.x; b < nt * nt * nt; b += gridDim.x) {
+        int tx, ty, tz;
+        tile_of_block(b, nt, tx, ty, tz);
+        const uint32_t key0 = (uint32_t)((tz * nt + ty) * nt + tx) * kTileCells;
+        stage_cell_starts<kBlock>(cst, cs, key0);
+        __syncthreads();
+        for (uint32_t p = cst[0] + tid; p < cst[kTileCells]; p += kBlock) {
+            const int u = seg_search_n<kTileCells>(cst, p);
+            int c[3];
+            uint16_t o[3];
+            float v1[3];
+            drifted(pos, vel, acc, n, p, tx * kTileIos + (u & 7), ty * kTileIos + ((u >> 3) & 7),
+                    tz * kTileIos + (u >> 6), n_f, kick, drift, c, o, v1, bad);
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            const int64_t i = (int64_t)d * n + p;
-            const double kv = kick * (double)acc[i];
-            const double v1 = (double)vel[i] + kv;
-            double dq = rint((drift * v1) * 32768.0);
-            if (!(fabs(dq) < 0x1p62)) {   // also NaN: the particle stays where it is
-                dq = 0.0;
-                bad = true;
-            }
-            int64_t q = ((int64_t)(cbase[d] + uc[d]) << 16) + pos[i];
-            q = (q + (int64_t)dq) % span;
-            if (q < 0) q += span;
-            c[d] = (int)(q >> 16);
-            offs[i] = (uint16_t)(q & 0xFFFF);
+            for (int d = 0; d < 3; ++d) offs[(int64_t)d * n + p] = o[d];
+            keys[p] = cell_key(c[0], c[1], c[2], nt);
+            vals[p] = p;
         }
-        keys[p] = cell_key(c[0], c[1], c[2], nt);
-        vals[p] = p;
+        __syncthreads();
     }
     if (bad) atomicOr(status, kStatusNonFinite);
+}
+
+// ---------------------------------------------------------------------------
+// The local re-sort: a step moves particles by a fraction of a tile, so a
+// tile's new particles come from itself and its 26 neighbours, and two passes
+// over the particles replace the four passes of the radix sort (each a count
+// and a scatter) and its final gather:
+//   local_split   one workgroup per old tile kicks and drifts its particles
+//                 and writes them, in their order, grouped by the tile they go
+//                 to (27 groups, within the tile's own particle range);
+//   local_starts  the new tiles' particle counts from the groups, scanned;
+//   local_merge   one workgroup per new tile sorts its up to 27 groups, taken
+//                 in the order of their old tiles, stably by cell.
+// Both orders are that of the input, so the result is the stable sort's.  A
+// particle that leaves the 27 tiles sets a flag, and the radix sort runs
+// instead (its kernels are launched either way and end at once if the flag is
+// not set: the host does not wait).  Both passes are bound by HBM, ~100 bytes
+// per particle together; the radix sort moved ~200.
+// ---------------------------------------------------------------------------
+
+constexpr int kDirs = 27;            // (dz + 1) * 9 + (dy + 1) * 3 + dx + 1
+constexpr int kSplitItems = 4;       // particles per thread and chunk
+constexpr int kSplitChunk = kBlock * kSplitItems;
+constexpr int kGroups = kSplitChunk / 64;   // waves' worths per chunk
+
+// new tile minus old on one axis of nt tiles, -1..1 (with two tiles: 0 or 1);
+// 2 if they are not neighbours
+__device__ __forceinline__ int tile_step(int from, int to, int nt) {
+    const int d = (to - from) & (nt - 1);
+    return d == 0 ? 0 : (d == 1 ? 1 : (d == nt - 1 ? -1 : 2));
+}
+
+// tile t + (dx, dy, dz), periodic
+__device__ __forceinline__ int tile_at(int tx, int ty, int tz, int nt) {
+    const int m = nt - 1;
+    return (((tz & m) * nt) + (ty & m)) * nt + (tx & m);
+}
+
+// Moved particles of the old tiles in group order: index, cell in the new tile,
+// offsets and kicked velocity, SoA over n.
+struct Moved {
+    uint32_t *idx;
+    uint16_t *cell, *offs;
+    float *vel;
+};
+
+// pre[t * 28 + d]: first particle of group d relative to the tile's first, [27]
+// the tile's particles; far[t] != 0 if a particle left the 27 tiles.
+__global__ __launch_bounds__(kBlock) void local_split(
+    const uint16_t *__restrict__ pos, const uint32_t *__restrict__ cs,
+    const float *__restrict__ vel, const float *__restrict__ acc, int n, int nt, int n_f,
+    double kick, double drift, Moved out, uint32_t *__restrict__ pre, uint32_t *__restrict__ far,
+    uint32_t *__restrict__ status) {
+    __shared__ uint32_t cst[kTileCells + 1];
+    __shared__ uint32_t cnt[kDirs][kGroups + 1];   // per group of 64 particles, then before it
+    __shared__ uint32_t base[kDirs + 1];           // next slot of each direction
+    __shared__ uint32_t far_sh;
+    int tx, ty, tz;
+    tile_of_block(blockIdx.x, nt, tx, ty, tz);
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const uint32_t t = (uint32_t)((tz * nt + ty) * nt + tx);
+    stage_cell_starts<kBlock>(cst, cs, t * kTileCells);
+    if (tid == 0) far_sh = 0u;
+    if (tid <= kDirs) base[tid] = 0u;
+    __syncthreads();
+    const uint32_t p0 = cst[0], p1 = cst[kTileCells];
+    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    bool bad = false, left = false;
+    // a tile of one chunk keeps its particles in registers between the count
+    // and the write; a denser one counts all its chunks first
+    const bool one = p1 - p0 <= (uint32_t)kSplitChunk;
+    for (int pass = one ? 1 : 0; pass < 2; ++pass) {
+        for (uint32_t c0 = p0; c0 < p1; c0 += kSplitChunk) {
+            int dir[kSplitItems], c[kSplitItems][3];
+            uint16_t o[kSplitItems][3];
+            float v1[kSplitItems][3];
+            uint32_t rank[kSplitItems];
+            for (int i = tid; i < kDirs * (kGroups + 1); i += kBlock) (&cnt[0][0])[i] = 0u;
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < kSplitItems; ++k) {
+                const uint32_t p = c0 + k * kBlock + tid;
+                dir[k] = -1;
+                if (p < p1) {
+                    const int u = seg_search_n<kTileCells>(cst, p);
+                    drifted(pos, vel, acc, n, p, tx * kTileIos + (u & 7),
+                            ty * kTileIos + ((u >> 3) & 7), tz * kTileIos + (u >> 6), n_f, kick,
+                            drift, c[k], o[k], v1[k], bad);
+                    const int dx = tile_step(tx, c[k][0] >> 3, nt), dy = tile_step(ty, c[k][1] >> 3, nt),
+                              dz = tile_step(tz, c[k][2] >> 3, nt);
+                    if (dx == 2 || dy == 2 || dz == 2)
+                        left = true;
+                    else
+                        dir[k] = (dz + 1) * 9 + (dy + 1) * 3 + dx + 1;
+                }
+                // rank among the group's earlier particles of the same direction
+                uint64_t peers = __ballot(dir[k] >= 0);
+#pragma unroll
+                for (int b = 0; b < 5; ++b) {
+                    const bool bit = (dir[k] >> b) & 1;
+                    const uint64_t m = __ballot(bit);
+                    peers &= bit ? m : ~m;
+                }
+                rank[k] = (uint32_t)__popcll(peers & lt);
+                if (dir[k] >= 0 && rank[k] == 0)
+                    cnt[dir[k]][k * (kBlock / 64) + w] = (uint32_t)__popcll(peers);
+            }
+            __syncthreads();
+            if (tid < kDirs) {
+                uint32_t sum = 0;
+#pragma unroll
+                for (int g = 0; g < kGroups; ++g) {
+                    const uint32_t v = cnt[tid][g];
+                    cnt[tid][g] = sum;
+                    sum += v;
+                }
+                cnt[tid][kGroups] = sum;
+                if (pass == 0) base[tid] += sum;
+            }
+            __syncthreads();
+            if (pass == 0) continue;
+            if (one && tid < 64) {      // group starts from the chunk's counts
+                uint32_t x = lane < kDirs ? cnt[lane][kGroups] : 0u;
+                const uint32_t v = x;
+#pragma unroll
+                for (int s = 1; s < 32; s <<= 1) {
+                    const uint32_t y = __shfl_up(x, s, 64);
+                    if (lane >= s) x += y;
+                }
+                if (lane <= kDirs) {
+                    base[lane] = lane < kDirs ? x - v : x;
+                    pre[t * 28 + lane] = lane < kDirs ? x - v : x;
+                }
+            }
+            if (one) __syncthreads();
+#pragma unroll
+            for (int k = 0; k < kSplitItems; ++k) {
+                if (dir[k] < 0) continue;
+                const uint32_t p = c0 + k * kBlock + tid;
+                const uint32_t s = p0 + base[dir[k]] + cnt[dir[k]][k * (kBlock / 64) + w] + rank[k];
+                out.idx[s] = p;
+                out.cell[s] = (uint16_t)(((c[k][2] & 7) * 8 + (c[k][1] & 7)) * 8 + (c[k][0] & 7));
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    out.offs[(int64_t)d * n + s] = o[k][d];
+                    out.vel[(int64_t)d * n + s] = v1[k][d];
+                }
+            }
+            __syncthreads();
+            if (!one && tid < kDirs) base[tid] += cnt[tid][kGroups];
+            __syncthreads();
+        }
+        if (pass == 0) {                // counts to starts
+            if (tid < 64) {
+                uint32_t x = lane < kDirs ? base[lane] : 0u;
+                const uint32_t v = x;
+#pragma unroll
+                for (int s = 1; s < 32; s <<= 1) {
+                    const uint32_t y = __shfl_up(x, s, 64);
+                    if (lane >= s) x += y;
+                }
+                if (lane <= kDirs) {
+                    base[lane] = lane < kDirs ? x - v : x;
+                    pre[t * 28 + lane] = lane < kDirs ? x - v : x;
+                }
+            }
+            __syncthreads();
+        }
+    }
+    if (p0 == p1 && tid <= kDirs) pre[t * 28 + tid] = 0u;
+    if (left) far_sh = 1u;
+    __syncthreads();
+    if (tid == 0) far[t] = far_sh;
+    if (bad) atomicOr(status, kStatusNonFinite);
+}
+
+// Particle counts of the new tiles, scanned within blocks of kStartTiles tiles,
+// with the blocks' sums and whether a particle of the block's old tiles is far.
+constexpr int kStartTiles = 1024;
+__global__ __launch_bounds__(kStartTiles) void local_starts(const uint32_t *__restrict__ pre,
+                                                            const uint32_t *__restrict__ far, int nt,
+                                                            uint32_t *__restrict__ starts,
+                                                            uint32_t *__restrict__ sums,
+                                                            uint32_t *__restrict__ fars) {
+    __shared__ uint32_t sh[kStartTiles / 64 + 1];
+    __shared__ uint32_t far_sh;
+    const int ntiles = nt * nt * nt, t = (int)(blockIdx.x * kStartTiles + threadIdx.x);
+    if (threadIdx.x == 0) far_sh = 0u;
+    __syncthreads();
+    uint32_t sum = 0;
+    if (t < ntiles) {
+        const int tx = t % nt, ty = (t / nt) % nt, tz = t / (nt * nt);
+        for (int d = 0; d < kDirs; ++d) {
+            const int dx = d % 3 - 1, dy = (d / 3) % 3 - 1, dz = d / 9 - 1;
+            const uint32_t *g = pre + (size_t)tile_at(tx - dx, ty - dy, tz - dz, nt) * 28 + d;
+            sum += g[1] - g[0];
+        }
+        if (far[t]) far_sh = 1u;
+    }
+    uint32_t total;
+    const uint32_t at = block_exclusive_scan<kStartTiles>(sum, sh, total);
+    if (t < ntiles) starts[t] = at;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        sums[blockIdx.x] = total;
+        fars[blockIdx.x] = far_sh;
+    }
+}
+
+// The new tile's groups in the order of their old tiles, sorted stably by cell:
+// each wave takes a contiguous part of them; the cells' counts per wave give
+// the starts of the cells and of each wave's part of them, and a second pass
+// ranks equal cells by wave ballots.
+__global__ __launch_bounds__(kBlock) void local_merge(
+    const uint32_t *__restrict__ cs, int n, int nt, Moved in, const uint32_t *__restrict__ pre,
+    const uint32_t *__restrict__ starts, const uint32_t *__restrict__ sums,
+    const uint32_t *__restrict__ fars, int nblocks, uint16_t *__restrict__ pos,
+    uint32_t *__restrict__ cell_start, float *__restrict__ vel, int32_t *__restrict__ perm,
+    uint32_t *__restrict__ run) {
+    constexpr int W = kBlock / 64;
+    __shared__ uint32_t hist[W][kTileCells];
+    __shared__ uint32_t seg_pre[32], seg_src[32];  // groups in order: first element, first slot
+    __shared__ uint32_t scan_sh[W + 1];
+    __shared__ uint32_t red_sh[2];
+    int tx, ty, tz;
+    tile_of_block(blockIdx.x, nt, tx, ty, tz);
+    const int t = (tz * nt + ty) * nt + tx;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if (tid < 2) red_sh[tid] = 0u;
+    __syncthreads();
+    {   // start of the tile's block of tiles, and the flag (at most 256 blocks)
+        const bool in_range = tid < nblocks;
+        uint32_t s = in_range && tid < t / kStartTiles ? sums[tid] : 0u;
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) s += (uint32_t)__shfl_xor((int)s, o, 64);
+        const bool f = __ballot(in_range && fars[in_range ? tid : 0] != 0u) != 0ull;
+        if (lane == 0) {
+            atomicAdd(&red_sh[0], s);
+            if (f) red_sh[1] = 1u;
+        }
+    }
+    for (int i = tid; i < W * kTileCells; i += kBlock) (&hist[0][0])[i] = 0u;
+    if (w == 0) {
+        // lane d: the group that came in direction d, ranked by its old tile
+        uint32_t src = 0xFFFFFFFFu, cnt = 0, first = 0;
+        if (lane < kDirs) {
+            const int dx = lane % 3 - 1, dy = (lane / 3) % 3 - 1, dz = lane / 9 - 1;
+            src = (uint32_t)tile_at(tx - dx, ty - dy, tz - dz, nt);
+            const uint32_t a = pre[(size_t)src * 28 + lane];
+            cnt = pre[(size_t)src * 28 + lane + 1] - a;
+            first = cs[(size_t)src * kTileCells] + a;
+        }
+        // (with fewer than three tiles per axis several directions meet the same
+        // tile, but only one of them has particles: tile_step)
+        uint32_t at = 0, rank = 0;
+        for (int j = 0; j < kDirs; ++j) {
+            const uint32_t sj = (uint32_t)__builtin_amdgcn_readlane((int)src, j),
+                           cj = (uint32_t)__builtin_amdgcn_readlane((int)cnt, j);
+            if (sj < src || (sj == src && j < lane)) {
+                at += cj;
+                ++rank;
+            }
+        }
+        if (lane < kDirs) {
+            seg_pre[rank] = at;
+            seg_src[rank] = first;
+        }
+        if (lane >= kDirs && lane < 32) seg_pre[lane] = 0xFFFFFFFFu;
+    }
+    __syncthreads();
+    if (t == 0 && tid == 0) *run = red_sh[1];
+    if (red_sh[1]) return;           // the radix sort does it
+    const uint32_t start = starts[t] + red_sh[0];
+    // all of the tile's elements: the last group's end
+    const uint32_t next = t + 1 < nt * nt * nt && (t + 1) % kStartTiles != 0
+                              ? starts[t + 1] : sums[t / kStartTiles];
+    const uint32_t total = next - starts[t];
+    const uint32_t per = (total + 64 * W - 1) / (64 * W) * 64;
+    const uint32_t e0 = min(w * per, total), e1 = min(e0 + per, total);
+    auto slot_of = [&](uint32_t e) {
+        int s = 0;
+#pragma unroll
+        for (int step = 16; step > 0; step >>= 1)
+            if (seg_pre[s + step] <= e) s += step;
+        return seg_src[s] + (e - seg_pre[s]);
+    };
+    for (uint32_t e = e0 + lane; e < e1; e += 64) atomicAdd(&hist[w][in.cell[slot_of(e)]], 1u);
+    __syncthreads();
+    // thread i: cells 2i, 2i + 1
+    uint32_t tot[2] = {0, 0};
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int v = 0; v < W; ++v) tot[k] += hist[v][2 * tid + k];
+    uint32_t all;
+    uint32_t at = block_exclusive_scan(tot[0] + tot[1], scan_sh, all);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        cell_start[(size_t)t * kTileCells + 2 * tid + k] = start + at;
+#pragma unroll
+        for (int v = 0; v < W; ++v) {
+            const uint32_t c = hist[v][2 * tid + k];
+            hist[v][2 * tid + k] = at;
+            at += c;
+        }
+    }
+    if (t == nt * nt * nt - 1 && tid == 0) cell_start[(size_t)(t + 1) * kTileCells] = (uint32_t)n;
+    __syncthreads();
+    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    for (uint32_t b = e0; b < e1; b += 64) {
+        const uint32_t e = b + lane;
+        const bool valid = e < e1;
+        const uint32_t s = slot_of(valid ? e : e1 - 1);
+        const uint32_t c = in.cell[s], p = in.idx[s];
+        uint64_t peers = __ballot(valid);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) {
+            const bool bit = (c >> k) & 1u;
+            const uint64_t m = __ballot(bit);
+            peers &= bit ? m : ~m;
+        }
+        const uint32_t rank = (uint32_t)__popcll(peers & lt);
+        const uint32_t at = hist[w][c];
+        if (valid && rank == 0) hist[w][c] = at + (uint32_t)__popcll(peers);
+        if (valid) {
+            const uint32_t i = start + at + rank;
+            perm[i] = (int32_t)p;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                pos[(int64_t)d * n + i] = in.offs[(int64_t)d * n + s];
+                vel[(int64_t)d * n + i] = in.vel[(int64_t)d * n + s];
+            }
+        }
+        // this wave's counts are written before its next loads (the LDS serves a
+        // wave in order; this keeps the compiler from reordering them)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
 }
 
 constexpr int kRedBlocks = 1024;
@@ -126,6 +483,10 @@ __global__ void kd_backward(const int32_t *__restrict__ perm, const float *__res
 
 }  // namespace
 
+// The local re-sort has a workgroup per tile in both passes; with only a few
+// particles per tile the radix sort costs less.
+constexpr int64_t kLocalPerTile = 32;
+
 int launch_kick_drift(cube2_ctx *ctx, const uint16_t *pos_in, const uint32_t *cs_in,
                       const float *vel_in, const float *acc, int64_t n64, double kick,
                       double drift, uint16_t *pos_out, uint32_t *cs_out, float *vel_out,
@@ -133,17 +494,41 @@ int launch_kick_drift(cube2_ctx *ctx, const uint16_t *pos_in, const uint32_t *cs
                       hipStream_t s) {
     const int n = (int)n64;
     const int nt = ctx->nt;
+    const int ntiles = nt * nt * nt;
     uint16_t *offs = reinterpret_cast<uint16_t *>(work + L.offs_tmp);
+    uint32_t *run = nullptr;
+    if (n64 >= kLocalPerTile * (int64_t)ntiles) {
+        // the groups and the tiles' tables take the places of the sort's
+        // buffers and of the fine mesh
+        Moved m;
+        m.idx = reinterpret_cast<uint32_t *>(work + L.keys);
+        m.cell = reinterpret_cast<uint16_t *>(work + L.vals);
+        m.offs = offs;
+        m.vel = reinterpret_cast<float *>(work + L.acc_pp);
+        uint32_t *pre = reinterpret_cast<uint32_t *>(work + L.real_f);
+        uint32_t *far = pre + (size_t)28 * ntiles, *starts = far + ntiles, *sums = starts + ntiles,
+                 *fars = sums + 256;
+        run = fars + 256;
+        const int nblocks = (ntiles + kStartTiles - 1) / kStartTiles;
+        local_split<<<(unsigned)ntiles, kBlock, 0, s>>>(pos_in, cs_in, vel_in, acc, n, nt, ctx->n_f,
+                                                        kick, drift, m, pre, far, status_word(ctx));
+        CUBE2_LAUNCH_CHECK();
+        local_starts<<<(unsigned)nblocks, kStartTiles, 0, s>>>(pre, far, nt, starts, sums, fars);
+        CUBE2_LAUNCH_CHECK();
+        local_merge<<<(unsigned)ntiles, kBlock, 0, s>>>(cs_in, n, nt, m, pre, starts, sums, fars, nblocks,
+                                                        pos_out, cs_out, vel_out, perm_out, run);
+        CUBE2_LAUNCH_CHECK();
+    }
     if (n > 0) {
-        kick_drift_kernel<<<(unsigned)(nt * nt * nt), kBlock, 0, s>>>(
+        kick_drift_kernel<<<(unsigned)(run ? std::min(ntiles, 2048) : ntiles), kBlock, 0, s>>>(
             pos_in, cs_in, vel_in, acc, n, nt, ctx->n_f, kick, drift,
             reinterpret_cast<uint32_t *>(work + L.keys), reinterpret_cast<uint32_t *>(work + L.vals),
-            offs, status_word(ctx));
+            offs, status_word(ctx), run);
         CUBE2_LAUNCH_CHECK();
     }
     // the re-sort's final gather also forms the kicked velocities
     return launch_sort_by_cell(ctx, n, offs, pos_out, cs_out, perm_out, work, L, s, vel_in, acc,
-                               kick, vel_out);
+                               kick, vel_out, run);
 }
 
 int launch_reduce(cube2_ctx *ctx, const float *vel, const float *acc, int64_t n64, double *out8,
