@@ -75,7 +75,7 @@ WorkLayout work_layout(const cube2_ctx *c, int64_t n) {
     L.vals2 = take(nn * 4);
     const size_t ntiles = (size_t)c->nt * c->nt * c->nt;
     size_t nblk = (std::max(nn, ntiles) + 4095) / 4096;
-    L.hist = take(nblk * 256 * 4 + 1024);
+    L.hist = take(nblk * 512 * 4 + 1024);    // digits of up to 9 bits
     L.tile_order = take((ntiles * 4 + 64) * sizeof(uint32_t));  // + the tile work counter
     L.vel_tmax = take(ntiles * sizeof(float));
     const size_t scan_len = std::max((size_t)(c->n_cells + 1), nblk * 256);

@@ -107,6 +107,12 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 WorkLayout work_layout(const cube2_ctx *ctx, int64_t n);
 
+// In-cell offsets of the particles to sort, 8 bytes each (in the area of the
+// concurrent PP output, which no sort overlaps).
+inline ushort4 *sort_offsets(unsigned char *work, const WorkLayout &L) {
+    return reinterpret_cast<ushort4 *>(work + L.acc_pp);
+}
+
 // bits of the device status word
 constexpr uint32_t kStatusOverflow = 1u;    // a deposit or codec accumulator could overflow
 constexpr uint32_t kStatusNonFinite = 2u;   // a kick-drift met a non-finite velocity or step
@@ -229,6 +235,68 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *s
     __syncthreads();
     total = tot;
     return off + x - v;
+}
+
+// Stable sort by cell of one tile's `total` elements, the first of which comes to
+// particle `start` (all kBlock threads call it): each wave takes a contiguous part of
+// them; the cells' counts per wave give the starts of the cells (written to
+// cell_start) and of each wave's part of them, and a second pass ranks equal
+// cells by wave ballots.  cell_of(e) is the cell (0..511) of element e, emit(e,
+// i) writes element e to sorted place i (counted from first_place).
+template <class CellOf, class Emit>
+__device__ __forceinline__ void tile_cell_sort(uint32_t (*hist)[kTileCells] /*[kBlock / 64]*/,
+                                               uint32_t *scan_sh /*kBlock / 64 + 1*/, uint32_t total,
+                                               uint32_t first_place, uint32_t start,
+                                               uint32_t *__restrict__ cell_start,
+                                               CellOf cell_of, Emit emit) {
+    constexpr int W = kBlock / 64;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    for (int i = tid; i < W * kTileCells; i += kBlock) hist[i / kTileCells][i % kTileCells] = 0u;
+    __syncthreads();
+    const uint32_t per = (total + 64 * W - 1) / (64 * W) * 64;
+    const uint32_t e0 = min(w * per, total), e1 = min(e0 + per, total);
+    for (uint32_t e = e0 + lane; e < e1; e += 64) atomicAdd(&hist[w][cell_of(e)], 1u);
+    __syncthreads();
+    // thread i: cells 2i, 2i + 1
+    uint32_t tot[2] = {0, 0};
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int v = 0; v < W; ++v) tot[k] += hist[v][2 * tid + k];
+    uint32_t all;
+    uint32_t at = block_exclusive_scan(tot[0] + tot[1], scan_sh, all);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        cell_start[2 * tid + k] = start + at;
+#pragma unroll
+        for (int v = 0; v < W; ++v) {
+            const uint32_t c = hist[v][2 * tid + k];
+            hist[v][2 * tid + k] = at;
+            at += c;
+        }
+    }
+    __syncthreads();
+    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    for (uint32_t b = e0; b < e1; b += 64) {
+        const uint32_t e = b + lane;
+        const bool valid = e < e1;
+        const uint32_t c = cell_of(valid ? e : e1 - 1);
+        uint64_t peers = __ballot(valid);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) {
+            const bool bit = (c >> k) & 1u;
+            const uint64_t m = __ballot(bit);
+            peers &= bit ? m : ~m;
+        }
+        const uint32_t rank = (uint32_t)__popcll(peers & lt);
+        const uint32_t first = hist[w][c];
+        if (valid && rank == 0) hist[w][c] = first + (uint32_t)__popcll(peers);
+        if (valid) emit(e, first_place + first + rank);
+        // this wave's counts are written before its next loads (the LDS serves a
+        // wave in order; this keeps the compiler from reordering them)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
 }
 
 // Tile scheduling of the per-tile kernels.  With a work queue (queue != 0)
@@ -416,16 +484,17 @@ __device__ __forceinline__ void stage_block(T *__restrict__ dst, const T *__rest
 // Host entry points of the kernel files (return CUBE2_* codes).
 int launch_pack(cube2_ctx *ctx, const float *x, int64_t n, uint16_t *pos, uint32_t *cell_start,
                 int32_t *perm, unsigned char *work, const WorkLayout &L, hipStream_t s);
-// The stable sort by IOS cell of keys/vals (work) with the offsets of the
-// unsorted particles; with vel != NULL the final gather also forms the kicked
+// The stable sort by IOS cell of the keys (work) with the offsets of the
+// unsorted particles (sort_offsets); with vel != NULL the final gather also forms the kicked
 // velocities vel_out[i] = vel[p] + kick acc[p] (FP64, separately rounded) of
 // the sorted particles, p = perm[i].  run != NULL (device): nothing is done
-// where *run is 0.
-int launch_sort_by_cell(cube2_ctx *ctx, int64_t n, const uint16_t *offs_in_unsorted,
-                        uint16_t *pos, uint32_t *cell_start, int32_t *perm,
+// where *run is 0.  counted: the first digit's block counts are in the
+// histogram area.
+int launch_sort_by_cell(cube2_ctx *ctx, int64_t n, uint16_t *pos, uint32_t *cell_start, int32_t *perm,
                         unsigned char *work, const WorkLayout &L, hipStream_t s,
                         const float *vel = nullptr, const float *acc = nullptr, double kick = 0.0,
-                        float *vel_out = nullptr, const uint32_t *run = nullptr);
+                        float *vel_out = nullptr, const uint32_t *run = nullptr,
+                        bool counted = false);
 int launch_deposit(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,
                    float *rho_f, uint64_t *rho_f_fx, float *rho_c, uint64_t *rho_c_fx,
                    unsigned char *work, const WorkLayout &L, hipStream_t s);

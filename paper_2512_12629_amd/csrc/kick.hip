@@ -47,9 +47,8 @@ __device__ __forceinline__ void drifted(const uint16_t *__restrict__ pos, const 
 __global__ __launch_bounds__(kBlock) void kick_drift_kernel(
     const uint16_t *__restrict__ pos, const uint32_t *__restrict__ cs,
     const float *__restrict__ vel, const float *__restrict__ acc, int n, int nt, int n_f,
-    double kick, double drift, uint32_t *__restrict__ keys, uint32_t *__restrict__ vals,
-    uint16_t *__restrict__ offs, uint32_t *__restrict__ status,
-    const uint32_t *__restrict__ run) {
+    double kick, double drift, uint32_t *__restrict__ keys, ushort4 *__restrict__ offs,
+    uint32_t *__restrict__ status, const uint32_t *__restrict__ run) {
     __shared__ uint32_t cst[kTileCells + 1];
     if (run && *run == 0u) return;      // the fallback of the local re-sort, not needed
     const int tid = threadIdx.x;
@@ -67,10 +66,8 @@ __global__ __launch_bounds__(kBlock) void kick_drift_kernel(
             float v1[3];
             drifted(pos, vel, acc, n, p, tx * kTileIos + (u & 7), ty * kTileIos + ((u >> 3) & 7),
                     tz * kTileIos + (u >> 6), n_f, kick, drift, c, o, v1, bad);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) offs[(int64_t)d * n + p] = o[d];
+            offs[p] = make_ushort4(o[0], o[1], o[2], 0);
             keys[p] = cell_key(c[0], c[1], c[2], nt);
-            vals[p] = p;
         }
         __syncthreads();
     }
@@ -284,10 +281,8 @@ __global__ __launch_bounds__(kStartTiles) void local_starts(const uint32_t *__re
     }
 }
 
-// The new tile's groups in the order of their old tiles, sorted stably by cell:
-// each wave takes a contiguous part of them; the cells' counts per wave give
-// the starts of the cells and of each wave's part of them, and a second pass
-// ranks equal cells by wave ballots.
+// The new tile's groups in the order of their old tiles, sorted stably by cell
+// (tile_cell_sort).
 __global__ __launch_bounds__(kBlock) void local_merge(
     const uint32_t *__restrict__ cs, int n, int nt, Moved in, const uint32_t *__restrict__ pre,
     const uint32_t *__restrict__ starts, const uint32_t *__restrict__ sums,
@@ -316,7 +311,6 @@ __global__ __launch_bounds__(kBlock) void local_merge(
             if (f) red_sh[1] = 1u;
         }
     }
-    for (int i = tid; i < W * kTileCells; i += kBlock) (&hist[0][0])[i] = 0u;
     if (w == 0) {
         // lane d: the group that came in direction d, ranked by its old tile
         uint32_t src = 0xFFFFFFFFu, cnt = 0, first = 0;
@@ -352,8 +346,6 @@ __global__ __launch_bounds__(kBlock) void local_merge(
     const uint32_t next = t + 1 < nt * nt * nt && (t + 1) % kStartTiles != 0
                               ? starts[t + 1] : sums[t / kStartTiles];
     const uint32_t total = next - starts[t];
-    const uint32_t per = (total + 64 * W - 1) / (64 * W) * 64;
-    const uint32_t e0 = min(w * per, total), e1 = min(e0 + per, total);
     auto slot_of = [&](uint32_t e) {
         int s = 0;
 #pragma unroll
@@ -361,58 +353,18 @@ __global__ __launch_bounds__(kBlock) void local_merge(
             if (seg_pre[s + step] <= e) s += step;
         return seg_src[s] + (e - seg_pre[s]);
     };
-    for (uint32_t e = e0 + lane; e < e1; e += 64) atomicAdd(&hist[w][in.cell[slot_of(e)]], 1u);
-    __syncthreads();
-    // thread i: cells 2i, 2i + 1
-    uint32_t tot[2] = {0, 0};
+    tile_cell_sort(hist, scan_sh, total, start, start, cell_start + (size_t)t * kTileCells,
+                   [&](uint32_t e) -> uint32_t { return in.cell[slot_of(e)]; },
+                   [&](uint32_t e, uint32_t i) {
+                       const uint32_t s = slot_of(e);
+                       perm[i] = (int32_t)in.idx[s];
 #pragma unroll
-    for (int k = 0; k < 2; ++k)
-#pragma unroll
-        for (int v = 0; v < W; ++v) tot[k] += hist[v][2 * tid + k];
-    uint32_t all;
-    uint32_t at = block_exclusive_scan(tot[0] + tot[1], scan_sh, all);
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        cell_start[(size_t)t * kTileCells + 2 * tid + k] = start + at;
-#pragma unroll
-        for (int v = 0; v < W; ++v) {
-            const uint32_t c = hist[v][2 * tid + k];
-            hist[v][2 * tid + k] = at;
-            at += c;
-        }
-    }
+                       for (int d = 0; d < 3; ++d) {
+                           pos[(int64_t)d * n + i] = in.offs[(int64_t)d * n + s];
+                           vel[(int64_t)d * n + i] = in.vel[(int64_t)d * n + s];
+                       }
+                   });
     if (t == nt * nt * nt - 1 && tid == 0) cell_start[(size_t)(t + 1) * kTileCells] = (uint32_t)n;
-    __syncthreads();
-    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    for (uint32_t b = e0; b < e1; b += 64) {
-        const uint32_t e = b + lane;
-        const bool valid = e < e1;
-        const uint32_t s = slot_of(valid ? e : e1 - 1);
-        const uint32_t c = in.cell[s], p = in.idx[s];
-        uint64_t peers = __ballot(valid);
-#pragma unroll
-        for (int k = 0; k < 9; ++k) {
-            const bool bit = (c >> k) & 1u;
-            const uint64_t m = __ballot(bit);
-            peers &= bit ? m : ~m;
-        }
-        const uint32_t rank = (uint32_t)__popcll(peers & lt);
-        const uint32_t at = hist[w][c];
-        if (valid && rank == 0) hist[w][c] = at + (uint32_t)__popcll(peers);
-        if (valid) {
-            const uint32_t i = start + at + rank;
-            perm[i] = (int32_t)p;
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                pos[(int64_t)d * n + i] = in.offs[(int64_t)d * n + s];
-                vel[(int64_t)d * n + i] = in.vel[(int64_t)d * n + s];
-            }
-        }
-        // this wave's counts are written before its next loads (the LDS serves a
-        // wave in order; this keeps the compiler from reordering them)
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    }
 }
 
 constexpr int kRedBlocks = 1024;
@@ -495,7 +447,6 @@ int launch_kick_drift(cube2_ctx *ctx, const uint16_t *pos_in, const uint32_t *cs
     const int n = (int)n64;
     const int nt = ctx->nt;
     const int ntiles = nt * nt * nt;
-    uint16_t *offs = reinterpret_cast<uint16_t *>(work + L.offs_tmp);
     uint32_t *run = nullptr;
     if (n64 >= kLocalPerTile * (int64_t)ntiles) {
         // the groups and the tiles' tables take the places of the sort's
@@ -503,7 +454,7 @@ int launch_kick_drift(cube2_ctx *ctx, const uint16_t *pos_in, const uint32_t *cs
         Moved m;
         m.idx = reinterpret_cast<uint32_t *>(work + L.keys);
         m.cell = reinterpret_cast<uint16_t *>(work + L.vals);
-        m.offs = offs;
+        m.offs = reinterpret_cast<uint16_t *>(work + L.offs_tmp);
         m.vel = reinterpret_cast<float *>(work + L.acc_pp);
         uint32_t *pre = reinterpret_cast<uint32_t *>(work + L.real_f);
         uint32_t *far = pre + (size_t)28 * ntiles, *starts = far + ntiles, *sums = starts + ntiles,
@@ -522,12 +473,11 @@ int launch_kick_drift(cube2_ctx *ctx, const uint16_t *pos_in, const uint32_t *cs
     if (n > 0) {
         kick_drift_kernel<<<(unsigned)(run ? std::min(ntiles, 2048) : ntiles), kBlock, 0, s>>>(
             pos_in, cs_in, vel_in, acc, n, nt, ctx->n_f, kick, drift,
-            reinterpret_cast<uint32_t *>(work + L.keys), reinterpret_cast<uint32_t *>(work + L.vals),
-            offs, status_word(ctx), run);
+            reinterpret_cast<uint32_t *>(work + L.keys), sort_offsets(work, L), status_word(ctx), run);
         CUBE2_LAUNCH_CHECK();
     }
     // the re-sort's final gather also forms the kicked velocities
-    return launch_sort_by_cell(ctx, n, offs, pos_out, cs_out, perm_out, work, L, s, vel_in, acc,
+    return launch_sort_by_cell(ctx, n, pos_out, cs_out, perm_out, work, L, s, vel_in, acc,
                                kick, vel_out, run);
 }
 

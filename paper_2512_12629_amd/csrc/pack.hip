@@ -3,14 +3,16 @@
 // order encodes cell membership and a prefix count per cell (cell_start)
 // replaces per-particle cell indices.
 //
-// The sort is a stable least-significant-digit radix sort on the cell key
-// (8-bit digits), written for 64-wide wavefronts: per 4096-key block a digit
-// histogram, one device-wide scan of the digit-major histogram, then a
-// scatter in which each key's rank among equal digits of its block comes
-// from wave ballots (a 64-lane match on the digit) plus per-wave counts in
-// LDS; the block's keys are staged in LDS in digit order and written out in
-// runs.  Ties keep their input order, so the result equals a stable argsort.
-// cell_start is read off the sorted keys (no per-cell atomics).
+// The sort is a stable radix sort of the cell key, written for 64-wide
+// wavefronts: per 4096-key block a digit histogram, one scan per digit row, then
+// a scatter in which each wave ranks its own 1024 keys by wave ballots (a
+// 64-lane match on the digit) and counts of its own in LDS; the block's keys are
+// staged in LDS in digit order and written out in runs.  It sorts by the tile
+// only (two passes of up to 9 bits); one workgroup per tile then sorts the
+// tile's particles by cell in LDS, which also gives cell_start, and gathers
+// them.  With few particles per tile it sorts by the whole key instead and
+// reads cell_start off the sorted keys.  Ties keep their input order, so the
+// result equals a stable argsort.  No global atomics.
 #include <algorithm>
 
 #include "common.hpp"
@@ -28,22 +30,37 @@ __global__ void fill_u32(uint32_t *p, uint32_t v, int64_t n) {
     if (i < n) p[i] = v;
 }
 
-// q = floor(x * n_f * 2^15) mod (n_f * 2^15); key of the IOS cell; offsets.
-__global__ void quantize_kernel(const float *__restrict__ x, int n, int n_f, int nt,
-                                uint32_t *__restrict__ keys, uint32_t *__restrict__ vals,
-                                uint16_t *__restrict__ offs) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+// q = floor(x * n_f * 2^15) mod (n_f * 2^15); key of the IOS cell; offsets; and
+// the block's histogram of the first digit (BITS bits at `shift`) of the sort.
+template <int BITS>
+__global__ __launch_bounds__(kBlock) void quantize_kernel(const float *__restrict__ x, int n, int n_f,
+                                                          int nt, uint32_t *__restrict__ keys,
+                                                          ushort4 *__restrict__ offs, int shift,
+                                                          int nblk, uint32_t *__restrict__ ghist) {
+    __shared__ uint32_t h[1 << BITS];
+    for (int i = threadIdx.x; i < (1 << BITS); i += kBlock) h[i] = 0;
+    __syncthreads();
     const double span = (double)n_f * 32768.0;
     const int64_t mask = (int64_t)n_f * 32768 - 1;
-    int c[3];
-    for (int d = 0; d < 3; ++d) {
-        const int64_t q = (int64_t)floor((double)x[(int64_t)d * n + i] * span) & mask;
-        c[d] = (int)(q >> 16);
-        offs[(int64_t)d * n + i] = (uint16_t)(q & 0xFFFF);
+#pragma unroll 4
+    for (int r = 0; r < kSortItems; ++r) {
+        const int64_t i = (int64_t)blockIdx.x * kSortTile + r * kBlock + threadIdx.x;
+        if (i >= n) break;
+        int c[3];
+        uint16_t o[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const int64_t q = (int64_t)floor((double)x[(int64_t)d * n + i] * span) & mask;
+            c[d] = (int)(q >> 16);
+            o[d] = (uint16_t)(q & 0xFFFF);
+        }
+        offs[i] = make_ushort4(o[0], o[1], o[2], 0);   // one line per particle for the final gather
+        const uint32_t key = cell_key(c[0], c[1], c[2], nt);
+        keys[i] = key;
+        atomicAdd(&h[(key >> shift) & ((1u << BITS) - 1u)], 1u);
     }
-    keys[i] = cell_key(c[0], c[1], c[2], nt);
-    vals[i] = (uint32_t)i;
+    __syncthreads();
+    for (int i = threadIdx.x; i < (1 << BITS); i += kBlock) ghist[(int64_t)i * nblk + blockIdx.x] = h[i];
 }
 
 // Exclusive scan, phase 1: scan each 1024-element tile, record tile sums.
@@ -101,20 +118,31 @@ int exclusive_scan(const uint32_t *in, uint32_t *out, int64_t m, uint32_t *tmp, 
 // little, and every kernel strides over its blocks.
 __device__ __forceinline__ bool runs(const uint32_t *run) { return !run || *run != 0u; }
 
-__global__ void radix_count(const uint32_t *__restrict__ keys, int n, int shift, int nblk,
-                            uint32_t *__restrict__ ghist, const uint32_t *__restrict__ run) {
-    __shared__ uint32_t h[256];
-    if (!runs(run)) return;
+template <int BITS>
+__global__ __launch_bounds__(kBlock) void radix_count(const uint32_t *__restrict__ keys, int n, int shift,
+                                                      int nblk, uint32_t *__restrict__ ghist,
+                                                      const uint32_t *__restrict__ go) {
+    __shared__ uint32_t h[1 << BITS];
+    if (!runs(go)) return;
     for (int blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
-        h[threadIdx.x] = 0;
+        for (int i = threadIdx.x; i < (1 << BITS); i += kBlock) h[i] = 0;
         __syncthreads();
         const int64_t base = (int64_t)blk * kSortTile;
         for (int r = 0; r < kSortItems; ++r) {
             const int64_t i = base + r * kBlock + threadIdx.x;
-            if (i < n) atomicAdd(&h[(keys[i] >> shift) & 255u], 1u);
+            // later digits come in runs (of the earlier pass's order): lanes that
+            // share the first lane's digit add once
+            const uint32_t dig = i < n ? (keys[i] >> shift) & ((1u << BITS) - 1u) : ~0u;
+            const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)dig);
+            const uint64_t same = __ballot(dig == first);
+            if (dig != first && i < n)
+                atomicAdd(&h[dig], 1u);
+            else if (dig == first && first != ~0u && (int)(threadIdx.x & 63) == first_lane(same))
+                atomicAdd(&h[first], (uint32_t)__popcll(same));
         }
         __syncthreads();
-        ghist[(int64_t)threadIdx.x * nblk + blk] = h[threadIdx.x];
+        for (int i = threadIdx.x; i < (1 << BITS); i += kBlock) ghist[(int64_t)i * nblk + blk] = h[i];
+        __syncthreads();
     }
 }
 
@@ -139,127 +167,218 @@ __global__ __launch_bounds__(kRowBlock) void radix_scan_rows(uint32_t *__restric
 }
 
 // Scatter of one 4096-key block.  The row-scanned digit-major histogram goff
-// and the digits' totals give each (digit, block) its global start; the
-// difference of consecutive entries is the block's own count of that digit.  Keys are first placed in
-// LDS in digit order (rank among equal digits from wave ballots plus per-wave
-// counts, so ties keep their input order), then written out in LDS order, so
-// that consecutive threads write consecutive addresses of one digit's run.
-__global__ void radix_scatter(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ vin,
-                              uint32_t *__restrict__ kout, uint32_t *__restrict__ vout, int n,
-                              int shift, int nblk, const uint32_t *__restrict__ goff,
-                              uint32_t *__restrict__ totals,
-                              const uint32_t *__restrict__ go) {
-    __shared__ uint32_t gbase[256];  // global start of each digit of this block
-    __shared__ uint32_t lpre[256];   // block-local start of each digit
-    __shared__ uint32_t run[256];    // next free block-local slot of each digit
-    __shared__ uint32_t wcnt[kBlock / 64][256];
-    __shared__ uint32_t scan_sh[kBlock / 64 + 1];
+// and the digits' totals give each (digit, block) its global start.  Each wave
+// ranks its own 1024 consecutive keys against its counts of the digits so far
+// (wave ballots give the rank among equal digits of 64 keys), without a
+// barrier; the waves' counts then give every key its place in digit order in
+// LDS, from where consecutive threads write consecutive addresses of one digit's
+// run.  vin == NULL: the values are the keys' own indices.  (With a barrier
+// per 256 keys and the ranks of all four waves taken together the pass ran at
+// 2.1 TB/s; 27 million keys 212 us.)
+template <int BITS>
+__global__ __launch_bounds__(kBlock) void radix_scatter(
+    const uint32_t *__restrict__ kin, const uint32_t *__restrict__ vin, uint32_t *__restrict__ kout,
+    uint32_t *__restrict__ vout, int n, int shift, int nblk, const uint32_t *__restrict__ goff,
+    uint32_t *__restrict__ totals, const uint32_t *__restrict__ go) {
+    constexpr int BINS = 1 << BITS, W = kBlock / 64, PER = BINS / kBlock;
+    __shared__ uint32_t gbase[BINS];       // global start of each digit of this block, less lpre
+    __shared__ uint32_t lpre[BINS];        // block-local start of each digit
+    __shared__ uint32_t wcnt[W][BINS];     // each wave's counts, then its start within the digit
+    __shared__ uint32_t scan_sh[W + 1];
     __shared__ uint32_t sk[kSortTile], sv[kSortTile];
     if (!runs(go)) return;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    uint32_t total;
-    const uint32_t mine = totals[tid];
-    const uint32_t dstart = block_exclusive_scan(mine, scan_sh, total);   // start of digit tid
-    if (blockIdx.x == 0 && tid == 255) totals[256] = dstart;
+    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    uint32_t dstart[PER], total, sum = 0;  // starts of digits tid PER + i
+#pragma unroll
+    for (int i = 0; i < PER; ++i) sum += totals[tid * PER + i];
+    sum = block_exclusive_scan(sum, scan_sh, total);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        dstart[i] = sum;
+        sum += totals[tid * PER + i];
+    }
+    if (blockIdx.x == 0 && tid == kBlock - 1) totals[BINS] = dstart[PER - 1];
     for (int blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
-        {
-            const int64_t e = (int64_t)tid * nblk + blk;
-            const uint32_t g = goff[e];
-            const uint32_t next = blk + 1 < nblk ? goff[e + 1] : mine;
-            const uint32_t lp = block_exclusive_scan(next - g, scan_sh, total);
-            gbase[tid] = dstart + g;
-            lpre[tid] = lp;
-            run[tid] = lp;
-        }
-        for (int k = 0; k < kBlock / 64; ++k) wcnt[k][tid] = 0;
+        for (int i = tid; i < W * BINS; i += kBlock) wcnt[i / BINS][i % BINS] = 0;
         __syncthreads();
-        const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
         const int64_t blk0 = (int64_t)blk * kSortTile;
         const int cnt = (int)min((int64_t)kSortTile, (int64_t)n - blk0);
+        uint32_t key[kSortItems], place[kSortItems];
+#pragma unroll
         for (int r = 0; r < kSortItems; ++r) {
-            const int li = r * kBlock + tid;
-            const bool valid = li < cnt;
-            uint32_t key = 0, val = 0, dig = 0;
-            if (valid) {
-                key = kin[blk0 + li];
-                val = vin[blk0 + li];
-                dig = (key >> shift) & 255u;
-            }
+            const int li = w * (kSortTile / W) + r * 64 + lane;
+            key[r] = li < cnt ? kin[blk0 + li] : 0u;
+        }
+#pragma unroll
+        for (int r = 0; r < kSortItems; ++r) {
+            const bool valid = w * (kSortTile / W) + r * 64 + lane < cnt;
+            const uint32_t dig = (key[r] >> shift) & (BINS - 1);
             uint64_t peers = __ballot(valid);
 #pragma unroll
-            for (int b = 0; b < 8; ++b) {
+            for (int b = 0; b < BITS; ++b) {
                 const bool bit = (dig >> b) & 1u;
                 const uint64_t m = __ballot(bit);
                 peers &= bit ? m : ~m;
             }
             const uint32_t rank = (uint32_t)__popcll(peers & lt);
-            if (valid && rank == 0) wcnt[w][dig] = (uint32_t)__popcll(peers);
-            __syncthreads();
-            if (valid) {
-                uint32_t o = run[dig] + rank;
-                for (int k = 0; k < w; ++k) o += wcnt[k][dig];
-                sk[o] = key;
-                sv[o] = val;
-            }
-            __syncthreads();
-            uint32_t add = 0;
-            for (int k = 0; k < kBlock / 64; ++k) {
-                add += wcnt[k][tid];
-                wcnt[k][tid] = 0;
-            }
-            run[tid] += add;
-            __syncthreads();
+            const uint32_t before = wcnt[w][dig];
+            if (valid && rank == 0) wcnt[w][dig] = before + (uint32_t)__popcll(peers);
+            place[r] = before + rank;
+            // written before this wave's next loads (the LDS serves a wave in
+            // order; this keeps the compiler from reordering them)
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
         }
+        __syncthreads();
+        uint32_t mine[PER], at = 0;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            mine[i] = 0;
+#pragma unroll
+            for (int v = 0; v < W; ++v) {
+                const uint32_t c = wcnt[v][tid * PER + i];
+                wcnt[v][tid * PER + i] = mine[i];
+                mine[i] += c;
+            }
+            at += mine[i];
+        }
+        at = block_exclusive_scan(at, scan_sh, total);
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            lpre[tid * PER + i] = at;
+            gbase[tid * PER + i] = dstart[i] + goff[(int64_t)(tid * PER + i) * nblk + blk] - at;
+            at += mine[i];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kSortItems; ++r) {
+            const int li = w * (kSortTile / W) + r * 64 + lane;
+            if (li >= cnt) continue;
+            const uint32_t dig = (key[r] >> shift) & (BINS - 1);
+            const uint32_t o = lpre[dig] + wcnt[w][dig] + place[r];
+            sk[o] = key[r];
+            sv[o] = vin ? vin[blk0 + li] : (uint32_t)(blk0 + li);
+        }
+        __syncthreads();
         for (int j = tid; j < cnt; j += kBlock) {
-            const uint32_t key = sk[j];
-            const uint32_t dig = (key >> shift) & 255u;
-            const uint32_t o = gbase[dig] + ((uint32_t)j - lpre[dig]);
-            kout[o] = key;
+            const uint32_t k = sk[j];
+            const uint32_t o = gbase[(k >> shift) & (BINS - 1)] + (uint32_t)j;
+            kout[o] = k;
             vout[o] = sv[j];
         }
         __syncthreads();   // the next block's counts
     }
 }
 
-// cell_start from the sorted keys: entry c is the first index whose key is
-// >= c, so index i (0..n) writes the entries (key[i-1], key[i]] (with key[-1]
+// The particles of each tile (keys and vals sorted by tile) sorted by cell, with
+// cell_start; offsets gathered and, with vel, the kicked velocities formed as
+// vel[p] + kick acc[p] in FP64 with separately rounded operations (the value
+// the kick-drift kernel drifted with).
+constexpr int kTileStage = 1536;
+__global__ __launch_bounds__(kBlock) void tile_sort_kernel(
+    const uint32_t *__restrict__ keys, const uint32_t *__restrict__ vals,
+    const uint32_t *__restrict__ tstart, const ushort4 *__restrict__ offs, int n, int nt,
+    uint16_t *__restrict__ pos, uint32_t *__restrict__ cell_start, int32_t *__restrict__ perm,
+    const float *__restrict__ vel, const float *__restrict__ acc, double kick,
+    float *__restrict__ vout, const uint32_t *__restrict__ go) {
+#pragma clang fp contract(off)
+    __shared__ uint32_t hist[kBlock / 64][kTileCells];
+    __shared__ uint32_t scan_sh[kBlock / 64 + 1];
+    __shared__ uint32_t staged[kTileStage];   // sorted indices: the gather then runs without order
+    if (!runs(go)) return;
+    const int ntiles = nt * nt * nt;
+    for (int b = blockIdx.x; b < ntiles; b += gridDim.x) {
+        int tx, ty, tz;
+        tile_of_block(b, nt, tx, ty, tz);   // neighbouring tiles gather from the same lines
+        const int t = (tz * nt + ty) * nt + tx;
+        const uint32_t start = tstart[t], total = tstart[t + 1] - start;
+        auto cell_of = [&](uint32_t e) -> uint32_t { return keys[start + e] % kTileCells; };
+        auto put = [&](uint32_t p, uint32_t i) {
+            const ushort4 o = offs[p];
+            perm[i] = (int32_t)p;
+            pos[i] = o.x;
+            pos[(int64_t)n + i] = o.y;
+            pos[2 * (int64_t)n + i] = o.z;
+            if (vel)
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    const double kv = kick * (double)acc[(int64_t)d * n + p];
+                    vout[(int64_t)d * n + i] = (float)((double)vel[(int64_t)d * n + p] + kv);
+                }
+        };
+        if (total <= (uint32_t)kTileStage) {
+            tile_cell_sort(hist, scan_sh, total, 0u, start, cell_start + (size_t)t * kTileCells, cell_of,
+                           [&](uint32_t e, uint32_t i) { staged[i] = vals[start + e]; });
+            __syncthreads();
+            for (uint32_t i = threadIdx.x; i < total; i += kBlock) put(staged[i], start + i);
+        } else {
+            tile_cell_sort(hist, scan_sh, total, start, start, cell_start + (size_t)t * kTileCells,
+                           cell_of, [&](uint32_t e, uint32_t i) { put(vals[start + e], i); });
+        }
+        if (t == ntiles - 1 && threadIdx.x == 0) cell_start[(size_t)ntiles * kTileCells] = (uint32_t)n;
+        __syncthreads();
+    }
+}
+
+// cell_start (shift = 0, n_cells entries and the end), or the tiles' starts
+// (shift = 9), from the sorted keys: entry c is the first index whose key >> shift
+// is >= c, so index i (0..n) writes the entries (key[i-1], key[i]] (with key[-1]
 // = -1 and key[n] = n_cells).  Every entry has exactly one writer.  A run of
 // more than 64 entries (a stretch of empty cells) is written by the whole
 // wave, so that sparse inputs do not leave one lane writing most of the mesh.
-__global__ void cell_starts_kernel(const uint32_t *__restrict__ keys, int n, int64_t n_cells,
+__global__ void cell_starts_kernel(const uint32_t *__restrict__ keys, int n, int shift, int64_t n_cells,
                                    uint32_t *__restrict__ cell_start,
                                    const uint32_t *__restrict__ run) {
     if (!runs(run)) return;
     const int lane = threadIdx.x & 63;
-    for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x; i0 <= n; i0 += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t i = i0 + threadIdx.x;
-        int64_t lo = 0, hi = -1;
-        if (i <= n) {
-            lo = i == 0 ? 0 : (int64_t)keys[i - 1] + 1;
-            hi = i == n ? n_cells : (int64_t)keys[i];
+    constexpr int PER = 4;                 // consecutive indices per lane
+    for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x * PER; i0 <= n;
+         i0 += (int64_t)gridDim.x * blockDim.x * PER) {
+        const int64_t i1 = i0 + (int64_t)threadIdx.x * PER;
+        uint4 k4 = make_uint4(0, 0, 0, 0);
+        if (i1 + 3 < n)
+            k4 = *reinterpret_cast<const uint4 *>(keys + i1);
+        else if (i1 < n) {
+            k4.x = keys[i1];
+            k4.y = i1 + 1 < n ? keys[i1 + 1] : 0u;
+            k4.z = i1 + 2 < n ? keys[i1 + 2] : 0u;
         }
-        const bool wide = hi - lo >= 64;
-        if (!wide)
-            for (int64_t c = lo; c <= hi; ++c) cell_start[c] = (uint32_t)i;
-        uint64_t m = __ballot(wide);
-        while (m) {
-            const int l = __ffsll((long long)m) - 1;
-            m &= m - 1;
-            const long long a = __shfl((long long)lo, l, 64), b = __shfl((long long)hi, l, 64);
-            const uint32_t v = (uint32_t)__shfl((int)i, l, 64);
-            for (long long c = a + lane; c <= b; c += 64) cell_start[c] = v;
+        const uint32_t k[PER] = {k4.x >> shift, k4.y >> shift, k4.z >> shift, k4.w >> shift};
+        uint32_t before = __shfl_up(k[PER - 1], 1, 64);
+        if (lane == 0 && i1 > 0 && i1 <= n) before = keys[i1 - 1] >> shift;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int64_t i = i1 + j;
+            int64_t lo = 0, hi = -1;
+            if (i <= n) {
+                lo = i == 0 ? 0 : (int64_t)(j ? k[j - 1] : before) + 1;
+                hi = i == n ? n_cells : (int64_t)k[j];
+            }
+            const bool wide = hi - lo >= 64;
+            if (!wide)
+                for (int64_t c = lo; c <= hi; ++c) cell_start[c] = (uint32_t)i;
+            uint64_t m = __ballot(wide);
+            while (m) {
+                const int l = __ffsll((long long)m) - 1;
+                m &= m - 1;
+                const long long a = __shfl((long long)lo, l, 64), b = __shfl((long long)hi, l, 64);
+                const uint32_t v = (uint32_t)__shfl((int)i, l, 64);
+                for (long long c = a + lane; c <= b; c += 64) cell_start[c] = v;
+            }
         }
     }
 }
 
-__global__ void gather_offsets(const uint32_t *__restrict__ perm, const uint16_t *__restrict__ offs,
+__global__ void gather_offsets(const uint32_t *__restrict__ perm, const ushort4 *__restrict__ offs,
                                int n, uint16_t *__restrict__ pos, int32_t *__restrict__ perm_out) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const uint32_t p = perm[i];
-    pos[i] = offs[p];
-    pos[(int64_t)n + i] = offs[(int64_t)n + p];
-    pos[2 * (int64_t)n + i] = offs[2 * (int64_t)n + p];
+    const ushort4 o = offs[p];
+    pos[i] = o.x;
+    pos[(int64_t)n + i] = o.y;
+    pos[2 * (int64_t)n + i] = o.z;
     if (perm_out) perm_out[i] = (int32_t)p;
 }
 
@@ -267,7 +386,7 @@ __global__ void gather_offsets(const uint32_t *__restrict__ perm, const uint16_t
 // permutation: vout[i] = vel[p] + kick acc[p] in FP64 with separately rounded
 // operations (the value the kick-drift kernel drifted with), p = perm[i].
 __global__ void gather_offsets_kick(const uint32_t *__restrict__ perm,
-                                    const uint16_t *__restrict__ offs, int n,
+                                    const ushort4 *__restrict__ offs, int n,
                                     uint16_t *__restrict__ pos, int32_t *__restrict__ perm_out,
                                     const float *__restrict__ vel, const float *__restrict__ acc,
                                     double kick, float *__restrict__ vout,
@@ -277,10 +396,13 @@ __global__ void gather_offsets_kick(const uint32_t *__restrict__ perm,
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
         const uint32_t p = perm[i];
+        const ushort4 q = offs[p];
+        pos[i] = q.x;
+        pos[(int64_t)n + i] = q.y;
+        pos[2 * (int64_t)n + i] = q.z;
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
             const int64_t o = (int64_t)d * n;
-            pos[o + i] = offs[o + p];
             const double kv = kick * (double)acc[o + p];
             vout[o + i] = (float)((double)vel[o + p] + kv);
         }
@@ -361,19 +483,45 @@ unsigned strided(int64_t blocks, const uint32_t *run) {
     return (unsigned)(run ? std::min<int64_t>(blocks, 2048) : blocks);
 }
 
-// One stable pass over the 8-bit digit at `shift` of n keys: counts, rows,
-// scatter.  totals: 257 words; the last receives the start of digit 255.
+// One stable pass over the BITS-bit digit at `shift` of n keys: counts (unless
+// they are there already), rows, scatter.  totals: 2^BITS + 1 words; the last
+// receives the start of the last digit.
+template <int BITS>
 int radix_pass(const uint32_t *kin, const uint32_t *vin, uint32_t *kout, uint32_t *vout, int n,
-               int shift, uint32_t *ghist, uint32_t *totals, const uint32_t *run, hipStream_t s) {
+               int shift, uint32_t *ghist, uint32_t *totals, const uint32_t *run, hipStream_t s,
+               bool counted = false) {
     const int nblk = (n + kSortTile - 1) / kSortTile;
-    radix_count<<<strided(nblk, run), kBlock, 0, s>>>(kin, n, shift, nblk, ghist, run);
+    if (!counted) {
+        radix_count<BITS><<<strided(nblk, run), kBlock, 0, s>>>(kin, n, shift, nblk, ghist, run);
+        CUBE2_LAUNCH_CHECK();
+    }
+    radix_scan_rows<<<1 << BITS, kRowBlock, 0, s>>>(ghist, nblk, totals, run);
     CUBE2_LAUNCH_CHECK();
-    radix_scan_rows<<<256, kRowBlock, 0, s>>>(ghist, nblk, totals, run);
-    CUBE2_LAUNCH_CHECK();
-    radix_scatter<<<strided(nblk, run), kBlock, 0, s>>>(kin, vin, kout, vout, n, shift, nblk, ghist,
-                                                        totals, run);
+    radix_scatter<BITS><<<strided(nblk, run), kBlock, 0, s>>>(kin, vin, kout, vout, n, shift, nblk,
+                                                              ghist, totals, run);
     CUBE2_LAUNCH_CHECK();
     return CUBE2_OK;
+}
+
+// How the particles are sorted: by tile in `passes` digits of `bits` bits from
+// key bit `shift` on and then by cell within the tiles, or (few particles per
+// tile, or one tile) by the whole key, 8 bits a pass.
+struct SortPlan {
+    bool by_tile;
+    int bits, shift, passes;
+};
+SortPlan sort_plan(const cube2_ctx *ctx, int64_t n) {
+    const int64_t ntiles = (int64_t)ctx->nt * ctx->nt * ctx->nt;
+    int bits = 0;
+    while (((int64_t)kTileCells << bits) < ctx->n_cells) ++bits;
+    SortPlan p;
+    // a workgroup per tile: 64 particles and more pay for it
+    p.by_tile = bits > 0 && n >= 64 * ntiles;
+    p.shift = p.by_tile ? 9 : 0;
+    const int all = p.by_tile ? bits : bits + 9;
+    p.bits = p.by_tile && (all == 9 || all > 16) ? 9 : 8;   // 18 bits in two passes
+    p.passes = (all + p.bits - 1) / p.bits;
+    return p;
 }
 
 }  // namespace
@@ -397,7 +545,7 @@ int launch_order_tiles(cube2_ctx *ctx, const uint32_t *cs, unsigned char *work,
     else
         tile_keys_kernel<<<(ntiles + 255) / 256, 256, 0, s>>>(cs, nt, kin, vin);
     CUBE2_LAUNCH_CHECK();
-    const int r = radix_pass(kin, vin, kout, order, ntiles, 0, ghist, tmp, nullptr, s);
+    const int r = radix_pass<8>(kin, vin, kout, order, ntiles, 0, ghist, tmp, nullptr, s);
     if (r) return r;
     if (light_cap > 0 && ntiles >= kLightQueueWords) {
         fill_u32<<<1, kLightQueueWords, 0, s>>>(light_tile_queue_ptr(ctx, work, L), 0u, kLightQueueWords);
@@ -414,11 +562,11 @@ int launch_reset_tile_queue(cube2_ctx *ctx, unsigned char *work, const WorkLayou
     return CUBE2_OK;
 }
 
-// keys/vals (work) and offs_tmp (work) hold the unsorted particles.
-int launch_sort_by_cell(cube2_ctx *ctx, int64_t n64, const uint16_t *offs, uint16_t *pos,
-                        uint32_t *cell_start, int32_t *perm, unsigned char *work,
+// keys and sort_offsets (work) hold the unsorted particles.
+int launch_sort_by_cell(cube2_ctx *ctx, int64_t n64, uint16_t *pos, uint32_t *cell_start,
+                        int32_t *perm, unsigned char *work,
                         const WorkLayout &L, hipStream_t s, const float *vel, const float *acc,
-                        double kick, float *vel_out, const uint32_t *run) {
+                        double kick, float *vel_out, const uint32_t *run, bool counted) {
     const int n = (int)n64;
     uint32_t *tmp = reinterpret_cast<uint32_t *>(work + L.scan_tmp);
     uint32_t *k0 = reinterpret_cast<uint32_t *>(work + L.keys);
@@ -426,24 +574,41 @@ int launch_sort_by_cell(cube2_ctx *ctx, int64_t n64, const uint16_t *offs, uint1
     uint32_t *k1 = reinterpret_cast<uint32_t *>(work + L.keys2);
     uint32_t *v1 = reinterpret_cast<uint32_t *>(work + L.vals2);
     uint32_t *ghist = reinterpret_cast<uint32_t *>(work + L.hist);
+    const ushort4 *offs = sort_offsets(work, L);
     int r = CUBE2_OK;
     if (n == 0) {
-        cell_starts_kernel<<<1, 64, 0, s>>>(k0, 0, ctx->n_cells, cell_start, nullptr);
+        cell_starts_kernel<<<1, 64, 0, s>>>(k0, 0, 0, ctx->n_cells, cell_start, nullptr);
         CUBE2_LAUNCH_CHECK();
         return CUBE2_OK;
     }
 
-    int bits = 0;
-    while (((int64_t)1 << bits) < ctx->n_cells) ++bits;
-    for (int shift = 0; shift < bits; shift += 8) {
-        r = radix_pass(k0, v0, k1, v1, n, shift, ghist, tmp, run, s);
+    const SortPlan plan = sort_plan(ctx, n);
+    const uint32_t *vin = nullptr;      // the first pass takes the keys' indices
+    for (int k = 0; k < plan.passes; ++k) {
+        const int shift = plan.shift + k * plan.bits;
+        const bool have = counted && k == 0;
+        r = plan.bits == 9 ? radix_pass<9>(k0, vin, k1, v1, n, shift, ghist, tmp, run, s, have)
+                           : radix_pass<8>(k0, vin, k1, v1, n, shift, ghist, tmp, run, s, have);
         if (r) return r;
         uint32_t *t = k0; k0 = k1; k1 = t;
         t = v0; v0 = v1; v1 = t;
+        vin = v0;
+    }
+    if (plan.by_tile) {
+        const int ntiles = ctx->nt * ctx->nt * ctx->nt;
+        uint32_t *tstart = reinterpret_cast<uint32_t *>(work + L.tile_order);
+        cell_starts_kernel<<<strided(((int64_t)n + 1 + 1023) / 1024, run), 256, 0, s>>>(k0, n, 9, ntiles,
+                                                                                      tstart, run);
+        CUBE2_LAUNCH_CHECK();
+        tile_sort_kernel<<<strided(ntiles, run), kBlock, 0, s>>>(k0, v0, tstart, offs, n, ctx->nt, pos,
+                                                                 cell_start, perm, vel, acc, kick,
+                                                                 vel_out, run);
+        CUBE2_LAUNCH_CHECK();
+        return CUBE2_OK;
     }
     // cell_start (n_cells + 1 entries, the last = n) from the sorted keys
-    cell_starts_kernel<<<strided(((int64_t)n + 1 + 255) / 256, run), 256, 0, s>>>(
-        k0, n, ctx->n_cells, cell_start, run);
+    cell_starts_kernel<<<strided(((int64_t)n + 1 + 1023) / 1024, run), 256, 0, s>>>(
+        k0, n, 0, ctx->n_cells, cell_start, run);
     CUBE2_LAUNCH_CHECK();
     if (vel)
         gather_offsets_kick<<<strided(((int64_t)n + 255) / 256, run), 256, 0, s>>>(
@@ -457,14 +622,17 @@ int launch_sort_by_cell(cube2_ctx *ctx, int64_t n64, const uint16_t *offs, uint1
 int launch_pack(cube2_ctx *ctx, const float *x, int64_t n64, uint16_t *pos, uint32_t *cell_start,
                 int32_t *perm, unsigned char *work, const WorkLayout &L, hipStream_t s) {
     const int n = (int)n64;
-    uint16_t *offs = reinterpret_cast<uint16_t *>(work + L.offs_tmp);
+    ushort4 *offs = sort_offsets(work, L);
     if (n > 0) {
-        quantize_kernel<<<(n + 255) / 256, 256, 0, s>>>(
-            x, n, ctx->n_f, ctx->nt, reinterpret_cast<uint32_t *>(work + L.keys),
-            reinterpret_cast<uint32_t *>(work + L.vals), offs);
+        const SortPlan plan = sort_plan(ctx, n);
+        const int nblk = (n + kSortTile - 1) / kSortTile;
+        auto k = plan.bits == 9 ? quantize_kernel<9> : quantize_kernel<8>;
+        k<<<nblk, kBlock, 0, s>>>(x, n, ctx->n_f, ctx->nt, reinterpret_cast<uint32_t *>(work + L.keys),
+                                  offs, plan.shift, nblk, reinterpret_cast<uint32_t *>(work + L.hist));
         CUBE2_LAUNCH_CHECK();
     }
-    return launch_sort_by_cell(ctx, n, offs, pos, cell_start, perm, work, L, s);
+    return launch_sort_by_cell(ctx, n, pos, cell_start, perm, work, L, s, nullptr, nullptr, 0.0,
+                               nullptr, nullptr, true);
 }
 
 }  // namespace cube2
