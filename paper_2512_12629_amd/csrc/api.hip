@@ -434,6 +434,13 @@ int cube2_pp_force_skip(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cel
 
 namespace {
 
+// Meshes of fewer than 8^3 tiles take PM and PP one after the other: there the
+// fork and the join of the second stream cost more than the overlap gives (4^3
+// tiles: force 73 us against 92, adjoint 135 against 151; 8^3 tiles: 118 against
+// 113 and 345 against 343).
+constexpr int kConcurrentFromNt = 8;
+constexpr int kPPOrderFirstFromNt = 32;
+
 // The PM part on `stream` and the PP part on the context's side stream,
 // joined on `stream`, then out = PM + PP.  abar == nullptr: the force; else
 // the adjoint for the cotangents abar.
@@ -442,11 +449,29 @@ int force_concurrent(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cell_s
                      cube2_stream_t stream, unsigned char *work_, const cube2::WorkLayout &L_) {
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     if (!ctx->side) return CUBE2_ESTATE;   // made by cube2_init_tables
+    if (ctx->nt < kConcurrentFromNt) {
+        // one after the other on the caller's stream, the PP adding to the PM's result
+        int rcode = abar ? cube2_pm_force_backward(ctx, pos, cell_start, n, abar, out, accumulate,
+                                                   work, work_bytes, stream)
+                         : cube2_pm_force(ctx, pos, cell_start, n, out, 0, work, work_bytes, stream);
+        if (rcode) return rcode;
+        return abar ? launch_pp_backward(ctx, pos, cell_start, n, abar, out, 1, work_, L_, s)
+                    : launch_pp(ctx, pos, cell_start, n, out, 1, work_, L_, s);
+    }
     float *acc_pp = reinterpret_cast<float *>(work_ + L_.acc_pp);
-    // PP first (it starts with a reduced persistent grid), the PM part beside it
-    CUBE2_CHECK_HIP(hipEventRecord(ctx->ev_fork, s));
-    CUBE2_CHECK_HIP(hipStreamWaitEvent(ctx->side, ctx->ev_fork, 0));
-    int rcode = launch_pp_concurrent(ctx, pos, cell_start, n, abar, acc_pp, work_, L_, ctx->side);
+    // PP first (it starts with a reduced persistent grid), the PM part beside it.
+    // On large meshes the PP's tile order is made on the caller's stream before
+    // the fork, so that the PP kernel starts before the deposit, which would
+    // fill the LDS of every CU and keep it out until its end (512^3 particles:
+    // 45 ms instead of 39).  On small ones the deposit goes first: it is over
+    // before the PP's order is made (128^3 particles: 300 us instead of 345).
+    const bool order_first = ctx->nt >= kPPOrderFirstFromNt;
+    if (!order_first) {
+        CUBE2_CHECK_HIP(hipEventRecord(ctx->ev_fork, s));
+        CUBE2_CHECK_HIP(hipStreamWaitEvent(ctx->side, ctx->ev_fork, 0));
+    }
+    int rcode = launch_pp_concurrent(ctx, pos, cell_start, n, abar, acc_pp, work_, L_, ctx->side,
+                                     order_first ? s : ctx->side);
     if (rcode == CUBE2_OK)
         rcode = abar ? cube2_pm_force_backward(ctx, pos, cell_start, n, abar, out, accumulate,
                                                work, work_bytes, stream)

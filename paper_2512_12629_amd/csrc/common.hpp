@@ -299,41 +299,43 @@ __device__ __forceinline__ void tile_cell_sort(uint32_t (*hist)[kTileCells] /*[k
     }
 }
 
-// Tile scheduling of the per-tile kernels.  With a work queue (queue != 0)
-// the workgroups are persistent: each takes the next tile of the
-// heaviest-first order (launch_order_tiles) from one global counter until the
-// order is exhausted.  Without a queue, workgroup b takes the tile
-// tile_of_block(b) once.  claim_tile is called by all threads of the
-// workgroup and returns false when the workgroup is done (a block-uniform
-// result).
+// Tile scheduling of the per-tile kernels: persistent workgroups (or, for light
+// PP tiles, waves) take the tiles of the heaviest-first order
+// (launch_order_tiles) until they are exhausted.
 
-// One claim on the work counter (a single thread calls it): the position in
+// One claim on a work counter (a single thread calls it): the position in
 // `order` of the next tile, or a value >= ntiles when all are taken.
 __device__ __forceinline__ int claim_slot(uint32_t *queue, int ntiles) {
     const uint32_t v = atomicAdd(queue, 1u);
     return v < (uint32_t)ntiles ? (int)v : ntiles;
 }
 
-__device__ __forceinline__ bool claim_tile(const uint32_t *order, uint32_t *queue, int ntiles,
-                                          int nt, int &round, int *tile_sh, int &tx, int &ty,
-                                          int &tz) {
-    if (queue) {
-        __syncthreads();  // the previous tile is done with the LDS arrays
-        if (threadIdx.x == 0) *tile_sh = claim_slot(queue, ntiles);
-        __syncthreads();
-        const int ti = *tile_sh;
-        if (ti >= ntiles) return false;
-        const int t = (int)order[ti];
-        tx = t % nt;
-        ty = (t / nt) % nt;
-        tz = t / (nt * nt);
-    } else {
-        if (round > 0) return false;
-        tile_of_block(blockIdx.x, nt, tx, ty, tz);
+// Claims that come often use a counter per XCD: one counter serves only some 70
+// million claims a second (14 ns each; the deposit's 262144 tiles of a 1024^3
+// mesh took 3.4 ms whatever they held).  Workgroups b = g (mod 8) run on one XCD
+// and take every 8th tile of the order, the XCD's slab of the mesh
+// (tile_of_block) where the order is that of the blocks.
+// When a group's share is taken, its workgroups go on with the next group's.
+struct XcdShare {
+    int ng, g, gx, first;      // groups, this workgroup's, its workgroups, its number among them
+    int done = 0;              // groups found exhausted
+    __device__ __forceinline__ XcdShare()
+        : ng(gridDim.x >= 8 ? 8 : 1), g((int)blockIdx.x % ng),
+          gx(((int)gridDim.x - g + ng - 1) / ng), first((int)blockIdx.x / ng) {}
+    // items of the group out of n
+    __device__ __forceinline__ int share(int n) const { return n > g ? (n - g + ng - 1) / ng : 0; }
+    // place in the order of the group's i-th item
+    __device__ __forceinline__ int place(int i) const { return i * ng + g; }
+    // a claim on the group's counter
+    __device__ __forceinline__ int claim(uint32_t *queues) const {
+        return (int)min(atomicAdd(queues + 32 * g, 1u), 0x3FFFFFFFu);
     }
-    ++round;
-    return true;
-}
+    // on to the next group; false when all are exhausted
+    __device__ __forceinline__ bool next_group() {
+        g = g + 1 < ng ? g + 1 : 0;
+        return ++done < ng;
+    }
+};
 
 // Sums over the 64 lanes of a wave (butterfly; every lane must be active).
 // The order of the additions is fixed, so float sums are deterministic.
@@ -546,11 +548,12 @@ inline uint32_t *tile_queue_ptr(const cube2_ctx *ctx, unsigned char *work, const
     return reinterpret_cast<uint32_t *>(work + L.tile_order) + 4 * (size_t)ctx->nt * ctx->nt * ctx->nt;
 }
 
-// The light tiles' work counters of the PP kernels, 8 of them 128 bytes apart:
-// in the part of the tile order region that the sort no longer needs (the keys
-// and values before it).  Meshes of fewer tiles than kLightQueueWords use none.
-constexpr int kLightQueueWords = 8 * 32;
-inline uint32_t *light_tile_queue_ptr(const cube2_ctx *ctx, unsigned char *work, const WorkLayout &L) {
+// The XCDs' work counters (XcdShare), 8 of them 128 bytes apart, cleared by
+// launch_order_tiles: in the part of the tile order region that the sort no
+// longer needs (the keys and values before it).  Meshes of fewer tiles than
+// kXcdQueueWords have none: their items are taken at fixed strides.
+constexpr int kXcdQueueWords = 8 * 32;
+inline uint32_t *xcd_queue_ptr(const cube2_ctx *ctx, unsigned char *work, const WorkLayout &L) {
     return reinterpret_cast<uint32_t *>(work + L.tile_order) + (size_t)ctx->nt * ctx->nt * ctx->nt;
 }
 
@@ -576,7 +579,7 @@ int launch_vel_decode(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, i
                       hipStream_t s);
 int launch_pp_concurrent(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,
                          const float *abar, float *acc_pp, unsigned char *work, const WorkLayout &L,
-                         hipStream_t s);
+                         hipStream_t s, hipStream_t order_stream);
 int launch_add3(float *acc, const float *acc_pp, int64_t m, hipStream_t s);
 // skip (device, one byte per tile, index (tz nt + ty) nt + tx, may be NULL):
 // tiles whose own particles the kernel leaves alone

@@ -251,21 +251,32 @@ __global__ __launch_bounds__(kBlock) void deposit_kernel(
         }
     };
 
-    // Persistent workgroups over the heaviest-first tile order.  The loop is
-    // software-pipelined: the claim of the next tile is in flight while the
-    // current one deposits, and the next tile's segment ranges are loaded
-    // while the current one writes its nodes.
+    // Persistent workgroups over the heaviest-first tile order, each XCD's share of
+    // it (XcdShare).  The loop is software-pipelined: the claim of the next tile
+    // is in flight while the current one deposits, and the next tile's segment
+    // ranges are loaded while the current one writes its nodes.
+    XcdShare xcd;
+    const bool fixed = ntiles < kXcdQueueWords;
+    // thread 0: the order's place of the next tile, ntiles when all are taken
+    int at = blockIdx.x;
+    auto claim = [&]() {
+        while (xcd.done < xcd.ng) {
+            const int i = xcd.claim(queue);
+            if (i < xcd.share(ntiles)) return xcd.place(i);
+            xcd.next_group();
+        }
+        return ntiles;
+    };
     if (tid == 0) {
-        const int slot = claim_slot(queue, ntiles);
-        next_sh = slot < ntiles ? (int)order[slot] : -1;
+        if (!fixed) at = claim();
+        next_sh = at < ntiles ? (int)order[at] : -1;
     }
     __syncthreads();
     int t = next_sh;
     if (t >= 0) load_segments(t);
     while (t >= 0) {
         const int tx = t % nt, ty = (t / nt) % nt, tz = t / (nt * nt);
-        int slot = ntiles;
-        if (tid == 0) slot = claim_slot(queue, ntiles);
+        if (tid == 0) at = fixed ? at + (int)gridDim.x : claim();
 
         if (FINE)
             for (int i = tid; i < kTileFine * kTileFine * kTileFine; i += kBlock) acc_f[i] = 0ull;
@@ -348,7 +359,7 @@ __global__ __launch_bounds__(kBlock) void deposit_kernel(
             }
         }
         // the next tile (the claim made at the top of this one has returned)
-        if (tid == 0) next_sh = slot < ntiles ? (int)order[slot] : -1;
+        if (tid == 0) next_sh = at < ntiles ? (int)order[at] : -1;
         __syncthreads();
         const int t_next = next_sh;
         if (t_next >= 0) load_segments(t_next);
@@ -457,7 +468,7 @@ int launch_deposit(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int6
     int r = launch_order_tiles(ctx, cs, work, L, s);
     if (r) return r;
     const uint32_t *order = tile_order_ptr(work, L);
-    uint32_t *queue = tile_queue_ptr(ctx, work, L);
+    uint32_t *queue = xcd_queue_ptr(ctx, work, L);
     const int ntiles = (int)blocks;
     if (ctx->tsc)
         r = launch_deposit_kernels<3>(fine, coarse, pos, cs, n, ctx->n_f, nt, rho_f, ffx, cacc, n_c,

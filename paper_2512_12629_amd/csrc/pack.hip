@@ -469,6 +469,77 @@ __global__ void pp_tile_keys_kernel(const uint32_t *__restrict__ cs, int nt, uin
     }
 }
 
+// The order of up to kOrderOne tiles by their keys in one workgroup, in place of
+// the three launches of a radix pass: each wave ranks its tiles as the radix
+// scatter does.  keys == NULL: the key of a tile is its particles in thousands,
+// most first (tile_keys_kernel).  start255 receives where the last key starts.
+constexpr int kOrderBlock = 1024, kOrderOne = 4 * kOrderBlock;
+__global__ __launch_bounds__(kOrderBlock) void order_tiles_kernel(
+    const uint32_t *__restrict__ cs, const uint32_t *__restrict__ keys, int nt,
+    uint32_t *__restrict__ order, uint32_t *__restrict__ start255, uint32_t *__restrict__ queue,
+    uint32_t *__restrict__ xcd_queue) {
+    constexpr int W = kOrderBlock / 64, PER = kOrderOne / kOrderBlock;
+    __shared__ uint32_t wcnt[W][256];
+    __shared__ uint32_t scan_sh[W + 1];
+    const int ntiles = nt * nt * nt, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    for (int i = tid; i < W * 256; i += kOrderBlock) wcnt[i / 256][i % 256] = 0;
+    const int per = (ntiles + 64 * W - 1) / (64 * W);   // rounds of 64 tiles per wave
+    uint32_t key[PER], tile[PER], place[PER];
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        const int b = (w * per + r) * 64 + lane;
+        key[r] = 256u;
+        tile[r] = 0;
+        if (r < per && b < ntiles) {
+            int tx, ty, tz;
+            tile_of_block(b, nt, tx, ty, tz);
+            tile[r] = (uint32_t)((tz * nt + ty) * nt + tx);
+            key[r] = keys ? keys[b]
+                          : 255u - min((cs[(tile[r] + 1) * kTileCells] - cs[tile[r] * kTileCells]) >> 10, 255u);
+        }
+    }
+    __syncthreads();
+    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        uint64_t peers = __ballot(key[r] < 256u);
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const bool bit = (key[r] >> b) & 1u;
+            const uint64_t m = __ballot(bit);
+            peers &= bit ? m : ~m;
+        }
+        const uint32_t rank = (uint32_t)__popcll(peers & lt);
+        const uint32_t before = wcnt[w][key[r] & 255u];
+        if (key[r] < 256u && rank == 0) wcnt[w][key[r]] = before + (uint32_t)__popcll(peers);
+        place[r] = before + rank;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // as in radix_scatter
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    uint32_t mine = 0, total;
+    if (tid < 256) {
+#pragma unroll
+        for (int v = 0; v < W; ++v) mine += wcnt[v][tid];
+    }
+    uint32_t at = block_exclusive_scan<kOrderBlock>(mine, scan_sh, total);
+    if (tid == 255) *start255 = at;
+    if (tid < 256) {
+#pragma unroll
+        for (int v = 0; v < W; ++v) {
+            const uint32_t c = wcnt[v][tid];
+            wcnt[v][tid] = at;
+            at += c;
+        }
+    }
+    if (tid == 0) *queue = 0u;
+    if (xcd_queue && tid < kXcdQueueWords) xcd_queue[tid] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < PER; ++r)
+        if (key[r] < 256u) order[wcnt[w][key[r]] + place[r]] = tile[r];
+}
+
 }  // namespace
 
 int launch_exclusive_scan(const uint32_t *in, uint32_t *out, int64_t m, uint32_t *tmp,
@@ -540,18 +611,28 @@ int launch_order_tiles(cube2_ctx *ctx, const uint32_t *cs, unsigned char *work,
     uint32_t *order = base, *vin = base + ntiles, *kin = base + 2 * ntiles, *kout = base + 3 * ntiles;
     uint32_t *tmp = reinterpret_cast<uint32_t *>(work + L.scan_tmp);
     uint32_t *ghist = reinterpret_cast<uint32_t *>(work + L.hist);
-    if (light_cap > 0)
+    uint32_t *xcd_queue = ntiles >= kXcdQueueWords ? xcd_queue_ptr(ctx, work, L) : nullptr;
+    if (n_heavy) *n_heavy = tmp + 256;   // where the last key starts
+    if (light_cap > 0) {
         pp_tile_keys_kernel<<<(ntiles + 3) / 4, 256, 0, s>>>(cs, nt, (uint32_t)light_cap, kin, vin);
-    else
-        tile_keys_kernel<<<(ntiles + 255) / 256, 256, 0, s>>>(cs, nt, kin, vin);
-    CUBE2_LAUNCH_CHECK();
-    const int r = radix_pass<8>(kin, vin, kout, order, ntiles, 0, ghist, tmp, nullptr, s);
-    if (r) return r;
-    if (light_cap > 0 && ntiles >= kLightQueueWords) {
-        fill_u32<<<1, kLightQueueWords, 0, s>>>(light_tile_queue_ptr(ctx, work, L), 0u, kLightQueueWords);
         CUBE2_LAUNCH_CHECK();
     }
-    if (n_heavy) *n_heavy = tmp + 256;   // where the last key starts
+    if (ntiles <= kOrderOne) {
+        order_tiles_kernel<<<1, kOrderBlock, 0, s>>>(cs, light_cap > 0 ? kin : nullptr, nt, order, tmp + 256,
+                                                     tile_queue_ptr(ctx, work, L), xcd_queue);
+        CUBE2_LAUNCH_CHECK();
+        return CUBE2_OK;
+    }
+    if (light_cap <= 0) {
+        tile_keys_kernel<<<(ntiles + 255) / 256, 256, 0, s>>>(cs, nt, kin, vin);
+        CUBE2_LAUNCH_CHECK();
+    }
+    const int r = radix_pass<8>(kin, vin, kout, order, ntiles, 0, ghist, tmp, nullptr, s);
+    if (r) return r;
+    if (xcd_queue) {
+        fill_u32<<<1, kXcdQueueWords, 0, s>>>(xcd_queue, 0u, kXcdQueueWords);
+        CUBE2_LAUNCH_CHECK();
+    }
     return launch_reset_tile_queue(ctx, work, L, s);
 }
 

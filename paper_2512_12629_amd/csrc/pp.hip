@@ -280,31 +280,34 @@ __device__ __forceinline__ void light_tiles(unsigned char *lds, const uint16_t *
     const int per_tile = kTileIos / layers;
     const int ncell = 100 * (layers + 2), nown = 8 * layers;
     auto part_of = [](int bx) { return bx < 1 ? 0 : (bx < 1 + kTileIos ? 1 : 2); };
-    // Workgroups b = g (mod 8) run on one XCD; they take every 8th tile of the
-    // order, which is the XCD's slab of the mesh (tile_of_block).  A wave's
-    // first chunk of items is its number among the group's waves; the next ones
-    // come from the group's counter, or, with up to 4 items per wave, at fixed
-    // strides: one atomic counter serves only some 70 million claims a second
-    // (measured, 14-18 ns each), too few for one claim per item.
-    const int ng = gridDim.x >= 8 ? 8 : 1, g = (int)blockIdx.x % ng;
-    const int gx = ((int)gridDim.x - g + ng - 1) / ng;                // workgroups of the group
-    const int nw = gx * P::WAVES;
-    const int nitems = ntiles > g ? (ntiles - g + ng - 1) / ng * per_tile : 0;
-    const bool fixed = nitems <= 4 * nw || nt * nt * nt < kLightQueueWords;
+    // A wave's first chunk of items is its number among its XCD's waves; the next
+    // ones come from the XCD's counter, or, with up to 4 items per wave, at fixed
+    // strides (one claim per item from one counter: 31.6 ms instead of 25.0 for
+    // 512^3 particles).
+    XcdShare xcd;
+    int nw = xcd.gx * P::WAVES, nitems = xcd.share(ntiles) * per_tile;
+    const bool fixed = nitems <= 4 * nw || nt * nt * nt < kXcdQueueWords;
     const int chunk = fixed ? 1 : min(nitems / (2 * nw), 64);
-    int next = wave * gx + (int)blockIdx.x / ng, item = 0, end = 0;
+    int next = wave * xcd.gx + xcd.first, item = 0, end = 0;
     for (;;) {
         if (item >= end) {
             const int c = __builtin_amdgcn_readfirstlane(next);
-            if (c >= (nitems + chunk - 1) / chunk) break;
+            if (c >= (nitems + chunk - 1) / chunk) {
+                if (fixed || !xcd.next_group()) break;
+                // the next group's chunks after those its own waves began with
+                nitems = xcd.share(ntiles) * per_tile;
+                nw = ((int)gridDim.x - xcd.g + xcd.ng - 1) / xcd.ng * P::WAVES;
+                if (lane == 0) next = nw + xcd.claim(queue);
+                continue;
+            }
             item = c * chunk;
             end = min(item + chunk, nitems);
             if (fixed)
                 next = c + nw;
             else if (lane == 0)
-                next = nw + (int)min(atomicAdd(queue + 32 * g, 1u), 0x3FFFFFFFu);
+                next = nw + xcd.claim(queue);
         }
-        const int t = (int)order[item / per_tile * ng + g], zp = item % per_tile;
+        const int t = (int)order[xcd.place(item / per_tile)], zp = item % per_tile;
         ++item;
         if (skip && skip[t]) continue;
         const int tx = t % nt, ty = (t / nt) % nt, tz = t / (nt * nt);
@@ -1022,7 +1025,7 @@ template <bool ADJ, int H, bool CLAMP>
 int launch_pp_kernel_h(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,
                      const float *abar, float *out, int accumulate, unsigned char *work,
                      const WorkLayout &L, hipStream_t s, float grid_frac,
-                     const uint8_t *skip) {
+                     const uint8_t *skip, hipStream_t order_stream) {
     const float4 *table =
         reinterpret_cast<const float4 *>(ctx->tables + (ADJ ? ctx->pp_aoff : ctx->pp_soff));
     PPLaw law;
@@ -1036,8 +1039,12 @@ int launch_pp_kernel_h(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, 
     // scanned digit counts say where they begin
     const int lcap = H == 1 ? PPLight<ADJ>::LCAP : 0;
     const uint32_t *n_heavy = nullptr;
-    int r = launch_order_tiles(ctx, cs, work, L, s, lcap, &n_heavy);
+    int r = launch_order_tiles(ctx, cs, work, L, order_stream, lcap, &n_heavy);
     if (r) return r;
+    if (order_stream != s) {
+        CUBE2_CHECK_HIP(hipEventRecord(ctx->ev_fork, order_stream));
+        CUBE2_CHECK_HIP(hipStreamWaitEvent(s, ctx->ev_fork, 0));
+    }
     const uint32_t *order = tile_order_ptr(work, L);
     uint32_t *queue = tile_queue_ptr(ctx, work, L);
     auto k = pp_kernel<ADJ, H, CLAMP>;
@@ -1050,7 +1057,7 @@ int launch_pp_kernel_h(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, 
     k<<<grid, PPGeo<ADJ, H>::BLOCK, 0, s>>>(
         pos, cs, (int)n, nt, table, law,
         (float)(ctx->cfg.g_newton * ctx->cfg.m_p), abar, out, accumulate, order, queue, ntiles,
-        nsplit, n_heavy, light_tile_queue_ptr(ctx, work, L), layers, skip);
+        nsplit, n_heavy, xcd_queue_ptr(ctx, work, L), layers, skip);
     CUBE2_LAUNCH_CHECK();
     return CUBE2_OK;
 }
@@ -1058,10 +1065,11 @@ int launch_pp_kernel_h(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, 
 template <bool ADJ>
 int launch_pp_kernel(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,
                      const float *abar, float *out, int accumulate, unsigned char *work,
-                     const WorkLayout &L, hipStream_t s, float grid_frac = 1.0f,
-                     const uint8_t *skip = nullptr) {
+                     const WorkLayout &L, hipStream_t s, hipStream_t order_stream,
+                     float grid_frac = 1.0f, const uint8_t *skip = nullptr) {
     auto go = [&](auto launch) {
-        return launch(ctx, pos, cs, n, abar, out, accumulate, work, L, s, grid_frac, skip);
+        return launch(ctx, pos, cs, n, abar, out, accumulate, work, L, s, grid_frac, skip,
+                      order_stream);
     };
     if (ctx->pp_halo == 1)
         return ctx->pp_clamp ? go(launch_pp_kernel_h<ADJ, 1, true>)
@@ -1086,18 +1094,13 @@ __global__ void add3_kernel4(float4 *__restrict__ acc, const float4 *__restrict_
 
 // Share of the persistent PP grid when the PM force runs beside it: the PM
 // kernels take the freed workgroup slots, and the memory-bound PM and the
-// VALU-bound PP then overlap on the same CUs.
+// VALU- and LDS-bound PP then overlap on the same CUs.  Measured (all of the
+// grid, 7/8, 3/4, 5/8, 1/2): 512^3 particles 42.5, 41.3, 39.1, 40.5, 48.5 ms;
+// 256^3 with 1000 halos 5.44, 5.33, 4.97, 5.27, 6.26 ms; two-cell reach, 201^3
+// with 300 halos 5.88, 5.95, 5.74, 6.04, 7.58 ms.
 constexpr float kPPConcurrentFrac = 0.75f;
-// ... on meshes of fewer than 64^3 tiles (256^3 particles on a 512^3 mesh),
-// where the PM part is a smaller share of the step and the PP has fewer
-// tiles per workgroup, the whole grid (measured: 7.08 ms, against 7.19 at
-// 7/8 and 7.46 at 3/4).
-constexpr int kPPConcurrentFullBelowNt = 64;
-// With the two-cell reach (b_f > 2) the PP has ~5x the pairs and the PM part
-// fits in what the PP leaves: the full grid (measured at b_f = 3.5 on 512^3
-// particles: 89.9 ms, against 91.9 at 7/8, 104.7 at 3/4 and 98.4 with PM and
-// PP one after the other).
-constexpr float kPPConcurrentFracH2 = 1.0f;
+// meshes of fewer tiles per axis take other shares of the adjoint's grid
+constexpr int kPPConcurrentSmallNt = 64;
 // The same for the PP adjoint beside the PM adjoint (1024-thread workgroups,
 // one per CU): measured on 512^3 particles, 5/8 of the CUs gave the shortest
 // force adjoint (106.0 ms; 3/4 107.6, 7/8 106.7, all 110.5, 9/16 110.6).
@@ -1115,25 +1118,24 @@ constexpr float kPPAdjConcurrentFracH2 = 0.875f;
 
 // PP force (abar == nullptr) or its adjoint for the cotangents abar into
 // acc_pp (not accumulated) with its own tile order and work counter (the
-// pp_order / pp_hist / pp_scan regions), so that it can run on another stream
-// while the PM part uses the shared ones.
+// pp_order / pp_hist / pp_scan regions), so that it can run on another stream s
+// while the PM part uses the shared ones.  The tile order is made on
+// `order_stream`; if that is not s, s waits for it.
 int launch_pp_concurrent(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,
                          const float *abar, float *acc_pp, unsigned char *work, const WorkLayout &L,
-                         hipStream_t s) {
+                         hipStream_t s, hipStream_t order_stream) {
     WorkLayout Lpp = L;
     Lpp.tile_order = L.pp_order;
     Lpp.hist = L.pp_hist;
     Lpp.scan_tmp = L.pp_scan;
-    const bool small = ctx->nt < kPPConcurrentFullBelowNt;
+    const bool small = ctx->nt < kPPConcurrentSmallNt;
     if (abar)
-        return launch_pp_kernel<true>(ctx, pos, cs, n, abar, acc_pp, 0, work, Lpp, s,
+        return launch_pp_kernel<true>(ctx, pos, cs, n, abar, acc_pp, 0, work, Lpp, s, order_stream,
                                       ctx->pp_halo != 1 ? kPPAdjConcurrentFracH2
                                       : small           ? kPPAdjConcurrentFracSmall
                                                         : kPPAdjConcurrentFrac);
-    const float frac = ctx->pp_halo != 1 ? kPPConcurrentFracH2
-                       : small           ? 1.0f
-                                         : kPPConcurrentFrac;
-    return launch_pp_kernel<false>(ctx, pos, cs, n, nullptr, acc_pp, 0, work, Lpp, s, frac);
+    return launch_pp_kernel<false>(ctx, pos, cs, n, nullptr, acc_pp, 0, work, Lpp, s, order_stream,
+                                   kPPConcurrentFrac);
 }
 
 int launch_add3(float *acc, const float *acc_pp, int64_t m, hipStream_t s) {
@@ -1155,14 +1157,14 @@ int launch_add3(float *acc, const float *acc_pp, int64_t m, hipStream_t s) {
 int launch_pp(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n, float *acc,
               int accumulate, unsigned char *work, const WorkLayout &L, hipStream_t s,
               const uint8_t *skip) {
-    return launch_pp_kernel<false>(ctx, pos, cs, n, nullptr, acc, accumulate, work, L, s, 1.0f,
+    return launch_pp_kernel<false>(ctx, pos, cs, n, nullptr, acc, accumulate, work, L, s, s, 1.0f,
                                    skip);
 }
 
 int launch_pp_backward(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,
                        const float *acc_bar, float *x_bar, int accumulate, unsigned char *work,
                        const WorkLayout &L, hipStream_t s) {
-    return launch_pp_kernel<true>(ctx, pos, cs, n, acc_bar, x_bar, accumulate, work, L, s);
+    return launch_pp_kernel<true>(ctx, pos, cs, n, acc_bar, x_bar, accumulate, work, L, s, s);
 }
 
 }  // namespace cube2
