@@ -629,6 +629,13 @@ class Cube2Tiled:
         if self.local is None or m > self.m_cap:
             self.m_cap = max(m, 1024)
             self.local = Cube2(self.cfg_local, self.m_cap, self.device)
+            # PP tiles of the local box outside the tile proper: their forces are
+            # not used, so their pair sums are not computed
+            nt = self.n_local // 16
+            lo, hi = self.buffer // 16, -(-(self.buffer + self.tile) // 16)
+            skip = torch.ones((nt, nt, nt), dtype=torch.uint8)
+            skip[lo:hi, lo:hi, lo:hi] = 0
+            self.skip = skip.reshape(-1).to(self.device)
             self.x_buf = torch.empty(3 * self.m_cap, dtype=torch.float32, device=self.device)
             self.i_buf = torch.empty(self.m_cap, dtype=torch.int32, device=self.device)
         return self.local
@@ -652,7 +659,7 @@ class Cube2Tiled:
         xl = self.x_buf[:3 * m].view(3, m)
         pos_l, cs_l, perm_l = loc.pack(xl)
         a_l = loc.pm_level_force(pos_l, cs_l, 0)
-        loc.pp_force(pos_l, cs_l, a_l)
+        cube2_pp_force_skip(loc.ctx, pos_l, cs_l, self.skip, a_l, loc.work, accumulate=True)
         cube2_tile_scatter_add(perm_l, xl, self.i_buf[:m], 1, self.tile, self.buffer, a_l, acc)
 
     def force(self, pos, cs, origins=None):

@@ -184,6 +184,58 @@ __device__ __forceinline__ void pair_adjoint(float dx, float dy, float dz, float
     oz = fmaf(du, dz, fmaf(g, uz, oz));
 }
 
+// The pairs of one particle with the staged neighbours v0, v0 + STEP, ... below v1:
+// four per iteration, so that the loop control and the LDS latency spread over
+// more work.  The loops run on the LDS address against precomputed bounds, never
+// below xs (LDS addresses compare unsigned).
+template <bool ADJ, bool CLAMP, int STEP>
+__device__ __forceinline__ void staged_pairs(const float4 *xs, const float2 *xa, uint32_t v0,
+                                             uint32_t v1, float xi, float yi, float zi, float aix,
+                                             float aiy, float aiz, uint32_t bmax, float &fx, float &fy,
+                                             float &fz) {
+    const float4 *q = xs + v0;
+    const float2 *qa = xa + v0;
+    const float4 *const qe = xs + v1;
+    const float4 *const qe4 = xs + (v1 > v0 + 3 * STEP ? v1 - 3 * STEP : v0);
+    auto pair = [&](const float4 &x, const float2 &a) {
+        if constexpr (ADJ)
+            pair_adjoint<CLAMP>(x.x - xi, x.y - yi, x.z - zi, x.w - aix, a.x - aiy, a.y - aiz, bmax, fx,
+                                fy, fz);
+        else
+            pair_accumulate<CLAMP>(x.x - xi, x.y - yi, x.z - zi, x.w, bmax, fx, fy, fz);
+    };
+    auto cot = [&](int t) { return ADJ ? qa[t] : make_float2(0.f, 0.f); };
+    for (; q < qe4; q += 4 * STEP, qa += 4 * STEP) {
+        float4 x[4];
+        float2 a[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            x[t] = q[t * STEP];
+            a[t] = cot(t * STEP);
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) pair(x[t], a[t]);
+    }
+    if constexpr (!ADJ && STEP == 1) {   // up to three more: two, then one
+        if ((v1 - v0) & 2u) {
+            const float4 x = q[0], y = q[1];
+            pair(x, cot(0));
+            pair(y, cot(1));
+            q += 2;
+        }
+        if ((v1 - v0) & 1u) pair(q[0], cot(0));
+    } else {
+        for (; q < qe; q += STEP, qa += STEP) pair(q[0], cot(0));
+    }
+}
+
+// Sum over the four lanes of a quad, the same in each of them.
+__device__ __forceinline__ float quad_sum(float v) {
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true));
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, true));
+    return v;
+}
+
 // The heaviest tiles are split: the first kSplitTiles entries of the
 // heaviest-first order are offered as kSplitParts work items each; a tile
 // with `own` particles uses min(kSplitParts, ceil(own / block)) of them,
@@ -194,7 +246,14 @@ __device__ __forceinline__ void pair_adjoint(float dx, float dy, float dz, float
 // alone; each particle's sum is still formed by one thread in the same
 // order.  (Splitting four tiles per workgroup was slower: every part
 // stages the box again.)
+//
+// Where the heavy tiles are so few that a workgroup gets at most two of them, all
+// are split, into parts of a quarter of a block: four lanes share a particle,
+// each taking every fourth neighbour, and their sums are added per range.  A part
+// of whole blocks would leave a CU to 8 or 16 waves whose pair loops wait on
+// the LDS (one halo of 2048 particles in a box alone: 276 us).
 constexpr int kSplitParts = 8, kSplitTiles = 128;
+constexpr int kFewTiles = 4096, kFewParts = 32, kFewLanes = 4;
 
 // The pair law's units (see above): ps = 2^j and its product with the 2^-15 of
 // a position unit, the scale of the sums (unit, and for the forward D's
@@ -466,7 +525,7 @@ __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK), 4) void pp_kernel(const uin
                                                      float *__restrict__ acc, int accumulate,
                                                      const uint32_t *__restrict__ order,
                                                      uint32_t *__restrict__ queue, int ntiles,
-                                                     int nsplit, const uint32_t *__restrict__ n_heavy,
+                                                     const uint32_t *__restrict__ n_heavy,
                                                      uint32_t *__restrict__ light_queue,
                                                      int layers, const uint8_t *__restrict__ skip) {
     using G = PPGeo<ADJ, H>;
@@ -503,11 +562,14 @@ __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK), 4) void pp_kernel(const uin
     // Persistent workgroups: each takes the next work item of the
     // heaviest-first order (claim_slot) until all are taken (the exit test
     // is block-uniform).  Thread 0 claims the next item while the current
-    // one is processed.  Items [0, nsplit kSplitParts) are the parts of the
-    // nsplit heaviest tiles, the rest one whole tile each.
-    constexpr int kParts = kSplitParts;
-    const int nheavy = H == 1 ? (int)*n_heavy : ntiles;
-    nsplit = min(nsplit, nheavy);
+    // one is processed.  Items [0, nsplit kParts) are the parts of the nsplit
+    // heaviest tiles, the rest one whole tile each.
+    // n_heavy: the tiles that are not light; only the one-cell reach takes the light
+    // ones by waves
+    const int nbig = (int)*n_heavy, nheavy = H == 1 ? nbig : ntiles;
+    const bool few = nbig <= kFewTiles;
+    const int kParts = few ? kFewParts : kSplitParts;
+    const int nsplit = few ? nbig : min(kSplitTiles, nbig);
     const int nitems = nheavy + nsplit * (kParts - 1);
     const int split_items = nsplit * kParts;
     int next = 0;
@@ -524,11 +586,13 @@ __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK), 4) void pp_kernel(const uin
         const bool split = item < split_items;
         const int ti = split ? item / kParts : item - split_items + nsplit;
         const int part = split ? item % kParts : 0;
+        const int lanes = few && split ? kFewLanes : 1;               // per particle
+        const int sub = tid & (lanes - 1), kOwn = kPPBlock / lanes;   // own particles per block
         const int t = (int)order[ti];
         int nparts = 1;
         if (split) {
             const uint32_t own = cs[(uint32_t)(t + 1) * kTileCells] - cs[(uint32_t)t * kTileCells];
-            nparts = (int)min((own + kPPBlock - 1) / kPPBlock, (uint32_t)kParts);
+            nparts = (int)min((own + kOwn - 1) / kOwn, (uint32_t)kParts);
             nparts = __builtin_amdgcn_readfirstlane(max(nparts, 1));
         }
         if ((skip && skip[t]) || part >= nparts) {   // another level's tile, or a spare part
@@ -593,8 +657,8 @@ __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK), 4) void pp_kernel(const uin
         // cells reach through LDS, CAP particles at a time, its sums staying in
         // registers.
         bool staged = false;
-        for (uint32_t l0 = (uint32_t)(part * kPPBlock); l0 < own; l0 += (uint32_t)(kPPBlock * nparts)) {
-            const uint32_t lp = l0 + tid;
+        for (uint32_t l0 = (uint32_t)(part * kOwn); l0 < own; l0 += (uint32_t)(kOwn * nparts)) {
+            const uint32_t lp = l0 + tid / lanes;
             const bool active = lp < own;
             const int u = seg_search_n<kTileCells>(cst, active ? lp : own - 1);
             const uint32_t p = p0 + (active ? lp : own - 1);
@@ -606,7 +670,7 @@ __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK), 4) void pp_kernel(const uin
             float aix = 0.f, aiy = 0.f, aiz = 0.f;
             if (!single) {
                 const int za = seg_search_n<kTileCells>(cst, l0) >> 6;
-                const int zb = seg_search_n<kTileCells>(cst, min(l0 + kPPBlock, own) - 1) >> 6;
+                const int zb = seg_search_n<kTileCells>(cst, min(l0 + kOwn, own) - 1) >> 6;
                 V0 = seg_pre[za * kPB * kPB];
                 V1 = seg_pre[(zb + 2 * H + 1) * kPB * kPB];
                 xi = (float)(2 * (bx - H)) * ps + (float)pos[p] * ips;
@@ -713,70 +777,22 @@ __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK), 4) void pp_kernel(const uin
                     const uint32_t r0 = max(seg_pre[sm - H], vb), r1 = min(seg_pre[sm + H + 1], ve);
                     const uint32_t v0 = r0 - vb, v1 = max(r0, r1) - vb;
                     float fx = 0.f, fy = 0.f, fz = 0.f;
-                    if (ADJ) {
-                        // four pairs per iteration: the loop control and the LDS
-                        // latency spread over more work.  The loops run on the
-                        // LDS address against precomputed bounds, never below xs
-                        // (LDS addresses compare unsigned).
-                        const float4 *q = xs + v0;
-                        const float2 *qa = xa + v0;
-                        const float4 *const qe = xs + v1;
-                        const float4 *const qe4 = xs + (v1 >= v0 + 3 ? v1 - 3 : v0);
-                        for (; q < qe4; q += 4, qa += 4) {
-                            float4 x[4];
-                            float2 a[4];
-#pragma unroll
-                            for (int t = 0; t < 4; ++t) {
-                                x[t] = q[t];
-                                a[t] = qa[t];
-                            }
-#pragma unroll
-                            for (int t = 0; t < 4; ++t)
-                                pair_adjoint<CLAMP>(x[t].x - xi, x[t].y - yi, x[t].z - zi,
-                                                    x[t].w - aix, a[t].x - aiy, a[t].y - aiz,
-                                                    bmax, fx, fy, fz);
-                        }
-                        for (; q < qe; ++q, ++qa) {
-                            const float4 x = q[0];
-                            const float2 a = qa[0];
-                            pair_adjoint<CLAMP>(x.x - xi, x.y - yi, x.z - zi, x.w - aix,
-                                                a.x - aiy, a.y - aiz, bmax, fx, fy, fz);
-                        }
-                    } else {
-                        // four pairs per iteration, then two, then one.  The
-                        // loop runs on the LDS address against a precomputed
-                        // bound, never below xs.
-                        const float4 *q = xs + v0;
-                        const float4 *const qe4 = xs + (v1 >= v0 + 3 ? v1 - 3 : v0);
-                        for (; q < qe4; q += 4) {
-                            float4 x[4];
-#pragma unroll
-                            for (int t = 0; t < 4; ++t) x[t] = q[t];
-#pragma unroll
-                            for (int t = 0; t < 4; ++t)
-                                pair_accumulate<CLAMP>(x[t].x - xi, x[t].y - yi, x[t].z - zi,
-                                                       x[t].w, bmax, fx, fy, fz);
-                        }
-                        if ((v1 - v0) & 2u) {
-                            const float4 qa = q[0], qb = q[1];
-                            pair_accumulate<CLAMP>(qa.x - xi, qa.y - yi, qa.z - zi, qa.w, bmax,
-                                                   fx, fy, fz);
-                            pair_accumulate<CLAMP>(qb.x - xi, qb.y - yi, qb.z - zi, qb.w, bmax,
-                                                   fx, fy, fz);
-                            q += 2;
-                        }
-                        if ((v1 - v0) & 1u) {
-                            const float4 qa = q[0];
-                            pair_accumulate<CLAMP>(qa.x - xi, qa.y - yi, qa.z - zi, qa.w, bmax,
-                                                   fx, fy, fz);
-                        }
+                    if (lanes == 1)
+                        staged_pairs<ADJ, CLAMP, 1>(xs, xa, v0, v1, xi, yi, zi, aix, aiy, aiz, bmax, fx,
+                                                    fy, fz);
+                    else {
+                        staged_pairs<ADJ, CLAMP, kFewLanes>(xs, xa, v0 + sub, v1, xi, yi, zi, aix, aiy,
+                                                            aiz, bmax, fx, fy, fz);
+                        fx = quad_sum(fx);
+                        fy = quad_sum(fy);
+                        fz = quad_sum(fz);
                     }
                     kahan_add(sx, cx, fx);
                     kahan_add(sy, cy, fy);
                     kahan_add(sz, cz, fz);
                 }
             }
-            if (!active) continue;
+            if (!active || sub != 0) continue;
             const float a[3] = {gm * (sx * law.unit), gm * (sy * law.unit), gm * (sz * law.unit)};
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
@@ -1035,9 +1051,8 @@ int launch_pp_kernel_h(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, 
     law.bmax = ADJ ? ctx->pp_bmax_adj : ctx->pp_bmax;
     const int nt = ctx->nt;
     const int ntiles = nt * nt * nt;
-    // with the one-cell reach the light tiles come last in the order, and the
-    // scanned digit counts say where they begin
-    const int lcap = H == 1 ? PPLight<ADJ>::LCAP : 0;
+    // the light tiles come last in the order; the digits' starts say where
+    const int lcap = PPLight<ADJ>::LCAP;
     const uint32_t *n_heavy = nullptr;
     int r = launch_order_tiles(ctx, cs, work, L, order_stream, lcap, &n_heavy);
     if (r) return r;
@@ -1048,8 +1063,7 @@ int launch_pp_kernel_h(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, 
     const uint32_t *order = tile_order_ptr(work, L);
     uint32_t *queue = tile_queue_ptr(ctx, work, L);
     auto k = pp_kernel<ADJ, H, CLAMP>;
-    const int nsplit = std::min(kSplitTiles, ntiles);
-    const int nitems = ntiles + nsplit * (kSplitParts - 1);
+    const int nitems = ntiles + std::min(ntiles, kFewTiles) * (kFewParts - 1);   // at most
     // one z-layer of cells per light item where there are few of them
     const int layers = ntiles <= kOneLayerTiles ? 1 : PPLight<ADJ>::LAYERS;
     const unsigned grid = std::max(
@@ -1057,7 +1071,7 @@ int launch_pp_kernel_h(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, 
     k<<<grid, PPGeo<ADJ, H>::BLOCK, 0, s>>>(
         pos, cs, (int)n, nt, table, law,
         (float)(ctx->cfg.g_newton * ctx->cfg.m_p), abar, out, accumulate, order, queue, ntiles,
-        nsplit, n_heavy, xcd_queue_ptr(ctx, work, L), layers, skip);
+        n_heavy, xcd_queue_ptr(ctx, work, L), layers, skip);
     CUBE2_LAUNCH_CHECK();
     return CUBE2_OK;
 }

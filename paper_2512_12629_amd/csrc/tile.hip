@@ -24,7 +24,8 @@ namespace {
 
 struct Region {
     int R, k, n_ios, nt;
-    const int32_t *r0;   // device: 3 T origin IOS cells (x, y, z per tile)
+    const int32_t *r0;   // device: 3 T origin IOS cells (x, y, z per tile), or
+    int one[3];          // (r0 == NULL) the origin of the only tile
 };
 
 // region cell r (tile t = r / R^3, then z-major over R^3) -> global IOS cell
@@ -36,7 +37,7 @@ __device__ __forceinline__ uint32_t region_key(int64_t r, const Region &g, int (
     c[0] = (int)(l % g.R);
     c[1] = (int)((l / g.R) % g.R);
     c[2] = (int)(l / ((int64_t)g.R * g.R));
-    const int32_t *o = g.r0 + 3 * t;
+    const int32_t *o = g.r0 ? g.r0 + 3 * t : g.one;
     return cell_key(wrapn(o[0] + c[0], g.n_ios), wrapn(o[1] + c[1], g.n_ios),
                     wrapn(o[2] + c[2], g.n_ios), g.nt);
 }
@@ -54,21 +55,24 @@ __global__ void region_count_kernel(const uint32_t *__restrict__ cs, Region g, i
     counts[r] = cs[key + 1] - cs[key];
 }
 
-// One wave per region cell: its particles go to out[offs[r] ...] with the
+// kCellLanes lanes per region cell: its particles go to out[offs[r] ...] with the
 // positions of their slot, (slot R + cell) << 16 | offset, over n_box 2^15,
-// exact in FP32 for n_box <= 512.
+// exact in FP32 for n_box <= 512.  A wave per cell left 63 of 64 lanes idle at
+// one particle per cell (262144 cells: 89 us).
+constexpr int kCellLanes = 4;
 __global__ __launch_bounds__(kBlock) void region_write_kernel(
     const uint16_t *__restrict__ pos, const uint32_t *__restrict__ cs, int n, Region g,
     int64_t cells, const uint32_t *__restrict__ offs, float inv_span, float *__restrict__ x_local,
     int32_t *__restrict__ idx, int64_t m) {
-    const int64_t r = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+    const int64_t r = (int64_t)blockIdx.x * (kBlock / kCellLanes) + threadIdx.x / kCellLanes;
     if (r >= cells) return;
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x % kCellLanes;
     int c[3], t;
     const uint32_t key = region_key(r, g, c, t);
     const int sl[3] = {t % g.k, (t / g.k) % g.k, t / (g.k * g.k)};
     const uint32_t b = cs[key], e = cs[key + 1], o0 = offs[r];
-    for (uint32_t p = b + (uint32_t)lane; p < e; p += 64) {
+#pragma unroll 4
+    for (uint32_t p = b + (uint32_t)lane; p < e; p += kCellLanes) {
         const int64_t o = (int64_t)o0 + (p - b);
         if (o >= m) break;
 #pragma unroll
@@ -124,10 +128,13 @@ int launch_tile_gather(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, 
     uint32_t *offs = reinterpret_cast<uint32_t *>(work + L.real_f);
     uint32_t *tmp = reinterpret_cast<uint32_t *>(work + L.scan_tmp);
     int32_t *r0 = reinterpret_cast<int32_t *>(work + L.red);
-    CUBE2_CHECK_HIP(hipMemcpyAsync(r0, r0_host, (size_t)T * 3 * sizeof(int32_t),
-                                   hipMemcpyHostToDevice, s));
     const int k = tile_slots(T);
-    const Region g{R, k, ctx->n_ios, ctx->nt, r0};
+    Region g{R, k, ctx->n_ios, ctx->nt, nullptr, {r0_host[0], r0_host[1], r0_host[2]}};
+    if (T > 1) {
+        g.r0 = r0;
+        CUBE2_CHECK_HIP(hipMemcpyAsync(r0, r0_host, (size_t)T * 3 * sizeof(int32_t),
+                                       hipMemcpyHostToDevice, s));
+    }
     region_count_kernel<<<(unsigned)((cells + 1 + 255) / 256), 256, 0, s>>>(cs, g, cells, offs);
     CUBE2_LAUNCH_CHECK();
     int rc = launch_exclusive_scan(offs, offs, cells + 1, tmp, s);
@@ -140,7 +147,7 @@ int launch_tile_gather(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, 
     if (total == 0) return CUBE2_OK;
     const int64_t n_box = (int64_t)2 * R * k;
     const float inv_span = 1.0f / (float)(n_box << kFracBits);
-    region_write_kernel<<<(unsigned)((cells + kBlock / 64 - 1) / (kBlock / 64)), kBlock, 0, s>>>(
+    region_write_kernel<<<(unsigned)((cells * kCellLanes + kBlock - 1) / kBlock), kBlock, 0, s>>>(
         pos, cs, (int)n, g, cells, offs, inv_span, x_local, idx, (int64_t)total);
     CUBE2_LAUNCH_CHECK();
     return CUBE2_OK;
