@@ -569,6 +569,9 @@ inline unsigned persistent_grid(K kernel, int block, int ntiles) {
     const long g = (long)(cus > 0 ? cus : 1) * (per_cu > 0 ? per_cu : 1);
     return (unsigned)(g < ntiles ? g : ntiles);
 }
+// max |x| over m > 0 floats into *out (device, zero before), as the bits of a
+// non-negative float.
+int launch_absmax(const float *x, int64_t m, unsigned int *out, hipStream_t s);
 int vel_bulk_side(const cube2_ctx *ctx);
 int vel_layout_check(const cube2_ctx *ctx, const WorkLayout &L);
 int launch_vel_encode(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,

@@ -11,24 +11,10 @@
 // with one level; a bulk cell lies inside one tile, so every tile computes
 // the means of its own cells.  The cell sums are exact 64-bit fixed point (a
 // scale S = 2^(41 - e) with max|v| < 2^e), so the means are deterministic.
-#include <algorithm>
-
 #include "common.hpp"
 
 namespace cube2 {
 namespace {
-
-// max |x| over m floats as the bit pattern of a non-negative float; *out
-// must be zero on entry
-__global__ void vabsmax_kernel(const float *__restrict__ x, int64_t m, unsigned int *out) {
-    float v = 0.0f;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m;
-         i += (int64_t)gridDim.x * blockDim.x)
-        v = fmaxf(v, fabsf(x[i]));
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    if ((threadIdx.x & 63) == 0) atomicMax(out, __float_as_uint(v));
-}
 
 __global__ void vset2_kernel(unsigned int *p) {
     p[0] = 0u;
@@ -44,11 +30,12 @@ __device__ __forceinline__ float vel_scale(unsigned int amax_bits) {
     return ldexpf(1.0f, min(41 - e, 100));
 }
 
-// bulk cell of a particle inside its tile: IOS cell u (0..511), offsets o
-__host__ __device__ __forceinline__ int bulk_cell(int u, const uint32_t (&o)[3], int shift, int ct) {
-    const int fx = 2 * (u & 7) + (int)(o[0] >> 15), fy = 2 * ((u >> 3) & 7) + (int)(o[1] >> 15),
-              fz = 2 * (u >> 6) + (int)(o[2] >> 15);
-    return ((fz >> shift) * ct + (fy >> shift)) * ct + (fx >> shift);
+// bulk cell, inside its tile, of the particles of IOS cell u (0..511): bulk
+// cells have 2^shift fine cells per axis, at least the 2 of an IOS cell, so
+// the particle's offsets do not matter
+__host__ __device__ __forceinline__ int bulk_cell(int u, int shift, int ct) {
+    const int s = shift - 1;
+    return (((u >> 6) >> s) * ct + (((u >> 3) & 7) >> s)) * ct + ((u & 7) >> s);
 }
 
 __host__ __device__ __forceinline__ int64_t bulk_index(int tx, int ty, int tz, int lc, int ct, int nb) {
@@ -56,16 +43,20 @@ __host__ __device__ __forceinline__ int64_t bulk_index(int tx, int ty, int tz, i
     return ((int64_t)cz * nb + cy) * nb + cx;
 }
 
-// Per tile: cell counts and fixed-point velocity sums of its bulk cells, the
-// means written to v_bulk, and max |v - v_bulk| of its particles written to
-// tmax[tile] (one global atomic per wave on a single address would
-// serialise; the tile maxima are reduced by a second pass).
+// Per tile: fixed-point velocity sums of its bulk cells, the means written to
+// v_bulk, and max |v - v_bulk| of its particles written to tmax[tile] (one global
+// atomic per wave on a single address would serialise; the tile maxima are
+// reduced by a second pass).  The counts are those of the cells' particle
+// ranges.  A tile of up to kKeep particles per thread keeps its velocities in
+// registers between the sums and the maxima.  Reading the positions for the bulk
+// cell and summing runs of equal cells by a segmented scan of LDS permutes, this
+// took 242 us for 256^3 particles, and the codes 130.
+constexpr int kKeep = 4;
 __global__ __launch_bounds__(kBlock) void vel_bulk_kernel(
-    const uint16_t *__restrict__ pos, const uint32_t *__restrict__ cs, const float *__restrict__ vel,
-    int n, int nt, int shift, int nb, const unsigned int *__restrict__ amax,
-    float *__restrict__ v_bulk, float *__restrict__ tmax, uint32_t *status) {
+    const uint32_t *__restrict__ cs, const float *__restrict__ vel, int n, int nt, int shift, int nb,
+    const unsigned int *__restrict__ amax, float *__restrict__ v_bulk, float *__restrict__ tmax,
+    uint32_t *status) {
     __shared__ float wmax[kBlock / 64];
-    __shared__ uint32_t cnt[kTileCells];
     __shared__ unsigned long long sum[3][kTileCells];
     __shared__ float vb[3][kTileCells];
     __shared__ uint32_t cst[kTileCells + 1];
@@ -74,64 +65,58 @@ __global__ __launch_bounds__(kBlock) void vel_bulk_kernel(
     const int tid = threadIdx.x;
     const int ct = kTileFine >> shift;       // bulk cells per tile axis
     const int ncell = ct * ct * ct;
-    for (int i = tid; i < ncell; i += kBlock) {
-        cnt[i] = 0u;
-        sum[0][i] = sum[1][i] = sum[2][i] = 0ull;
-    }
+    for (int i = tid; i < ncell; i += kBlock) sum[0][i] = sum[1][i] = sum[2][i] = 0ull;
     const uint32_t key0 = (uint32_t)((tz * nt + ty) * nt + tx) * kTileCells;
     stage_cell_starts<kBlock>(cst, cs, key0);
     __syncthreads();
     const float S = vel_scale(amax[0]), invS = 1.0f / S;
     const uint32_t p0 = cst[0], p1 = cst[kTileCells];
-    // Particles are sorted by IOS cell, so equal bulk cells come in runs of
-    // consecutive lanes.  A segmented inclusive scan (exact integer sums)
-    // leaves each run's count and sums in its last lane, which adds them:
-    // one LDS atomic per run instead of one per particle on a few addresses.
     const int lane = tid & 63;
-    for (uint32_t w0 = p0 + (uint32_t)(tid - lane); w0 < p1; w0 += kBlock) {
-        const uint32_t p = w0 + (uint32_t)lane;
-        const bool valid = p < p1;
-        int lc = -1;
-        uint32_t c = 0u;
-        unsigned long long f[3] = {0ull, 0ull, 0ull};
-        if (valid) {
-            const int u = seg_search_n<kTileCells>(cst, p);
-            uint32_t o[3];
+    float v[kKeep][3];
+    int lc[kKeep];
+    // Particles are sorted by IOS cell: in a dense cell a whole wave feeds one
+    // bulk cell and adds its sum once, elsewhere a few lanes share one.
+    for (uint32_t c0 = p0; c0 < p1; c0 += kBlock * kKeep) {
 #pragma unroll
-            for (int d = 0; d < 3; ++d) o[d] = pos[(int64_t)d * n + p];
-            lc = bulk_cell(u, o, shift, ct);
-            c = 1u;
+        for (int k = 0; k < kKeep; ++k) {
+            const uint32_t p = c0 + k * kBlock + tid;
+            lc[k] = -1;
+            if (p < p1) {
 #pragma unroll
-            for (int d = 0; d < 3; ++d)
-                f[d] = (unsigned long long)__float2ll_rn(vel[(int64_t)d * n + p] * S);
-        }
-        const int lc_up = __shfl_up(lc, 1, 64), lc_dn = __shfl_down(lc, 1, 64);
-        int head = (lane == 0 || lc != lc_up) ? 1 : 0;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t c_up = __shfl_up(c, off, 64);
-            const unsigned long long f0 = __shfl_up(f[0], off, 64), f1 = __shfl_up(f[1], off, 64),
-                                     f2 = __shfl_up(f[2], off, 64);
-            const int h_up = __shfl_up(head, off, 64);
-            if (lane >= off) {
-                if (!head) {
-                    c += c_up;
-                    f[0] += f0;
-                    f[1] += f1;
-                    f[2] += f2;
-                }
-                head |= h_up;
+                for (int d = 0; d < 3; ++d) v[k][d] = vel[(int64_t)d * n + p];
+                lc[k] = bulk_cell(seg_search_n<kTileCells>(cst, p), shift, ct);
             }
         }
-        if (valid && (lane == 63 || lc_dn != lc)) {
-            atomicAdd(&cnt[lc], c);
 #pragma unroll
-            for (int d = 0; d < 3; ++d) atomicAdd(&sum[d][lc], f[d]);
+        for (int k = 0; k < kKeep; ++k) {
+            const unsigned long long on = __ballot(lc[k] >= 0);
+            if (on == 0ull) continue;
+            const int lead = first_lane(on);
+            const int lc0 = __builtin_amdgcn_readlane(lc[k], lead);
+            const bool uniform = __ballot(lc[k] >= 0 && lc[k] != lc0) == 0ull;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const unsigned long long f =
+                    lc[k] >= 0 ? (unsigned long long)__float2ll_rn(v[k][d] * S) : 0ull;
+                if (uniform) {
+                    const unsigned long long t = wave_sum(f);
+                    if (lane == lead) atomicAdd(&sum[d][lc0], t);
+                } else if (lc[k] >= 0) {
+                    atomicAdd(&sum[d][lc[k]], f);
+                }
+            }
         }
     }
     __syncthreads();
     for (int i = tid; i < ncell; i += kBlock) {
-        const uint32_t c = cnt[i];
+        // the bulk cell's particles: its IOS cells' x-rows
+        const int w = 1 << (shift - 1), bx = (i % ct) * w, by = ((i / ct) % ct) * w, bz = i / (ct * ct) * w;
+        uint32_t c = 0;
+        for (int z = 0; z < w; ++z)
+            for (int y = 0; y < w; ++y) {
+                const int u = ((bz + z) * 8 + by + y) * 8 + bx;
+                c += cst[u + w] - cst[u];
+            }
         // 2^22 values below 2^41 each keep the sum within 63 bits
         if (c >= (1u << 22)) atomicOr(status, kStatusOverflow);
         const int64_t g = bulk_index(tx, ty, tz, i, ct, nb);
@@ -146,15 +131,20 @@ __global__ __launch_bounds__(kBlock) void vel_bulk_kernel(
     }
     __syncthreads();
     float dmax = 0.0f;
-    for (uint32_t p = p0 + tid; p < p1; p += kBlock) {
-        const int u = seg_search_n<kTileCells>(cst, p);
-        uint32_t o[3];
+    if (p1 - p0 <= (uint32_t)(kBlock * kKeep)) {
 #pragma unroll
-        for (int d = 0; d < 3; ++d) o[d] = pos[(int64_t)d * n + p];
-        const int lc = bulk_cell(u, o, shift, ct);
+        for (int k = 0; k < kKeep; ++k) {
+            if (p0 + k * kBlock + tid >= p1) continue;
 #pragma unroll
-        for (int d = 0; d < 3; ++d)
-            dmax = fmaxf(dmax, fabsf(__fsub_rn(vel[(int64_t)d * n + p], vb[d][lc])));
+            for (int d = 0; d < 3; ++d) dmax = fmaxf(dmax, fabsf(__fsub_rn(v[k][d], vb[d][lc[k]])));
+        }
+    } else {
+        for (uint32_t p = p0 + tid; p < p1; p += kBlock) {
+            const int b = bulk_cell(seg_search_n<kTileCells>(cst, p), shift, ct);
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+                dmax = fmaxf(dmax, fabsf(__fsub_rn(vel[(int64_t)d * n + p], vb[d][b])));
+        }
     }
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) dmax = fmaxf(dmax, __shfl_xor(dmax, m, 64));
@@ -178,39 +168,56 @@ __device__ __forceinline__ float vel_step(unsigned int dmax_bits) {
 // v_scale, writes vel_out).
 template <bool ENCODE>
 __global__ __launch_bounds__(kBlock) void vel_code_kernel(
-    const uint16_t *__restrict__ pos, const uint32_t *__restrict__ cs, int n, int nt, int shift,
-    int nb, const float *__restrict__ v_bulk, const unsigned int *__restrict__ amax,
+    const uint32_t *__restrict__ cs, int n, int nt, int shift, int nb,
+    const float *__restrict__ v_bulk, const unsigned int *__restrict__ amax,
     const float *__restrict__ vel_in, int16_t *__restrict__ vq_out, float *__restrict__ v_scale_out,
     const float *__restrict__ v_scale, const int16_t *__restrict__ vq_in,
     float *__restrict__ vel_out) {
     __shared__ uint32_t cst[kTileCells + 1];
+    __shared__ float vb[3][kTileCells];
     int tx, ty, tz;
     tile_of_block(blockIdx.x, nt, tx, ty, tz);
     const int tid = threadIdx.x;
     const int ct = kTileFine >> shift;
     const uint32_t key0 = (uint32_t)((tz * nt + ty) * nt + tx) * kTileCells;
+    const int64_t m3 = (int64_t)nb * nb * nb;
+    for (int i = tid; i < ct * ct * ct; i += kBlock) {
+        const int64_t g = bulk_index(tx, ty, tz, i, ct, nb);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) vb[d][i] = v_bulk[d * m3 + g];
+    }
     stage_cell_starts<kBlock>(cst, cs, key0);
     __syncthreads();
     const float s = ENCODE ? vel_step(amax[1]) : v_scale[0];
     if (ENCODE && blockIdx.x == 0 && tid == 0) v_scale_out[0] = s;
-    const int64_t m3 = (int64_t)nb * nb * nb;
-    for (uint32_t p = cst[0] + tid; p < cst[kTileCells]; p += kBlock) {
-        const int u = seg_search_n<kTileCells>(cst, p);
-        uint32_t o[3];
+    const uint32_t p1 = cst[kTileCells];
+    constexpr int kBatch = 2;      // particles per thread whose loads are issued together
+    for (uint32_t c0 = cst[0] + tid; c0 < p1; c0 += kBlock * kBatch) {
+        float v[kBatch][3];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) o[d] = pos[(int64_t)d * n + p];
-        const int64_t g = bulk_index(tx, ty, tz, bulk_cell(u, o, shift, ct), ct, nb);
+        for (int k = 0; k < kBatch; ++k) {
+            const uint32_t p = min(c0 + k * kBlock, p1 - 1);
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            const float b = v_bulk[d * m3 + g];
-            if (ENCODE) {
-                const float r = rintf(__fdiv_rn(__fsub_rn(vel_in[(int64_t)d * n + p], b), s));
-                vq_out[(int64_t)d * n + p] = (int16_t)fminf(fmaxf(r, -32767.0f), 32767.0f);
-            } else {
-                // two roundings, as documented: no contraction into an FMA
+            for (int d = 0; d < 3; ++d)
+                v[k][d] = ENCODE ? vel_in[(int64_t)d * n + p] : (float)vq_in[(int64_t)d * n + p];
+        }
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k) {
+            const uint32_t p = c0 + k * kBlock;
+            if (p >= p1) continue;
+            const int lc = bulk_cell(seg_search_n<kTileCells>(cst, p), shift, ct);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const float b = vb[d][lc];
+                if (ENCODE) {
+                    const float r = rintf(__fdiv_rn(__fsub_rn(v[k][d], b), s));
+                    vq_out[(int64_t)d * n + p] = (int16_t)fminf(fmaxf(r, -32767.0f), 32767.0f);
+                } else {
+                    // two roundings, as documented: no contraction into an FMA
 #pragma clang fp contract(off)
-                const float sq = s * (float)vq_in[(int64_t)d * n + p];
-                vel_out[(int64_t)d * n + p] = b + sq;
+                    const float sq = s * v[k][d];
+                    vel_out[(int64_t)d * n + p] = b + sq;
+                }
             }
         }
     }
@@ -224,20 +231,23 @@ int bulk_shift(const cube2_ctx *ctx) { return ctx->n_levels > 1 ? ctx->lv[1].hsh
 int vel_bulk_side(const cube2_ctx *ctx) { return ctx->n_f >> bulk_shift(ctx); }
 
 // The codec's index arithmetic for this context, run on the host with the
-// kernels' own functions: every particle position of every IOS cell of a tile
-// (offsets at both ends of both fine cells) lands in one of the tile's
-// ct^3 <= 512 bulk cells (the LDS arrays), every bulk cell of every tile in
+// kernels' own functions: every IOS cell of a tile lands in the bulk cell of each
+// of its fine cells, one of the tile's ct^3 <= 512 (the LDS arrays), every bulk
+// cell of every tile in
 // [0, nb^3) (v_bulk), and the tile maxima fit their work area.
 int vel_layout_check(const cube2_ctx *ctx, const WorkLayout &L) {
     const int shift = bulk_shift(ctx), nb = ctx->n_f >> shift, nt = ctx->nt;
     const int ct = kTileFine >> shift;
     if (ct < 1 || ct * ct * ct > kTileCells || (int64_t)nt * ct != nb) return CUBE2_EUNSUPPORTED;
-    static const uint32_t offs[4] = {0u, 0x7FFFu, 0x8000u, 0xFFFFu};
+    if (shift < 1) return CUBE2_EUNSUPPORTED;
     for (int u = 0; u < kTileCells; ++u)
-        for (int a = 0; a < 64; ++a) {
-            const uint32_t o[3] = {offs[a & 3], offs[(a >> 2) & 3], offs[a >> 4]};
-            const int lc = bulk_cell(u, o, shift, ct);
-            if (lc < 0 || lc >= ct * ct * ct) return CUBE2_EUNSUPPORTED;
+        for (int a = 0; a < 8; ++a) {
+            const int fx = 2 * (u & 7) + (a & 1), fy = 2 * ((u >> 3) & 7) + ((a >> 1) & 1),
+                      fz = 2 * (u >> 6) + (a >> 2);
+            const int lc = bulk_cell(u, shift, ct);
+            if (lc != ((fz >> shift) * ct + (fy >> shift)) * ct + (fx >> shift) || lc < 0 ||
+                lc >= ct * ct * ct)
+                return CUBE2_EUNSUPPORTED;
         }
     const int64_t nb3 = (int64_t)nb * nb * nb;
     for (int tz = 0; tz < nt; ++tz)
@@ -262,20 +272,18 @@ int launch_vel_encode(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, i
     vset2_kernel<<<1, 1, 0, s>>>(amax);
     CUBE2_LAUNCH_CHECK();
     if (n > 0) {
-        const int64_t m3 = 3 * n;
-        const unsigned gb = (unsigned)std::min<int64_t>(4096, (m3 + 255) / 256);
-        vabsmax_kernel<<<gb, 256, 0, s>>>(vel, m3, amax);
-        CUBE2_LAUNCH_CHECK();
+        const int r = launch_absmax(vel, 3 * n, amax, s);
+        if (r) return r;
     }
     // per-tile maxima in their own work area (one float per tile)
     float *tmax = reinterpret_cast<float *>(work + L.vel_tmax);
-    vel_bulk_kernel<<<blocks, kBlock, 0, s>>>(pos, cs, vel, (int)n, nt, shift, nb, amax, v_bulk, tmax,
+    vel_bulk_kernel<<<blocks, kBlock, 0, s>>>(cs, vel, (int)n, nt, shift, nb, amax, v_bulk, tmax,
                                               status_word(ctx));
     CUBE2_LAUNCH_CHECK();
-    vabsmax_kernel<<<(unsigned)std::min<int64_t>(1024, ((int64_t)blocks + 255) / 256), 256, 0, s>>>(
-        tmax, (int64_t)blocks, amax + 1);
-    CUBE2_LAUNCH_CHECK();
-    vel_code_kernel<true><<<blocks, kBlock, 0, s>>>(pos, cs, (int)n, nt, shift, nb, v_bulk, amax,
+    const int r = launch_absmax(tmax, (int64_t)blocks, amax + 1, s);
+    if (r) return r;
+    (void)pos;
+    vel_code_kernel<true><<<blocks, kBlock, 0, s>>>(cs, (int)n, nt, shift, nb, v_bulk, amax,
                                                     vel, vq, v_scale, nullptr, nullptr, nullptr);
     CUBE2_LAUNCH_CHECK();
     return CUBE2_OK;
@@ -288,7 +296,8 @@ int launch_vel_decode(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, i
     const int nt = ctx->nt;
     const unsigned blocks = (unsigned)(nt * nt * nt);
     const int shift = bulk_shift(ctx), nb = ctx->n_f >> shift;
-    vel_code_kernel<false><<<blocks, kBlock, 0, s>>>(pos, cs, (int)n, nt, shift, nb, v_bulk, nullptr,
+    (void)pos;
+    vel_code_kernel<false><<<blocks, kBlock, 0, s>>>(cs, (int)n, nt, shift, nb, v_bulk, nullptr,
                                                      nullptr, nullptr, nullptr, v_scale, vq, vel);
     CUBE2_LAUNCH_CHECK();
     return CUBE2_OK;
