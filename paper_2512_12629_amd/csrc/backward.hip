@@ -85,121 +85,117 @@ __device__ __forceinline__ float fixed_to_float(long long d) { return (float)(do
 
 // ---------------------------------------------------------------------------
 // fine level: phibar on a 16^3 node tile.  For each component d in turn, the
-// workgroup scatters c*abar_d with the CIC weights onto the nodes of the
-// tile plus a 2-node halo (20^3 nodes, fixed point in LDS), from every
-// particle whose CIC footprint reaches that region (an 11^3 box of IOS cells:
-// a particle in fine cell j feeds nodes j and j+1), then adds the d term of
-// the stencil transpose phibar = D . Abar on the 16^3 interior.
+// workgroup scatters c*abar_d with the CIC weights onto the nodes that the d
+// term of the stencil transpose phibar = D . Abar reads: the tile's 16^3 and
+// two more at each end of axis d alone (20 x 16 x 16 nodes, fixed point in
+// LDS), from the particles whose CIC footprint reaches them (an 11 x 9 x 9 box
+// of IOS cells: a particle in fine cell j feeds nodes j and j+1), then adds that
+// term on the tile's nodes.
+// Bound by the LDS (the clearing, the 64-bit additions and the stencil's reads) and
+// the VALU together.  The 20^3 nodes and 11^3 cells of all three components in each
+// pass, with a search per particle, took 12.8 ms for 134 million particles on a 1024^3
+// mesh at 14 waves per CU (this: PHI_NOW, at 24).
 // ---------------------------------------------------------------------------
 
-constexpr int kAN = kTileFine + 4;           // 20 nodes per axis: [a0-2, a0+18)
-constexpr int kAN3 = kAN * kAN * kAN;
 constexpr int kPhiBlock = 512;
-// IOS cells per axis whose particles reach the 20^3 nodes: [c0-2, c0+9) for
-// CIC, [c0-2, c0+10) for TSC (a particle in fine cell j feeds j-1 .. j+2)
-// LUT: staged particles whose box cell is looked up once per tile (not in
-// each of the three passes), as many as fit beside the rest at two
-// workgroups per CU
+constexpr int kPhiLine = kTileFine + 4;      // nodes along the pass's axis: [a0-2, a0+18)
+constexpr int kPhiNodes = kPhiLine * kTileFine * kTileFine;
+// IOS cells of the box: along the axis [c0-2, c0+9) for CIC, [c0-2, c0+10) for TSC (a
+// particle in fine cell j feeds j-1 .. j+2), across it [c0-1, c0+8) and [c0-1, c0+9)
 template <int P> struct PhiGeo {
-    static constexpr int AB = kTileIos + (P == 3 ? 4 : 3);   // 11 or 12
-    static constexpr int SEGS = AB * AB * AB;
-    static constexpr int SEG_PER_THREAD = (SEGS + kPhiBlock - 1) / kPhiBlock;
-    static constexpr int LUT = P == 3 ? 1984 : 3584;
+    static constexpr int ALONG = kTileIos + (P == 3 ? 4 : 3), ACROSS = kTileIos + (P == 3 ? 2 : 1);
+    static constexpr int SEGS = ALONG * ACROSS * ACROSS;
+    using List = BoxList<SEGS, kPhiBlock>;
 };
 
-template <int P>
-__global__ __launch_bounds__(kPhiBlock) void fine_phibar_kernel(
-    const uint16_t *__restrict__ pos, const uint32_t *__restrict__ cs,
-    const float *__restrict__ abar, int n, int n_f, int nt, float c,
-    const unsigned int *__restrict__ amax_bits, float *__restrict__ phibar) {
-    constexpr int kAB = PhiGeo<P>::AB, kASegs = PhiGeo<P>::SEGS;
-    constexpr int kASegPerThread = PhiGeo<P>::SEG_PER_THREAD;
-    __shared__ uint32_t seg_pre[kASegs + 1];
-    __shared__ uint32_t seg_src[kASegs];
-    __shared__ unsigned long long A[kAN3];   // one component at a time, fixed point
-    __shared__ uint32_t scan_sh[kPhiBlock / 64 + 1];
-    __shared__ uint16_t lut[PhiGeo<P>::LUT];   // box cell of each staged particle
-    int tx, ty, tz;
-    tile_of_block(blockIdx.x, nt, tx, ty, tz);
-    const int tid = threadIdx.x;
+template <int P> struct PhiShared {
+    unsigned long long A[kPhiNodes];         // one component at a time, fixed point
+    typename PhiGeo<P>::List::Shared list;
+};
+
+// particle starts and counts of this thread's cells of the box of pass D around the
+// tile whose first IOS cell is c0, and each cell's first node per axis in the pass's nodes
+// (a signed byte per axis)
+template <int P, int D>
+__device__ __forceinline__ void phi_box(const uint32_t *__restrict__ cs, int nt, const int (&c0)[3],
+                                        uint32_t (&src)[PhiGeo<P>::List::PER],
+                                        uint32_t (&cnt)[PhiGeo<P>::List::PER],
+                                        uint32_t (&tag)[PhiGeo<P>::List::PER]) {
+    using G = PhiGeo<P>;
+    constexpr int B0 = D == 0 ? G::ALONG : G::ACROSS, B1 = D == 1 ? G::ALONG : G::ACROSS;
     const int n_ios = nt * kTileIos;
-    const int c0x = tx * kTileIos, c0y = ty * kTileIos, c0z = tz * kTileIos;
-    uint32_t cnt[kASegPerThread], src[kASegPerThread], sum = 0;
 #pragma unroll
-    for (int k = 0; k < kASegPerThread; ++k) {
-        const int s = tid * kASegPerThread + k;
-        cnt[k] = 0;
-        src[k] = 0;
-        if (s < kASegs) {
-            const int bx = s % kAB, by = (s / kAB) % kAB, bz = s / (kAB * kAB);
-            const uint32_t key = cell_key(wrapn(c0x + bx - 2, n_ios), wrapn(c0y + by - 2, n_ios),
-                                          wrapn(c0z + bz - 2, n_ios), nt);
+    for (int k = 0; k < G::List::PER; ++k) {
+        const int s = threadIdx.x * G::List::PER + k;
+        src[k] = cnt[k] = tag[k] = 0u;
+        if (s < G::SEGS) {
+            const int b[3] = {s % B0, (s / B0) % B1, s / (B0 * B1)};
+            int c[3];
+#pragma unroll
+            for (int e = 0; e < 3; ++e) {
+                const int r = b[e] - (e == D ? 2 : 1);     // relative to the tile
+                c[e] = wrapn(c0[e] + r, n_ios);
+                tag[k] |= (uint32_t)((2 * r + (e == D ? 2 : 0)) & 0xFF) << (8 * e);
+            }
+            const uint32_t key = cell_key(c[0], c[1], c[2], nt);
             src[k] = cs[key];
             cnt[k] = cs[key + 1] - src[k];
         }
-        sum += cnt[k];
     }
-    uint32_t total;
-    uint32_t pre = block_exclusive_scan<kPhiBlock>(sum, scan_sh, total);
-#pragma unroll
-    for (int k = 0; k < kASegPerThread; ++k) {
-        const int s = tid * kASegPerThread + k;
-        if (s < kASegs) {
-            seg_pre[s] = pre;
-            seg_src[s] = src[k];
-        }
-        pre += cnt[k];
-    }
-    if (tid == 0) seg_pre[kASegs] = total;
-    // the box cell of every staged particle, searched once for the three passes
-    const bool use_lut = total <= (uint32_t)PhiGeo<P>::LUT;   // block-uniform
-    __syncthreads();
-    if (use_lut)
-        for (uint32_t v = tid; v < total; v += kPhiBlock) lut[v] = (uint16_t)seg_search_n<kASegs>(seg_pre, v);
-    const float S = fixed_scale(amax_bits, c), invS = 1.0f / S;
-    const float cS = c * S;
+}
+
+// One pass: component D of phibar added to out, the tile's nodes (x, y) = tid % 16,
+// tid / 16 % 16 and z = 8 (tid / 256) + k.  src, cnt and tag hold the pass's box, and
+// the next pass's afterwards (its loads fly while this one scatters).
+template <int P, int D>
+__device__ __forceinline__ void phi_pass(const uint16_t *__restrict__ pos,
+                                         const uint32_t *__restrict__ cs,
+                                         const float *__restrict__ abar, int n, int nt,
+                                         const int (&c0)[3], float cS, float invS,
+                                         uint32_t (&src)[PhiGeo<P>::List::PER],
+                                         uint32_t (&cnt)[PhiGeo<P>::List::PER],
+                                         uint32_t (&tag)[PhiGeo<P>::List::PER], PhiShared<P> &sh,
+                                         float (&out)[8]) {
+    constexpr int T = kTileFine, PER = PhiGeo<P>::List::PER;
+    constexpr int N0 = D == 0 ? kPhiLine : T, N1 = D == 1 ? kPhiLine : T, N2 = D == 2 ? kPhiLine : T;
+    const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
     const float inv = 1.0f / 32768.0f;
-    constexpr int T = kTileFine;
-    constexpr int NPT = T * T * T / kPhiBlock;   // interior nodes per thread
-    float out[NPT];
-#pragma unroll
-    for (int k = 0; k < NPT; ++k) out[k] = 0.0f;
-    // phibar(m) = sum_d (2/3)(A_d(m+e_d) - A_d(m-e_d)) - (1/12)(A_d(m+2e_d) - A_d(m-2e_d)),
-    // one component d per pass
-    for (int d = 0; d < 3; ++d) {
-        for (int i = tid; i < kAN3; i += kPhiBlock) A[i] = 0ull;
-        __syncthreads();
+    for (int i = tid; i < kPhiNodes; i += kPhiBlock) sh.A[i] = 0ull;
+    typename PhiGeo<P>::List list;
+    list.build(sh.list, src, cnt, tag);
+    uint32_t nsrc[PER], ncnt[PER], ntag[PER];
+    if constexpr (D < 2) phi_box<P, D + 1>(cs, nt, c0, nsrc, ncnt, ntag);
+    for (uint32_t base = 0; base < list.total; base += kBoxSpan) {
+        if (base) list.span(sh.list, cnt, base);
+        const uint32_t m = min(list.total - base, (uint32_t)kBoxSpan);
         constexpr int kBatch = 2;
-        for (uint32_t v0 = tid; v0 < total; v0 += kPhiBlock * kBatch) {
-            int sg[kBatch];
+        for (uint32_t i0 = wave; 64 * i0 < m; i0 += kBatch * (kPhiBlock / 64)) {
+            uint2 g[kBatch];
             uint32_t o[kBatch][3];
             float ab[kBatch];
 #pragma unroll
             for (int k = 0; k < kBatch; ++k) {
-                // looked up for every lane (past the end: the last particle,
-                // total >= 1 here) so that the lookups of the batch interleave
-                const uint32_t v = v0 + k * kPhiBlock, vv = v < total ? v : total - 1;
-                const int u = use_lut ? (int)lut[vv] : seg_search_n<kASegs>(seg_pre, vv);
-                sg[k] = v < total ? u : -1;
+                // a word past the end: the first word's cells, not used
+                const uint32_t i = i0 + k * (kPhiBlock / 64);
+                g[k] = list.cell(sh.list, 64 * i < m ? (int)i : (int)i0);
             }
 #pragma unroll
             for (int k = 0; k < kBatch; ++k) {
-                if (sg[k] < 0) continue;
-                const uint32_t p = seg_src[sg[k]] + (v0 + k * kPhiBlock - seg_pre[sg[k]]);
+                const uint32_t v = 64 * (i0 + k * (kPhiBlock / 64)) + lane;
+                if (v >= m) continue;
+                const uint32_t p = g[k].x + base + v;
 #pragma unroll
                 for (int e = 0; e < 3; ++e) o[k][e] = pos[(int64_t)e * n + p];
-                ab[k] = cS * abar[(int64_t)d * n + p];
+                ab[k] = cS * abar[(int64_t)D * n + p];
             }
 #pragma unroll
             for (int k = 0; k < kBatch; ++k) {
-                if (sg[k] < 0) continue;
-                const int s = sg[k];
-                const int b[3] = {s % kAB, (s / kAB) % kAB, s / (kAB * kAB)};
-                int j[3];          // first node of the footprint in the 20^3 box
+                if (64 * (i0 + k * (kPhiBlock / 64)) + lane >= m) continue;
+                int j[3];          // first node of the footprint among the pass's nodes
                 float w[3][P];
 #pragma unroll
                 for (int e = 0; e < 3; ++e) {
-                    j[e] = 2 * (b[e] - 2) + (int)(o[k][e] >> 15) + 2;  // fine cell's node
+                    j[e] = (int)(int8_t)(g[k].y >> (8 * e)) + (int)(o[k][e] >> 15);
                     const int f = (int)(o[k][e] & 0x7FFFu);
                     if constexpr (P == 3) {
                         j[e] += tsc_axis<float>(f, w[e]) - 1;
@@ -213,42 +209,70 @@ __global__ __launch_bounds__(kPhiBlock) void fine_phibar_kernel(
 #pragma unroll
                     for (int sy = 0; sy < P; ++sy) {
                         const int nz = j[2] + sz, ny = j[1] + sy;
-                        if ((unsigned)nz >= (unsigned)kAN || (unsigned)ny >= (unsigned)kAN) continue;
+                        if ((unsigned)nz >= (unsigned)N2 || (unsigned)ny >= (unsigned)N1) continue;
                         const float wyz = w[1][sy] * w[2][sz] * ab[k];
-                        // row of the node line, as two small products (24-bit
-                        // multiplies; a product of the sum is a 32-bit one)
-                        const int row = nz * (kAN * kAN) + ny * kAN;
+                        const int row = nz * (N1 * N0) + ny * N0;
 #pragma unroll
                         for (int sx = 0; sx < P; ++sx) {
                             const int nx = j[0] + sx;
-                            if ((unsigned)nx >= (unsigned)kAN) continue;
-                            atomicAdd(&A[row + nx], to_fixed(wyz * w[0][sx]));
+                            if ((unsigned)nx >= (unsigned)N0) continue;
+                            atomicAdd(&sh.A[row + nx], to_fixed(wyz * w[0][sx]));
                         }
                     }
             }
         }
-        __syncthreads();
-        const int st = d == 0 ? 1 : (d == 1 ? kAN : kAN * kAN);
-#pragma unroll
-        for (int k = 0; k < NPT; ++k) {
-            const int i = tid + k * kPhiBlock;
-            const int lx = i % T, ly = (i / T) % T, lz = i / (T * T);
-            const int m = ((lz + 2) * kAN + ly + 2) * kAN + lx + 2;
-            const long long d1 = (long long)(A[m + st] - A[m - st]);
-            const long long d2 = (long long)(A[m + 2 * st] - A[m - 2 * st]);
-            out[k] += invS * ((2.0f / 3.0f) * fixed_to_float(d1) - (1.0f / 12.0f) * fixed_to_float(d2));
-        }
-        __syncthreads();  // the next pass clears A
     }
-    // node i = tid + k kPhiBlock: the same (x, y) for every k, z advancing by
-    // kPhiBlock / T^2 layers per k
-    static_assert(kPhiBlock % (T * T) == 0, "whole z-layers per step");
-    const int a0x = tx * T, a0y = ty * T, a0z = tz * T;
-    const int lx = tid % T, ly = (tid / T) % T, lz = tid / (T * T);
-    float *dst = phibar + ((int64_t)(a0z + lz) * n_f + (a0y + ly)) * n_f + (a0x + lx);
-    const int64_t zstep = (int64_t)(kPhiBlock / (T * T)) * n_f * n_f;
+    __syncthreads();
+    // phibar(m) = sum_d (2/3)(A_d(m+e_d) - A_d(m-e_d)) - (1/12)(A_d(m+2e_d) - A_d(m-2e_d))
+    constexpr int ST = D == 0 ? 1 : (D == 1 ? N0 : N0 * N1);
+    const unsigned long long *a = sh.A + (8 * (tid >> 8) * N1 + ((tid >> 4) & 15)) * N0 + (tid & 15);
 #pragma unroll
-    for (int k = 0; k < NPT; ++k) dst[k * zstep] = out[k];
+    for (int k = 0; k < 8; ++k, a += N0 * N1) {
+        const long long d1 = (long long)(a[3 * ST] - a[ST]);
+        const long long d2 = (long long)(a[4 * ST] - a[0]);
+        out[k] += invS * ((2.0f / 3.0f) * fixed_to_float(d1) - (1.0f / 12.0f) * fixed_to_float(d2));
+        // summed here: left to the compiler, all passes' reads wait in registers (and
+        // scratch) for the stores
+        asm volatile("" : "+v"(out[k]));
+    }
+    if constexpr (D < 2) {
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            src[k] = nsrc[k];
+            cnt[k] = ncnt[k];
+            tag[k] = ntag[k];
+        }
+    }
+    __syncthreads();  // the next pass clears A
+}
+
+template <int P>
+__global__ __launch_bounds__(kPhiBlock, P == 2 ? 6 : 4) void fine_phibar_kernel(
+    const uint16_t *__restrict__ pos, const uint32_t *__restrict__ cs,
+    const float *__restrict__ abar, int n, int n_f, int nt, float c,
+    const unsigned int *__restrict__ amax_bits, float *__restrict__ phibar) {
+    __shared__ PhiShared<P> sh;
+    static_assert(kPhiBlock == 2 * kTileFine * kTileFine, "a thread's nodes: 8 layers of one column");
+    constexpr int PER = PhiGeo<P>::List::PER;
+    int t[3];
+    tile_of_block(blockIdx.x, nt, t[0], t[1], t[2]);
+    const int c0[3] = {t[0] * kTileIos, t[1] * kTileIos, t[2] * kTileIos};
+    const float S = fixed_scale(amax_bits, c), invS = 1.0f / S, cS = c * S;
+    uint32_t src[PER], cnt[PER], tag[PER];
+    float out[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) out[k] = 0.0f;
+    phi_box<P, 0>(cs, nt, c0, src, cnt, tag);
+    phi_pass<P, 0>(pos, cs, abar, n, nt, c0, cS, invS, src, cnt, tag, sh, out);
+    phi_pass<P, 1>(pos, cs, abar, n, nt, c0, cS, invS, src, cnt, tag, sh, out);
+    phi_pass<P, 2>(pos, cs, abar, n, nt, c0, cS, invS, src, cnt, tag, sh, out);
+    const int tid = threadIdx.x;
+    float *dst = phibar + ((int64_t)(t[2] * kTileFine + 8 * (tid >> 8)) * n_f +
+                           (t[1] * kTileFine + ((tid >> 4) & 15))) * n_f +
+                 (t[0] * kTileFine + (tid & 15));
+    const int64_t zstep = (int64_t)n_f * n_f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) dst[k * zstep] = out[k];
 }
 
 // ---------------------------------------------------------------------------
@@ -450,10 +474,15 @@ __device__ __forceinline__ int axis_footprint(int j, int f, float (&w)[P], float
     }
 }
 
+// 512 threads: the staged tiles let two workgroups on a CU, so that 256 threads were 8
+// waves per CU for latency- and LDS-bound work (134 million particles, two levels, 1024^3:
+// 7.72 ms at 256 threads, 6.40 at 512, 9.71 at 1024; one level, 256^3: 74.5, 62.3, 60.3 us).
+constexpr int kGatherBlock = 512;
+
 // HS > 0 fixes log2 of the coarse ratio at compile time (the coarse tiles'
 // LDS strides then fold into immediate offsets); HS = 0 reads it from hshift.
 template <bool WITH_E, bool TWO, int P, int HS = 0>
-__global__ __launch_bounds__(kBlock) void xbar_gather_kernel(
+__global__ __launch_bounds__(kGatherBlock) void xbar_gather_kernel(
     const uint16_t *__restrict__ pos, const uint32_t *__restrict__ cs,
     const float *__restrict__ abar, int n, int n_f, int nt, const float *__restrict__ phi_f,
     const float *__restrict__ rb_f, float c_f, const float *__restrict__ phi_c,
@@ -471,31 +500,31 @@ __global__ __launch_bounds__(kBlock) void xbar_gather_kernel(
     tile_of_block(blockIdx.x, nt, tx, ty, tz);
     const int tid = threadIdx.x;
     const uint32_t key0 = (uint32_t)((tz * nt + ty) * nt + tx) * kTileCells;
-    stage_cell_starts<kBlock>(cst, cs, key0);
+    stage_cell_starts<kGatherBlock>(cst, cs, key0);
     const int a0x = tx * kTileFine, a0y = ty * kTileFine, a0z = tz * kTileFine;
-    if (WITH_E) stage_block<kFS, kBlock>(pf, phi_f, n_f, a0x - G::PLO, a0y - G::PLO, a0z - G::PLO);
+    if (WITH_E) stage_block<kFS, kGatherBlock>(pf, phi_f, n_f, a0x - G::PLO, a0y - G::PLO, a0z - G::PLO);
     if (rb_f) {
-        stage_block<kRS, kBlock>(rf, rb_f, n_f, a0x - G::RLO, a0y - G::RLO, a0z - G::RLO);
+        stage_block<kRS, kGatherBlock>(rf, rb_f, n_f, a0x - G::RLO, a0y - G::RLO, a0z - G::RLO);
     } else {
-        for (int i = tid; i < kRS * kRS * kRS; i += kBlock) rf[i] = 0.0f;
+        for (int i = tid; i < kRS * kRS * kRS; i += kGatherBlock) rf[i] = 0.0f;
     }
     const int CS = (kTileFine >> hshift) + G::PX, CR = (kTileFine >> hshift) + G::RX;
     if (TWO) {
         const int cx0 = a0x >> hshift, cy0 = a0y >> hshift, cz0 = a0z >> hshift;
         if (WITH_E)
-            for (int i = tid; i < CS * CS * CS; i += kBlock) {
+            for (int i = tid; i < CS * CS * CS; i += kGatherBlock) {
                 const int lx = i % CS, ly = (i / CS) % CS, lz = i / (CS * CS);
                 pc[i] = phi_c[((int64_t)wrapn(cz0 + lz - G::PLO, n_c) * n_c +
                                wrapn(cy0 + ly - G::PLO, n_c)) * n_c + wrapn(cx0 + lx - G::PLO, n_c)];
             }
-        for (int i = tid; i < CR * CR * CR; i += kBlock) {
+        for (int i = tid; i < CR * CR * CR; i += kGatherBlock) {
             const int lx = i % CR, ly = (i / CR) % CR, lz = i / (CR * CR);
             rc[i] = rb_c[((int64_t)wrapn(cz0 + lz - G::RLO, n_c) * n_c +
                           wrapn(cy0 + ly - G::RLO, n_c)) * n_c + wrapn(cx0 + lx - G::RLO, n_c)];
         }
     }
     __syncthreads();
-    for (uint32_t p = cst[0] + tid; p < cst[kTileCells]; p += kBlock) {
+    for (uint32_t p = cst[0] + tid; p < cst[kTileCells]; p += kGatherBlock) {
         const int u = seg_search_n<kTileCells>(cst, p);
         const int uc[3] = {u & 7, (u >> 3) & 7, u >> 6};
         int jf[3], jc[3];
@@ -535,13 +564,13 @@ void launch_deposit_backward_p(cube2_ctx *ctx, const uint16_t *pos, const uint32
     const int nt = ctx->nt;
     const unsigned blocks = (unsigned)(nt * nt * nt);
     if (level == 0) {
-        xbar_gather_kernel<false, false, P><<<blocks, kBlock, 0, s>>>(
+        xbar_gather_kernel<false, false, P><<<blocks, kGatherBlock, 0, s>>>(
             pos, cs, nullptr, (int)n, ctx->n_f, nt, nullptr, rho_bar, 0.f, nullptr, nullptr, 0.f, 1,
             0, x_bar, accumulate);
     } else {
         // coarse only: a zero fine rhobar contributes nothing
         const Level &C = ctx->lv[1];
-        xbar_gather_kernel<false, true, P><<<blocks, kBlock, 0, s>>>(
+        xbar_gather_kernel<false, true, P><<<blocks, kGatherBlock, 0, s>>>(
             pos, cs, nullptr, (int)n, ctx->n_f, nt, nullptr, nullptr, 0.f, nullptr, rho_bar, 0.f,
             C.n, C.hshift, x_bar, accumulate);
     }
@@ -612,10 +641,10 @@ int launch_pm_backward_p(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs
         if (r) return r;
         auto *k = C.hshift == 2 ? xbar_gather_kernel<true, true, P, 2>
                                 : xbar_gather_kernel<true, true, P>;
-        k<<<blocks, kBlock, 0, s>>>(pos, cs, acc_bar, (int)n, ctx->n_f, nt, rf, bf, (float)gm, rc,
+        k<<<blocks, kGatherBlock, 0, s>>>(pos, cs, acc_bar, (int)n, ctx->n_f, nt, rf, bf, (float)gm, rc,
                                     bc, cc, C.n, C.hshift, x_bar, accumulate);
     } else {
-        xbar_gather_kernel<true, false, P><<<blocks, kBlock, 0, s>>>(
+        xbar_gather_kernel<true, false, P><<<blocks, kGatherBlock, 0, s>>>(
             pos, cs, acc_bar, (int)n, ctx->n_f, nt, rf, bf, (float)gm, nullptr, nullptr, 0.f, 1, 0,
             x_bar, accumulate);
     }

@@ -212,17 +212,30 @@ __device__ __forceinline__ int seg_search_n(const uint32_t *pre, uint32_t v) {
     return lo;
 }
 
+// Index of this thread's wave in its workgroup, known uniform (a scalar).
+__device__ __forceinline__ int wave_id() {
+    return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+}
+
+// Inclusive sums over the lanes of a wave (every lane active): DPP shifts within the
+// rows of 16 lanes, then the rows' sums broadcast to the rows above.  6 additions; by
+// shuffles, 6 dependent LDS round trips.
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x) {
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);   // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);   // row_bcast:15
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);   // row_bcast:31
+    return x;
+}
+
 // Block-wide exclusive scan of one uint32 per thread (blockDim == BLOCK).
 template <int BLOCK = kBlock>
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *sh /*BLOCK/64+1*/,
                                                          uint32_t &total) {
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    uint32_t x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        uint32_t y = __shfl_up(x, o, 64);
-        if (lane >= o) x += y;
-    }
+    const uint32_t x = wave_inclusive_scan(v);
     if (lane == 63) sh[wid] = x;
     __syncthreads();
     uint32_t off = 0, tot = 0;
@@ -373,6 +386,99 @@ __device__ __forceinline__ float wave_sum(float v) {
     for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
     return v;
 }
+
+// The particles of a box of cells as one list, cell after cell in box order: position v
+// of the list belongs to cell `cell` and is particle `from + v`.  The nonempty cells are
+// kept in LDS, and one bit per position tells where a cell begins, kBoxSpan positions
+// at a time; a wave then finds its 64 positions' cells by counting bits of one word
+// (two lane reads, a bit count and one LDS read, most lanes of the same address),
+// where a binary search of the cells' first positions is ten dependent LDS reads.
+constexpr int kBoxSpan = 4096;
+template <int SEGS, int BLOCK> struct BoxList {
+    static constexpr int PER = (SEGS + BLOCK - 1) / BLOCK;   // cells per thread
+    struct Shared {
+        uint2 seg[SEGS];                     // {from, the caller's word for the cell}
+        uint32_t head[kBoxSpan / 32];        // bit: a cell begins here
+        uint32_t before;                     // nonempty cells wholly before the span
+        uint2 scan[BLOCK / 64];
+    };
+    uint32_t total, first[PER], rank;        // this thread's cells: first positions, nonempty cells before
+    uint32_t pfx;                            // of head word pair `lane` of the span
+    unsigned long long word;
+
+    // the list of this thread's cells tid * PER + k (starts src, counts cnt, words tag);
+    // the first span is ready after it.  All threads call it; the LDS is free before.
+    __device__ __forceinline__ void build(Shared &sh, const uint32_t (&src)[PER], const uint32_t (&cnt)[PER],
+                                          const uint32_t (&tag)[PER]) {
+        const int tid = threadIdx.x, lane = tid & 63, w = wave_id();
+        if (tid < kBoxSpan / 32) sh.head[tid] = 0u;
+        uint32_t c = 0, ne = 0;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            c += cnt[k];
+            ne += cnt[k] != 0u;
+        }
+        const uint32_t xc = wave_inclusive_scan(c), xn = wave_inclusive_scan(ne);
+        if (lane == 63) sh.scan[w] = make_uint2(xc, xn);
+        __syncthreads();
+        uint32_t at = xc - c, all = 0;
+        rank = xn - ne;
+#pragma unroll
+        for (int i = 0; i < BLOCK / 64; ++i) {
+            const uint2 t = sh.scan[i];
+            if (i < w) {
+                at += t.x;
+                rank += t.y;
+            }
+            all += t.x;
+        }
+        total = (uint32_t)__builtin_amdgcn_readfirstlane((int)all);
+        uint32_t r = rank;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            first[k] = at;
+            if (cnt[k]) sh.seg[r++] = make_uint2(src[k] - at, tag[k]);
+            at += cnt[k];
+        }
+        mark(sh, cnt, 0u);
+    }
+    // the heads of the span of positions [base, base + kBoxSpan); sh.head is clear
+    __device__ __forceinline__ void mark(Shared &sh, const uint32_t (&cnt)[PER], uint32_t base) {
+        uint32_t r = rank;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const uint32_t end = first[k] + cnt[k];
+            if (cnt[k] && end > base && first[k] < base + kBoxSpan) {
+                const uint32_t i = first[k] > base ? first[k] - base : 0u;
+                atomicOr(&sh.head[i >> 5], 1u << (i & 31u));
+                if (first[k] <= base) sh.before = r;
+            }
+            r += cnt[k] != 0u;
+        }
+        __syncthreads();
+        const int lane = threadIdx.x & 63;
+        word = ((unsigned long long)sh.head[2 * lane + 1] << 32) | sh.head[2 * lane];
+        const uint32_t c = (uint32_t)__popcll(word);
+        pfx = sh.before + wave_inclusive_scan(c) - c;
+    }
+    // moves on to the span at `base`; all threads call it
+    __device__ __forceinline__ void span(Shared &sh, const uint32_t (&cnt)[PER], uint32_t base) {
+        __syncthreads();
+        if (threadIdx.x < kBoxSpan / 32) sh.head[threadIdx.x] = 0u;
+        __syncthreads();
+        mark(sh, cnt, base);
+    }
+    // {from, word} of the cell of position 64 i + lane of the span (i wave-uniform,
+    // 64 i < the span's positions; a lane past the list's end gets its last cell)
+    __device__ __forceinline__ uint2 cell(const Shared &sh, int i) const {
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)word, i),
+                       hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(word >> 32), i);
+        const uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)pfx, i) + (lo & 1u) - 1u;
+        // heads at or below the lane: those of the word shifted down below it, and bit 0
+        const uint32_t l1 = (lo >> 1) | (hi << 31), h1 = hi >> 1;
+        return sh.seg[__builtin_amdgcn_mbcnt_hi(h1, __builtin_amdgcn_mbcnt_lo(l1, p))];
+    }
+};
 
 // Lane of the first set bit of a nonzero wave mask.
 __device__ __forceinline__ int first_lane(unsigned long long mask) {

@@ -12,7 +12,7 @@
 // every particle that touches them: its own 8^3 IOS cells plus the layer of
 // IOS cells below it on each axis (a particle in fine cell a-1 feeds node a).
 // The contributing cells form a 9^3 box of IOS cells, i.e. 729 contiguous
-// particle ranges, flattened by a prefix sum and searched per particle.
+// particle ranges, gathered as one list (BoxList).
 // Each fine node is then written once, as FP32: no global atomics and no
 // 64-bit mesh in HBM.
 // Coarse level: only the tile's own particles are assigned; the tile's
@@ -40,7 +40,6 @@ namespace {
 template <int P, int CR = 4> struct DepGeo {
     static constexpr int BOX = kTileIos + (P == 3 ? 2 : 1);
     static constexpr int SEGS = BOX * BOX * BOX;              // 729 or 1000
-    static constexpr int SEG_PER_THREAD = (SEGS + kBlock - 1) / kBlock;
     static constexpr int CMAX = kTileFine / CR + (P == 3 ? 3 : 1);  // coarse nodes per axis
 };
 
@@ -57,8 +56,8 @@ __global__ void fill_u64(unsigned long long *p, int64_t n) {
     if (i < n) p[i] = 0ull;
 }
 
-// Fine CIC weights of one particle of box segment b (IOS cell coordinates in
-// the 9^3 box, own cells at 1..8) with in-cell offsets o, added to the
+// Fine CIC weights of one particle of box segment b (IOS cell coordinates
+// relative to the tile, own cells at 0..7) with in-cell offsets o, added to the
 // tile's fine nodes that it reaches.
 __device__ __forceinline__ void deposit_fine(const int (&b)[3], const uint32_t (&o)[3],
                                              unsigned long long *acc_f) {
@@ -66,7 +65,7 @@ __device__ __forceinline__ void deposit_fine(const int (&b)[3], const uint32_t (
     uint32_t w[3][2];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        j[d] = 2 * (b[d] - 1) + (int)(o[d] >> 15);  // fine cell rel. to the tile
+        j[d] = 2 * b[d] + (int)(o[d] >> 15);  // fine cell rel. to the tile
         const uint32_t f = o[d] & 0x7FFFu;
         w[d][0] = 32768u - f;
         w[d][1] = f;
@@ -99,7 +98,7 @@ __device__ __forceinline__ void deposit_fine_tsc(const int (&b)[3], const uint32
     for (int d = 0; d < 3; ++d) {
         const int f = (int)(o[d] & 0x7FFFu);
         const int hi = f >= 16384 ? 1 : 0;
-        j[d] = 2 * (b[d] - 1) + (int)(o[d] >> 15) + hi - 1;  // node n0 - 1, rel. to the tile
+        j[d] = 2 * b[d] + (int)(o[d] >> 15) + hi - 1;  // node n0 - 1, rel. to the tile
         tsc_weights(f - (hi << 15), w[d]);
     }
 #pragma unroll
@@ -132,7 +131,7 @@ __device__ __forceinline__ void deposit_coarse_wave_tsc(bool own, const int (&b)
     uint32_t w[3][3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        const uint32_t q = ((uint32_t)(b[d] - 1) << 16) + o[d];  // tile-relative
+        const uint32_t q = ((uint32_t)b[d] << 16) + o[d];  // tile-relative
         const uint32_t y = q >> hshift;                           // 2^-15 coarse cells
         const int f = (int)(y & 0x7FFFu);
         const int hi = f >= 16384 ? 1 : 0;
@@ -177,7 +176,7 @@ __device__ __forceinline__ void deposit_coarse_wave(bool own, const int (&b)[3],
     uint32_t w[3][2];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        const uint32_t q = ((uint32_t)(b[d] - 1) << 16) + o[d];  // tile-relative
+        const uint32_t q = ((uint32_t)b[d] << 16) + o[d];  // tile-relative
         j[d] = (int)(q >> (kFracBits + hshift));
         const uint32_t f = (q >> hshift) & 0x7FFFu;
         w[d][0] = own ? 32768u - f : 0u;
@@ -213,34 +212,36 @@ __global__ __launch_bounds__(kBlock) void deposit_kernel(
     unsigned long long *__restrict__ coarse_acc, int n_c, int hshift, uint32_t *status,
     const uint32_t *__restrict__ order, uint32_t *__restrict__ queue) {
     using Geo = DepGeo<P, CR>;
+    using List = BoxList<Geo::SEGS, kBlock>;
     constexpr int kBox = Geo::BOX, kSegs = Geo::SEGS;
-    constexpr int kSegPerThread = Geo::SEG_PER_THREAD, kCoarseMax = Geo::CMAX;
-    __shared__ uint32_t seg_pre[kSegs + 1];
-    __shared__ uint32_t seg_src[kSegs];
+    constexpr int kSegPerThread = List::PER, kCoarseMax = Geo::CMAX;
+    __shared__ typename List::Shared list_sh;
     __shared__ unsigned long long acc_f[FINE ? kTileFine * kTileFine * kTileFine : 1];
     __shared__ unsigned long long acc_c[COARSE ? kCoarseMax * kCoarseMax * kCoarseMax : 1];
-    __shared__ uint32_t scan_sh[kBlock / 64 + 1];
     __shared__ int next_sh;
 
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
     const int n_ios = nt * kTileIos;
     const int NC = (kTileFine >> hshift) + (P == 3 ? 3 : 1);  // coarse nodes per axis touched
     const int ntiles = nt * nt * nt;
 
     // Particle ranges (start, count) of this thread's segments of the box of
-    // IOS cells [c0-1, c0+kBox-1) around tile t.
-    uint32_t cnt[kSegPerThread], src[kSegPerThread];
+    // IOS cells [c0-1, c0+kBox-1) around tile t, and each segment's IOS cell relative
+    // to the tile (a signed byte per axis; bit 24: one of the tile's own).
+    uint32_t cnt[kSegPerThread], src[kSegPerThread], tag[kSegPerThread];
     auto load_segments = [&](int t) {
         const int c0x = (t % nt) * kTileIos, c0y = ((t / nt) % nt) * kTileIos,
                   c0z = (t / (nt * nt)) * kTileIos;
 #pragma unroll
         for (int k = 0; k < kSegPerThread; ++k) {
             const int s = tid * kSegPerThread + k;
-            cnt[k] = 0;
-            src[k] = 0;
+            cnt[k] = src[k] = tag[k] = 0u;
             if (s < kSegs) {
                 const int bx = s % kBox, by = (s / kBox) % kBox, bz = s / (kBox * kBox);
-                const bool own = bx > 0 && by > 0 && bz > 0;
+                const bool own = bx > 0 && by > 0 && bz > 0 && bx <= kTileIos && by <= kTileIos &&
+                                 bz <= kTileIos;
+                tag[k] = (uint32_t)((bx - 1) & 0xFF) | (uint32_t)((by - 1) & 0xFF) << 8 |
+                         (uint32_t)((bz - 1) & 0xFF) << 16 | (own ? 1u << 24 : 0u);
                 if (FINE || own) {
                     const uint32_t key = cell_key(wrapn(c0x + bx - 1, n_ios), wrapn(c0y + by - 1, n_ios),
                                                   wrapn(c0z + bz - 1, n_ios), nt);
@@ -283,78 +284,60 @@ __global__ __launch_bounds__(kBlock) void deposit_kernel(
         if (COARSE)
             for (int i = tid; i < NC * NC * NC; i += kBlock) acc_c[i] = 0ull;
 
-        uint32_t sum = 0;
 #pragma unroll
-        for (int k = 0; k < kSegPerThread; ++k) {
-            cnt[k] -= src[k];
-            sum += cnt[k];
-        }
-        uint32_t total;
-        uint32_t pre = block_exclusive_scan(sum, scan_sh, total);
-#pragma unroll
-        for (int k = 0; k < kSegPerThread; ++k) {
-            const int s = tid * kSegPerThread + k;
-            if (s < kSegs) {
-                seg_pre[s] = pre;
-                seg_src[s] = src[k];
-            }
-            pre += cnt[k];
-        }
-        if (tid == 0) seg_pre[kSegs] = total;
-        __syncthreads();
+        for (int k = 0; k < kSegPerThread; ++k) cnt[k] -= src[k];
+        List list;
+        list.build(list_sh, src, cnt, tag);
         if (tid == 0) {
             // Overflow guard: a fine node sums at most `total` weights of 2^45
             // (CIC) or 2^47 (TSC) each; a coarse node sums the own particles
-            // of at most 8 tiles.  The own cells' particles are one contiguous
-            // range, from the first own segment to the end of the last.
-            const int s_first = (1 * kBox + 1) * kBox + 1;
-            const int s_last = (kTileIos * kBox + kTileIos) * kBox + kTileIos;
-            const uint32_t own =
-                seg_src[s_last] + (seg_pre[s_last + 1] - seg_pre[s_last]) - seg_src[s_first];
+            // of at most 8 tiles.
+            const uint32_t own = cs[(uint32_t)(t + 1) * kTileCells] - cs[(uint32_t)t * kTileCells];
             const uint32_t fine_max = P == 3 ? (1u << 17) : (1u << 19);
             const uint32_t own_max = P == 3 ? (1u << 14) : (1u << 16);
-            if ((FINE && total >= fine_max) || (COARSE && own >= own_max)) atomicOr(status, kStatusOverflow);
+            if ((FINE && list.total >= fine_max) || (COARSE && own >= own_max))
+                atomicOr(status, kStatusOverflow);
         }
 
         // The loop runs wave-uniformly (every lane of a wave takes the same
         // trips) so that the coarse weights can be summed over the wave; each
-        // trip takes kBatch particles per lane, whose segment searches and
-        // position loads are all issued before the first deposit.
-        constexpr int kBatch = 4;
-        const int lane = tid & 63;
-        for (uint32_t w0 = (uint32_t)(tid - lane); w0 < total; w0 += kBlock * kBatch) {
-            int sg[kBatch];
-            uint32_t o[kBatch][3];
+        // trip takes kBatch particles per lane, whose position loads are all
+        // issued before the first deposit.
+        constexpr int kBatch = 4, kWaves = kBlock / 64;
+        for (uint32_t base = 0; base < list.total; base += kBoxSpan) {
+            if (base) list.span(list_sh, cnt, base);
+            const uint32_t m = min(list.total - base, (uint32_t)kBoxSpan);
+            for (uint32_t i0 = wave; 64 * i0 < m; i0 += kBatch * kWaves) {
+                uint2 g[kBatch];
+                uint32_t o[kBatch][3];
 #pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-                // searched for every lane (a lane past the end searches for the
-                // last particle, total >= 1 here), so that the kBatch searches
-                // interleave their LDS reads outside any branch
-                const uint32_t v = w0 + k * kBlock + lane;
-                const int u = seg_search_n<kSegs>(seg_pre, v < total ? v : total - 1);
-                sg[k] = v < total ? u : -1;
-            }
+                for (int k = 0; k < kBatch; ++k) {
+                    // a word past the end: the first word's cells, not used
+                    const uint32_t i = i0 + k * kWaves;
+                    g[k] = list.cell(list_sh, 64 * i < m ? (int)i : (int)i0);
+                }
 #pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-                o[k][0] = o[k][1] = o[k][2] = 0u;
-                if (sg[k] < 0) continue;
-                const uint32_t p = seg_src[sg[k]] + (w0 + k * kBlock + lane - seg_pre[sg[k]]);
+                for (int k = 0; k < kBatch; ++k) {
+                    const uint32_t v = 64 * (i0 + k * kWaves) + lane;
+                    o[k][0] = o[k][1] = o[k][2] = 0u;
+                    if (v >= m) continue;
+                    const uint32_t p = g[k].x + base + v;
 #pragma unroll
-                for (int d = 0; d < 3; ++d) o[k][d] = pos[(int64_t)d * n + p];
-            }
+                    for (int d = 0; d < 3; ++d) o[k][d] = pos[(int64_t)d * n + p];
+                }
 #pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-                const bool valid = sg[k] >= 0;
-                const int s = valid ? sg[k] : 0;
-                const int b[3] = {s % kBox, (s / kBox) % kBox, s / (kBox * kBox)};
-                const bool own = valid && b[0] > 0 && b[1] > 0 && b[2] > 0 && b[0] <= kTileIos &&
-                                 b[1] <= kTileIos && b[2] <= kTileIos;
-                if (P == 3) {
-                    if (FINE && valid) deposit_fine_tsc(b, o[k], acc_f);
-                    if (COARSE) deposit_coarse_wave_tsc(own, b, o[k], hshift, NC, acc_c);
-                } else {
-                    if (FINE && valid) deposit_fine(b, o[k], acc_f);
-                    if (COARSE) deposit_coarse_wave(own, b, o[k], hshift, NC, acc_c);
+                for (int k = 0; k < kBatch; ++k) {
+                    const bool valid = 64 * (i0 + k * kWaves) + lane < m;
+                    const int b[3] = {(int)(int8_t)g[k].y, (int)(int8_t)(g[k].y >> 8),
+                                      (int)(int8_t)(g[k].y >> 16)};
+                    const bool own = valid && (g[k].y >> 24) != 0u;
+                    if (P == 3) {
+                        if (FINE && valid) deposit_fine_tsc(b, o[k], acc_f);
+                        if (COARSE) deposit_coarse_wave_tsc(own, b, o[k], hshift, NC, acc_c);
+                    } else {
+                        if (FINE && valid) deposit_fine(b, o[k], acc_f);
+                        if (COARSE) deposit_coarse_wave(own, b, o[k], hshift, NC, acc_c);
+                    }
                 }
             }
         }

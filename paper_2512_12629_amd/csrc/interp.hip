@@ -114,8 +114,8 @@ __device__ __forceinline__ void gather3(const T *P, int S, int nx, int ny, int n
 // coarse level only (the tile+buffer mode computes the fine level per tile).
 // HS > 0 fixes log2 of the coarse ratio at compile time (the coarse tile's
 // LDS strides then fold into immediate offsets); HS = 0 reads it from hshift.
-template <bool TWO, int P, typename T, bool FINE = true, int HS = 0>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) void interp_kernel(
+template <bool TWO, int P, typename T, bool FINE, int HS, int BLOCK>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void interp_kernel(
     const uint16_t *__restrict__ pos, const uint32_t *__restrict__ cs, int n, int n_f, int nt,
     const T *__restrict__ phi_f, const T *__restrict__ phi_c, int n_c, int hshift_arg, T scale_f,
     T scale_c, T *__restrict__ acc, int accumulate) {
@@ -129,17 +129,17 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
     const int tid = threadIdx.x;
     const int hshift = HS > 0 ? HS : hshift_arg;
     const uint32_t key0 = (uint32_t)((tz * nt + ty) * nt + tx) * kTileCells;
-    stage_cell_starts<kBlock>(cst, cs, key0);
+    stage_cell_starts<BLOCK>(cst, cs, key0);
     const int ax0 = tx * kTileFine, ay0 = ty * kTileFine, az0 = tz * kTileFine;
-    if (FINE) stage_block<FS, kBlock>(pf, phi_f, n_f, ax0 - HLO, ay0 - HLO, az0 - HLO);
+    if (FINE) stage_block<FS, BLOCK>(pf, phi_f, n_f, ax0 - HLO, ay0 - HLO, az0 - HLO);
     const int CS = (kTileFine >> hshift) + FS - kTileFine;
     if (TWO) {
         const int cx0 = (ax0 >> hshift) - HLO, cy0 = (ay0 >> hshift) - HLO,
                   cz0 = (az0 >> hshift) - HLO;
         switch (hshift) {
-            case 1: stage_block<kTileFine / 2 + FS - kTileFine, kBlock>(pc, phi_c, n_c, cx0, cy0, cz0); break;
-            case 2: stage_block<kTileFine / 4 + FS - kTileFine, kBlock>(pc, phi_c, n_c, cx0, cy0, cz0); break;
-            default: stage_block<kTileFine / 8 + FS - kTileFine, kBlock>(pc, phi_c, n_c, cx0, cy0, cz0); break;
+            case 1: stage_block<kTileFine / 2 + FS - kTileFine, BLOCK>(pc, phi_c, n_c, cx0, cy0, cz0); break;
+            case 2: stage_block<kTileFine / 4 + FS - kTileFine, BLOCK>(pc, phi_c, n_c, cx0, cy0, cz0); break;
+            default: stage_block<kTileFine / 8 + FS - kTileFine, BLOCK>(pc, phi_c, n_c, cx0, cy0, cz0); break;
         }
     }
     __syncthreads();
@@ -149,14 +149,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
     // more registers): the cell searches and all position loads are issued
     // before the first particle is processed
     constexpr int kBatch = P == 3 ? 1 : 2;
-    for (uint32_t pb = p0 + tid; pb < p1; pb += kBlock * kBatch) {
+    for (uint32_t pb = p0 + tid; pb < p1; pb += BLOCK * kBatch) {
         int ub[kBatch];
         uint32_t ob[kBatch][3];
 #pragma unroll
         for (int k = 0; k < kBatch; ++k) {
             // searched for every lane (past the end: the last particle) so
             // that the searches of the batch interleave outside any branch
-            const uint32_t p = pb + k * kBlock;
+            const uint32_t p = pb + k * BLOCK;
             const int u = seg_search_n<kTileCells>(cst, p < p1 ? p : p1 - 1);
             ub[k] = p < p1 ? u : -1;
         }
@@ -164,12 +164,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
         for (int k = 0; k < kBatch; ++k) {
             if (ub[k] < 0) continue;
 #pragma unroll
-            for (int d = 0; d < 3; ++d) ob[k][d] = pos[(int64_t)d * n + pb + k * kBlock];
+            for (int d = 0; d < 3; ++d) ob[k][d] = pos[(int64_t)d * n + pb + k * BLOCK];
         }
 #pragma unroll
         for (int k = 0; k < kBatch; ++k) {
             if (ub[k] < 0) continue;
-            const uint32_t p = pb + k * kBlock;
+            const uint32_t p = pb + k * BLOCK;
             const int u = ub[k];
             const int uc[3] = {u & 7, (u >> 3) & 7, u >> 6};
             int jf[3], jc[3];
@@ -244,28 +244,46 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
 
 }  // namespace
 
+template <int P, typename T, int BLOCK>
+void launch_interp_block(cube2_ctx *ctx, unsigned blocks, const uint16_t *pos, const uint32_t *cs,
+                         int64_t n, const T *phi_f, const T *phi_c, double gm, T *acc,
+                         int accumulate, bool fine, bool coarse, hipStream_t s) {
+    const int nt = ctx->nt;
+    if (coarse && !fine) {
+        const Level &C = ctx->lv[1];
+        interp_kernel<true, P, T, false, 0, BLOCK><<<blocks, BLOCK, 0, s>>>(
+            pos, cs, (int)n, ctx->n_f, nt, nullptr, phi_c, C.n, C.hshift, T(0),
+            (T)(gm / ((double)C.H * C.H)), acc, accumulate);
+    } else if (coarse) {
+        const Level &C = ctx->lv[1];
+        auto *k = C.hshift == 2 ? interp_kernel<true, P, T, true, 2, BLOCK>
+                                : interp_kernel<true, P, T, true, 0, BLOCK>;
+        k<<<blocks, BLOCK, 0, s>>>(pos, cs, (int)n, ctx->n_f, nt, phi_f, phi_c, C.n, C.hshift,
+                                   (T)gm, (T)(gm / ((double)C.H * C.H)), acc, accumulate);
+    } else {
+        interp_kernel<false, P, T, true, 0, BLOCK><<<blocks, BLOCK, 0, s>>>(
+            pos, cs, (int)n, ctx->n_f, nt, phi_f, nullptr, 1, 0, (T)gm, T(0), acc, accumulate);
+    }
+}
+
+// Threads per workgroup.  512 where few workgroups are resident in any case and a tile
+// is the latency of its staging and of one wave's particles: up to two tiles per CU
+// (64 tiles: 7.7 us at 256 threads, 5.8 at 512), and the TSC tiles in single precision,
+// whose LDS lets two workgroups on a CU (848 us at 256, 724 at 512, on a 512^3 mesh).
+// Else 256: three or four workgroups per CU, one staging while another gathers
+// (1024^3 CIC: 3.72 ms at 256, 4.45 at 512, 6.58 at 1024; FP64 CIC, 256^3: 93 us, 115
+// and 114).
+constexpr int kSmallTiles = 512;
+
 // levels: bit 0 the fine level, bit 1 the coarse level (if the context has one)
 template <int P, typename T>
 void launch_interp_kernel(cube2_ctx *ctx, unsigned blocks, const uint16_t *pos, const uint32_t *cs,
                           int64_t n, const T *phi_f, const T *phi_c, double gm, T *acc,
                           int accumulate, int levels, hipStream_t s) {
-    const int nt = ctx->nt;
     const bool fine = (levels & 1) != 0, coarse = ctx->n_levels > 1 && (levels & 2) != 0;
-    if (coarse && !fine) {
-        const Level &C = ctx->lv[1];
-        interp_kernel<true, P, T, false><<<blocks, kBlock, 0, s>>>(
-            pos, cs, (int)n, ctx->n_f, nt, nullptr, phi_c, C.n, C.hshift, T(0),
-            (T)(gm / ((double)C.H * C.H)), acc, accumulate);
-    } else if (coarse) {
-        const Level &C = ctx->lv[1];
-        auto *k = C.hshift == 2 ? interp_kernel<true, P, T, true, 2> : interp_kernel<true, P, T>;
-        k<<<blocks, kBlock, 0, s>>>(pos, cs, (int)n, ctx->n_f, nt, phi_f, phi_c, C.n, C.hshift,
-                                    (T)gm, (T)(gm / ((double)C.H * C.H)), acc, accumulate);
-    } else {
-        interp_kernel<false, P, T><<<blocks, kBlock, 0, s>>>(pos, cs, (int)n, ctx->n_f, nt, phi_f,
-                                                             nullptr, 1, 0, (T)gm, T(0), acc,
-                                                             accumulate);
-    }
+    auto *launch = launch_interp_block<P, T, sizeof(T) == 4 && P == 3 ? 512 : kBlock>;
+    if (sizeof(T) == 4 && blocks <= kSmallTiles) launch = launch_interp_block<P, T, sizeof(T) == 4 ? 512 : kBlock>;
+    launch(ctx, blocks, pos, cs, n, phi_f, phi_c, gm, acc, accumulate, fine, coarse, s);
 }
 
 template <typename T>
