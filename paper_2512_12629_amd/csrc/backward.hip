@@ -93,8 +93,8 @@ __device__ __forceinline__ float fixed_to_float(long long d) { return (float)(do
 // term on the tile's nodes.
 // Bound by the LDS (the clearing, the 64-bit additions and the stencil's reads) and
 // the VALU together.  The 20^3 nodes and 11^3 cells of all three components in each
-// pass, with a search per particle, took 12.8 ms for 134 million particles on a 1024^3
-// mesh at 14 waves per CU (this: PHI_NOW, at 24).
+// pass, with a search per particle, took 12.75 ms for 134 million particles on a 1024^3
+// mesh at 14 waves per CU (this: 8.7, at 21).
 // ---------------------------------------------------------------------------
 
 constexpr int kPhiBlock = 512;
@@ -487,7 +487,7 @@ __global__ __launch_bounds__(kGatherBlock) void xbar_gather_kernel(
     const float *__restrict__ abar, int n, int n_f, int nt, const float *__restrict__ phi_f,
     const float *__restrict__ rb_f, float c_f, const float *__restrict__ phi_c,
     const float *__restrict__ rb_c, float c_c, int n_c, int hshift_arg, float *__restrict__ xbar,
-    int accumulate) {
+    int accumulate, const float *__restrict__ extra) {
     const int hshift = HS > 0 ? HS : hshift_arg;
     using G = GatherGeo<P>;
     constexpr int kFS = G::FS, kRS = G::RS, kCSMax = G::CSMAX, kCRMax = G::CRMAX;
@@ -528,12 +528,13 @@ __global__ __launch_bounds__(kGatherBlock) void xbar_gather_kernel(
         const int u = seg_search_n<kTileCells>(cst, p);
         const int uc[3] = {u & 7, (u >> 3) & 7, u >> 6};
         int jf[3], jc[3];
-        float wf[3][P], dwf[3][P], wc[3][P], dwc[3][P], ab[3];
+        float wf[3][P], dwf[3][P], wc[3][P], dwc[3][P], ab[3], eb[3];
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
             const uint32_t o = pos[(int64_t)d * n + p];
             jf[d] = axis_footprint<P>(2 * uc[d] + (int)(o >> 15), (int)(o & 0x7FFFu), wf[d], dwf[d]);
             ab[d] = WITH_E ? abar[(int64_t)d * n + p] : 0.0f;
+            eb[d] = extra ? extra[(int64_t)d * n + p] : 0.0f;
             if (TWO) {
                 const uint32_t q = ((uint32_t)uc[d] << 16) + o;
                 jc[d] = axis_footprint<P>((int)(q >> (kFracBits + hshift)), (int)((q >> hshift) & 0x7FFFu),
@@ -548,7 +549,8 @@ __global__ __launch_bounds__(kGatherBlock) void xbar_gather_kernel(
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
             float *dst = xbar + (int64_t)d * n + p;
-            *dst = accumulate ? *dst + xb[d] : xb[d];
+            const float v = accumulate ? *dst + xb[d] : xb[d];
+            *dst = extra ? v + eb[d] : v;
         }
     }
 }
@@ -566,20 +568,20 @@ void launch_deposit_backward_p(cube2_ctx *ctx, const uint16_t *pos, const uint32
     if (level == 0) {
         xbar_gather_kernel<false, false, P><<<blocks, kGatherBlock, 0, s>>>(
             pos, cs, nullptr, (int)n, ctx->n_f, nt, nullptr, rho_bar, 0.f, nullptr, nullptr, 0.f, 1,
-            0, x_bar, accumulate);
+            0, x_bar, accumulate, nullptr);
     } else {
         // coarse only: a zero fine rhobar contributes nothing
         const Level &C = ctx->lv[1];
         xbar_gather_kernel<false, true, P><<<blocks, kGatherBlock, 0, s>>>(
             pos, cs, nullptr, (int)n, ctx->n_f, nt, nullptr, nullptr, 0.f, nullptr, rho_bar, 0.f,
-            C.n, C.hshift, x_bar, accumulate);
+            C.n, C.hshift, x_bar, accumulate, nullptr);
     }
 }
 
 template <int P>
 int launch_pm_backward_p(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,
                          const float *acc_bar, float *x_bar, int accumulate, unsigned char *work,
-                         const WorkLayout &L, hipStream_t s) {
+                         const WorkLayout &L, const float *extra, hipStream_t s) {
     const int nt = ctx->nt;
     const unsigned blocks = (unsigned)(nt * nt * nt);
     const double gm = ctx->cfg.g_newton * ctx->cfg.m_p;
@@ -639,14 +641,16 @@ int launch_pm_backward_p(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs
         CUBE2_LAUNCH_CHECK();
         r = launch_potential(ctx, 1, bc, bc, spec, s);
         if (r) return r;
+        if (extra) CUBE2_CHECK_HIP(hipStreamWaitEvent(s, ctx->ev_join, 0));
         auto *k = C.hshift == 2 ? xbar_gather_kernel<true, true, P, 2>
                                 : xbar_gather_kernel<true, true, P>;
         k<<<blocks, kGatherBlock, 0, s>>>(pos, cs, acc_bar, (int)n, ctx->n_f, nt, rf, bf, (float)gm, rc,
-                                    bc, cc, C.n, C.hshift, x_bar, accumulate);
+                                    bc, cc, C.n, C.hshift, x_bar, accumulate, extra);
     } else {
+        if (extra) CUBE2_CHECK_HIP(hipStreamWaitEvent(s, ctx->ev_join, 0));
         xbar_gather_kernel<true, false, P><<<blocks, kGatherBlock, 0, s>>>(
             pos, cs, acc_bar, (int)n, ctx->n_f, nt, rf, bf, (float)gm, nullptr, nullptr, 0.f, 1, 0,
-            x_bar, accumulate);
+            x_bar, accumulate, extra);
     }
     CUBE2_LAUNCH_CHECK();
     return CUBE2_OK;
@@ -674,10 +678,10 @@ int launch_deposit_backward(cube2_ctx *ctx, const uint16_t *pos, const uint32_t 
 
 int launch_pm_backward(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,
                        const float *acc_bar, float *x_bar, int accumulate, unsigned char *work,
-                       const WorkLayout &L, hipStream_t s) {
+                       const WorkLayout &L, const float *extra, hipStream_t s) {
     if (ctx->tsc)
-        return launch_pm_backward_p<3>(ctx, pos, cs, n, acc_bar, x_bar, accumulate, work, L, s);
-    return launch_pm_backward_p<2>(ctx, pos, cs, n, acc_bar, x_bar, accumulate, work, L, s);
+        return launch_pm_backward_p<3>(ctx, pos, cs, n, acc_bar, x_bar, accumulate, work, L, extra, s);
+    return launch_pm_backward_p<2>(ctx, pos, cs, n, acc_bar, x_bar, accumulate, work, L, extra, s);
 }
 
 }  // namespace cube2

@@ -618,9 +618,11 @@ int launch_interp64(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int
 int launch_pp64(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n, double *acc,
                 int accumulate, hipStream_t s);
 int launch_fx_to_f64(uint64_t *buf, int64_t m, double unit, hipStream_t s);
+// acc (+)= the interpolated force, + extra where that is given (3 n floats; the PP part,
+// ready once ev_join has passed)
 int launch_interp(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,
                   const float *phi_f, const float *phi_c, float *acc, int accumulate,
-                  hipStream_t s);
+                  const float *extra, hipStream_t s);
 // light_cap > 0: the PP kernels' order, with the light tiles (every box of
 // kPPLightLayers cell layers holds at most light_cap particles) last;
 // *n_heavy receives the device address of the number of the others.
@@ -689,7 +691,6 @@ int launch_vel_decode(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, i
 int launch_pp_concurrent(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,
                          const float *abar, float *acc_pp, unsigned char *work, const WorkLayout &L,
                          hipStream_t s, hipStream_t order_stream);
-int launch_add3(float *acc, const float *acc_pp, int64_t m, hipStream_t s);
 // skip (device, one byte per tile, index (tz nt + ty) nt + tx, may be NULL):
 // tiles whose own particles the kernel leaves alone
 int launch_pp(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n, float *acc,
@@ -711,7 +712,7 @@ int launch_deposit_backward(cube2_ctx *ctx, const uint16_t *pos, const uint32_t 
                             hipStream_t s);
 int launch_pm_backward(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,
                        const float *acc_bar, float *x_bar, int accumulate, unsigned char *work,
-                       const WorkLayout &L, hipStream_t s);
+                       const WorkLayout &L, const float *extra, hipStream_t s);
 int launch_pp_backward(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,
                        const float *acc_bar, float *x_bar, int accumulate, unsigned char *work,
                        const WorkLayout &L, hipStream_t s);

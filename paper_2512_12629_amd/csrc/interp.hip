@@ -118,7 +118,7 @@ template <bool TWO, int P, typename T, bool FINE, int HS, int BLOCK>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void interp_kernel(
     const uint16_t *__restrict__ pos, const uint32_t *__restrict__ cs, int n, int n_f, int nt,
     const T *__restrict__ phi_f, const T *__restrict__ phi_c, int n_c, int hshift_arg, T scale_f,
-    T scale_c, T *__restrict__ acc, int accumulate) {
+    T scale_c, T *__restrict__ acc, int accumulate, const T *__restrict__ extra) {
     constexpr int FS = InterpGeo<P>::FS, HLO = InterpGeo<P>::HLO, CSM = InterpGeo<P>::CSMAX;
     __shared__ T pf[FINE ? FS * FS * FS : 1];
     __shared__ T pc[TWO ? CSM * CSM * CSM : 1];
@@ -152,6 +152,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
     for (uint32_t pb = p0 + tid; pb < p1; pb += BLOCK * kBatch) {
         int ub[kBatch];
         uint32_t ob[kBatch][3];
+        T eb[kBatch][3];
 #pragma unroll
         for (int k = 0; k < kBatch; ++k) {
             // searched for every lane (past the end: the last particle) so
@@ -164,7 +165,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
         for (int k = 0; k < kBatch; ++k) {
             if (ub[k] < 0) continue;
 #pragma unroll
-            for (int d = 0; d < 3; ++d) ob[k][d] = pos[(int64_t)d * n + pb + k * BLOCK];
+            for (int d = 0; d < 3; ++d) {
+                ob[k][d] = pos[(int64_t)d * n + pb + k * BLOCK];
+                eb[k][d] = extra ? extra[(int64_t)d * n + pb + k * BLOCK] : T(0);
+            }
         }
 #pragma unroll
         for (int k = 0; k < kBatch; ++k) {
@@ -236,7 +240,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
                 T *dst = acc + (int64_t)d * n + p;
-                *dst = accumulate ? *dst + a[d] : a[d];
+                const T v = accumulate ? *dst + a[d] : a[d];
+                *dst = extra ? v + eb[k][d] : v;
             }
         }
     }
@@ -247,22 +252,22 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
 template <int P, typename T, int BLOCK>
 void launch_interp_block(cube2_ctx *ctx, unsigned blocks, const uint16_t *pos, const uint32_t *cs,
                          int64_t n, const T *phi_f, const T *phi_c, double gm, T *acc,
-                         int accumulate, bool fine, bool coarse, hipStream_t s) {
+                         int accumulate, const T *extra, bool fine, bool coarse, hipStream_t s) {
     const int nt = ctx->nt;
     if (coarse && !fine) {
         const Level &C = ctx->lv[1];
         interp_kernel<true, P, T, false, 0, BLOCK><<<blocks, BLOCK, 0, s>>>(
             pos, cs, (int)n, ctx->n_f, nt, nullptr, phi_c, C.n, C.hshift, T(0),
-            (T)(gm / ((double)C.H * C.H)), acc, accumulate);
+            (T)(gm / ((double)C.H * C.H)), acc, accumulate, extra);
     } else if (coarse) {
         const Level &C = ctx->lv[1];
         auto *k = C.hshift == 2 ? interp_kernel<true, P, T, true, 2, BLOCK>
                                 : interp_kernel<true, P, T, true, 0, BLOCK>;
         k<<<blocks, BLOCK, 0, s>>>(pos, cs, (int)n, ctx->n_f, nt, phi_f, phi_c, C.n, C.hshift,
-                                   (T)gm, (T)(gm / ((double)C.H * C.H)), acc, accumulate);
+                                   (T)gm, (T)(gm / ((double)C.H * C.H)), acc, accumulate, extra);
     } else {
         interp_kernel<false, P, T, true, 0, BLOCK><<<blocks, BLOCK, 0, s>>>(
-            pos, cs, (int)n, ctx->n_f, nt, phi_f, nullptr, 1, 0, (T)gm, T(0), acc, accumulate);
+            pos, cs, (int)n, ctx->n_f, nt, phi_f, nullptr, 1, 0, (T)gm, T(0), acc, accumulate, extra);
     }
 }
 
@@ -279,46 +284,46 @@ constexpr int kSmallTiles = 512;
 template <int P, typename T>
 void launch_interp_kernel(cube2_ctx *ctx, unsigned blocks, const uint16_t *pos, const uint32_t *cs,
                           int64_t n, const T *phi_f, const T *phi_c, double gm, T *acc,
-                          int accumulate, int levels, hipStream_t s) {
+                          int accumulate, const T *extra, int levels, hipStream_t s) {
     const bool fine = (levels & 1) != 0, coarse = ctx->n_levels > 1 && (levels & 2) != 0;
     auto *launch = launch_interp_block<P, T, sizeof(T) == 4 && P == 3 ? 512 : kBlock>;
     if (sizeof(T) == 4 && blocks <= kSmallTiles) launch = launch_interp_block<P, T, sizeof(T) == 4 ? 512 : kBlock>;
-    launch(ctx, blocks, pos, cs, n, phi_f, phi_c, gm, acc, accumulate, fine, coarse, s);
+    launch(ctx, blocks, pos, cs, n, phi_f, phi_c, gm, acc, accumulate, extra, fine, coarse, s);
 }
 
 template <typename T>
 int interp_levels(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,
-                  const T *phi_f, const T *phi_c, T *acc, int accumulate, int levels,
+                  const T *phi_f, const T *phi_c, T *acc, int accumulate, const T *extra, int levels,
                   hipStream_t s) {
     const int nt = ctx->nt;
     const unsigned blocks = (unsigned)(nt * nt * nt);
     const double gm = ctx->cfg.g_newton * ctx->cfg.m_p;
     if (ctx->tsc)
         launch_interp_kernel<3, T>(ctx, blocks, pos, cs, n, phi_f, phi_c, gm, acc, accumulate,
-                                   levels, s);
+                                   extra, levels, s);
     else
         launch_interp_kernel<2, T>(ctx, blocks, pos, cs, n, phi_f, phi_c, gm, acc, accumulate,
-                                   levels, s);
+                                   extra, levels, s);
     CUBE2_LAUNCH_CHECK();
     return CUBE2_OK;
 }
 
 int launch_interp(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,
                   const float *phi_f, const float *phi_c, float *acc, int accumulate,
-                  hipStream_t s) {
-    return interp_levels<float>(ctx, pos, cs, n, phi_f, phi_c, acc, accumulate, 3, s);
+                  const float *extra, hipStream_t s) {
+    return interp_levels<float>(ctx, pos, cs, n, phi_f, phi_c, acc, accumulate, extra, 3, s);
 }
 
 int launch_interp_levels(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,
                          const float *phi_f, const float *phi_c, float *acc, int accumulate,
                          int levels, hipStream_t s) {
-    return interp_levels<float>(ctx, pos, cs, n, phi_f, phi_c, acc, accumulate, levels, s);
+    return interp_levels<float>(ctx, pos, cs, n, phi_f, phi_c, acc, accumulate, nullptr, levels, s);
 }
 
 int launch_interp64(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,
                     const double *phi_f, const double *phi_c, double *acc, int accumulate,
                     hipStream_t s) {
-    return interp_levels<double>(ctx, pos, cs, n, phi_f, phi_c, acc, accumulate, 3, s);
+    return interp_levels<double>(ctx, pos, cs, n, phi_f, phi_c, acc, accumulate, nullptr, 3, s);
 }
 
 }  // namespace cube2
