@@ -58,30 +58,52 @@ __global__ void region_count_kernel(const uint32_t *__restrict__ cs, Region g, i
 // kCellLanes lanes per region cell: its particles go to out[offs[r] ...] with the
 // positions of their slot, (slot R + cell) << 16 | offset, over n_box 2^15,
 // exact in FP32 for n_box <= 512.  A wave per cell left 63 of 64 lanes idle at
-// one particle per cell (262144 cells: 89 us).
-constexpr int kCellLanes = 4;
+// one particle per cell (262144 cells: 89 us).  Cells of more than kCellMany
+// particles are then taken by the whole wave, one after another: the four lanes'
+// serial chain through a halo's densest cell was all of the kernel's time there
+// (2.1 million particles in 60 halos, 64^3 cells: 72 us; this: 18).
+constexpr int kCellLanes = 4, kCellMany = 64;
 __global__ __launch_bounds__(kBlock) void region_write_kernel(
     const uint16_t *__restrict__ pos, const uint32_t *__restrict__ cs, int n, Region g,
     int64_t cells, const uint32_t *__restrict__ offs, float inv_span, float *__restrict__ x_local,
     int32_t *__restrict__ idx, int64_t m) {
     const int64_t r = (int64_t)blockIdx.x * (kBlock / kCellLanes) + threadIdx.x / kCellLanes;
-    if (r >= cells) return;
-    const int lane = threadIdx.x % kCellLanes;
-    int c[3], t;
-    const uint32_t key = region_key(r, g, c, t);
-    const int sl[3] = {t % g.k, (t / g.k) % g.k, t / (g.k * g.k)};
-    const uint32_t b = cs[key], e = cs[key + 1], o0 = offs[r];
-#pragma unroll 4
-    for (uint32_t p = b + (uint32_t)lane; p < e; p += kCellLanes) {
-        const int64_t o = (int64_t)o0 + (p - b);
-        if (o >= m) break;
+    int q[3] = {0, 0, 0};      // the cell in the packed box
+    uint32_t b = 0, cnt = 0, o0 = 0;
+    if (r < cells) {
+        int c[3], t;
+        const uint32_t key = region_key(r, g, c, t);
+        const int sl[3] = {t % g.k, (t / g.k) % g.k, t / (g.k * g.k)};
+        b = cs[key];
+        cnt = cs[key + 1] - b;
+        o0 = offs[r];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            const uint32_t cell = (uint32_t)(sl[d] * g.R + c[d]);
-            const uint32_t rel = (cell << 16) | (uint32_t)pos[(int64_t)d * n + p];
-            x_local[(int64_t)d * m + o] = (float)rel * inv_span;
+        for (int d = 0; d < 3; ++d) q[d] = sl[d] * g.R + c[d];
+    }
+    auto copy = [&](uint32_t first, uint32_t count, uint32_t out, int qx, int qy, int qz, int at,
+                    int step) {
+        const int cell[3] = {qx, qy, qz};
+#pragma unroll 4
+        for (uint32_t i = (uint32_t)at; i < count; i += (uint32_t)step) {
+            const int64_t o = (int64_t)out + i;
+            if (o >= m) break;
+            const uint32_t p = first + i;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const uint32_t rel = ((uint32_t)cell[d] << 16) | (uint32_t)pos[(int64_t)d * n + p];
+                x_local[(int64_t)d * m + o] = (float)rel * inv_span;
+            }
+            idx[o] = (int32_t)p;
         }
-        idx[o] = (int32_t)p;
+    };
+    const int sub = threadIdx.x % kCellLanes, lane = threadIdx.x & 63;
+    const bool many = cnt > (uint32_t)kCellMany;
+    if (!many) copy(b, cnt, o0, q[0], q[1], q[2], sub, kCellLanes);
+    for (unsigned long long left = __ballot(many && sub == 0); left; left &= left - 1) {
+        const int l = first_lane(left);
+        auto of = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); };
+        copy(of(b), of(cnt), of(o0), (int)of((uint32_t)q[0]), (int)of((uint32_t)q[1]),
+             (int)of((uint32_t)q[2]), lane, 64);
     }
 }
 
