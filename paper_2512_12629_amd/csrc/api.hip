@@ -674,22 +674,15 @@ int cube2_pm_force_f64(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cell
     CHECK_WORK(n);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const bool two = ctx->n_levels > 1;
-    // the deposit writes its FP32 density into the FP32 scratch meshes and the
-    // exact accumulators into the FP64 meshes, converted there in place
-    float *rf = reinterpret_cast<float *>(work_ + L_.real_f);
-    float *rc = two ? reinterpret_cast<float *>(work_ + L_.real_c) : nullptr;
+    // the deposit writes the FP64 density (the exact accumulator times its unit)
     uint64_t *ff = reinterpret_cast<uint64_t *>(work_ + L_.real64_f);
     uint64_t *fc = two ? reinterpret_cast<uint64_t *>(work_ + L_.real64_c) : nullptr;
     double2 *spec = reinterpret_cast<double2 *>(work_ + L_.spec64);
-    int rcode = launch_deposit(ctx, pos, cell_start, n, rf, ff, rc, fc, work_, L_, s);
+    int rcode = launch_deposit(ctx, pos, cell_start, n, nullptr, ff, nullptr, fc, work_, L_, s, true);
     if (rcode) return rcode;
     for (int l = 0; l < ctx->n_levels; ++l) {
-        uint64_t *m = l == 0 ? ff : fc;
-        const int64_t nl = ctx->lv[l].n;
-        rcode = launch_fx_to_f64(m, nl * nl * nl, ctx->tsc ? 0x1p-48 : 0x1p-45, s);
-        if (rcode) return rcode;
-        double *md = reinterpret_cast<double *>(m);
-        rcode = launch_potential64(ctx, l, md, md, spec, s);
+        double *m = reinterpret_cast<double *>(l == 0 ? ff : fc);
+        rcode = launch_potential64(ctx, l, m, m, spec, s);
         if (rcode) return rcode;
     }
     if (n == 0) return CUBE2_OK;

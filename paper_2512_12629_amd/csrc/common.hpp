@@ -603,9 +603,10 @@ int launch_sort_by_cell(cube2_ctx *ctx, int64_t n, uint16_t *pos, uint32_t *cell
                         const float *vel = nullptr, const float *acc = nullptr, double kick = 0.0,
                         float *vel_out = nullptr, const uint32_t *run = nullptr,
                         bool counted = false);
+// as_f64: rho_f_fx and rho_c_fx receive the FP64 density instead of the integers
 int launch_deposit(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,
                    float *rho_f, uint64_t *rho_f_fx, float *rho_c, uint64_t *rho_c_fx,
-                   unsigned char *work, const WorkLayout &L, hipStream_t s);
+                   unsigned char *work, const WorkLayout &L, hipStream_t s, bool as_f64 = false);
 int launch_green(cube2_ctx *ctx, hipStream_t s);
 int launch_fft_r2c(cube2_ctx *ctx, int level, const float *mesh, float2 *spec, hipStream_t s);
 int launch_potential(cube2_ctx *ctx, int level, const float *rho, float *phi, float2 *spec,
@@ -617,7 +618,6 @@ int launch_interp64(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int
                     hipStream_t s);
 int launch_pp64(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n, double *acc,
                 int accumulate, hipStream_t s);
-int launch_fx_to_f64(uint64_t *buf, int64_t m, double unit, hipStream_t s);
 // acc (+)= the interpolated force, + extra where that is given (3 n floats; the PP part,
 // ready once ev_join has passed)
 int launch_interp(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,

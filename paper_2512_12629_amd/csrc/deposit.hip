@@ -51,6 +51,11 @@ __device__ __forceinline__ void tsc_weights(int m, uint32_t (&w)[3]) {
     w[1] = 65536u - w[0] - w[2];
 }
 
+// What the integer meshes receive: the accumulator, or, with a unit, its FP64 density
+__device__ __forceinline__ unsigned long long fx_word(unsigned long long v, double unit) {
+    return unit != 0.0 ? (unsigned long long)__double_as_longlong((double)v * unit) : v;
+}
+
 __global__ void fill_u64(unsigned long long *p, int64_t n) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0ull;
@@ -210,7 +215,7 @@ __global__ __launch_bounds__(kBlock) void deposit_kernel(
     const uint16_t *__restrict__ pos, const uint32_t *__restrict__ cs, int n, int n_f, int nt,
     float *__restrict__ rho_f, unsigned long long *__restrict__ rho_f_fx,
     unsigned long long *__restrict__ coarse_acc, int n_c, int hshift, uint32_t *status,
-    const uint32_t *__restrict__ order, uint32_t *__restrict__ queue) {
+    const uint32_t *__restrict__ order, uint32_t *__restrict__ queue, double fx_unit) {
     using Geo = DepGeo<P, CR>;
     using List = BoxList<Geo::SEGS, kBlock>;
     constexpr int kBox = Geo::BOX, kSegs = Geo::SEGS;
@@ -356,8 +361,9 @@ __global__ __launch_bounds__(kBlock) void deposit_kernel(
                 const unsigned long long v = acc_f[i];
                 // streaming store: a tile row is half a cache line, and the
                 // mesh is read back only by the next kernel
-                __builtin_nontemporal_store((float)v * (P == 3 ? 0x1p-48f : 0x1p-45f), &rho_f[g]);
-                if (rho_f_fx) rho_f_fx[g] = v;
+                if (rho_f)
+                    __builtin_nontemporal_store((float)v * (P == 3 ? 0x1p-48f : 0x1p-45f), &rho_f[g]);
+                if (rho_f_fx) rho_f_fx[g] = fx_word(v, fx_unit);
             }
         }
         if (COARSE) {
@@ -380,48 +386,49 @@ __global__ __launch_bounds__(kBlock) void deposit_kernel(
 
 __global__ void coarse_finalize(const unsigned long long *__restrict__ accum, int64_t m,
                                 float *__restrict__ rho, unsigned long long *__restrict__ fx,
-                                float unit) {
+                                float unit, double fx_unit) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= m) return;
     const unsigned long long v = accum[i];
-    rho[i] = (float)v * unit;
-    if (fx) fx[i] = v;
+    if (rho) rho[i] = (float)v * unit;
+    if (fx) fx[i] = fx_word(v, fx_unit);
 }
 
 template <bool FINE, bool COARSE, int P, int CR>
 void launch_one_deposit(const uint16_t *pos, const uint32_t *cs, int64_t n, int n_f, int nt,
                         float *rho_f, unsigned long long *ffx, unsigned long long *cacc, int n_c,
                         int hshift, uint32_t *status, const uint32_t *order, uint32_t *queue,
-                        int ntiles, hipStream_t s) {
+                        int ntiles, double fx_unit, hipStream_t s) {
     auto k = deposit_kernel<FINE, COARSE, P, CR>;
     k<<<persistent_grid(k, kBlock, ntiles), kBlock, 0, s>>>(pos, cs, (int)n, n_f, nt, rho_f, ffx, cacc,
-                                                          n_c, hshift, status, order, queue);
+                                                          n_c, hshift, status, order, queue, fx_unit);
 }
 
 template <int P>
 int launch_deposit_kernels(bool fine, bool coarse, const uint16_t *pos, const uint32_t *cs, int64_t n,
                            int n_f, int nt, float *rho_f, unsigned long long *ffx,
                            unsigned long long *cacc, int n_c, int hshift, uint32_t *status,
-                           const uint32_t *order, uint32_t *queue, int ntiles, hipStream_t s) {
+                           const uint32_t *order, uint32_t *queue, int ntiles, double fx_unit,
+                           hipStream_t s) {
     if (coarse && (kTileFine >> hshift) + (P == 3 ? 3 : 1) > DepGeo<P, 2>::CMAX) return CUBE2_EINVAL;
     const bool r2 = hshift < 2;  // coarse ratio 2: the wider footprint
     if (fine && coarse) {
         if (r2)
             launch_one_deposit<true, true, P, 2>(pos, cs, n, n_f, nt, rho_f, ffx, cacc, n_c, hshift,
-                                                 status, order, queue, ntiles, s);
+                                                 status, order, queue, ntiles, fx_unit, s);
         else
             launch_one_deposit<true, true, P, 4>(pos, cs, n, n_f, nt, rho_f, ffx, cacc, n_c, hshift,
-                                                 status, order, queue, ntiles, s);
+                                                 status, order, queue, ntiles, fx_unit, s);
     } else if (fine) {
         launch_one_deposit<true, false, P, 4>(pos, cs, n, n_f, nt, rho_f, ffx, cacc, n_c, hshift,
-                                              status, order, queue, ntiles, s);
+                                              status, order, queue, ntiles, fx_unit, s);
     } else {
         if (r2)
             launch_one_deposit<false, true, P, 2>(pos, cs, n, n_f, nt, nullptr, nullptr, cacc, n_c,
-                                                  hshift, status, order, queue, ntiles, s);
+                                                  hshift, status, order, queue, ntiles, fx_unit, s);
         else
             launch_one_deposit<false, true, P, 4>(pos, cs, n, n_f, nt, nullptr, nullptr, cacc, n_c,
-                                                  hshift, status, order, queue, ntiles, s);
+                                                  hshift, status, order, queue, ntiles, fx_unit, s);
     }
     CUBE2_LAUNCH_CHECK();
     return CUBE2_OK;
@@ -431,12 +438,13 @@ int launch_deposit_kernels(bool fine, bool coarse, const uint16_t *pos, const ui
 
 int launch_deposit(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,
                    float *rho_f, uint64_t *rho_f_fx, float *rho_c, uint64_t *rho_c_fx,
-                   unsigned char *work, const WorkLayout &L, hipStream_t s) {
+                   unsigned char *work, const WorkLayout &L, hipStream_t s, bool as_f64) {
+    const double fx_unit = as_f64 ? (ctx->tsc ? 0x1p-48 : 0x1p-45) : 0.0;
     const int nt = ctx->nt;
     const unsigned blocks = (unsigned)(nt * nt * nt);
     uint32_t *status = status_word(ctx);
-    const bool coarse = rho_c != nullptr && ctx->n_levels > 1;
-    const bool fine = rho_f != nullptr;
+    const bool coarse = (rho_c || (as_f64 && rho_c_fx)) && ctx->n_levels > 1;
+    const bool fine = rho_f || (as_f64 && rho_f_fx);
     auto *cacc = reinterpret_cast<unsigned long long *>(work + L.coarse_acc);
     const int n_c = coarse ? ctx->lv[1].n : 1;
     const int hshift = coarse ? ctx->lv[1].hshift : 0;
@@ -455,15 +463,15 @@ int launch_deposit(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int6
     const int ntiles = (int)blocks;
     if (ctx->tsc)
         r = launch_deposit_kernels<3>(fine, coarse, pos, cs, n, ctx->n_f, nt, rho_f, ffx, cacc, n_c,
-                                      hshift, status, order, queue, ntiles, s);
+                                      hshift, status, order, queue, ntiles, fx_unit, s);
     else
         r = launch_deposit_kernels<2>(fine, coarse, pos, cs, n, ctx->n_f, nt, rho_f, ffx, cacc, n_c,
-                                      hshift, status, order, queue, ntiles, s);
+                                      hshift, status, order, queue, ntiles, fx_unit, s);
     if (r) return r;
     if (coarse) {
         coarse_finalize<<<(unsigned)((mc + 255) / 256), 256, 0, s>>>(
             cacc, mc, rho_c, reinterpret_cast<unsigned long long *>(rho_c_fx),
-            ctx->tsc ? 0x1p-48f : 0x1p-45f);
+            ctx->tsc ? 0x1p-48f : 0x1p-45f, fx_unit);
         CUBE2_LAUNCH_CHECK();
     }
     return CUBE2_OK;

@@ -95,3 +95,24 @@ def test_gather_of_dense_cells(counts):
     want = order[inside[order]]
     assert np.array_equal(idx, want)
     assert np.array_equal(got, (rel[:, want] / float(32 << 15)).astype(np.float32))
+
+
+@pytest.mark.parametrize("b_fine,b_pp", [(2.0, 0.2), (3.5, 0.0625)])
+@pytest.mark.parametrize("counts,around", [((1,), 0), ((2, 0, 511), 0), ((4096,), 1), ((4097, 600), 3000)])
+def test_pp_force_f64_spans(counts, around, b_fine, b_pp):
+    """The FP64 PP force, whose box is staged in the same spans, against the oracle's
+    (both FP64: the bars of the FP64 form's own tests)."""
+    import paper_2512_12629_amd as m
+    rng = np.random.default_rng(sum(counts))
+    x = _cells(rng, counts, around)
+    c = m.Cube2(m.Config(n_fine=128, b_fine=b_fine, b_pp=b_pp, flags=m.CUBE2_FP64_FORM),
+                n_max=x.shape[1])
+    pos, cs, _ = c.pack(torch.from_numpy(x).cuda())
+    xf = ios_decode(pos.cpu().numpy().view(np.uint16), cs.cpu().numpy().view(np.uint32), 128) / 2.0 ** 15
+    got = c.pp_force_f64(pos, cs).cpu().numpy()
+    ref = oracle.Oracle(oracle.Params(n_fine=128, b_fine=b_fine, b_pp=b_pp)).pp_accel(xf)
+    has = np.linalg.norm(ref, axis=0) > 0
+    assert np.all(got[:, ~has] == 0)
+    if has.any():
+        med, p99 = _stats(got, ref)
+        assert med < 1e-12 and p99 < 1e-10, (med, p99)
