@@ -20,6 +20,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <utility>
 
 #include "common.hpp"
 
@@ -247,13 +248,25 @@ __device__ __forceinline__ float quad_sum(float v) {
 // order.  (Splitting four tiles per workgroup was slower: every part
 // stages the box again.)
 //
-// Where the heavy tiles are so few that a workgroup gets at most two of them, all
-// are split, into parts of a quarter of a block: four lanes share a particle,
-// each taking every fourth neighbour, and their sums are added per range.  A part
-// of whole blocks would leave a CU to 8 or 16 waves whose pair loops wait on
-// the LDS (one halo of 2048 particles in a box alone: 276 us).
+// Where the heavy tiles are few, all are split: a workgroup gets so few that the heaviest
+// ends the kernel alone.  Up to kFewTiles of them, into parts of a quarter of a
+// block: four lanes share a particle, each taking every fourth neighbour, and their
+// sums are added per range (parts of whole blocks would leave a CU to 8 or 16 waves
+// whose pair loops wait on the LDS).  Up to kBlockTiles, into whole blocks, which
+// stage the box a quarter as often.  Beyond, only the heaviest kSplitTiles.  Measured
+// (us: quarters, blocks, the heaviest alone):
+//   forward, one-cell reach: 256^3 cells with 40, 400, 1000 halos (tiles up to 10^2, 10^3,
+//   2 10^3) 265 516 454, 1121 1198 2143, 2359 2285 3101; 512^3 with 300, 1000 (with
+//   256^3 particles) 1337 1257 1716, 3292 3090 2866.  Adjoint: 343 745 729, 1629 1822
+//   2011, 3497 3692 3550; 1987 2074 2036, 5100 5340 4725.
+//   forward, two-cell reach: 256^3 with 80, 400 halos 482 468 437, 938 834 877; 512^3
+//   with 300 2553 2423 2398.  Adjoint: 794 774 763, 1469 1429 1325; 4954 4935 4858.
 constexpr int kSplitParts = 8, kSplitTiles = 128;
-constexpr int kFewTiles = 4096, kFewParts = 32, kFewLanes = 4;
+constexpr int kFewParts = 32, kFewLanes = 4, kSplitAllTiles = 4096;
+template <bool ADJ, int H> struct PPSplit {
+    static constexpr int kFewTiles = H == 1 ? (ADJ ? 2048 : 1024) : 0;
+    static constexpr int kBlockTiles = ADJ ? 0 : (H == 1 ? 2048 : kSplitAllTiles);
+};
 
 // The pair law's units (see above): ps = 2^j and its product with the 2^-15 of
 // a position unit, the scale of the sums (unit, and for the forward D's
@@ -296,6 +309,59 @@ __device__ __forceinline__ void light_row(const unsigned char *base, uint32_t v0
         if (v0 < v1) pair_accumulate<CLAMP>(x[v0] - xi, y[v0] - yi, z[v0] - zi, kPairS0, bmax, fx, fy, fz);
     }
 }
+
+// The ranges of a particle's neighbour rows, length << 16 | start, longest first
+// (merge exchange, Knuth vol. 3, 5.2.2 M: 26 comparators for 9 rows, two instructions
+// each).  All lanes of a wave go through their rows together, so that a wave's trips are
+// the sum over the rows of the longest of its lanes'.  Rows in the order of the cells give
+// nine times the densest row to a wave of sparse cells around a halo, where each
+// lane meets the halo in another row; longest first, every lane meets it at once
+// (512^3 particles with 8000 halos: 25.1 -> 21.9 ms, adjoint 43.8 -> 35.8; two-cell
+// reach, 201^3 with 300: 3.52 -> 2.57 ms).  The light tiles' rows are short and
+// alike: there it gained nothing (103 us for 128^3 particles, 106 sorted).
+template <int N> struct RowSort {
+    struct Pair { int i, j; };
+    static constexpr int MAX = N * N;
+    struct Net { Pair p[MAX]; int n; };
+    static constexpr Net make() {
+        Net net{};
+        int top = 1;
+        while (2 * top < N) top *= 2;
+        for (int p = top; p > 0; p /= 2) {
+            int q = top, r = 0, d = p;
+            for (;;) {
+                for (int i = 0; i < N - d; ++i)
+                    if ((i & p) == r) net.p[net.n++] = Pair{i, i + d};
+                if (q == p) break;
+                d = q - p;
+                q /= 2;
+                r = p;
+            }
+        }
+        return net;
+    }
+    static constexpr Net net = make();
+    template <int... K>
+    static __device__ __forceinline__ void run(uint32_t (&a)[N], std::integer_sequence<int, K...>) {
+        auto step = [&](int i, int j) {
+            const uint32_t x = a[i], y = a[j];
+            a[i] = max(x, y);
+            a[j] = min(x, y);
+        };
+        (step(net.p[K].i, net.p[K].j), ...);
+    }
+    static __device__ __forceinline__ void sort(uint32_t (&a)[N]) {
+        run(a, std::make_integer_sequence<int, net.n>{});
+    }
+    // the next row: the first of a, and the others move up
+    static __device__ __forceinline__ uint32_t next(uint32_t (&a)[N]) {
+        const uint32_t x = a[0];
+#pragma unroll
+        for (int k = 0; k + 1 < N; ++k) a[k] = a[k + 1];
+        a[N - 1] = 0u;
+        return x;
+    }
+};
 
 // LDS stores of this wave are visible to its own later loads (the LDS serves
 // a wave in order; this keeps the compiler from reordering them).
@@ -567,9 +633,10 @@ __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK), 4) void pp_kernel(const uin
     // n_heavy: the tiles that are not light; only the one-cell reach takes the light
     // ones by waves
     const int nbig = (int)*n_heavy, nheavy = H == 1 ? nbig : ntiles;
-    const bool few = nbig <= kFewTiles;
-    const int kParts = few ? kFewParts : kSplitParts;
-    const int nsplit = few ? nbig : min(kSplitTiles, nbig);
+    const bool few = nbig <= PPSplit<ADJ, H>::kFewTiles;
+    const bool all = few || nbig <= PPSplit<ADJ, H>::kBlockTiles;
+    const int kParts = all ? kFewParts : kSplitParts;
+    const int nsplit = all ? nbig : min(kSplitTiles, nbig);
     const int nitems = nheavy + nsplit * (kParts - 1);
     const int split_items = nsplit * kParts;
     int next = 0;
@@ -771,11 +838,19 @@ __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK), 4) void pp_kernel(const uin
                 }
                 // the 2H + 1 x-neighbours of a cell are consecutive box segments, so the
                 // neighbour cells are (2H + 1)^2 contiguous ranges of xs
+                uint32_t rows[kW * kW];
+#pragma unroll
                 for (int row = 0; row < kW * kW; ++row) {
-                    const int oy = row % kW - H, oz = row / kW - H;
-                    const int sm = ((bz + oz) * kPB + (by + oy)) * kPB + bx;
+                    const int sm = su + ((row / kW - H) * kPB + row % kW - H) * kPB;
                     const uint32_t r0 = max(seg_pre[sm - H], vb), r1 = min(seg_pre[sm + H + 1], ve);
-                    const uint32_t v0 = r0 - vb, v1 = max(r0, r1) - vb;
+                    rows[row] = r1 > r0 ? (r1 - r0) << 16 | (r0 - vb) : 0u;
+                }
+                RowSort<kW * kW>::sort(rows);
+#pragma unroll 1
+                for (int row = 0; row < kW * kW; ++row) {
+                    const uint32_t key = RowSort<kW * kW>::next(rows);
+                    if (!__any(key >= 0x10000u)) break;
+                    const uint32_t v0 = key & 0xFFFFu, v1 = v0 + (key >> 16);
                     float fx = 0.f, fy = 0.f, fz = 0.f;
                     if (lanes == 1)
                         staged_pairs<ADJ, CLAMP, 1>(xs, xa, v0, v1, xi, yi, zi, aix, aiy, aiz, bmax, fx,
@@ -1063,7 +1138,7 @@ int launch_pp_kernel_h(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, 
     const uint32_t *order = tile_order_ptr(work, L);
     uint32_t *queue = tile_queue_ptr(ctx, work, L);
     auto k = pp_kernel<ADJ, H, CLAMP>;
-    const int nitems = ntiles + std::min(ntiles, kFewTiles) * (kFewParts - 1);   // at most
+    const int nitems = ntiles + std::min(ntiles, kSplitAllTiles) * (kFewParts - 1);   // at most
     // one z-layer of cells per light item where there are few of them
     const int layers = ntiles <= kOneLayerTiles ? 1 : PPLight<ADJ>::LAYERS;
     const unsigned grid = std::max(
