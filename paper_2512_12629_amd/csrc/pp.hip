@@ -1169,25 +1169,17 @@ int launch_pp_kernel(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, in
 
 // Share of the persistent PP grid when the PM force runs beside it: the PM
 // kernels take the freed workgroup slots, and the memory-bound PM and the
-// VALU- and LDS-bound PP then overlap on the same CUs.  Measured (all of the
-// grid, 7/8, 3/4, 5/8, 1/2): 512^3 particles 42.5, 41.3, 39.1, 40.5, 48.5 ms;
-// 256^3 with 1000 halos 5.44, 5.33, 4.97, 5.27, 6.26 ms; two-cell reach, 201^3
-// with 300 halos 5.88, 5.95, 5.74, 6.04, 7.58 ms.
-constexpr float kPPConcurrentFrac = 0.75f;
-// meshes of fewer tiles per axis take other shares of the adjoint's grid
-constexpr int kPPConcurrentSmallNt = 64;
-// The same for the PP adjoint beside the PM adjoint (1024-thread workgroups,
-// one per CU): measured on 512^3 particles, 5/8 of the CUs gave the shortest
-// force adjoint (106.0 ms; 3/4 107.6, 7/8 106.7, all 110.5, 9/16 110.6).
-constexpr float kPPAdjConcurrentFrac = 0.625f;
-// ... and on meshes of fewer than 64^3 tiles, 7/8 (measured on 256^3
-// particles: force adjoint 14.2 ms, against 14.3 with the whole grid and
-// 17.6 at 5/8).
-constexpr float kPPAdjConcurrentFracSmall = 0.875f;
-// ... and with the two-cell reach, 7/8 (measured at b_f = 3.5 on 512^3
-// particles: 212.5 ms, against 214.9 with the full grid, 280.0 at 5/8 and
-// 226.7 with PM and PP adjoints one after the other).
-constexpr float kPPAdjConcurrentFracH2 = 0.875f;
+// VALU- and LDS-bound PP then overlap on the same CUs.  Measured with PM, ms at
+// 5/8, 3/4, 7/8 and all of the grid (workgroups of 512 threads, two per CU; the
+// adjoint's of 1024, one per CU):
+//   one-cell reach: 512^3 particles with 8000 halos 36.6 35.7 37.2 38.0, 256^3 with
+//   1000 4.85 4.51 4.86 4.94; adjoint 73.3 74.5 75.3 75.8, 9.47 9.60 9.68 9.82, and
+//   128^3 without halos 0.631 0.641 0.656 0.660
+//   two-cell reach, the same: 63.6 55.2 52.8 55.7, 8.58 7.41 6.88 7.26; adjoint 119.2
+//   105.1 108.8 109.1, 15.5 13.5 13.8 14.0
+template <bool ADJ> constexpr float concurrent_frac(int halo) {
+    return ADJ ? (halo == 1 ? 0.625f : 0.75f) : (halo == 1 ? 0.75f : 0.875f);
+}
 
 }  // namespace
 
@@ -1203,14 +1195,11 @@ int launch_pp_concurrent(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs
     Lpp.tile_order = L.pp_order;
     Lpp.hist = L.pp_hist;
     Lpp.scan_tmp = L.pp_scan;
-    const bool small = ctx->nt < kPPConcurrentSmallNt;
     if (abar)
         return launch_pp_kernel<true>(ctx, pos, cs, n, abar, acc_pp, 0, work, Lpp, s, order_stream,
-                                      ctx->pp_halo != 1 ? kPPAdjConcurrentFracH2
-                                      : small           ? kPPAdjConcurrentFracSmall
-                                                        : kPPAdjConcurrentFrac);
+                                      concurrent_frac<true>(ctx->pp_halo));
     return launch_pp_kernel<false>(ctx, pos, cs, n, nullptr, acc_pp, 0, work, Lpp, s, order_stream,
-                                   kPPConcurrentFrac);
+                                   concurrent_frac<false>(ctx->pp_halo));
 }
 
 int launch_pp(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n, float *acc,
