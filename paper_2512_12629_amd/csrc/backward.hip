@@ -412,15 +412,14 @@ __global__ void divergence_kernel(const unsigned long long *__restrict__ A, int 
 //   T = c (abar . E) + rhobar   (PM adjoint)   or   T = rhobar (deposit adjoint)
 // ---------------------------------------------------------------------------
 
-// Staged tiles per level (side S, first node o below the tile origin): the
-// potential with the stencil halo and the rhobar nodes of the footprints.
+// The staged tile of the fine level: the potential with the stencil halo and the
+// rhobar nodes of the footprints.
 template <int P> struct GatherGeo {
     static constexpr int PLO = P == 3 ? 3 : 2;   // potential: nodes from -PLO
     static constexpr int PX = P == 3 ? 7 : 5;    // potential side = tile nodes + PX
     static constexpr int RLO = P == 3 ? 1 : 0;   // rhobar: nodes from -RLO
     static constexpr int RX = P == 3 ? 3 : 1;    // rhobar side = tile nodes + RX
     static constexpr int FS = kTileFine + PX, RS = kTileFine + RX;
-    static constexpr int CSMAX = kTileFine / 2 + PX, CRMAX = kTileFine / 2 + RX;
 };
 
 __device__ __forceinline__ float fd_at(const float *P, int idx, int st) {
@@ -458,6 +457,33 @@ __device__ __forceinline__ void level_gather(const float *Pt, int S, const float
     xb[2] += g[2] * invH;
 }
 
+// the same for the coarse level: its force and rhobar staged per node (F, side S)
+template <int P>
+__device__ __forceinline__ void field_gather(const Vec4<float> *F, int S, const int (&j)[3],
+                                             const float (&w)[3][P], const float (&dw)[3][P],
+                                             const float (&ab)[3], float c, float invH,
+                                             float (&xb)[3]) {
+    float g[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+    for (int sz = 0; sz < P; ++sz)
+#pragma unroll
+        for (int sy = 0; sy < P; ++sy) {
+            const Vec4<float> *row = F + ((j[2] + sz + coarse_field_lo<P>()) * S + j[1] + sy +
+                                          coarse_field_lo<P>()) * S + j[0] + coarse_field_lo<P>();
+#pragma unroll
+            for (int sx = 0; sx < P; ++sx) {
+                const Vec4<float> e = row[sx];
+                const float T = e.w + c * (ab[0] * e.x + ab[1] * e.y + ab[2] * e.z);
+                g[0] += dw[0][sx] * w[1][sy] * w[2][sz] * T;
+                g[1] += dw[1][sy] * w[0][sx] * w[2][sz] * T;
+                g[2] += dw[2][sz] * w[0][sx] * w[1][sy] * T;
+            }
+        }
+    xb[0] += g[0] * invH;
+    xb[1] += g[1] * invH;
+    xb[2] += g[2] * invH;
+}
+
 // weights, slopes and first footprint node of one axis from the 15-bit
 // fraction f of the level coordinate whose cell is j
 template <int P>
@@ -490,11 +516,10 @@ __global__ __launch_bounds__(kGatherBlock) void xbar_gather_kernel(
     int accumulate, const float *__restrict__ extra) {
     const int hshift = HS > 0 ? HS : hshift_arg;
     using G = GatherGeo<P>;
-    constexpr int kFS = G::FS, kRS = G::RS, kCSMax = G::CSMAX, kCRMax = G::CRMAX;
+    constexpr int kFS = G::FS, kRS = G::RS, kCMax = coarse_field_max<P, HS>();
     __shared__ float pf[WITH_E ? kFS * kFS * kFS : 1];
     __shared__ float rf[kRS * kRS * kRS];
-    __shared__ float pc[(WITH_E && TWO) ? kCSMax * kCSMax * kCSMax : 1];
-    __shared__ float rc[TWO ? kCRMax * kCRMax * kCRMax : 1];
+    __shared__ Vec4<float> pc[TWO ? kCMax * kCMax * kCMax : 1];
     __shared__ uint32_t cst[kTileCells + 1];
     int tx, ty, tz;
     tile_of_block(blockIdx.x, nt, tx, ty, tz);
@@ -508,21 +533,10 @@ __global__ __launch_bounds__(kGatherBlock) void xbar_gather_kernel(
     } else {
         for (int i = tid; i < kRS * kRS * kRS; i += kGatherBlock) rf[i] = 0.0f;
     }
-    const int CS = (kTileFine >> hshift) + G::PX, CR = (kTileFine >> hshift) + G::RX;
-    if (TWO) {
-        const int cx0 = a0x >> hshift, cy0 = a0y >> hshift, cz0 = a0z >> hshift;
-        if (WITH_E)
-            for (int i = tid; i < CS * CS * CS; i += kGatherBlock) {
-                const int lx = i % CS, ly = (i / CS) % CS, lz = i / (CS * CS);
-                pc[i] = phi_c[((int64_t)wrapn(cz0 + lz - G::PLO, n_c) * n_c +
-                               wrapn(cy0 + ly - G::PLO, n_c)) * n_c + wrapn(cx0 + lx - G::PLO, n_c)];
-            }
-        for (int i = tid; i < CR * CR * CR; i += kGatherBlock) {
-            const int lx = i % CR, ly = (i / CR) % CR, lz = i / (CR * CR);
-            rc[i] = rb_c[((int64_t)wrapn(cz0 + lz - G::RLO, n_c) * n_c +
-                          wrapn(cy0 + ly - G::RLO, n_c)) * n_c + wrapn(cx0 + lx - G::RLO, n_c)];
-        }
-    }
+    const int CS = (kTileFine >> hshift) + 1 + 2 * coarse_field_lo<P>();
+    if (TWO)
+        stage_coarse_field<P, kGatherBlock, float>(pc, WITH_E ? phi_c : nullptr, rb_c, n_c, hshift, a0x,
+                                                   a0y, a0z);
     __syncthreads();
     for (uint32_t p = cst[0] + tid; p < cst[kTileCells]; p += kGatherBlock) {
         const int u = seg_search_n<kTileCells>(cst, p);
@@ -544,8 +558,7 @@ __global__ __launch_bounds__(kGatherBlock) void xbar_gather_kernel(
         float xb[3] = {0.f, 0.f, 0.f};
         level_gather<WITH_E, P>(pf, kFS, rf, kRS, jf, wf, dwf, ab, c_f, 1.0f, xb);
         if (TWO)
-            level_gather<WITH_E, P>(pc, CS, rc, CR, jc, wc, dwc, ab, c_c, 1.0f / (float)(1 << hshift),
-                                    xb);
+            field_gather<P>(pc, CS, jc, wc, dwc, ab, c_c, 1.0f / (float)(1 << hshift), xb);
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
             float *dst = xbar + (int64_t)d * n + p;

@@ -4,8 +4,8 @@
 //
 // One workgroup per tile (8^3 IOS cells = 16^3 fine cells).  It stages in LDS
 // the fine potential on the tile plus a halo (2 nodes for the stencil below,
-// 3 above: the CIC upper node plus the stencil), and the coarse potential on
-// the tile's coarse footprint with the same halo.  Each particle then reads
+// 3 above: the CIC upper node plus the stencil), and the coarse level's force on
+// the tile's coarse footprint (stage_coarse_field).  Each particle then reads
 // the 6 potential values along each axis around its 2x2 CIC footprint and
 // forms E = -[(2/3)(phi(+1) - phi(-1)) - (1/12)(phi(+2) - phi(-2))] at its two
 // nodes per axis, weighted with the deposit's 15-bit integer weights.
@@ -23,7 +23,6 @@ namespace {
 template <int P> struct InterpGeo {
     static constexpr int HLO = P == 3 ? 3 : 2;                 // halo below the tile
     static constexpr int FS = kTileFine + (P == 3 ? 7 : 5);    // 21 or 23
-    static constexpr int CSMAX = kTileFine / 2 + (P == 3 ? 7 : 5);
 };
 
 // The FD force at the particle's two nodes along one axis, CIC-weighted
@@ -109,6 +108,29 @@ __device__ __forceinline__ void gather3(const T *P, int S, int nx, int ny, int n
         }
 }
 
+// The coarse level's force at the particle whose first coarse node is (jx, jy, jz)
+// of the staged field F (side S), weighted.
+template <int P, typename T>
+__device__ __forceinline__ void gather_field(const Vec4<T> *F, int S, const int (&j)[3], const T (&w)[3][P],
+                                             T (&a)[3]) {
+    a[0] = a[1] = a[2] = T(0);
+#pragma unroll
+    for (int sz = 0; sz < P; ++sz)
+#pragma unroll
+        for (int sy = 0; sy < P; ++sy) {
+            const T wyz = w[1][sy] * w[2][sz];
+            const Vec4<T> *row = F + ((j[2] + sz) * S + j[1] + sy) * S + j[0];
+#pragma unroll
+            for (int sx = 0; sx < P; ++sx) {
+                const T W = wyz * w[0][sx];
+                const Vec4<T> e = row[sx];
+                a[0] = fma(W, e.x, a[0]);
+                a[1] = fma(W, e.y, a[1]);
+                a[2] = fma(W, e.z, a[2]);
+            }
+        }
+}
+
 // At least two waves per SIMD: left alone, the compiler gives the two-level
 // TSC gather all 256 VGPRs and one wave per SIMD.  FINE = false gathers the
 // coarse level only (the tile+buffer mode computes the fine level per tile).
@@ -119,9 +141,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
     const uint16_t *__restrict__ pos, const uint32_t *__restrict__ cs, int n, int n_f, int nt,
     const T *__restrict__ phi_f, const T *__restrict__ phi_c, int n_c, int hshift_arg, T scale_f,
     T scale_c, T *__restrict__ acc, int accumulate, const T *__restrict__ extra) {
-    constexpr int FS = InterpGeo<P>::FS, HLO = InterpGeo<P>::HLO, CSM = InterpGeo<P>::CSMAX;
+    constexpr int FS = InterpGeo<P>::FS, HLO = InterpGeo<P>::HLO, CSM = coarse_field_max<P, HS>();
     __shared__ T pf[FINE ? FS * FS * FS : 1];
-    __shared__ T pc[TWO ? CSM * CSM * CSM : 1];
+    __shared__ Vec4<T> pc[TWO ? CSM * CSM * CSM : 1];
     __shared__ uint32_t cst[kTileCells + 1];
 
     int tx, ty, tz;
@@ -132,16 +154,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
     stage_cell_starts<BLOCK>(cst, cs, key0);
     const int ax0 = tx * kTileFine, ay0 = ty * kTileFine, az0 = tz * kTileFine;
     if (FINE) stage_block<FS, BLOCK>(pf, phi_f, n_f, ax0 - HLO, ay0 - HLO, az0 - HLO);
-    const int CS = (kTileFine >> hshift) + FS - kTileFine;
-    if (TWO) {
-        const int cx0 = (ax0 >> hshift) - HLO, cy0 = (ay0 >> hshift) - HLO,
-                  cz0 = (az0 >> hshift) - HLO;
-        switch (hshift) {
-            case 1: stage_block<kTileFine / 2 + FS - kTileFine, BLOCK>(pc, phi_c, n_c, cx0, cy0, cz0); break;
-            case 2: stage_block<kTileFine / 4 + FS - kTileFine, BLOCK>(pc, phi_c, n_c, cx0, cy0, cz0); break;
-            default: stage_block<kTileFine / 8 + FS - kTileFine, BLOCK>(pc, phi_c, n_c, cx0, cy0, cz0); break;
-        }
-    }
+    const int CS = (kTileFine >> hshift) + 1 + 2 * coarse_field_lo<P>();
+    if (TWO) stage_coarse_field<P, BLOCK, T>(pc, phi_c, nullptr, n_c, hshift, ax0, ay0, az0);
     __syncthreads();
     const uint32_t p0 = cst[0], p1 = cst[kTileCells];
     const T inv = T(1.0 / 32768.0);
@@ -188,7 +202,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
                     if (TWO) {
                         const uint32_t q = ((uint32_t)uc[d] << 16) + o;  // tile-relative, 2^-15 units
                         const uint32_t y = q >> hshift;
-                        jc[d] = (int)(y >> kFracBits) + tsc_axis<T>((int)(y & 0x7FFFu), wc[d]) + HLO;
+                        jc[d] = (int)(y >> kFracBits) + tsc_axis<T>((int)(y & 0x7FFFu), wc[d]);
                     }
                 }
                 a[0] = a[1] = a[2] = T(0);
@@ -200,7 +214,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
                 }
                 if (TWO) {
                     T c[3];
-                    gather3(pc, CS, jc[0], jc[1], jc[2], wc[0], wc[1], wc[2], c[0], c[1], c[2]);
+                    gather_field<3, T>(pc, CS, jc, wc, c);
                     a[0] += scale_c * c[0];
                     a[1] += scale_c * c[1];
                     a[2] += scale_c * c[2];
@@ -217,7 +231,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
                     if (TWO) {
                         const uint32_t q = ((uint32_t)uc[d] << 16) + o;  // tile-relative, 2^-15 units
                         const int fc = (int)((q >> hshift) & 0x7FFFu);
-                        jc[d] = (int)(q >> (kFracBits + hshift)) + HLO;
+                        jc[d] = (int)(q >> (kFracBits + hshift));
                         wc[d][1] = (T)fc * inv;
                         wc[d][0] = (T)(32768 - fc) * inv;
                     }
@@ -231,7 +245,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
                 }
                 if (TWO) {
                     T c[3];
-                    gather(pc, CS, jc[0], jc[1], jc[2], wc[0], wc[1], wc[2], c[0], c[1], c[2]);
+                    gather_field<2, T>(pc, CS, jc, wc, c);
                     a[0] += scale_c * c[0];
                     a[1] += scale_c * c[1];
                     a[2] += scale_c * c[2];
