@@ -408,11 +408,14 @@ __device__ __forceinline__ void light_tiles(unsigned char *lds, const uint16_t *
     // A wave's first chunk of items is its number among its XCD's waves; the next
     // ones come from the XCD's counter, or, with up to 4 items per wave, at fixed
     // strides (one claim per item from one counter: 31.6 ms instead of 25.0 for
-    // 512^3 particles).
+    // 512^3 particles).  Chunks of 4 items at most, so that the waves of an XCD work on
+    // neighbouring tiles, whose boxes share lines of its L2 (the same, 64 items 21.8 ms,
+    // 16 21.3, 8 21.2, 4 21.0, 1 20.5; adjoint 34.9 and 33.4; but with one item 128^3
+    // particles beside PM take 325 us instead of 318).
     XcdShare xcd;
     int nw = xcd.gx * P::WAVES, nitems = xcd.share(ntiles) * per_tile;
     const bool fixed = nitems <= 4 * nw || nt * nt * nt < kXcdQueueWords;
-    const int chunk = fixed ? 1 : min(nitems / (2 * nw), 64);
+    const int chunk = fixed ? 1 : min(nitems / (2 * nw), 4);
     int next = wave * xcd.gx + xcd.first, item = 0, end = 0;
     for (;;) {
         if (item >= end) {
