@@ -54,16 +54,16 @@ WORKLOADS = {
 
 # Algorithmic FP32 flops (FMA = 2) of one in-cutoff PP pair, counted from
 # the arithmetic of the compiled inner loop: 3 differences, s = r^2 with its
-# offset (3 FMA, 6), the local variable (1), w = 1 - s/b_f^2 (1 FMA, 2),
-# 3 Horner FMA (6), w^2, w^4, h w and g (4), 3 accumulating FMA (6).  The
-# table index (shift, mask, or) is integer work and is not counted.
-PP_FLOPS_PER_PAIR = 28
+# offset (3 FMA, 6), the local variable (1 FMA, 2), the row's quadratic (2 FMA,
+# 4), its square, fourth and fifth power (3), 3 accumulating FMA (6).  The
+# table index (a bit field and an address) is integer work and is not counted.
+PP_FLOPS_PER_PAIR = 24
 
 
 # VALU instructions per candidate pair of the compiled forward PP inner loop
-# (gfx950 ISA: 42 per iteration of the two-pair unrolled loop), and the
+# (gfx950 ISA: 70 per iteration of the four-pair unrolled loop), and the
 # unpacked FP32 VALU issue rate (lane-ops per second).
-PP_VALU_PER_PAIR = 21.0
+PP_VALU_PER_PAIR = 17.5
 VALU_LANE_OPS = 256 * 4 * 16 * 2.4e9
 
 

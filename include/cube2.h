@@ -305,9 +305,10 @@ int cube2_pp_force_noalloc(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *
  * runs on a stream of the context (made with its two events by
  * cube2_init_tables, default priority) beside the PM part on `stream`, with
  * its own tile queue and a 3*n FP32 staging area in `work`; `stream` waits
- * for both before the sum, so the call is ordered on `stream` like every
- * other.  Calls that share a context must not overlap (they share that
- * stream and the work regions). */
+ * for it before the last PM kernel, which adds it to its own result, so the
+ * call is ordered on `stream` like every other.  Meshes of fewer than 128 fine
+ * cells per side take PM and then PP, both on `stream`.  Calls that share a
+ * context must not overlap (they share that stream and the work regions). */
 int cube2_force(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cell_start, int64_t n,
                 float *acc, void *work, size_t work_bytes, cube2_stream_t stream);
 
@@ -317,7 +318,7 @@ int cube2_force(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cell_start,
  * cube2_pp_force_backward with accumulate (every adjoint scatter sums in
  * exact fixed point, so the result does not depend on the order of the
  * atomics), run the same way as cube2_force (PP adjoint on the context's
- * stream beside the PM adjoint on `stream`, joined before the sum). */
+ * stream beside the PM adjoint on `stream`, joined before its last kernel). */
 int cube2_force_backward(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cell_start,
                          int64_t n, const float *acc_bar, float *x_bar, int accumulate, void *work,
                          size_t work_bytes, cube2_stream_t stream);
