@@ -323,18 +323,17 @@ __device__ __forceinline__ int claim_slot(uint32_t *queue, int ntiles) {
     return v < (uint32_t)ntiles ? (int)v : ntiles;
 }
 
-// Claims that come often use a counter per XCD: one counter serves only some 70
+// Claims that come often use a counter per XCD (the deposit's here, the light PP tiles' in
+// light_claims.hpp): one counter serves only some 70
 // million claims a second (14 ns each; the deposit's 262144 tiles of a 1024^3
 // mesh took 3.4 ms whatever they held).  Workgroups b = g (mod 8) run on one XCD
 // and take every 8th tile of the order, the XCD's slab of the mesh
 // (tile_of_block) where the order is that of the blocks.
 // When a group's share is taken, its workgroups go on with the next group's.
 struct XcdShare {
-    int ng, g, gx, first;      // groups, this workgroup's, its workgroups, its number among them
+    int ng, g;                 // groups, this workgroup's
     int done = 0;              // groups found exhausted
-    __device__ __forceinline__ XcdShare()
-        : ng(gridDim.x >= 8 ? 8 : 1), g((int)blockIdx.x % ng),
-          gx(((int)gridDim.x - g + ng - 1) / ng), first((int)blockIdx.x / ng) {}
+    __device__ __forceinline__ XcdShare() : ng(gridDim.x >= 8 ? 8 : 1), g((int)blockIdx.x % ng) {}
     // items of the group out of n
     __device__ __forceinline__ int share(int n) const { return n > g ? (n - g + ng - 1) / ng : 0; }
     // place in the order of the group's i-th item

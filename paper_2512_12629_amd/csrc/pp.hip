@@ -23,6 +23,7 @@
 #include <utility>
 
 #include "common.hpp"
+#include "light_claims.hpp"
 
 namespace cube2 {
 namespace {
@@ -405,38 +406,18 @@ __device__ __forceinline__ void light_tiles(unsigned char *lds, const uint16_t *
     const int per_tile = kTileIos / layers;
     const int ncell = 100 * (layers + 2), nown = 8 * layers;
     auto part_of = [](int bx) { return bx < 1 ? 0 : (bx < 1 + kTileIos ? 1 : 2); };
-    // A wave's first chunk of items is its number among its XCD's waves; the next
-    // ones come from the XCD's counter, or, with up to 4 items per wave, at fixed
-    // strides (one claim per item from one counter: 31.6 ms instead of 25.0 for
-    // 512^3 particles).  Chunks of 4 items at most, so that the waves of an XCD work on
-    // neighbouring tiles, whose boxes share lines of its L2 (the same, 64 items 21.8 ms,
-    // 16 21.3, 8 21.2, 4 21.0, 1 20.5; adjoint 34.9 and 33.4; but with one item 128^3
-    // particles beside PM take 325 us instead of 318).
-    XcdShare xcd;
-    int nw = xcd.gx * P::WAVES, nitems = xcd.share(ntiles) * per_tile;
-    const bool fixed = nitems <= 4 * nw || nt * nt * nt < kXcdQueueWords;
-    const int chunk = fixed ? 1 : min(nitems / (2 * nw), 4);
-    int next = wave * xcd.gx + xcd.first, item = 0, end = 0;
-    for (;;) {
-        if (item >= end) {
-            const int c = __builtin_amdgcn_readfirstlane(next);
-            if (c >= (nitems + chunk - 1) / chunk) {
-                if (fixed || !xcd.next_group()) break;
-                // the next group's chunks after those its own waves began with
-                nitems = xcd.share(ntiles) * per_tile;
-                nw = ((int)gridDim.x - xcd.g + xcd.ng - 1) / xcd.ng * P::WAVES;
-                if (lane == 0) next = nw + xcd.claim(queue);
-                continue;
-            }
-            item = c * chunk;
-            end = min(item + chunk, nitems);
-            if (fixed)
-                next = c + nw;
-            else if (lane == 0)
-                next = nw + xcd.claim(queue);
-        }
-        const int t = (int)order[xcd.place(item / per_tile)], zp = item % per_tile;
-        ++item;
+    // Claims per XCD (LightClaims): one claim per item from one counter took 31.6 ms
+    // instead of 25.0 for 512^3 particles.  Chunks of 4 items at most, so that the waves of
+    // an XCD work on neighbouring tiles, whose boxes share lines of its L2 (the same, 64
+    // items 21.8 ms, 16 21.3, 8 21.2, 4 21.0, 1 20.5; adjoint 34.9 and 33.4; but with one
+    // item 128^3 particles beside PM take 325 us instead of 318).
+    LightClaims claims((int)gridDim.x, (int)blockIdx.x, wave, P::WAVES, ntiles, per_tile,
+                       nt * nt * nt >= kXcdQueueWords);
+    auto claim = [&](int g) { return lane == 0 ? (int)min(atomicAdd(queue + 32 * g, 1u), 0x3FFFFFFFu) : 0; };
+    auto first = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    int place, zp;
+    while (claims.take(place, zp, claim, first)) {
+        const int t = (int)order[place];
         if (skip && skip[t]) continue;
         const int tx = t % nt, ty = (t / nt) % nt, tz = t / (nt * nt);
         const int c0x = tx * kTileIos - 1, c0y = ty * kTileIos - 1,
