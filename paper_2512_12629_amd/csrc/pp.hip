@@ -87,27 +87,32 @@ template <bool ADJ> struct PPLight {
 // r >= b_f is zero.  This exact table, in FP64, serves the plain FP64 form.
 //
 // The FP32 kernels evaluate g as a function of s = r^2 instead, which needs
-// neither a square root nor r^-3, through its fifth root: g = unit L(s)^5.
+// neither a square root nor r^-3, through its fifth root: g = (unit/4) L(s)^5.
 // Near the cutoff g vanishes like (1 - r/b_f)^5, and sparse particles often
 // have all their neighbours there, so a table of g itself would lose its
 // relative accuracy; L has a simple zero at the cutoff, which a table follows
 // to the last bit, and 0.3 times the curvature of g where g ~ 1/r^3.  L is a
 // quadratic per row of 1/64 octave of s (the adjoint, which also needs dL/ds:
-// 1/128), in y = s/10 - k with k, the row's centre, in the row's fourth
-// word: L = c0 + y (c1 + c2 y).  Among the floats next to the centre, k is
+// 1/128), in y = 0.4 s - k with k, the row's centre, in the row's fourth
+// word: L = c0 + t y, t = c1 + c2 y.  Among the floats next to the centre, k is
 // the one whose L is nearest to a float, so that c0 adds no error of its own.
-// With y in tenths of s the derivative comes free: dg/ds = unit 5 L^4 dL/ds
-// and 2 dg/ds = unit L^4 (c1 + 2 c2 y).  unit is a power of two that puts L
-// in [0, 1]; in the row that holds the cutoff c0 = 0 and k = b_f^2/10, so that
-// the FMA's clamp to [0, 1] gives exactly 0 at and beyond b_f, and the rows
-// beyond are zero.  Against a cubic of g / (1 - s/b_f^2)^4 on rows of 1/16
-// octave this takes 17 instructions per pair instead of 20 (and 30 instead of
-// 39 in the adjoint), with the same error (FP32 operations against extended
-// precision, b_f = 2, b_pp = 0.2: rms 3.0e-7 against 3.2e-7 for r < 0.9 b_f;
-// the adjoint's derivative term 2.9e-6 of the Jacobian against 7.0e-6).
+// The fifth power would take the rounding of l = fl(L) five times; one of the five
+// factors is therefore L - 3/4 l (root_rest), so that the product l^4 (L - 3/4 l) has it
+// once, for two instructions.  With y in 0.4 s the derivative comes free: 2 dg/ds = unit
+// L^4 (c1 + 2 c2 y).  unit/4 is a power of two that puts L in [0, 1]; in the row that
+// holds the cutoff c0 = 0 and k = 0.4 b_f^2, so that the FMA's clamp to [0, 1] gives
+// l = 0, and so exactly g = 0, at and beyond b_f, and the rows beyond are zero.
 //
-// s0 = 2^e0 is added to s, with e0 at least 3 octaves below (b_pp/2)^2: below
-// that g is nearly constant, so the table has no use for finer octaves and a
+// Against a cubic of g / (1 - s/b_f^2)^4 on rows of 1/16 octave: 19 instructions per
+// pair instead of 20, 32 instead of 39 in the adjoint.  Errors (FP32 operations against
+// extended precision, that cubic -> l^5 -> now; b_f = 2, b_pp = 0.2): of g r, over
+// separations uniform in the sphere of b_f, 1.23e-7 -> 1.46e-7 -> 0.90e-7 rms; relative,
+// for r < 0.9 b_f, 3.8e-7 -> 3.7e-7 -> 3.5e-7; times 1 - r/b_f beyond it 6.33e-8 ->
+// 6.36e-8 -> 6.36e-8 (the rounding of s); the adjoint's derivative term, of the Jacobian,
+// 5.8e-6 -> 1.9e-6 -> 1.9e-6.
+//
+// s0 = 2^e0 is added to s, with e0 at most -13 and at least 3 octaves below
+// (b_pp/2)^2: below that g is nearly constant, so the table has no use for finer octaves and a
 // coincident pair has a row (g finite, g D = 0).  Positions are staged in
 // units of 2^-j fine cells, which are exact too, with j such that s0 has
 // float exponent field 128: a row's place in the table is then its bits modulo
@@ -124,6 +129,7 @@ namespace {
 // access is a 32-bit LDS address.
 // s0 in the scaled units: float exponent field 128
 constexpr float kPairS0 = 2.0f;
+constexpr float kPairY = 0.4f;     // y in units of s
 __shared__ float4 pair_srows[kSRows];
 __shared__ float4 pair_arows[kSRowsAdj];
 
@@ -141,6 +147,13 @@ __host__ __device__ __forceinline__ uint32_t row_place(uint32_t b, int mant) {
     return (b >> (23 - mant)) & (uint32_t)((kSOctaves << mant) - 1);
 }
 
+// L - 3/4 l for the rounded l of L = c0 + t y: a quarter of L, less three times l's
+// rounding error.  The product of it with l^4, which holds that error four times, is a
+// quarter of g / unit with the error once instead of five times.  c0 - 3/4 l is exact.
+__host__ __device__ __forceinline__ float root_rest(float t, float y, float c0, float l) {
+    return fmaf(t, y, fmaf(-0.75f, l, c0));
+}
+
 // g(r) D / unit accumulated into (fx, fy, fz).  s0 is staged as the fourth
 // word of the neighbour: with all four words in use the position is one
 // 128-bit LDS read, which takes 4.7 cycles of the CU's LDS for a wave that
@@ -153,10 +166,11 @@ __device__ __forceinline__ void pair_accumulate(float dx, float dy, float dz, fl
     uint32_t b = __float_as_uint(s);
     if (CLAMP) b = min(b, bmax);
     const float4 c = pair_srows[row_place(b, kSMant)];
-    const float y = fmaf(s, 0.1f, c.w);
-    const float l = unit_clamp(fmaf(fmaf(c.z, y, c.y), y, c.x));
+    const float y = fmaf(s, kPairY, c.w);
+    const float t = fmaf(c.z, y, c.y);
+    const float l = unit_clamp(fmaf(t, y, c.x));
     const float l2 = l * l;
-    const float g = (l2 * l2) * l;
+    const float g = (l2 * l2) * root_rest(t, y, c.x, l);
     fx = fmaf(g, dx, fx);
     fy = fmaf(g, dy, fy);
     fz = fmaf(g, dz, fz);
@@ -173,13 +187,13 @@ __device__ __forceinline__ void pair_adjoint(float dx, float dy, float dz, float
     uint32_t b = __float_as_uint(s);
     if (CLAMP) b = min(b, bmax);
     const float4 c = pair_arows[row_place(b, kSMantAdj)];
-    const float y = fmaf(s, 0.1f, c.w);
+    const float y = fmaf(s, kPairY, c.w);
     const float t = fmaf(c.z, y, c.y);
     const float l = unit_clamp(fmaf(t, y, c.x));
-    const float ls = fmaf(c.z, y, t);                   // 10 dL/ds
+    const float ls = fmaf(c.z, y, t);                   // 2.5 dL/ds
     const float l2 = l * l;
     const float l4 = l2 * l2;
-    const float g = l4 * l;
+    const float g = l4 * root_rest(t, y, c.x, l);
     const float du = fmaf(dz, uz, fmaf(dy, uy, dx * ux)) * (l4 * ls);   // D.u 2 g_s
     ox = fmaf(du, dx, fmaf(g, ux, ox));
     oy = fmaf(du, dy, fmaf(g, uy, oy));
@@ -923,8 +937,8 @@ double pair_root(double b_pp, double b_f, double s, double unit) {
 void fit_root_rows(const cube2_ctx *ctx, int mant, int nrows, const std::vector<double> &grid,
                    std::vector<float> &out) {
     const double bpp = ctx->cfg.b_pp, bf = ctx->cfg.b_fine;
-    const double p2 = (double)ctx->pp_pscale * ctx->pp_pscale, unit = ctx->pp_unit, s0 = kPairS0;
-    const double cut = bf * bf * p2 + s0, c = 0.1f;
+    const double p2 = (double)ctx->pp_pscale * ctx->pp_pscale, unit = ctx->pp_unit / 4, s0 = kPairS0;
+    const double cut = bf * bf * p2 + s0, c = kPairY;
     const int per = 1 << (kSMantAdj + 1 - mant);     // grid points per row
     for (int t = 0; t < nrows; ++t) {
         const double oct = std::ldexp(s0, t >> mant), w = std::ldexp(oct, -mant);
@@ -988,23 +1002,25 @@ void fit_root_rows(const cube2_ctx *ctx, int mant, int nrows, const std::vector<
 // The law's units and both tables.
 void build_root_tables(cube2_ctx *ctx) {
     const double bpp = ctx->cfg.b_pp, bf = ctx->cfg.b_fine;
-    // the largest odd e0 at least 3 octaves below (b_pp/2)^2, but not below
-    // the 2^-31 under the smallest separation (2^-15)
-    int e0 = (int)std::floor(2.0 * std::log2(bpp / 2)) - 3;
+    // the largest odd e0 at least 3 octaves below (b_pp/2)^2 and at most -13 (the table
+    // holds the octaves up from there, and s0 moves s across a power of two, where FP32
+    // halves its resolution, in a smaller part of the range before the cutoff), but not
+    // below the 2^-31 under the smallest separation (2^-15)
+    int e0 = std::min((int)std::floor(2.0 * std::log2(bpp / 2)) - 3, -13);
     if ((e0 & 1) == 0) --e0;
     e0 = std::max(e0, -31);
     const int j = (1 - e0) / 2;
     ctx->pp_pscale = std::ldexp(1.0f, j);
-        const int top = ctx->pp_halo == 1 ? 6 : 7;           // s < 2^top
+    const int top = ctx->pp_halo == 1 ? 6 : 7;           // s < 2^top
     ctx->pp_clamp = top - e0 > (kSRows >> kSMant);
     ctx->pp_unit = 1.0f;
     ctx->pp_srows.assign((size_t)kSRows * 4, 0.0f);
     ctx->pp_arows.assign((size_t)kSRowsAdj * 4, 0.0f);
     ctx->pp_bmax = ctx->pp_bmax_adj = 0x40000000u;       // the row of s0
     if (bf * bf <= 0x1p-30) return;                      // no pair of different positions: zero rows
-    // unit >= 1.05 g(0): L stays below the clamp
+    // unit / 4 >= 1.05 g(0): L stays below the clamp
     const double g0 = 64.0 / 5 * (1.0 / (bpp * bpp * bpp) - 1.0 / (bf * bf * bf));
-    ctx->pp_unit = (float)std::ldexp(1.0, (int)std::ceil(std::log2(1.05 * g0)));
+    ctx->pp_unit = (float)std::ldexp(4.0, (int)std::ceil(std::log2(1.05 * g0)));
     // L at both ends and in the middle of the adjoint's rows, up to the cutoff
     const double p2 = (double)ctx->pp_pscale * ctx->pp_pscale, s0 = kPairS0, last = bf * bf * p2 + s0;
     std::vector<double> grid((size_t)2 * kSRowsAdj + 1, 0.0);
@@ -1012,7 +1028,7 @@ void build_root_tables(cube2_ctx *ctx) {
         const double oct = std::ldexp(s0, (int)(i >> (kSMantAdj + 1)));
         const double x = oct + std::ldexp(oct, -kSMantAdj - 1) * (i & ((2 << kSMantAdj) - 1));
         if (x >= last) break;
-        grid[i] = pair_root(bpp, bf, (x - s0) / p2, ctx->pp_unit);
+        grid[i] = pair_root(bpp, bf, (x - s0) / p2, ctx->pp_unit / 4);
     }
     fit_root_rows(ctx, kSMant, kSRows, grid, ctx->pp_srows);
     fit_root_rows(ctx, kSMantAdj, kSRowsAdj, grid, ctx->pp_arows);
@@ -1222,11 +1238,11 @@ bool pair_law_host(const cube2_ctx *ctx, bool adj, float dx, float dy, float dz,
     if (ctx->pp_clamp) b = std::min(b, adj ? ctx->pp_bmax_adj : ctx->pp_bmax);
     const int mant = adj ? kSMantAdj : kSMant;
     const float *c = &(adj ? ctx->pp_arows : ctx->pp_srows)[(size_t)row_place(b, mant) * 4];
-    const float y = std::fmaf(s, 0.1f, c[3]);
+    const float y = std::fmaf(s, kPairY, c[3]);
     const float t = std::fmaf(c[2], y, c[1]);
     const float l = std::fmin(std::fmax(std::fmaf(t, y, c[0]), 0.0f), 1.0f);
     const float l2 = l * l, l4 = l2 * l2;
-    *g = (l4 * l) * ctx->pp_unit;
+    *g = (l4 * root_rest(t, y, c[0], l)) * ctx->pp_unit;
     *gs2 = (l4 * std::fmaf(c[2], y, t)) * (ctx->pp_unit * ps * ps);
     return true;
 }
