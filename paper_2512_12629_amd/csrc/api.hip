@@ -77,6 +77,7 @@ WorkLayout work_layout(const cube2_ctx *c, int64_t n) {
     size_t nblk = (std::max(nn, ntiles) + 4095) / 4096;
     L.hist = take(nblk * 512 * 4 + 1024);    // digits of up to 9 bits
     L.tile_order = take((ntiles * 4 + 64) * sizeof(uint32_t));  // + the tile work counter
+    L.tile_parts = take(kPPListMax * sizeof(uint32_t));
     L.vel_tmax = take(ntiles * sizeof(float));
     const size_t scan_len = std::max((size_t)(c->n_cells + 1), nblk * 256);
     L.scan_tmp = take((scan_len / 1024 + 64) * 4 * 2 + 4096);
@@ -85,6 +86,7 @@ WorkLayout work_layout(const cube2_ctx *c, int64_t n) {
     {
         const size_t tblk = (ntiles + 4095) / 4096;
         L.pp_order = take((ntiles * 4 + 64) * sizeof(uint32_t));
+        L.pp_parts = take(kPPListMax * sizeof(uint32_t));
         L.pp_hist = take(tblk * 256 * 4 + 1024);
         L.pp_scan = take((tblk * 256 / 1024 + 64) * 4 * 2 + 4096);
         L.acc_pp = take(nn * 3 * sizeof(float));
@@ -195,6 +197,8 @@ int cube2_self_check(const cube2_ctx *ctx, int64_t n_max) {
     }
     if (!fits(L.acc_pp, (size_t)3 * n_max * sizeof(float))) return CUBE2_EWORKSPACE;
     if (!fits(L.tile_order, (ntiles * 4 + 64) * sizeof(uint32_t))) return CUBE2_EWORKSPACE;
+    if (!fits(L.tile_parts, kPPListMax * sizeof(uint32_t)) || !fits(L.pp_parts, kPPListMax * sizeof(uint32_t)))
+        return CUBE2_EWORKSPACE;
     if (!fits(L.vel_tmax, ntiles * sizeof(float))) return CUBE2_EWORKSPACE;
     return vel_layout_check(ctx, L);
 }

@@ -56,6 +56,13 @@ constexpr int kSRowsAdj = 20 << kSMantAdj;
 // a wave takes at once, and how many particles their box may hold.
 constexpr int kPPLightLayers = 2;
 constexpr int kPPLightCap = 520, kPPLightCapAdj = 512;
+// Words of the PP kernels' lists: a tile in the low bits; above it, in the list of parts,
+// the part, the tile's parts less one and whether lanes share a particle; in the order,
+// what the list is made from.
+constexpr int kTileBits = 18, kPartBits = 5;
+constexpr uint32_t kTileMask = (1u << kTileBits) - 1u, kMaxParts = 1u << kPartBits;
+constexpr uint32_t kLanesBit = 1u << (kTileBits + 2 * kPartBits);
+constexpr int kPPListMax = 8192;             // entries of the list of parts
 }  // namespace cube2
 
 struct cube2_ctx {
@@ -98,6 +105,7 @@ struct WorkLayout {
     size_t real64_f, real64_c, spec64;  // FP64 form (zero-sized without it)
     size_t keys, vals, keys2, vals2, hist, scan_tmp, offs_tmp, red;
     size_t pp_order, pp_hist, pp_scan, acc_pp;  // cube2_force's concurrent PP: own tile queue, output
+    size_t tile_parts, pp_parts;        // the PP's list of parts, and that of the concurrent PP
     size_t tile_order;  // 4 x (tiles) + 64 uint32: PP tile order, its sort buffers, work counter
     size_t vel_tmax;    // velocity codec: one FP32 maximum per tile
     size_t total;
@@ -661,12 +669,21 @@ int launch_pp64(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t
 int launch_interp(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,
                   const float *phi_f, const float *phi_c, float *acc, int accumulate,
                   const float *extra, hipStream_t s);
-// light_cap > 0: the PP kernels' order, with the light tiles (every box of
-// kPPLightLayers cell layers holds at most light_cap particles) last;
-// *n_heavy receives the device address of the number of the others.
+// The PP kernels' order of the tiles (launch_order_tiles): heavy ones by estimated work,
+// then the light ones, and a list of the heavy ones' parts.
+struct PPOrder {
+    uint32_t light_cap;    // light: every box of kPPLightLayers cell layers holds at most so many
+    uint32_t smallest;     // own particles of the smallest part
+    float pairs;           // candidate pairs per product of an x-row's particles and those around it
+    float gain;            // pairs per staged particle that a part must have
+    float chip, threads;   // workgroups that the chip holds, threads of each
+    // set by launch_order_tiles (device): {heavy tiles, those of them in the list, its
+    // entries}, and the list
+    const uint32_t *counts;
+    const uint32_t *parts;
+};
 int launch_order_tiles(cube2_ctx *ctx, const uint32_t *cs, unsigned char *work,
-                       const WorkLayout &L, hipStream_t s, int light_cap = 0,
-                       const uint32_t **n_heavy = nullptr);
+                       const WorkLayout &L, hipStream_t s, PPOrder *pp = nullptr);
 int launch_reset_tile_queue(cube2_ctx *ctx, unsigned char *work, const WorkLayout &L,
                             hipStream_t s);
 // Device-wide exclusive scan of m uint32 (in may equal out); tmp: the

@@ -2,7 +2,8 @@
 //
 // The items are `per` parts of each of n tiles.  Workgroups b = g (mod 8) run on one
 // XCD and own every 8th tile of the order, from the g-th on: group g's share.  A wave's
-// first chunk of items is its number among its group's waves; the next ones come from
+// first chunk of items is its number among its group's waves, the last workgroups' first
+// (the first ones to start have the heavy tiles); the next ones come from
 // the group's counter, or, where there are at most 4 items per wave, at fixed strides.
 // When a group's share is taken, its waves go on with the next group's.  The shares
 // differ by a tile where n is not a multiple of 8, and the groups' waves where the grid
@@ -35,7 +36,9 @@ struct LightClaims {
         fixed = most <= 4 * few || !counters;
         chunk = fixed ? 1 : (each < 4 ? each : 4);
         enter();
-        next = wave * (nw / waves) + block / ng;
+        // numbered by pairs of waves, the last workgroup's pair first
+        const int blocks = nw / waves, pair = wave / 2 * 2;
+        next = pair * blocks + (blocks - 1 - block / ng) * (pair + 1 < waves ? 2 : 1) + wave % 2;
     }
 
     constexpr void enter() {

@@ -1,6 +1,6 @@
 // noalloc.hip -- cube2_pp_force without a caller-provided work buffer, for
 // callers that cannot allocate.  The PP kernel's scratch (the heaviest-first
-// tile order, its radix-sort histogram and scan temporaries, and the tile
+// tile order, the list of parts, its radix-sort histogram and scan temporaries, and the tile
 // work counter) lives in one file-scope device array of a fixed size.  Each
 // device holds its own copy at its own address, taken once per device with
 // hipGetSymbolAddress (at cube2_init_tables, else at the entry point's first
@@ -15,8 +15,8 @@
 namespace cube2 {
 
 // Enough for every supported mesh: at n_fine = 1024 there are 64^3 tiles,
-// whose order needs (4 * 64^3 + 64) words (4.2 MB), the histogram 66.6 KB
-// and the scan temporaries 4.7 KB.
+// whose order needs (4 * 64^3 + 64) words (4.2 MB), the list of parts 32 KB, the
+// histogram 66.6 KB and the scan temporaries 4.7 KB.
 constexpr size_t kNoallocScratchBytes = size_t(5) << 20;
 
 static __device__ __align__(256) unsigned char scratch[kNoallocScratchBytes];
@@ -36,6 +36,7 @@ bool noalloc_layout(const cube2_ctx *c, WorkLayout &L) {
     const size_t ntiles = (size_t)c->nt * c->nt * c->nt;
     const size_t nblk = (ntiles + 4095) / 4096;
     L.tile_order = take((ntiles * 4 + 64) * sizeof(uint32_t));  // + the tile work counter
+    L.tile_parts = take(kPPListMax * sizeof(uint32_t));
     L.hist = take(nblk * 256 * 4 + 1024);
     L.scan_tmp = take((nblk * 256 / 1024 + 64) * 4 * 2 + 4096);
     L.total = off;

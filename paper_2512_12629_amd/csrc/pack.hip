@@ -425,14 +425,60 @@ __global__ void tile_keys_kernel(const uint32_t *__restrict__ cs, int nt, uint32
     vals[b] = t;
 }
 
-// The same for the PP kernels, one wave per tile: light tiles get the last
-// key, the others 254 less their thousands.  A tile is light if each of its
-// boxes of kPPLightLayers layers of cells and the halo holds at most light_cap
-// particles.
-__global__ void pp_tile_keys_kernel(const uint32_t *__restrict__ cs, int nt, uint32_t light_cap,
-                                    uint32_t *__restrict__ keys, uint32_t *__restrict__ vals) {
+// ---------------------------------------------------------------------------
+// The PP kernels' order.  A heavy tile's work is estimated in candidate pairs: the sum
+// over its 64 x-rows of cells of their particles times those of the 9 rows around them
+// (10 cells long; `pairs` scales it to the 3 or 5 cells in reach: between the 0.3 of a
+// uniform density and the 1 of a halo inside one cell), and what staging its box costs.
+// Tiles with the most work come first, and those with more than a share of the whole
+// work per workgroup are listed in parts.  A part stages the whole box again, so a tile
+// has at most as many as leave each `gain` pairs per staged particle: halos are split, a
+// tile of a uniform density is not.  Where halos are so few that the neighbours of one
+// particle would take half as long as the work per thread, their tiles are split as finely
+// as they can be and lanes share a particle (kLanesBit); so they do in parts of at most
+// half a block, and larger parts are whole blocks.
+//
+// The PP alone, us, with a rule on the number of heavy tiles alone (all in quarters of
+// blocks up to 1024, in blocks up to 2048 or, two-cell reach, 4096, else the 128 with the
+// most particles in 8 blocks), without any parts, and so.  The rule offered up to 32 parts
+// for each heavy tile, at 14 ns a claim.
+//   uniform, 0.53 / 0.6 / 1.0 particles per cell side: 128^3 cells 110 68 70, 227 78 73,
+//   639 488 373; adjoint 134 82 86, 225 76 79, 785 461 454; two-cell reach 183 135 129,
+//   280 182 129, 1420 2179 1336; 256^3 cells 769 205 220, 305 279 297, 2387 2220 2414.
+//   halos of 2048: 256^3 cells with 5 170 695 162, 40 272 1184 249, 100 428 1172 404, 400
+//   1139 2436 1156; adjoint 237 776 221, 350 1353 330, 606 1161 582, 1672 3283 1805;
+//   two-cell reach 313 944 312, 583 1679 545, 839 1343 834, 1705 3941 1680; 512^3 with
+//   1000 2884 2743 2829, adjoint 4588 4485 4485; two-cell reach 5481 5311 5192.
+// Measured besides: gains of half and twice those of launch_pp_kernel_h (twice: uniform
+// 64^3 cells at 0.7, 74 us instead of 50; half: adjoint of 128^3 at 0.56, 111 instead of
+// 89); 2 shares (256^3 with 400 halos 1270 us) and 8 (1178).
+// ---------------------------------------------------------------------------
+
+constexpr float kStagePairs = 8.0f;    // pairs that staging a particle costs as much as
+constexpr float kWorkShares = 4.0f;    // a part is at most the work per workgroup over this
+constexpr uint32_t kNearLanes = 9;     // lanes share a particle from 2^9 neighbours on
+constexpr uint32_t kWorkFirst = (127u + 12u) << 3;   // work class 0: 2^12 pairs, 8 classes an octave
+
+// work class of a tile (0..254) and its middle
+__device__ __forceinline__ uint32_t work_class(float w) {
+    const uint32_t c = __float_as_uint(w) >> 20;
+    return min(c > kWorkFirst ? c - kWorkFirst : 0u, 254u);
+}
+__device__ __forceinline__ float work_of_key(uint32_t key) {
+    return __uint_as_float((kWorkFirst + 254u - min(key, 254u)) << 20 | 1u << 19);
+}
+
+// Keys of the tiles in dispatch order b, one wave per tile: light tiles get the last key,
+// the others 254 less their work class; values: the tile, the parts that its particles make,
+// the most that pay (each less one) and the log2 of the most neighbours, limited to 15.
+// A tile is light if each of its boxes of kPPLightLayers layers of cells and the halo
+// holds at most light_cap particles.
+__global__ __launch_bounds__(256) void pp_tile_keys_kernel(const uint32_t *__restrict__ cs, int nt,
+                                                           PPOrder pp, uint32_t *__restrict__ keys,
+                                                           uint32_t *__restrict__ vals) {
+    __shared__ uint32_t rows[4][100], own_rows[4][100];   // particles: 10 cells of an x-row, its own 8
     const int ntiles = nt * nt * nt;
-    const int b = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
+    const int w = (int)(threadIdx.x >> 6), b = (int)blockIdx.x * 4 + w;
     const int lane = threadIdx.x & 63;
     if (b >= ntiles) return;
     int tx, ty, tz;
@@ -440,7 +486,7 @@ __global__ void pp_tile_keys_kernel(const uint32_t *__restrict__ cs, int nt, uin
     const uint32_t t = (uint32_t)((tz * nt + ty) * nt + tx);
     const int n_ios = nt * kTileIos;
     constexpr int NB = kTileIos / kPPLightLayers;
-    uint32_t sum[NB] = {};
+    uint32_t sum[NB] = {}, all = 0;
 #pragma unroll
     for (int k = 0; k < 2; ++k) {            // the 100 x-rows of the 10^3 box
         const int r = lane + 64 * k;
@@ -450,7 +496,10 @@ __global__ void pp_tile_keys_kernel(const uint32_t *__restrict__ cs, int nt, uin
         const uint32_t a = cell_key(wrapn(tx * kTileIos - 1, n_ios), cy, cz, nt),
                        m = cell_key(tx * kTileIos, cy, cz, nt),
                        e = cell_key(wrapn(tx * kTileIos + 8, n_ios), cy, cz, nt);
-        const uint32_t c = (cs[a + 1] - cs[a]) + (cs[m + 8] - cs[m]) + (cs[e + 1] - cs[e]);
+        const uint32_t o = cs[m + 8] - cs[m], c = (cs[a + 1] - cs[a]) + o + (cs[e + 1] - cs[e]);
+        rows[w][r] = c;
+        own_rows[w][r] = o;
+        all += c;
 #pragma unroll
         for (int i = 0; i < NB; ++i)
             if (bz >= i * kPPLightLayers && bz < (i + 1) * kPPLightLayers + 2) sum[i] += c;
@@ -462,25 +511,125 @@ __global__ void pp_tile_keys_kernel(const uint32_t *__restrict__ cs, int nt, uin
         for (int o = 32; o >= 1; o >>= 1) sum[i] += (uint32_t)__shfl_xor((int)sum[i], o, 64);
         most = max(most, sum[i]);
     }
-    if (lane == 0) {
-        const uint32_t cnt = cs[(t + 1) * kTileCells] - cs[t * kTileCells];
-        keys[b] = most <= light_cap ? 255u : 254u - min(cnt >> 10, 254u);
-        vals[b] = t;
+    if (most <= pp.light_cap) {
+        if (lane == 0) {
+            keys[b] = 255u;
+            vals[b] = t;
+        }
+        return;
     }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the rows, before they are read
+    __builtin_amdgcn_wave_barrier();
+    const int r0 = (1 + (lane >> 3)) * 10 + 1 + (lane & 7);   // this lane's own row
+    float near = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) near += (float)rows[w][r0 + (i / 3 - 1) * 10 + i % 3 - 1];
+    const float pairs = wave_sum((float)own_rows[w][r0] * near) * pp.pairs, staged = wave_sum((float)all);
+    float nearest = own_rows[w][r0] ? near * pp.pairs : 0.0f;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) nearest = fmaxf(nearest, __shfl_xor(nearest, o, 64));
+    if (lane == 0) {
+        const uint32_t own = cs[(t + 1) * kTileCells] - cs[t * kTileCells];
+        const uint32_t by_own = min((own + pp.smallest - 1) / pp.smallest, kMaxParts),
+                       by_gain = (uint32_t)fminf(pairs / (pp.gain * staged), (float)by_own);
+        const uint32_t log_near = min(31u - (uint32_t)__clz((int)max((uint32_t)nearest, 1u)), 15u);
+        keys[b] = 254u - work_class(pairs + kStagePairs * staged);
+        vals[b] = t | (max(by_own, 1u) - 1u) << kTileBits |
+                  (max(by_gain, 1u) - 1u) << (kTileBits + kPartBits) | log_near << (kTileBits + 2 * kPartBits);
+    }
+}
+
+constexpr int kOrderBlock = 1024, kOrderOne = 4 * kOrderBlock;
+
+// The whole work, from each thread's part of it.
+__device__ __forceinline__ float whole_work(float work, float *sh /*kOrderBlock / 64*/) {
+    work = wave_sum(work);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = work;
+    __syncthreads();
+    float all = 0.0f;
+#pragma unroll
+    for (int v = 0; v < kOrderBlock / 64; ++v) all += sh[v];
+    return fmaxf(all, 1.0f);
+}
+
+// The list of the parts of the first heavy tiles in the order (kOrderOne of them at most,
+// and as many as the list holds); key(i) and val(i) are the i-th tile's.
+template <class Key, class Val>
+__device__ __forceinline__ void list_parts(uint32_t n_heavy, float work, const PPOrder &pp, Key key, Val val,
+                                           uint32_t *__restrict__ parts, uint32_t *__restrict__ counts,
+                                           uint32_t *scan_sh) {
+    constexpr int PER = kOrderOne / kOrderBlock;
+    const float rate = kWorkShares * pp.chip / work, per_thread = work / (pp.chip * pp.threads);
+    uint32_t v[PER], k[PER], sum = 0, total;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const uint32_t i = threadIdx.x * PER + j;
+        k[j] = v[j] = 0u;
+        if (i < n_heavy) {
+            const uint32_t x = val(i), by_own = (x >> kTileBits & (kMaxParts - 1u)) + 1u,
+                           by_gain = (x >> (kTileBits + kPartBits) & (kMaxParts - 1u)) + 1u,
+                           log_near = x >> (kTileBits + 2 * kPartBits);
+            const float want = ceilf(fminf(work_of_key(key(i)) * rate, (float)kMaxParts));
+            bool lanes = log_near >= kNearLanes && (float)(2u << log_near) >= per_thread;
+            k[j] = lanes ? by_own : max(min((uint32_t)want, by_gain), 1u);
+            if (!lanes && k[j] > 1u) {       // whole blocks, or parts of at most half a one
+                lanes = 2u * k[j] >= by_own;
+                if (!lanes) k[j] = min(k[j], (by_own + 3u) / 4u);
+            }
+            v[j] = (x & kTileMask) | (lanes ? kLanesBit : 0u) | (k[j] - 1u) << (kTileBits + kPartBits);
+        }
+        sum += k[j];
+    }
+    uint32_t at = block_exclusive_scan<kOrderBlock>(sum, scan_sh, total);
+    uint32_t in = 0, entries = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        if (k[j] && at + k[j] <= (uint32_t)kPPListMax) {
+            for (uint32_t p = 0; p < k[j]; ++p) parts[at + p] = v[j] | p << kTileBits;
+            ++in;
+            entries += k[j];
+        }
+        at += k[j];
+    }
+    uint32_t all_in, all_entries;
+    block_exclusive_scan<kOrderBlock>(in, scan_sh, all_in);
+    block_exclusive_scan<kOrderBlock>(entries, scan_sh, all_entries);
+    if (threadIdx.x == 0) {
+        counts[1] = all_in;
+        counts[2] = all_entries;
+    }
+}
+
+// The list for an order made by a radix pass: totals are the tiles of each key, sorted the
+// sorted keys.
+__global__ __launch_bounds__(kOrderBlock) void pp_parts_kernel(
+    const uint32_t *__restrict__ totals, const uint32_t *__restrict__ sorted,
+    const uint32_t *__restrict__ order, PPOrder pp, uint32_t *__restrict__ counts,
+    uint32_t *__restrict__ parts) {
+    __shared__ uint32_t scan_sh[kOrderBlock / 64 + 1];
+    __shared__ float sum_sh[kOrderBlock / 64];
+    const int tid = threadIdx.x;
+    const float work = whole_work(tid < 255 ? (float)totals[tid] * work_of_key((uint32_t)tid) : 0.0f, sum_sh);
+    list_parts(counts[0], work, pp, [&](uint32_t i) { return sorted[i]; }, [&](uint32_t i) { return order[i]; },
+               parts, counts, scan_sh);
 }
 
 // The order of up to kOrderOne tiles by their keys in one workgroup, in place of
 // the three launches of a radix pass: each wave ranks its tiles as the radix
 // scatter does.  keys == NULL: the key of a tile is its particles in thousands,
-// most first (tile_keys_kernel).  start255 receives where the last key starts.
-constexpr int kOrderBlock = 1024, kOrderOne = 4 * kOrderBlock;
+// most first (tile_keys_kernel).  Else vals are the tiles' words, counts[0] receives
+// where the last key starts, and the list of parts is made.
 __global__ __launch_bounds__(kOrderBlock) void order_tiles_kernel(
-    const uint32_t *__restrict__ cs, const uint32_t *__restrict__ keys, int nt,
-    uint32_t *__restrict__ order, uint32_t *__restrict__ start255, uint32_t *__restrict__ queue,
-    uint32_t *__restrict__ xcd_queue) {
+    const uint32_t *__restrict__ cs, const uint32_t *__restrict__ keys,
+    const uint32_t *__restrict__ vals, int nt, uint32_t *__restrict__ order,
+    uint32_t *__restrict__ queue, uint32_t *__restrict__ xcd_queue, PPOrder pp,
+    uint32_t *__restrict__ counts, uint32_t *__restrict__ parts) {
     constexpr int W = kOrderBlock / 64, PER = kOrderOne / kOrderBlock;
     __shared__ uint32_t wcnt[W][256];
     __shared__ uint32_t scan_sh[W + 1];
+    __shared__ float sum_sh[W];
+    __shared__ uint32_t sv[kOrderOne];       // the sorted tiles' words
+    __shared__ uint8_t sk[kOrderOne];        // and keys
     const int ntiles = nt * nt * nt, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     for (int i = tid; i < W * 256; i += kOrderBlock) wcnt[i / 256][i % 256] = 0;
     const int per = (ntiles + 64 * W - 1) / (64 * W);   // rounds of 64 tiles per wave
@@ -491,11 +640,15 @@ __global__ __launch_bounds__(kOrderBlock) void order_tiles_kernel(
         key[r] = 256u;
         tile[r] = 0;
         if (r < per && b < ntiles) {
-            int tx, ty, tz;
-            tile_of_block(b, nt, tx, ty, tz);
-            tile[r] = (uint32_t)((tz * nt + ty) * nt + tx);
-            key[r] = keys ? keys[b]
-                          : 255u - min((cs[(tile[r] + 1) * kTileCells] - cs[tile[r] * kTileCells]) >> 10, 255u);
+            if (keys) {
+                tile[r] = vals[b];
+                key[r] = keys[b];
+            } else {
+                int tx, ty, tz;
+                tile_of_block(b, nt, tx, ty, tz);
+                tile[r] = (uint32_t)((tz * nt + ty) * nt + tx);
+                key[r] = 255u - min((cs[(tile[r] + 1) * kTileCells] - cs[tile[r] * kTileCells]) >> 10, 255u);
+            }
         }
     }
     __syncthreads();
@@ -523,7 +676,7 @@ __global__ __launch_bounds__(kOrderBlock) void order_tiles_kernel(
         for (int v = 0; v < W; ++v) mine += wcnt[v][tid];
     }
     uint32_t at = block_exclusive_scan<kOrderBlock>(mine, scan_sh, total);
-    if (tid == 255) *start255 = at;
+    const uint32_t key_start = at;
     if (tid < 256) {
 #pragma unroll
         for (int v = 0; v < W; ++v) {
@@ -537,7 +690,18 @@ __global__ __launch_bounds__(kOrderBlock) void order_tiles_kernel(
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < PER; ++r)
-        if (key[r] < 256u) order[wcnt[w][key[r]] + place[r]] = tile[r];
+        if (key[r] < 256u) {
+            const uint32_t i = wcnt[w][key[r]] + place[r];
+            order[i] = tile[r];
+            sv[i] = tile[r];
+            sk[i] = (uint8_t)key[r];
+        }
+    if (!keys) return;
+    __shared__ uint32_t heavy_sh;
+    if (tid == 255) heavy_sh = counts[0] = key_start;
+    const float work = whole_work(tid < 255 ? (float)mine * work_of_key((uint32_t)tid) : 0.0f, sum_sh);
+    list_parts(heavy_sh, work, pp, [&](uint32_t i) { return (uint32_t)sk[i]; }, [&](uint32_t i) { return sv[i]; },
+               parts, counts, scan_sh);
 }
 
 }  // namespace
@@ -600,11 +764,11 @@ SortPlan sort_plan(const cube2_ctx *ctx, int64_t n) {
 // Work order of the persistent per-tile kernels: the tiles sorted (stably,
 // one 8-bit radix pass) by their particle count in units of 1024, descending,
 // so that the heaviest tiles start first and the light ones keep the
-// XCD-slab order.  The tile indices land in the first ntiles words of the
-// tile_order region; the work counter (tile_queue_ptr) is reset to zero.
+// XCD-slab order; for the PP kernels by work, with a list of parts (PPOrder).  The
+// tile words land in the first ntiles words of the tile_order region; the work
+// counter (tile_queue_ptr) is reset to zero.
 int launch_order_tiles(cube2_ctx *ctx, const uint32_t *cs, unsigned char *work,
-                       const WorkLayout &L, hipStream_t s, int light_cap,
-                       const uint32_t **n_heavy) {
+                       const WorkLayout &L, hipStream_t s, PPOrder *pp) {
     const int nt = ctx->nt;
     const int ntiles = nt * nt * nt;
     uint32_t *base = reinterpret_cast<uint32_t *>(work + L.tile_order);
@@ -612,23 +776,32 @@ int launch_order_tiles(cube2_ctx *ctx, const uint32_t *cs, unsigned char *work,
     uint32_t *tmp = reinterpret_cast<uint32_t *>(work + L.scan_tmp);
     uint32_t *ghist = reinterpret_cast<uint32_t *>(work + L.hist);
     uint32_t *xcd_queue = ntiles >= kXcdQueueWords ? xcd_queue_ptr(ctx, work, L) : nullptr;
-    if (n_heavy) *n_heavy = tmp + 256;   // where the last key starts
-    if (light_cap > 0) {
-        pp_tile_keys_kernel<<<(ntiles + 3) / 4, 256, 0, s>>>(cs, nt, (uint32_t)light_cap, kin, vin);
+    uint32_t *counts = tmp + 256;   // a radix pass writes where the last key starts there
+    uint32_t *parts = reinterpret_cast<uint32_t *>(work + L.tile_parts);
+    if (pp) {
+        pp->counts = counts;
+        pp->parts = parts;
+        pp_tile_keys_kernel<<<(ntiles + 3) / 4, 256, 0, s>>>(cs, nt, *pp, kin, vin);
         CUBE2_LAUNCH_CHECK();
     }
     if (ntiles <= kOrderOne) {
-        order_tiles_kernel<<<1, kOrderBlock, 0, s>>>(cs, light_cap > 0 ? kin : nullptr, nt, order, tmp + 256,
-                                                     tile_queue_ptr(ctx, work, L), xcd_queue);
+        // (vin is read before the counters in its place are cleared)
+        order_tiles_kernel<<<1, kOrderBlock, 0, s>>>(cs, pp ? kin : nullptr, vin, nt, order,
+                                                     tile_queue_ptr(ctx, work, L), xcd_queue,
+                                                     pp ? *pp : PPOrder{}, counts, parts);
         CUBE2_LAUNCH_CHECK();
         return CUBE2_OK;
     }
-    if (light_cap <= 0) {
+    if (!pp) {
         tile_keys_kernel<<<(ntiles + 255) / 256, 256, 0, s>>>(cs, nt, kin, vin);
         CUBE2_LAUNCH_CHECK();
     }
     const int r = radix_pass<8>(kin, vin, kout, order, ntiles, 0, ghist, tmp, nullptr, s);
     if (r) return r;
+    if (pp) {
+        pp_parts_kernel<<<1, kOrderBlock, 0, s>>>(tmp, kout, order, *pp, counts, parts);
+        CUBE2_LAUNCH_CHECK();
+    }
     if (xcd_queue) {
         fill_u32<<<1, kXcdQueueWords, 0, s>>>(xcd_queue, 0u, kXcdQueueWords);
         CUBE2_LAUNCH_CHECK();

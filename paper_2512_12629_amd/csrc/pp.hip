@@ -252,36 +252,15 @@ __device__ __forceinline__ float quad_sum(float v) {
     return v;
 }
 
-// The heaviest tiles are split: the first kSplitTiles entries of the
-// heaviest-first order are offered as kSplitParts work items each; a tile
-// with `own` particles uses min(kSplitParts, ceil(own / block)) of them,
-// each part staging the tile's box and taking every nparts-th block of its
-// own particles, and the other items end at once.  A tile where Plummer
-// spheres overlap holds several times the pairs of one sphere, and when a
-// workload has few tiles per workgroup such a tile would end the kernel
-// alone; each particle's sum is still formed by one thread in the same
-// order.  (Splitting four tiles per workgroup was slower: every part
-// stages the box again.)
-//
-// Where the heavy tiles are few, all are split: a workgroup gets so few that the heaviest
-// ends the kernel alone.  Up to kFewTiles of them, into parts of a quarter of a
-// block: four lanes share a particle, each taking every fourth neighbour, and their
-// sums are added per range (parts of whole blocks would leave a CU to 8 or 16 waves
-// whose pair loops wait on the LDS).  Up to kBlockTiles, into whole blocks, which
-// stage the box a quarter as often.  Beyond, only the heaviest kSplitTiles.  Measured
-// (us: quarters, blocks, the heaviest alone):
-//   forward, one-cell reach: 256^3 cells with 40, 400, 1000 halos (tiles up to 10^2, 10^3,
-//   2 10^3) 265 516 454, 1121 1198 2143, 2359 2285 3101; 512^3 with 300, 1000 (with
-//   256^3 particles) 1337 1257 1716, 3292 3090 2866.  Adjoint: 343 745 729, 1629 1822
-//   2011, 3497 3692 3550; 1987 2074 2036, 5100 5340 4725.
-//   forward, two-cell reach: 256^3 with 80, 400 halos 482 468 437, 938 834 877; 512^3
-//   with 300 2553 2423 2398.  Adjoint: 794 774 763, 1469 1429 1325; 4954 4935 4858.
-constexpr int kSplitParts = 8, kSplitTiles = 128;
-constexpr int kFewParts = 32, kFewLanes = 4, kSplitAllTiles = 4096;
-template <bool ADJ, int H> struct PPSplit {
-    static constexpr int kFewTiles = H == 1 ? (ADJ ? 2048 : 1024) : 0;
-    static constexpr int kBlockTiles = ADJ ? 0 : (H == 1 ? 2048 : kSplitAllTiles);
-};
+// Heavy tiles with much work are taken in parts (the list of PPOrder, pack.hip): each
+// part stages the tile's box and takes every nparts-th block of its own particles.  In
+// small parts, and where a single particle's neighbours would outlast the other work
+// (kLanesBit), four lanes share a particle, each taking every fourth neighbour, and their
+// sums are added per range (parts of whole blocks would leave a CU to 8 or 16 waves whose
+// pair loops wait on the LDS).  The FP32 rounding of a heavy
+// tile's sums therefore depends on the work of the others; it is the same for every call
+// on the same particles.
+constexpr int kFewLanes = 4;
 
 // The pair law's units (see above): ps = 2^j and its product with the 2^-15 of
 // a position unit, the scale of the sums (unit, and for the forward D's
@@ -431,7 +410,7 @@ __device__ __forceinline__ void light_tiles(unsigned char *lds, const uint16_t *
     auto first = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
     int place, zp;
     while (claims.take(place, zp, claim, first)) {
-        const int t = (int)order[place];
+        const int t = (int)(order[place] & kTileMask);
         if (skip && skip[t]) continue;
         const int tx = t % nt, ty = (t / nt) % nt, tz = t / (nt * nt);
         const int c0x = tx * kTileIos - 1, c0y = ty * kTileIos - 1,
@@ -589,7 +568,8 @@ __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK), 4) void pp_kernel(const uin
                                                      float *__restrict__ acc, int accumulate,
                                                      const uint32_t *__restrict__ order,
                                                      uint32_t *__restrict__ queue, int ntiles,
-                                                     const uint32_t *__restrict__ n_heavy,
+                                                     const uint32_t *__restrict__ counts,
+                                                     const uint32_t *__restrict__ parts,
                                                      uint32_t *__restrict__ light_queue,
                                                      int layers, const uint8_t *__restrict__ skip) {
     using G = PPGeo<ADJ, H>;
@@ -623,20 +603,14 @@ __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK), 4) void pp_kernel(const uin
     // part of a box row that holds the box coordinate bx
     auto part_of = [](int bx) { return bx < H ? 0 : (bx < H + kTileIos ? 1 : 2); };
 
-    // Persistent workgroups: each takes the next work item of the
-    // heaviest-first order (claim_slot) until all are taken (the exit test
-    // is block-uniform).  Thread 0 claims the next item while the current
-    // one is processed.  Items [0, nsplit kParts) are the parts of the nsplit
-    // heaviest tiles, the rest one whole tile each.
-    // n_heavy: the tiles that are not light; only the one-cell reach takes the light
+    // Persistent workgroups: each takes the next work item (claim_slot) until all are
+    // taken (the exit test is block-uniform).  Thread 0 claims the next item while the
+    // current one is processed.  Items are the listed parts of the tiles with the most
+    // work, then whole tiles in order.
+    // counts[0]: the tiles that are not light; only the one-cell reach takes the light
     // ones by waves
-    const int nbig = (int)*n_heavy, nheavy = H == 1 ? nbig : ntiles;
-    const bool few = nbig <= PPSplit<ADJ, H>::kFewTiles;
-    const bool all = few || nbig <= PPSplit<ADJ, H>::kBlockTiles;
-    const int kParts = all ? kFewParts : kSplitParts;
-    const int nsplit = all ? nbig : min(kSplitTiles, nbig);
-    const int nitems = nheavy + nsplit * (kParts - 1);
-    const int split_items = nsplit * kParts;
+    const int nheavy = H == 1 ? (int)counts[0] : ntiles;
+    const int nlisted = (int)counts[1], nlist = (int)counts[2], nitems = nheavy - nlisted + nlist;
     // Without heavy tiles there is nothing to claim: the claim's round trip is 4 us
     // (32^3 particles, 64 tiles: 34.5 -> 30.4 us).
     int next = 0;
@@ -650,19 +624,10 @@ __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK), 4) void pp_kernel(const uin
         const int item = __builtin_amdgcn_readfirstlane(tile_sh);   // block-uniform
         if (item >= nitems) break;
         if (tid == 0) next = claim_slot(queue, nitems);
-        const bool split = item < split_items;
-        const int ti = split ? item / kParts : item - split_items + nsplit;
-        const int part = split ? item % kParts : 0;
-        const int lanes = few && split ? kFewLanes : 1;               // per particle
-        const int sub = tid & (lanes - 1), kOwn = kPPBlock / lanes;   // own particles per block
-        const int t = (int)order[ti];
-        int nparts = 1;
-        if (split) {
-            const uint32_t own = cs[(uint32_t)(t + 1) * kTileCells] - cs[(uint32_t)t * kTileCells];
-            nparts = (int)min((own + kOwn - 1) / kOwn, (uint32_t)kParts);
-            nparts = __builtin_amdgcn_readfirstlane(max(nparts, 1));
-        }
-        if ((skip && skip[t]) || part >= nparts) {   // another level's tile, or a spare part
+        const uint32_t word = item < nlist ? parts[item] : order[item - nlist + nlisted] & kTileMask;
+        const int t = (int)(word & kTileMask), part = (int)(word >> kTileBits & (kMaxParts - 1u)),
+                  nparts = (int)(word >> (kTileBits + kPartBits) & (kMaxParts - 1u)) + 1;
+        if (skip && skip[t]) {   // another level's tile
             __syncthreads();     // every thread has read tile_sh
             continue;
         }
@@ -716,6 +681,8 @@ __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK), 4) void pp_kernel(const uin
         __syncthreads();
         const uint32_t maxcnt = maxcnt_sh;
         const uint32_t own = cst[kTileCells];
+        const int lanes = word & kLanesBit ? kFewLanes : 1;           // per particle
+        const int sub = tid & (lanes - 1), kOwn = kPPBlock / lanes;   // own particles per block
         const bool single = total <= (uint32_t)CAP;   // the whole box is staged at once
 
         // Blocks of own particles, one particle per thread; part p of a split
@@ -846,7 +813,9 @@ __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK), 4) void pp_kernel(const uin
                     rows[row] = r1 > r0 ? (r1 - r0) << 16 | (r0 - vb) : 0u;
                 }
                 RowSort<kW * kW>::sort(rows);
-#pragma unroll 1
+                // (the 25 rows of the two-cell reach in fives, which saves four in five of the
+                // moves: a uniform density, 256^3 cells, 286 -> 271 us)
+#pragma unroll (H == 2 ? 5 : 1)
                 for (int row = 0; row < kW * kW; ++row) {
                     const uint32_t key = RowSort<kW * kW>::next(rows);
                     if (!__any(key >= 0x10000u)) break;
@@ -1128,10 +1097,17 @@ int launch_pp_kernel_h(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, 
     law.bmax = ADJ ? ctx->pp_bmax_adj : ctx->pp_bmax;
     const int nt = ctx->nt;
     const int ntiles = nt * nt * nt;
-    // the light tiles come last in the order; the digits' starts say where
-    const int lcap = PPLight<ADJ>::LCAP;
-    const uint32_t *n_heavy = nullptr;
-    int r = launch_order_tiles(ctx, cs, work, L, order_stream, lcap, &n_heavy);
+    auto k = pp_kernel<ADJ, H, CLAMP>;
+    constexpr int kThreads = PPGeo<ADJ, H>::BLOCK;
+    const unsigned chip = persistent_grid(k, kThreads, ntiles * (int)kMaxParts);
+    PPOrder pp{};
+    pp.light_cap = PPLight<ADJ>::LCAP;
+    pp.smallest = kThreads / kFewLanes;
+    pp.pairs = H == 1 ? 0.5f : 1.2f;
+    pp.gain = (H == 1 ? 16.0f : 32.0f) * (ADJ ? 2.0f : 1.0f);
+    pp.chip = (float)chip;
+    pp.threads = (float)kThreads;
+    const int r = launch_order_tiles(ctx, cs, work, L, order_stream, &pp);
     if (r) return r;
     if (order_stream != s) {
         CUBE2_CHECK_HIP(hipEventRecord(ctx->ev_fork, order_stream));
@@ -1139,16 +1115,13 @@ int launch_pp_kernel_h(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, 
     }
     const uint32_t *order = tile_order_ptr(work, L);
     uint32_t *queue = tile_queue_ptr(ctx, work, L);
-    auto k = pp_kernel<ADJ, H, CLAMP>;
-    const int nitems = ntiles + std::min(ntiles, kSplitAllTiles) * (kFewParts - 1);   // at most
     // one z-layer of cells per light item where there are few of them
     const int layers = ntiles <= kOneLayerTiles ? 1 : PPLight<ADJ>::LAYERS;
-    const unsigned grid = std::max(
-        1u, (unsigned)((float)persistent_grid(k, PPGeo<ADJ, H>::BLOCK, nitems) * grid_frac));
-    k<<<grid, PPGeo<ADJ, H>::BLOCK, 0, s>>>(
+    const unsigned grid = std::max(1u, (unsigned)((float)chip * grid_frac));
+    k<<<grid, kThreads, 0, s>>>(
         pos, cs, (int)n, nt, table, law,
         (float)(ctx->cfg.g_newton * ctx->cfg.m_p), abar, out, accumulate, order, queue, ntiles,
-        n_heavy, xcd_queue_ptr(ctx, work, L), layers, skip);
+        pp.counts, pp.parts, xcd_queue_ptr(ctx, work, L), layers, skip);
     CUBE2_LAUNCH_CHECK();
     return CUBE2_OK;
 }
@@ -1187,7 +1160,7 @@ template <bool ADJ> constexpr float concurrent_frac(int halo) {
 
 // PP force (abar == nullptr) or its adjoint for the cotangents abar into
 // acc_pp (not accumulated) with its own tile order and work counter (the
-// pp_order / pp_hist / pp_scan regions), so that it can run on another stream s
+// pp_order / pp_parts / pp_hist / pp_scan regions), so that it can run on another stream s
 // while the PM part uses the shared ones.  The tile order is made on
 // `order_stream`; if that is not s, s waits for it.
 int launch_pp_concurrent(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n,
@@ -1195,6 +1168,7 @@ int launch_pp_concurrent(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs
                          hipStream_t s, hipStream_t order_stream) {
     WorkLayout Lpp = L;
     Lpp.tile_order = L.pp_order;
+    Lpp.tile_parts = L.pp_parts;
     Lpp.hist = L.pp_hist;
     Lpp.scan_tmp = L.pp_scan;
     if (abar)
