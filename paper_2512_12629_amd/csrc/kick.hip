@@ -77,22 +77,30 @@ __global__ __launch_bounds__(kBlock) void kick_drift_kernel(
 // ---------------------------------------------------------------------------
 // The local re-sort: a step moves particles by a fraction of a tile, so a
 // tile's new particles come from itself and its 26 neighbours, and two passes
-// over the particles replace the four passes of the radix sort (each a count
+// over the particles replace the passes of the radix sort (each a count
 // and a scatter) and its final gather:
 //   local_split   one workgroup per old tile kicks and drifts its particles
 //                 and writes them, in their order, grouped by the tile they go
-//                 to (27 groups, within the tile's own particle range);
-//   local_starts  the new tiles' particle counts from the groups, scanned;
+//                 to (27 groups, within the tile's own particle range); those that
+//                 leave the 27 tiles come last, and a list tells their tiles;
+//   local_starts  the new tiles' particle counts from the groups and the list, scanned;
 //   local_merge   one workgroup per new tile sorts its up to 27 groups, taken
-//                 in the order of their old tiles, stably by cell.
-// Both orders are that of the input, so the result is the stable sort's.  A
-// particle that leaves the 27 tiles sets a flag, and the radix sort runs
-// instead (its kernels are launched either way and end at once if the flag is
-// not set: the host does not wait).  Both passes are bound by HBM, ~100 bytes
-// per particle together; the radix sort moved ~200.
+//                 in the order of their old tiles with the listed particles among
+//                 them, stably by cell.
+// Both orders are that of the input, so the result is the stable sort's.  If more
+// particles than the list holds leave the 27 tiles, or more than a few into one tile,
+// the radix sort runs instead (its kernels are launched either way and end at once if
+// they are not needed: the host does not wait), and the local kernels end as soon as
+// they see it.  Both passes are bound by HBM, ~100 bytes per particle together; the
+// radix sort moved ~200.  512^3 particles: 8.17 ms by a radix sort of the whole key (all
+// particles far: 21.8), 4.1 so, 4.1 with one far particle (9.4 when one sent all to the
+// radix sort), 21.7 with all.
 // ---------------------------------------------------------------------------
 
 constexpr int kDirs = 27;            // (dz + 1) * 9 + (dy + 1) * 3 + dx + 1
+constexpr int kFarDir = kDirs;       // the group of those that leave the 27 tiles
+constexpr uint32_t kFarMax = 2048;   // of them in the list
+constexpr int kFarTile = 32;         // of them into one tile
 constexpr int kSplitItems = 4;       // particles per thread and chunk
 constexpr int kSplitChunk = kBlock * kSplitItems;
 constexpr int kGroups = kSplitChunk / 64;   // waves' worths per chunk
@@ -118,28 +126,37 @@ struct Moved {
     float *vel;
 };
 
-// pre[t * 28 + d]: first particle of group d relative to the tile's first, [27]
-// the tile's particles; far[t] != 0 if a particle left the 27 tiles.
+// Particles that left the 27 tiles around theirs: how many, and the new tile and the slot
+// of each of the first kFarMax, in any order.
+struct Far {
+    uint32_t *count;
+    uint2 *list;
+};
+
+__global__ void far_clear(uint32_t *count) { *count = 0u; }
+
+// pre[t * 28 + d]: first particle of group d (kFarDir: the far ones) relative to the
+// tile's first.
 __global__ __launch_bounds__(kBlock) void local_split(
     const uint16_t *__restrict__ pos, const uint32_t *__restrict__ cs,
     const float *__restrict__ vel, const float *__restrict__ acc, int n, int nt, int n_f,
-    double kick, double drift, Moved out, uint32_t *__restrict__ pre, uint32_t *__restrict__ far,
-    uint32_t *__restrict__ status) {
+    double kick, double drift, Moved out, uint32_t *__restrict__ pre, Far far, uint32_t *__restrict__ status) {
     __shared__ uint32_t cst[kTileCells + 1];
-    __shared__ uint32_t cnt[kDirs][kGroups + 1];   // per group of 64 particles, then before it
-    __shared__ uint32_t base[kDirs + 1];           // next slot of each direction
+    __shared__ uint32_t cnt[kDirs + 1][kGroups + 1];   // per group of 64 particles, then before it
+    __shared__ uint32_t base[kDirs + 1];               // next slot of each direction
     __shared__ uint32_t far_sh;
     int tx, ty, tz;
     tile_of_block(blockIdx.x, nt, tx, ty, tz);
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const uint32_t t = (uint32_t)((tz * nt + ty) * nt + tx);
     stage_cell_starts<kBlock>(cst, cs, t * kTileCells);
-    if (tid == 0) far_sh = 0u;
+    if (tid == 0) far_sh = __hip_atomic_load(far.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (tid <= kDirs) base[tid] = 0u;
     __syncthreads();
+    if (far_sh > kFarMax) return;      // the radix sort does it
     const uint32_t p0 = cst[0], p1 = cst[kTileCells];
     const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    bool bad = false, left = false;
+    bool bad = false;
     // a tile of one chunk keeps its particles in registers between the count
     // and the write; a denser one counts all its chunks first
     const bool one = p1 - p0 <= (uint32_t)kSplitChunk;
@@ -149,7 +166,7 @@ __global__ __launch_bounds__(kBlock) void local_split(
             uint16_t o[kSplitItems][3];
             float v1[kSplitItems][3];
             uint32_t rank[kSplitItems];
-            for (int i = tid; i < kDirs * (kGroups + 1); i += kBlock) (&cnt[0][0])[i] = 0u;
+            for (int i = tid; i < (kDirs + 1) * (kGroups + 1); i += kBlock) (&cnt[0][0])[i] = 0u;
             __syncthreads();
 #pragma unroll
             for (int k = 0; k < kSplitItems; ++k) {
@@ -162,10 +179,7 @@ __global__ __launch_bounds__(kBlock) void local_split(
                             drift, c[k], o[k], v1[k], bad);
                     const int dx = tile_step(tx, c[k][0] >> 3, nt), dy = tile_step(ty, c[k][1] >> 3, nt),
                               dz = tile_step(tz, c[k][2] >> 3, nt);
-                    if (dx == 2 || dy == 2 || dz == 2)
-                        left = true;
-                    else
-                        dir[k] = (dz + 1) * 9 + (dy + 1) * 3 + dx + 1;
+                    dir[k] = dx == 2 || dy == 2 || dz == 2 ? kFarDir : (dz + 1) * 9 + (dy + 1) * 3 + dx + 1;
                 }
                 // rank among the group's earlier particles of the same direction
                 uint64_t peers = __ballot(dir[k] >= 0);
@@ -180,7 +194,7 @@ __global__ __launch_bounds__(kBlock) void local_split(
                     cnt[dir[k]][k * (kBlock / 64) + w] = (uint32_t)__popcll(peers);
             }
             __syncthreads();
-            if (tid < kDirs) {
+            if (tid <= kDirs) {
                 uint32_t sum = 0;
 #pragma unroll
                 for (int g = 0; g < kGroups; ++g) {
@@ -194,7 +208,7 @@ __global__ __launch_bounds__(kBlock) void local_split(
             __syncthreads();
             if (pass == 0) continue;
             if (one && tid < 64) {      // group starts from the chunk's counts
-                uint32_t x = lane < kDirs ? cnt[lane][kGroups] : 0u;
+                uint32_t x = lane <= kDirs ? cnt[lane][kGroups] : 0u;
                 const uint32_t v = x;
 #pragma unroll
                 for (int s = 1; s < 32; s <<= 1) {
@@ -202,11 +216,13 @@ __global__ __launch_bounds__(kBlock) void local_split(
                     if (lane >= s) x += y;
                 }
                 if (lane <= kDirs) {
-                    base[lane] = lane < kDirs ? x - v : x;
-                    pre[t * 28 + lane] = lane < kDirs ? x - v : x;
+                    base[lane] = x - v;
+                    pre[t * 28 + lane] = x - v;
                 }
             }
-            if (one) __syncthreads();
+            // one claim of the list's places per chunk
+            if (tid == 0 && cnt[kFarDir][kGroups]) far_sh = atomicAdd(far.count, cnt[kFarDir][kGroups]);
+            __syncthreads();
 #pragma unroll
             for (int k = 0; k < kSplitItems; ++k) {
                 if (dir[k] < 0) continue;
@@ -219,14 +235,19 @@ __global__ __launch_bounds__(kBlock) void local_split(
                     out.offs[(int64_t)d * n + s] = o[k][d];
                     out.vel[(int64_t)d * n + s] = v1[k][d];
                 }
+                if (dir[k] == kFarDir) {
+                    const uint32_t i = far_sh + cnt[kFarDir][k * (kBlock / 64) + w] + rank[k];
+                    if (i < kFarMax)
+                        far.list[i] = make_uint2((uint32_t)tile_at(c[k][0] >> 3, c[k][1] >> 3, c[k][2] >> 3, nt), s);
+                }
             }
             __syncthreads();
-            if (!one && tid < kDirs) base[tid] += cnt[tid][kGroups];
+            if (!one && tid <= kDirs) base[tid] += cnt[tid][kGroups];
             __syncthreads();
         }
         if (pass == 0) {                // counts to starts
             if (tid < 64) {
-                uint32_t x = lane < kDirs ? base[lane] : 0u;
+                uint32_t x = lane <= kDirs ? base[lane] : 0u;
                 const uint32_t v = x;
 #pragma unroll
                 for (int s = 1; s < 32; s <<= 1) {
@@ -234,32 +255,37 @@ __global__ __launch_bounds__(kBlock) void local_split(
                     if (lane >= s) x += y;
                 }
                 if (lane <= kDirs) {
-                    base[lane] = lane < kDirs ? x - v : x;
-                    pre[t * 28 + lane] = lane < kDirs ? x - v : x;
+                    base[lane] = x - v;
+                    pre[t * 28 + lane] = x - v;
                 }
             }
             __syncthreads();
         }
     }
     if (p0 == p1 && tid <= kDirs) pre[t * 28 + tid] = 0u;
-    if (left) far_sh = 1u;
-    __syncthreads();
-    if (tid == 0) far[t] = far_sh;
     if (bad) atomicOr(status, kStatusNonFinite);
 }
 
 // Particle counts of the new tiles, scanned within blocks of kStartTiles tiles,
-// with the blocks' sums and whether a particle of the block's old tiles is far.
+// with the blocks' sums and whether a tile of the block gets too many far particles.
 constexpr int kStartTiles = 1024;
-__global__ __launch_bounds__(kStartTiles) void local_starts(const uint32_t *__restrict__ pre,
-                                                            const uint32_t *__restrict__ far, int nt,
+__global__ __launch_bounds__(kStartTiles) void local_starts(const uint32_t *__restrict__ pre, Far far, int nt,
                                                             uint32_t *__restrict__ starts,
                                                             uint32_t *__restrict__ sums,
                                                             uint32_t *__restrict__ fars) {
     __shared__ uint32_t sh[kStartTiles / 64 + 1];
+    __shared__ uint32_t extra[kStartTiles];
     __shared__ uint32_t far_sh;
-    const int ntiles = nt * nt * nt, t = (int)(blockIdx.x * kStartTiles + threadIdx.x);
+    const int ntiles = nt * nt * nt, t0 = (int)blockIdx.x * kStartTiles, t = t0 + (int)threadIdx.x;
+    const uint32_t nfar = *far.count;
+    if (nfar > kFarMax) return;
     if (threadIdx.x == 0) far_sh = 0u;
+    extra[threadIdx.x] = 0u;
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < nfar; i += kStartTiles) {
+        const uint32_t to = far.list[i].x - (uint32_t)t0;
+        if (to < (uint32_t)kStartTiles) atomicAdd(&extra[to], 1u);
+    }
     __syncthreads();
     uint32_t sum = 0;
     if (t < ntiles) {
@@ -269,7 +295,8 @@ __global__ __launch_bounds__(kStartTiles) void local_starts(const uint32_t *__re
             const uint32_t *g = pre + (size_t)tile_at(tx - dx, ty - dy, tz - dz, nt) * 28 + d;
             sum += g[1] - g[0];
         }
-        if (far[t]) far_sh = 1u;
+        sum += extra[threadIdx.x];
+        if (extra[threadIdx.x] > (uint32_t)kFarTile) far_sh = 1u;
     }
     uint32_t total;
     const uint32_t at = block_exclusive_scan<kStartTiles>(sum, sh, total);
@@ -281,25 +308,35 @@ __global__ __launch_bounds__(kStartTiles) void local_starts(const uint32_t *__re
     }
 }
 
-// The new tile's groups in the order of their old tiles, sorted stably by cell
-// (tile_cell_sort).
+// The new tile's groups and far particles in the order of their slots, which is that of
+// their old tiles, sorted stably by cell (tile_cell_sort).
 __global__ __launch_bounds__(kBlock) void local_merge(
     const uint32_t *__restrict__ cs, int n, int nt, Moved in, const uint32_t *__restrict__ pre,
     const uint32_t *__restrict__ starts, const uint32_t *__restrict__ sums,
-    const uint32_t *__restrict__ fars, int nblocks, uint16_t *__restrict__ pos,
+    const uint32_t *__restrict__ fars, int nblocks, Far far, uint16_t *__restrict__ pos,
     uint32_t *__restrict__ cell_start, float *__restrict__ vel, int32_t *__restrict__ perm,
     uint32_t *__restrict__ run) {
     constexpr int W = kBlock / 64;
     __shared__ uint32_t hist[W][kTileCells];
-    __shared__ uint32_t seg_pre[32], seg_src[32];  // groups in order: first element, first slot
+    __shared__ uint32_t seg_pre[64], seg_src[64];  // groups in order: first element, first slot
     __shared__ uint32_t scan_sh[W + 1];
-    __shared__ uint32_t red_sh[2];
+    __shared__ uint32_t red_sh[3], far_slot[kFarTile];
     int tx, ty, tz;
     tile_of_block(blockIdx.x, nt, tx, ty, tz);
     const int t = (tz * nt + ty) * nt + tx;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    if (tid < 2) red_sh[tid] = 0u;
+    const uint32_t nfar = *far.count;
+    if (nfar > kFarMax) {            // the radix sort does it
+        if (t == 0 && tid == 0) *run = 1u;
+        return;
+    }
+    if (tid < 3) red_sh[tid] = 0u;
     __syncthreads();
+    for (uint32_t i = tid; i < nfar; i += kBlock)
+        if (far.list[i].x == (uint32_t)t) {
+            const uint32_t k = atomicAdd(&red_sh[2], 1u);
+            if (k < (uint32_t)kFarTile) far_slot[k] = far.list[i].y;
+        }
     {   // start of the tile's block of tiles, and the flag (at most 256 blocks)
         const bool in_range = tid < nblocks;
         uint32_t s = in_range && tid < t / kStartTiles ? sums[tid] : 0u;
@@ -311,32 +348,38 @@ __global__ __launch_bounds__(kBlock) void local_merge(
             if (f) red_sh[1] = 1u;
         }
     }
+    __syncthreads();
+    const int nseg = kDirs + (int)min(red_sh[2], (uint32_t)kFarTile);
     if (w == 0) {
-        // lane d: the group that came in direction d, ranked by its old tile
-        uint32_t src = 0xFFFFFFFFu, cnt = 0, first = 0;
+        // lane d: the group that came in direction d; then the far particles
+        uint32_t cnt = 0, first = 0xFFFFFFFFu;
         if (lane < kDirs) {
             const int dx = lane % 3 - 1, dy = (lane / 3) % 3 - 1, dz = lane / 9 - 1;
-            src = (uint32_t)tile_at(tx - dx, ty - dy, tz - dz, nt);
+            const uint32_t src = (uint32_t)tile_at(tx - dx, ty - dy, tz - dz, nt);
             const uint32_t a = pre[(size_t)src * 28 + lane];
             cnt = pre[(size_t)src * 28 + lane + 1] - a;
             first = cs[(size_t)src * kTileCells] + a;
+        } else if (lane < nseg) {
+            cnt = 1u;
+            first = far_slot[lane - kDirs];
         }
         // (with fewer than three tiles per axis several directions meet the same
         // tile, but only one of them has particles: tile_step)
         uint32_t at = 0, rank = 0;
-        for (int j = 0; j < kDirs; ++j) {
-            const uint32_t sj = (uint32_t)__builtin_amdgcn_readlane((int)src, j),
+        for (int j = 0; j < nseg; ++j) {
+            const uint32_t fj = (uint32_t)__builtin_amdgcn_readlane((int)first, j),
                            cj = (uint32_t)__builtin_amdgcn_readlane((int)cnt, j);
-            if (sj < src || (sj == src && j < lane)) {
+            if (fj < first || (fj == first && j < lane)) {
                 at += cj;
                 ++rank;
             }
         }
-        if (lane < kDirs) {
+        if (lane < nseg) {
             seg_pre[rank] = at;
             seg_src[rank] = first;
+        } else {
+            seg_pre[lane] = 0xFFFFFFFFu;
         }
-        if (lane >= kDirs && lane < 32) seg_pre[lane] = 0xFFFFFFFFu;
     }
     __syncthreads();
     if (t == 0 && tid == 0) *run = red_sh[1];
@@ -347,7 +390,7 @@ __global__ __launch_bounds__(kBlock) void local_merge(
                               ? starts[t + 1] : sums[t / kStartTiles];
     const uint32_t total = next - starts[t];
     auto slot_of = [&](uint32_t e) {
-        int s = 0;
+        int s = nseg > 32 && seg_pre[32] <= e ? 32 : 0;
 #pragma unroll
         for (int step = 16; step > 0; step >>= 1)
             if (seg_pre[s + step] <= e) s += step;
@@ -456,18 +499,24 @@ int launch_kick_drift(cube2_ctx *ctx, const uint16_t *pos_in, const uint32_t *cs
         m.cell = reinterpret_cast<uint16_t *>(work + L.vals);
         m.offs = reinterpret_cast<uint16_t *>(work + L.offs_tmp);
         m.vel = reinterpret_cast<float *>(work + L.acc_pp);
+        // (30 words per tile and 4610 of the mesh's 4096 per tile; one tile, on the
+        // smallest mesh, has no far particles and so no list)
         uint32_t *pre = reinterpret_cast<uint32_t *>(work + L.real_f);
-        uint32_t *far = pre + (size_t)28 * ntiles, *starts = far + ntiles, *sums = starts + ntiles,
-                 *fars = sums + 256;
+        uint32_t *starts = pre + (size_t)28 * ntiles, *sums = starts + ntiles, *fars = sums + 256;
         run = fars + 256;
+        Far far;
+        far.count = run + 1;
+        far.list = reinterpret_cast<uint2 *>(run + 2);
         const int nblocks = (ntiles + kStartTiles - 1) / kStartTiles;
+        far_clear<<<1, 1, 0, s>>>(far.count);
+        CUBE2_LAUNCH_CHECK();
         local_split<<<(unsigned)ntiles, kBlock, 0, s>>>(pos_in, cs_in, vel_in, acc, n, nt, ctx->n_f,
                                                         kick, drift, m, pre, far, status_word(ctx));
         CUBE2_LAUNCH_CHECK();
         local_starts<<<(unsigned)nblocks, kStartTiles, 0, s>>>(pre, far, nt, starts, sums, fars);
         CUBE2_LAUNCH_CHECK();
         local_merge<<<(unsigned)ntiles, kBlock, 0, s>>>(cs_in, n, nt, m, pre, starts, sums, fars, nblocks,
-                                                        pos_out, cs_out, vel_out, perm_out, run);
+                                                        far, pos_out, cs_out, vel_out, perm_out, run);
         CUBE2_LAUNCH_CHECK();
     }
     if (n > 0) {
