@@ -258,25 +258,39 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *s
     return off + x - v;
 }
 
+// A tile of more particles than this is sorted, and drifted, in chunks of so many by
+// several workgroups: one takes 5 ns a particle to sort and 9 to drift.
+constexpr uint32_t kHeavyTile = 8192;
+
 // Stable sort by cell of one tile's `total` elements, the first of which comes to
 // particle `start` (all kBlock threads call it): each wave takes a contiguous part of
 // them; the cells' counts per wave give the starts of the cells (written to
-// cell_start) and of each wave's part of them, and a second pass ranks equal
-// cells by wave ballots.  cell_of(e) is the cell (0..511) of element e, emit(e,
+// cell_start, or given in `base`) and of each wave's part of them, and a second pass
+// ranks equal cells by wave ballots.  cell_of(e) is the cell (0..511) of element e, emit(e,
 // i) writes element e to sorted place i (counted from first_place).
 template <class CellOf, class Emit>
 __device__ __forceinline__ void tile_cell_sort(uint32_t (*hist)[kTileCells] /*[kBlock / 64]*/,
                                                uint32_t *scan_sh /*kBlock / 64 + 1*/, uint32_t total,
                                                uint32_t first_place, uint32_t start,
                                                uint32_t *__restrict__ cell_start,
-                                               CellOf cell_of, Emit emit) {
+                                               CellOf cell_of, Emit emit,
+                                               const uint32_t *base = nullptr) {
     constexpr int W = kBlock / 64;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     for (int i = tid; i < W * kTileCells; i += kBlock) hist[i / kTileCells][i % kTileCells] = 0u;
     __syncthreads();
     const uint32_t per = (total + 64 * W - 1) / (64 * W) * 64;
     const uint32_t e0 = min(w * per, total), e1 = min(e0 + per, total);
-    for (uint32_t e = e0 + lane; e < e1; e += 64) atomicAdd(&hist[w][cell_of(e)], 1u);
+    // (kAhead words of 64 elements at a time: their loads are issued together)
+    constexpr int kAhead = 4;
+    for (uint32_t b = e0; b < e1; b += 64 * kAhead) {
+        uint32_t c[kAhead];
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) c[k] = cell_of(min(b + 64 * k + lane, e1 - 1));
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k)
+            if (b + 64 * k + lane < e1) atomicAdd(&hist[w][c[k]], 1u);
+    }
     __syncthreads();
     // thread i: cells 2i, 2i + 1
     uint32_t tot[2] = {0, 0};
@@ -288,7 +302,10 @@ __device__ __forceinline__ void tile_cell_sort(uint32_t (*hist)[kTileCells] /*[k
     uint32_t at = block_exclusive_scan(tot[0] + tot[1], scan_sh, all);
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-        cell_start[2 * tid + k] = start + at;
+        if (base)
+            at = base[2 * tid + k];
+        else
+            cell_start[2 * tid + k] = start + at;
 #pragma unroll
         for (int v = 0; v < W; ++v) {
             const uint32_t c = hist[v][2 * tid + k];
@@ -298,25 +315,31 @@ __device__ __forceinline__ void tile_cell_sort(uint32_t (*hist)[kTileCells] /*[k
     }
     __syncthreads();
     const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    for (uint32_t b = e0; b < e1; b += 64) {
-        const uint32_t e = b + lane;
-        const bool valid = e < e1;
-        const uint32_t c = cell_of(valid ? e : e1 - 1);
-        uint64_t peers = __ballot(valid);
+    for (uint32_t b0 = e0; b0 < e1; b0 += 64 * kAhead) {
+        uint32_t cell[kAhead];
 #pragma unroll
-        for (int k = 0; k < 9; ++k) {
-            const bool bit = (c >> k) & 1u;
-            const uint64_t m = __ballot(bit);
-            peers &= bit ? m : ~m;
+        for (int k = 0; k < kAhead; ++k) cell[k] = cell_of(min(b0 + 64 * k + lane, e1 - 1));
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            const uint32_t e = b0 + 64 * k + lane, c = cell[k];
+            if (b0 + 64 * k >= e1) break;        // wave-uniform
+            const bool valid = e < e1;
+            uint64_t peers = __ballot(valid);
+#pragma unroll
+            for (int i = 0; i < 9; ++i) {
+                const bool bit = (c >> i) & 1u;
+                const uint64_t m = __ballot(bit);
+                peers &= bit ? m : ~m;
+            }
+            const uint32_t rank = (uint32_t)__popcll(peers & lt);
+            const uint32_t first = hist[w][c];
+            if (valid && rank == 0) hist[w][c] = first + (uint32_t)__popcll(peers);
+            if (valid) emit(e, first_place + first + rank);
+            // this wave's counts are written before its next loads (the LDS serves a
+            // wave in order; this keeps the compiler from reordering them)
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
         }
-        const uint32_t rank = (uint32_t)__popcll(peers & lt);
-        const uint32_t first = hist[w][c];
-        if (valid && rank == 0) hist[w][c] = first + (uint32_t)__popcll(peers);
-        if (valid) emit(e, first_place + first + rank);
-        // this wave's counts are written before its next loads (the LDS serves a
-        // wave in order; this keeps the compiler from reordering them)
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
     }
 }
 

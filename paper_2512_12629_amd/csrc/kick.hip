@@ -44,22 +44,44 @@ __device__ __forceinline__ void drifted(const uint16_t *__restrict__ pos, const 
     }
 }
 
+// Tiles of more than kHeavyTile particles that the local re-sort left: the entries {tile,
+// slice} of all their slices of so many.
+struct HeavySlices {
+    uint32_t *count;
+    uint2 *list;
+};
+
 __global__ __launch_bounds__(kBlock) void kick_drift_kernel(
     const uint16_t *__restrict__ pos, const uint32_t *__restrict__ cs,
     const float *__restrict__ vel, const float *__restrict__ acc, int n, int nt, int n_f,
     double kick, double drift, uint32_t *__restrict__ keys, ushort4 *__restrict__ offs,
-    uint32_t *__restrict__ status, const uint32_t *__restrict__ run) {
+    uint32_t *__restrict__ status, HeavySlices heavy, const uint32_t *__restrict__ run) {
     __shared__ uint32_t cst[kTileCells + 1];
     if (run && *run == 0u) return;      // the fallback of the local re-sort, not needed
     const int tid = threadIdx.x;
     bool bad = false;
-    for (int b = blockIdx.x; b < nt * nt * nt; b += gridDim.x) {
+    const int ntiles = nt * nt * nt, items = ntiles + (run ? (int)*heavy.count : 0);
+    for (int b = blockIdx.x; b < items; b += gridDim.x) {
         int tx, ty, tz;
-        tile_of_block(b, nt, tx, ty, tz);
+        uint32_t slice = 0;
+        if (b < ntiles) {
+            tile_of_block(b, nt, tx, ty, tz);
+        } else {
+            const uint2 h = heavy.list[b - ntiles];
+            tx = (int)h.x % nt;
+            ty = ((int)h.x / nt) % nt;
+            tz = (int)h.x / (nt * nt);
+            slice = h.y;
+        }
         const uint32_t key0 = (uint32_t)((tz * nt + ty) * nt + tx) * kTileCells;
         stage_cell_starts<kBlock>(cst, cs, key0);
         __syncthreads();
-        for (uint32_t p = cst[0] + tid; p < cst[kTileCells]; p += kBlock) {
+        uint32_t p0 = cst[0], p1 = cst[kTileCells];
+        if (run && p1 - p0 > kHeavyTile) {
+            p0 = b < ntiles ? p1 : p0 + slice * kHeavyTile;
+            p1 = min(p1, p0 + kHeavyTile);
+        }
+        for (uint32_t p = p0 + tid; p < p1; p += kBlock) {
             const int u = seg_search_n<kTileCells>(cst, p);
             int c[3];
             uint16_t o[3];
@@ -88,8 +110,8 @@ __global__ __launch_bounds__(kBlock) void kick_drift_kernel(
 //                 in the order of their old tiles with the listed particles among
 //                 them, stably by cell.
 // Both orders are that of the input, so the result is the stable sort's.  If more
-// particles than the list holds leave the 27 tiles, or more than a few into one tile,
-// the radix sort runs instead (its kernels are launched either way and end at once if
+// particles than the list holds leave the 27 tiles, or more than a few into one tile, or a
+// tile holds very many, the radix sort runs instead (its kernels are launched either way and end at once if
 // they are not needed: the host does not wait), and the local kernels end as soon as
 // they see it.  Both passes are bound by HBM, ~100 bytes per particle together; the
 // radix sort moved ~200.  512^3 particles: 8.17 ms by a radix sort of the whole key (all
@@ -133,14 +155,18 @@ struct Far {
     uint2 *list;
 };
 
-__global__ void far_clear(uint32_t *count) { *count = 0u; }
+__global__ void far_clear(uint32_t *count, uint32_t *heavy) {
+    *count = 0u;
+    *heavy = 0u;
+}
 
 // pre[t * 28 + d]: first particle of group d (kFarDir: the far ones) relative to the
 // tile's first.
 __global__ __launch_bounds__(kBlock) void local_split(
     const uint16_t *__restrict__ pos, const uint32_t *__restrict__ cs,
     const float *__restrict__ vel, const float *__restrict__ acc, int n, int nt, int n_f,
-    double kick, double drift, Moved out, uint32_t *__restrict__ pre, Far far, uint32_t *__restrict__ status) {
+    double kick, double drift, Moved out, uint32_t *__restrict__ pre, Far far,
+    HeavySlices heavy, uint32_t *__restrict__ status) {
     __shared__ uint32_t cst[kTileCells + 1];
     __shared__ uint32_t cnt[kDirs + 1][kGroups + 1];   // per group of 64 particles, then before it
     __shared__ uint32_t base[kDirs + 1];               // next slot of each direction
@@ -153,8 +179,18 @@ __global__ __launch_bounds__(kBlock) void local_split(
     if (tid == 0) far_sh = __hip_atomic_load(far.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (tid <= kDirs) base[tid] = 0u;
     __syncthreads();
-    if (far_sh > kFarMax) return;      // the radix sort does it
     const uint32_t p0 = cst[0], p1 = cst[kTileCells];
+    if (p1 - p0 > kHeavyTile) {        // listed for the radix sort's drift
+        const uint32_t slices = (p1 - p0 + kHeavyTile - 1) / kHeavyTile;
+        if (tid == 0) {
+            base[0] = atomicAdd(heavy.count, slices);
+            atomicAdd(far.count, kFarMax + 1u);
+        }
+        __syncthreads();
+        for (uint32_t k = tid; k < slices; k += kBlock) heavy.list[base[0] + k] = make_uint2(t, k);
+        return;
+    }
+    if (far_sh > kFarMax) return;      // the radix sort does it
     const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     bool bad = false;
     // a tile of one chunk keeps its particles in registers between the count
@@ -491,6 +527,7 @@ int launch_kick_drift(cube2_ctx *ctx, const uint16_t *pos_in, const uint32_t *cs
     const int nt = ctx->nt;
     const int ntiles = nt * nt * nt;
     uint32_t *run = nullptr;
+    HeavySlices heavy{};
     if (n64 >= kLocalPerTile * (int64_t)ntiles) {
         // the groups and the tiles' tables take the places of the sort's
         // buffers and of the fine mesh
@@ -499,19 +536,22 @@ int launch_kick_drift(cube2_ctx *ctx, const uint16_t *pos_in, const uint32_t *cs
         m.cell = reinterpret_cast<uint16_t *>(work + L.vals);
         m.offs = reinterpret_cast<uint16_t *>(work + L.offs_tmp);
         m.vel = reinterpret_cast<float *>(work + L.acc_pp);
-        // (30 words per tile and 4610 of the mesh's 4096 per tile; one tile, on the
-        // smallest mesh, has no far particles and so no list)
+        // (29 words per tile and 516 of the mesh's 4096 per tile, then the list's 4096; one
+        // tile, on the smallest mesh, has no far particles and so no list)
         uint32_t *pre = reinterpret_cast<uint32_t *>(work + L.real_f);
         uint32_t *starts = pre + (size_t)28 * ntiles, *sums = starts + ntiles, *fars = sums + 256;
         run = fars + 256;
         Far far;
         far.count = run + 1;
-        far.list = reinterpret_cast<uint2 *>(run + 2);
+        heavy.count = run + 2;
+        far.list = reinterpret_cast<uint2 *>(run + 4);
+        heavy.list = reinterpret_cast<uint2 *>(work + L.keys2);   // at most n / 4096 entries
         const int nblocks = (ntiles + kStartTiles - 1) / kStartTiles;
-        far_clear<<<1, 1, 0, s>>>(far.count);
+        far_clear<<<1, 1, 0, s>>>(far.count, heavy.count);
         CUBE2_LAUNCH_CHECK();
         local_split<<<(unsigned)ntiles, kBlock, 0, s>>>(pos_in, cs_in, vel_in, acc, n, nt, ctx->n_f,
-                                                        kick, drift, m, pre, far, status_word(ctx));
+                                                        kick, drift, m, pre, far, heavy,
+                                                        status_word(ctx));
         CUBE2_LAUNCH_CHECK();
         local_starts<<<(unsigned)nblocks, kStartTiles, 0, s>>>(pre, far, nt, starts, sums, fars);
         CUBE2_LAUNCH_CHECK();
@@ -522,7 +562,8 @@ int launch_kick_drift(cube2_ctx *ctx, const uint16_t *pos_in, const uint32_t *cs
     if (n > 0) {
         kick_drift_kernel<<<(unsigned)(run ? std::min(ntiles, 2048) : ntiles), kBlock, 0, s>>>(
             pos_in, cs_in, vel_in, acc, n, nt, ctx->n_f, kick, drift,
-            reinterpret_cast<uint32_t *>(work + L.keys), sort_offsets(work, L), status_word(ctx), run);
+            reinterpret_cast<uint32_t *>(work + L.keys), sort_offsets(work, L), status_word(ctx),
+            heavy, run);
         CUBE2_LAUNCH_CHECK();
     }
     // the re-sort's final gather also forms the kicked velocities

@@ -10,7 +10,7 @@
 // staged in LDS in digit order and written out in runs.  It sorts by the tile
 // only (two passes of up to 9 bits); one workgroup per tile then sorts the
 // tile's particles by cell in LDS, which also gives cell_start, and gathers
-// them.  With few particles per tile it sorts by the whole key instead and
+// them; a tile of very many is left to several workgroups, by chunks.  With few particles per tile it sorts by the whole key instead and
 // reads cell_start off the sorted keys.  Ties keep their input order, so the
 // result equals a stable argsort.  No global atomics.
 #include <algorithm>
@@ -271,21 +271,50 @@ __global__ __launch_bounds__(kBlock) void radix_scatter(
     }
 }
 
+// Particle p to place i of the sorted ones; with vel, the kicked velocity vel[p] + kick
+// acc[p] in FP64 with separately rounded operations (the value the kick-drift kernel
+// drifted with).
+__device__ __forceinline__ void put_particle(const ushort4 *__restrict__ offs, int n,
+                                             uint16_t *__restrict__ pos, int32_t *__restrict__ perm,
+                                             const float *__restrict__ vel, const float *__restrict__ acc,
+                                             double kick, float *__restrict__ vout, uint32_t p,
+                                             uint32_t i) {
+#pragma clang fp contract(off)
+    const ushort4 o = offs[p];
+    perm[i] = (int32_t)p;
+    pos[i] = o.x;
+    pos[(int64_t)n + i] = o.y;
+    pos[2 * (int64_t)n + i] = o.z;
+    if (vel)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const double kv = kick * (double)acc[(int64_t)d * n + p];
+            vout[(int64_t)d * n + i] = (float)((double)vel[(int64_t)d * n + p] + kv);
+        }
+}
+
+// Tiles of more than kHeavyTile particles: the entries {tile, chunk} of all their chunks,
+// a tile's in order, and each entry's counts of the cells.  A tile of T has at most 2 T /
+// kHeavyTile chunks, so that n / 4096 entries and n / 8 counts hold any input.
+struct HeavyTiles {
+    uint32_t *count;
+    uint2 *list;
+    uint32_t *hist;
+};
+
 // The particles of each tile (keys and vals sorted by tile) sorted by cell, with
-// cell_start; offsets gathered and, with vel, the kicked velocities formed as
-// vel[p] + kick acc[p] in FP64 with separately rounded operations (the value
-// the kick-drift kernel drifted with).
+// cell_start; offsets gathered, velocities kicked (put_particle).
 constexpr int kTileStage = 1536;
 __global__ __launch_bounds__(kBlock) void tile_sort_kernel(
     const uint32_t *__restrict__ keys, const uint32_t *__restrict__ vals,
     const uint32_t *__restrict__ tstart, const ushort4 *__restrict__ offs, int n, int nt,
     uint16_t *__restrict__ pos, uint32_t *__restrict__ cell_start, int32_t *__restrict__ perm,
     const float *__restrict__ vel, const float *__restrict__ acc, double kick,
-    float *__restrict__ vout, const uint32_t *__restrict__ go) {
-#pragma clang fp contract(off)
+    float *__restrict__ vout, HeavyTiles heavy, const uint32_t *__restrict__ go) {
     __shared__ uint32_t hist[kBlock / 64][kTileCells];
     __shared__ uint32_t scan_sh[kBlock / 64 + 1];
     __shared__ uint32_t staged[kTileStage];   // sorted indices: the gather then runs without order
+    __shared__ uint32_t at_sh;
     if (!runs(go)) return;
     const int ntiles = nt * nt * nt;
     for (int b = blockIdx.x; b < ntiles; b += gridDim.x) {
@@ -294,19 +323,16 @@ __global__ __launch_bounds__(kBlock) void tile_sort_kernel(
         const int t = (tz * nt + ty) * nt + tx;
         const uint32_t start = tstart[t], total = tstart[t + 1] - start;
         auto cell_of = [&](uint32_t e) -> uint32_t { return keys[start + e] % kTileCells; };
-        auto put = [&](uint32_t p, uint32_t i) {
-            const ushort4 o = offs[p];
-            perm[i] = (int32_t)p;
-            pos[i] = o.x;
-            pos[(int64_t)n + i] = o.y;
-            pos[2 * (int64_t)n + i] = o.z;
-            if (vel)
-#pragma unroll
-                for (int d = 0; d < 3; ++d) {
-                    const double kv = kick * (double)acc[(int64_t)d * n + p];
-                    vout[(int64_t)d * n + i] = (float)((double)vel[(int64_t)d * n + p] + kv);
-                }
-        };
+        auto put = [&](uint32_t p, uint32_t i) { put_particle(offs, n, pos, perm, vel, acc, kick, vout, p, i); };
+        if (heavy.count && total > kHeavyTile) {
+            const uint32_t chunks = (total + kHeavyTile - 1) / kHeavyTile;
+            if (threadIdx.x == 0) at_sh = atomicAdd(heavy.count, chunks);
+            __syncthreads();
+            for (uint32_t k = threadIdx.x; k < chunks; k += kBlock) heavy.list[at_sh + k] = make_uint2((uint32_t)t, k);
+            if (t == ntiles - 1 && threadIdx.x == 0) cell_start[(size_t)ntiles * kTileCells] = (uint32_t)n;
+            __syncthreads();
+            continue;
+        }
         if (total <= (uint32_t)kTileStage) {
             tile_cell_sort(hist, scan_sh, total, 0u, start, cell_start + (size_t)t * kTileCells, cell_of,
                            [&](uint32_t e, uint32_t i) { staged[i] = vals[start + e]; });
@@ -321,16 +347,92 @@ __global__ __launch_bounds__(kBlock) void tile_sort_kernel(
     }
 }
 
+// The chunks of the heavy tiles: each chunk's counts of the cells; then each chunk to its
+// place, which the counts of the tile's chunks before it and of its cells before give.
+// (131072 of 2.1 million particles in one tile: one workgroup per tile 890 us, with the
+// chunks 165; the radix sort of the whole key 209.  Where there is none the two launches
+// cost 5 to 10 us.)
+__global__ __launch_bounds__(kBlock) void heavy_count_kernel(const uint32_t *__restrict__ keys,
+                                                             const uint32_t *__restrict__ tstart,
+                                                             HeavyTiles heavy,
+                                                             const uint32_t *__restrict__ go) {
+    __shared__ uint32_t h[kTileCells];
+    if (!runs(go)) return;
+    const uint32_t entries = *heavy.count;
+    for (uint32_t i = blockIdx.x; i < entries; i += gridDim.x) {
+        const uint2 c = heavy.list[i];
+        const uint32_t e0 = tstart[c.x] + c.y * kHeavyTile, e1 = min(e0 + kHeavyTile, tstart[c.x + 1]);
+        for (int k = threadIdx.x; k < kTileCells; k += kBlock) h[k] = 0u;
+        __syncthreads();
+#pragma unroll 8
+        for (uint32_t e = e0 + threadIdx.x; e < e1; e += kBlock) atomicAdd(&h[keys[e] % kTileCells], 1u);
+        __syncthreads();
+        for (int k = threadIdx.x; k < kTileCells; k += kBlock) heavy.hist[(size_t)i * kTileCells + k] = h[k];
+        __syncthreads();
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void heavy_sort_kernel(
+    const uint32_t *__restrict__ keys, const uint32_t *__restrict__ vals,
+    const uint32_t *__restrict__ tstart, const ushort4 *__restrict__ offs, int n,
+    uint16_t *__restrict__ pos, uint32_t *__restrict__ cell_start, int32_t *__restrict__ perm,
+    const float *__restrict__ vel, const float *__restrict__ acc, double kick,
+    float *__restrict__ vout, HeavyTiles heavy, const uint32_t *__restrict__ go) {
+    __shared__ uint32_t hist[kBlock / 64][kTileCells];
+    __shared__ uint32_t scan_sh[kBlock / 64 + 1];
+    __shared__ uint32_t base[kTileCells];
+    if (!runs(go)) return;
+    const int tid = threadIdx.x;
+    const uint32_t entries = *heavy.count;
+    for (uint32_t i = blockIdx.x; i < entries; i += gridDim.x) {
+        const uint2 c = heavy.list[i];
+        const uint32_t start = tstart[c.x], total = tstart[c.x + 1] - start;
+        const uint32_t chunks = (total + kHeavyTile - 1) / kHeavyTile, e0 = c.y * kHeavyTile,
+                       cnt = min(kHeavyTile, total - e0);
+        // thread tid: cells 2 tid, 2 tid + 1
+        uint2 all = make_uint2(0u, 0u), before = all;
+        const uint2 *h = reinterpret_cast<const uint2 *>(heavy.hist + (size_t)(i - c.y) * kTileCells) + tid;
+#pragma unroll 8
+        for (uint32_t k = 0; k < chunks; ++k) {
+            const uint2 v = h[(size_t)k * (kTileCells / 2)];
+            all.x += v.x;
+            all.y += v.y;
+            if (k < c.y) {
+                before.x += v.x;
+                before.y += v.y;
+            }
+        }
+        uint32_t sum;
+        const uint32_t at = block_exclusive_scan(all.x + all.y, scan_sh, sum);
+        base[2 * tid] = at + before.x;
+        base[2 * tid + 1] = at + all.x + before.y;
+        if (c.y == 0) {
+            cell_start[(size_t)c.x * kTileCells + 2 * tid] = start + at;
+            cell_start[(size_t)c.x * kTileCells + 2 * tid + 1] = start + at + all.x;
+        }
+        __syncthreads();
+        tile_cell_sort(hist, scan_sh, cnt, start, start, nullptr,
+                       [&](uint32_t e) -> uint32_t { return keys[start + e0 + e] % kTileCells; },
+                       [&](uint32_t e, uint32_t j) {
+                           put_particle(offs, n, pos, perm, vel, acc, kick, vout, vals[start + e0 + e], j);
+                       },
+                       base);
+        __syncthreads();
+    }
+}
+
 // cell_start (shift = 0, n_cells entries and the end), or the tiles' starts
 // (shift = 9), from the sorted keys: entry c is the first index whose key >> shift
 // is >= c, so index i (0..n) writes the entries (key[i-1], key[i]] (with key[-1]
 // = -1 and key[n] = n_cells).  Every entry has exactly one writer.  A run of
 // more than 64 entries (a stretch of empty cells) is written by the whole
-// wave, so that sparse inputs do not leave one lane writing most of the mesh.
+// wave, so that sparse inputs do not leave one lane writing most of the mesh.  A word
+// that the next kernel counts in may be cleared as well.
 __global__ void cell_starts_kernel(const uint32_t *__restrict__ keys, int n, int shift, int64_t n_cells,
-                                   uint32_t *__restrict__ cell_start,
+                                   uint32_t *__restrict__ cell_start, uint32_t *__restrict__ clear,
                                    const uint32_t *__restrict__ run) {
     if (!runs(run)) return;
+    if (clear && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0u;
     const int lane = threadIdx.x & 63;
     constexpr int PER = 4;                 // consecutive indices per lane
     for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x * PER; i0 <= n;
@@ -831,7 +933,7 @@ int launch_sort_by_cell(cube2_ctx *ctx, int64_t n64, uint16_t *pos, uint32_t *ce
     const ushort4 *offs = sort_offsets(work, L);
     int r = CUBE2_OK;
     if (n == 0) {
-        cell_starts_kernel<<<1, 64, 0, s>>>(k0, 0, 0, ctx->n_cells, cell_start, nullptr);
+        cell_starts_kernel<<<1, 64, 0, s>>>(k0, 0, 0, ctx->n_cells, cell_start, nullptr, nullptr);
         CUBE2_LAUNCH_CHECK();
         return CUBE2_OK;
     }
@@ -851,18 +953,33 @@ int launch_sort_by_cell(cube2_ctx *ctx, int64_t n64, uint16_t *pos, uint32_t *ce
     if (plan.by_tile) {
         const int ntiles = ctx->nt * ctx->nt * ctx->nt;
         uint32_t *tstart = reinterpret_cast<uint32_t *>(work + L.tile_order);
-        cell_starts_kernel<<<strided(((int64_t)n + 1 + 1023) / 1024, run), 256, 0, s>>>(k0, n, 9, ntiles,
-                                                                                      tstart, run);
+        // (in the buffers that the sorted keys and values are not in)
+        HeavyTiles heavy{};
+        if (n > (int)kHeavyTile) {
+            heavy.count = tmp;
+            heavy.list = reinterpret_cast<uint2 *>(v1);
+            heavy.hist = k1;
+        }
+        cell_starts_kernel<<<strided(((int64_t)n + 1 + 1023) / 1024, run), 256, 0, s>>>(k0, n, 9, ntiles, tstart,
+                                                                                      heavy.count, run);
         CUBE2_LAUNCH_CHECK();
         tile_sort_kernel<<<strided(ntiles, run), kBlock, 0, s>>>(k0, v0, tstart, offs, n, ctx->nt, pos,
                                                                  cell_start, perm, vel, acc, kick,
-                                                                 vel_out, run);
+                                                                 vel_out, heavy, run);
         CUBE2_LAUNCH_CHECK();
+        if (heavy.count) {
+            const unsigned blocks = (unsigned)std::min(2048, n / 4096);
+            heavy_count_kernel<<<blocks, kBlock, 0, s>>>(k0, tstart, heavy, run);
+            CUBE2_LAUNCH_CHECK();
+            heavy_sort_kernel<<<blocks, kBlock, 0, s>>>(k0, v0, tstart, offs, n, pos, cell_start, perm, vel,
+                                                        acc, kick, vel_out, heavy, run);
+            CUBE2_LAUNCH_CHECK();
+        }
         return CUBE2_OK;
     }
     // cell_start (n_cells + 1 entries, the last = n) from the sorted keys
     cell_starts_kernel<<<strided(((int64_t)n + 1 + 1023) / 1024, run), 256, 0, s>>>(
-        k0, n, 0, ctx->n_cells, cell_start, run);
+        k0, n, 0, ctx->n_cells, cell_start, nullptr, run);
     CUBE2_LAUNCH_CHECK();
     if (vel)
         gather_offsets_kick<<<strided(((int64_t)n + 255) / 256, run), 256, 0, s>>>(
