@@ -251,10 +251,8 @@ int cube2_init_tables(cube2_ctx *ctx, void *tables, size_t table_bytes, cube2_st
     if (sr) return sr;
     ctx->tables = static_cast<unsigned char *>(tables);
     CUBE2_CHECK_HIP(hipMemsetAsync(ctx->tables, 0, 256, s));
-    CUBE2_CHECK_HIP(hipMemcpyAsync(ctx->tables + ctx->pp_soff, ctx->pp_srows.data(),
-                                   ctx->pp_srows.size() * sizeof(float), hipMemcpyHostToDevice, s));
-    CUBE2_CHECK_HIP(hipMemcpyAsync(ctx->tables + ctx->pp_aoff, ctx->pp_arows.data(),
-                                   ctx->pp_arows.size() * sizeof(float), hipMemcpyHostToDevice, s));
+    const int pr = launch_pair_tables(ctx, s);
+    if (pr) return pr;
     if (ctx->fp64)
         CUBE2_CHECK_HIP(hipMemcpyAsync(ctx->tables + ctx->pp64_off, ctx->pp_rows64.data(),
                                        ctx->pp_rows64.size() * sizeof(double),

@@ -68,17 +68,14 @@ constexpr int kPPListMax = 8192;             // entries of the list of parts
 struct cube2_ctx {
     cube2_config cfg;
     int pp_K = 0;                      // intervals of the pair-law grid
-    float pp_kinv = 0.f;               // K / b_f
     // the FP32 pair law's units (pp.hip): position scale and scale of g (powers
     // of two), and whether s is clamped to the table
     float pp_pscale = 1.f, pp_unit = 1.f;
     bool pp_clamp = false;
     uint32_t pp_bmax = 0, pp_bmax_adj = 0;   // float bits of s that the clamped form stops at
     int pp_halo = 1;                   // PP neighbour reach in IOS cells: 1 (b_f <= 2), 2 (b_f <= 4)
-    std::vector<float> pp_srows;       // kSRows * 4 floats: the FP32 forward pair law by s = r^2
-    std::vector<float> pp_arows;       // kSRowsAdj * 4 floats: the same for the adjoint
-    size_t pp_soff = 0, pp_aoff = 0;   // byte offsets of the two in `tables`
-    std::vector<double> pp_rows64;     // the same rows in FP64
+    size_t pp_soff = 0, pp_aoff = 0;   // byte offsets of the FP32 tables (forward, adjoint) in `tables`
+    std::vector<double> pp_rows64;     // the exact pair law by r, in FP64
     size_t pp64_off = 0;               // FP64 rows (CUBE2_FP64_FORM only)
     bool fp64 = false;                 // CUBE2_FP64_FORM
     bool tsc = false;                  // CUBE2_ASSIGN_TSC: TSC instead of CIC on every PM level
@@ -778,6 +775,7 @@ int launch_pp(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n
 // device (taken once per device); out may be NULL.
 int noalloc_setup(unsigned char **out);
 int build_pair_table(cube2_ctx *ctx);
+int launch_pair_tables(cube2_ctx *ctx, hipStream_t s);
 int launch_kick_drift(cube2_ctx *ctx, const uint16_t *pos_in, const uint32_t *cs_in,
                       const float *vel_in, const float *acc, int64_t n, double kick,
                       double drift, uint16_t *pos_out, uint32_t *cs_out, float *vel_out,

@@ -899,103 +899,150 @@ void compose(const double P[9], double alpha, double beta, double Q[9]) {
 
 namespace {
 
-// The fifth root of the pair law g(r) / unit (eqs. 2 and 4d), in FP64: where
+// The rows of L.  They are formed on the device by cube2_init_tables and, for the host's
+// evaluation of the law, on the host: of correctly rounded FP64 operations alone (no
+// contraction, the fifth root by Newton steps), so that both give the same floats.  On the
+// host, for every context, they took 0.25 ms of cube2_create's 0.35.
+struct RootLaw {
+    double bpp, bf;
+    double p2;        // scaled units: s and s0 times 4^j
+    double unit;      // of L^5; 0: no pair of different positions, zero rows
+    double cut;       // b_f^2 p2 + s0
+};
+
+__host__ __device__ inline double bits_double(uint64_t b) {
+    double x;
+    memcpy(&x, &b, 8);
+    return x;
+}
+__host__ __device__ inline uint64_t double_bits(double x) {
+    uint64_t b;
+    memcpy(&b, &x, 8);
+    return b;
+}
+// the next float from a positive one, by `ulps`
+__host__ __device__ inline float next_float(float x, int ulps) {
+    uint32_t b;
+    memcpy(&b, &x, 4);
+    b += (uint32_t)ulps;
+    memcpy(&x, &b, 4);
+    return x;
+}
+
+// x > 0, to a few 1e-16: a fifth of the exponent and mantissa bits (within 4%), then
+// Newton steps, whose error is twice the square of the last.
+__host__ __device__ inline double fifth_root(double x) {
+#pragma clang fp contract(off)
+    double y = bits_double(double_bits(x) / 5 + (0x3FF0000000000000ull / 5) * 4);
+    for (int i = 0; i < 5; ++i) {
+        const double y2 = y * y;
+        y = y - (y - x / (y2 * y2)) * 0.2;
+    }
+    return y;
+}
+
+// R(r, b) / r (eq. 2)
+__host__ __device__ inline double r_over_r(double r, double b) {
+#pragma clang fp contract(off)
+    const double t = r / b;
+    if (t >= 1) return 1 / (r * r * r);
+    if (2 * t < 1)
+        return (64.0 / 5 + t * t * (-256.0 / 5 + t * (32 + t * (1536.0 / 35 + t * (-192.0 / 5))))) /
+               (b * b * b);
+    return (3.0 / 35 / (t * t) - 32.0 / 5 +
+            t * (256.0 / 5 + t * (-96 + t * (256.0 / 5 + t * (32 + t * (-1536.0 / 35 + t * (64.0 / 5))))))) /
+           (b * b * r);
+}
+
+// The fifth root of the pair law g(r) / unit (eqs. 2 and 4d) at the scaled s = x: where
 // 1/r^2 - R(r, b_f) would cancel (r >= b_pp and r >= b_f/2) through its
 // factorised form, which also continues it, negative, past the cutoff;
 // elsewhere from the branches of R(r, b).
-double pair_root(double b_pp, double b_f, double s, double unit) {
-    const double r = std::sqrt(s);
-    if (r >= b_pp && 2 * r >= b_f) {  // g = q^5 Q(q) / r^3, q = 1 - r/b_f
-        const double q = 1 - r / b_f;
+__host__ __device__ inline double pair_root(const RootLaw &p, double x) {
+#pragma clang fp contract(off)
+    const double r = sqrt((x - (double)kPairS0) / p.p2);
+    if (r >= p.bpp && 2 * r >= p.bf) {  // g = q^5 Q(q) / r^3, q = 1 - r/b_f
+        const double q = 1 - r / p.bf;
         const double Q = 1344.0 / 35 + q * (-2912.0 / 35 + q * (2048.0 / 35 + q * (-64.0 / 5)));
-        return q * std::pow(Q / (r * r * r * unit), 0.2);
+        return q * fifth_root(Q / (r * r * r * p.unit));
     }
-    auto r_over_r = [&](double b) {   // R(r, b) / r
-        const double t = r / b;
-        if (t >= 1) return 1 / (r * r * r);
-        if (2 * t < 1)
-            return (64.0 / 5 + t * t * (-256.0 / 5 + t * (32 + t * (1536.0 / 35 + t * (-192.0 / 5))))) /
-                   (b * b * b);
-        return (3.0 / 35 / (t * t) - 32.0 / 5 +
-                t * (256.0 / 5 + t * (-96 + t * (256.0 / 5 + t * (32 + t * (-1536.0 / 35 + t * (64.0 / 5))))))) /
-               (b * b * r);
-    };
-    return std::pow((r_over_r(b_pp) - r_over_r(b_f)) / unit, 0.2);
+    return fifth_root((r_over_r(r, p.bpp) - r_over_r(r, p.bf)) / p.unit);
 }
 
-// The rows of L (see the comment at the top of the law) for 2^mant rows per
-// octave, from the octave of s0 on, in scaled units (s and s0 times 4^j).
-// grid holds L at 2^(kSMantAdj + 1) points per octave: the adjoint's rows are
-// the quadratics through both ends and the middle, which leaves the smallest
-// rms error in dL/ds; the forward's, twice as wide, the least-squares fit to
-// five points, close to the smallest error in L.
-void fit_root_rows(const cube2_ctx *ctx, int mant, int nrows, const std::vector<double> &grid,
-                   std::vector<float> &out) {
-    const double bpp = ctx->cfg.b_pp, bf = ctx->cfg.b_fine;
-    const double p2 = (double)ctx->pp_pscale * ctx->pp_pscale, unit = ctx->pp_unit / 4, s0 = kPairS0;
-    const double cut = bf * bf * p2 + s0, c = kPairY;
-    const int per = 1 << (kSMantAdj + 1 - mant);     // grid points per row
-    for (int t = 0; t < nrows; ++t) {
-        const double oct = std::ldexp(s0, t >> mant), w = std::ldexp(oct, -mant);
-        const double lo = oct + (t & ((1 << mant) - 1)) * w, hi = lo + w;
-        if (lo >= cut) break;        // this and the following rows lie beyond the cutoff: zero
-        const double mid = lo + w / 2, half = w / 2;
-        float k, c0;
-        double c1, c2;
-        if (hi >= cut) {
-            // L = (x - cut) (h0 + h1 (x - cut)) through two points on the far
-            // side of the row from the cutoff; k rounded down, so that s >=
-            // b_f^2 has y >= 0 and L <= 0
-            auto h = [&](double x) { return pair_root(bpp, bf, (x - s0) / p2, unit) / (x - cut); };
-            const double x0 = cut > mid ? lo + w / 8 : mid + w / 8, x1 = x0 + w / 4;
-            const double a = h(x0), h1 = (h(x1) - a) / (x1 - x0), h0 = a + h1 * (cut - x0);
-            k = (float)(c * cut);
-            if (k > c * cut) k = std::nextafter(k, 0.0f);
-            c0 = 0.0f;
-            c1 = h0 / c;
-            c2 = h1 / (c * c);
-        } else {
-            const double *g = &grid[(size_t)t * per];
-            double l0, a1, a2;       // L = l0 + e (a1 + e a2), e in [-1, 1]
-            if (per == 2) {
-                l0 = g[1];
-                a1 = (g[2] - g[0]) / 2;
-                a2 = (g[2] + g[0] - 2 * g[1]) / 2;
-            } else {                 // least squares over e = -1, -1/2, 0, 1/2, 1
-                const double m0 = g[0] + g[1] + g[2] + g[3] + g[4], m2 = g[0] + g[4] + (g[1] + g[3]) / 4;
-                a1 = (g[4] - g[0] + (g[3] - g[1]) / 2) / 2.5;
-                a2 = (m2 - m0 / 2) / 0.875;
-                l0 = (m0 - 2.5 * a2) / 5;
-            }
-            // 8 neighbouring floats kc + i ulp
-            const float kc = (float)(c * mid);
-            const double ulp = (double)std::nextafter(kc, 2 * kc) - kc, ich = 1 / (c * half);
-            const double e0 = (kc - c * mid) * ich, de = ulp * ich;
-            double best = 1, d = 0;
-            int at = 0;
-            for (int i = 0; i < 8; ++i) {
-                const double e = e0 + i * de, v = l0 + e * (a1 + e * a2), err = std::fabs((float)v - v);
-                if (err < best) {
-                    best = err;
-                    at = i;
-                    d = e;
-                }
-            }
-            k = (float)(kc + at * ulp);
-            c0 = (float)(l0 + d * (a1 + d * a2));
-            c1 = (a1 + 2 * d * a2) * ich;
-            c2 = a2 * ich * ich;
+// Row t (see the comment at the top of the law) of 2^mant per octave, from the octave of
+// s0 on, in scaled units.  The adjoint's rows (kSMantAdj) are the quadratics through both
+// ends and the middle, which leaves the smallest rms error in dL/ds; the forward's, twice
+// as wide, the least-squares fit to five points, close to the smallest error in L.
+__host__ __device__ inline float4 root_row(const RootLaw &p, int mant, int t) {
+#pragma clang fp contract(off)
+    // powers of two by their exponent; s0 has exponent 1
+    const double oct = bits_double((uint64_t)(1024 + (t >> mant)) << 52),
+                 w = bits_double((uint64_t)(1024 + (t >> mant) - mant) << 52);
+    const double lo = oct + (t & ((1 << mant) - 1)) * w, hi = lo + w, c = (double)kPairY, cut = p.cut;
+    if (p.unit == 0.0 || lo >= cut) return make_float4(0.0f, 0.0f, 0.0f, 0.0f);   // beyond the cutoff
+    const double mid = lo + w / 2, half = w / 2;
+    if (hi >= cut) {
+        // L = (x - cut) (h0 + h1 (x - cut)) through two points on the far
+        // side of the row from the cutoff; k rounded down, so that s >=
+        // b_f^2 has y >= 0 and L <= 0
+        const double x0 = cut > mid ? lo + w / 8 : mid + w / 8, x1 = x0 + w / 4;
+        const double a = pair_root(p, x0) / (x0 - cut), b = pair_root(p, x1) / (x1 - cut);
+        const double h1 = (b - a) / (x1 - x0), h0 = a + h1 * (cut - x0);
+        float k = (float)(c * cut);
+        if ((double)k > c * cut) k = next_float(k, -1);
+        return make_float4(0.0f, (float)(h0 / c), (float)(h1 / (c * c)), -k);
+    }
+    double l0, a1, a2;               // L = l0 + e (a1 + e a2), e in [-1, 1]
+    const double g0 = pair_root(p, lo), g2 = pair_root(p, mid), g4 = pair_root(p, hi);
+    if (mant == kSMantAdj) {
+        l0 = g2;
+        a1 = (g4 - g0) / 2;
+        a2 = (g4 + g0 - 2 * g2) / 2;
+    } else {                         // least squares over e = -1, -1/2, 0, 1/2, 1
+        const double g1 = pair_root(p, lo + w / 4), g3 = pair_root(p, mid + w / 4);
+        const double m0 = g0 + g1 + g2 + g3 + g4, m2 = g0 + g4 + (g1 + g3) / 4;
+        a1 = (g4 - g0 + (g3 - g1) / 2) / 2.5;
+        a2 = (m2 - m0 / 2) / 0.875;
+        l0 = (m0 - 2.5 * a2) / 5;
+    }
+    // 8 neighbouring floats kc + i ulp
+    const float kc = (float)(c * mid);
+    const double ulp = (double)next_float(kc, 1) - kc, ich = 1 / (c * half);
+    const double e0 = (kc - c * mid) * ich, de = ulp * ich;
+    double best = 1, d = 0;
+    int at = 0;
+    for (int i = 0; i < 8; ++i) {
+        const double e = e0 + i * de, v = l0 + e * (a1 + e * a2), err = fabs((double)(float)v - v);
+        if (err < best) {
+            best = err;
+            at = i;
+            d = e;
         }
-        float *row = &out[(size_t)t * 4];
-        row[0] = c0;
-        row[1] = (float)c1;
-        row[2] = (float)c2;
-        row[3] = -k;
     }
+    return make_float4((float)(l0 + d * (a1 + d * a2)), (float)((a1 + 2 * d * a2) * ich),
+                       (float)(a2 * ich * ich), -(float)(kc + at * ulp));
 }
 
-// The law's units and both tables.
-void build_root_tables(cube2_ctx *ctx) {
+RootLaw root_law(const cube2_ctx *ctx) {
+    RootLaw p;
+    p.bpp = ctx->cfg.b_pp;
+    p.bf = ctx->cfg.b_fine;
+    p.p2 = (double)ctx->pp_pscale * ctx->pp_pscale;
+    p.unit = p.bf * p.bf <= 0x1p-30 ? 0.0 : (double)ctx->pp_unit / 4;
+    p.cut = p.bf * p.bf * p.p2 + kPairS0;
+    return p;
+}
+
+__global__ void root_rows_kernel(RootLaw p, float4 *__restrict__ srows, float4 *__restrict__ arows) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < kSRows)
+        srows[i] = root_row(p, kSMant, i);
+    else if (i < kSRows + kSRowsAdj)
+        arows[i - kSRows] = root_row(p, kSMantAdj, i - kSRows);
+}
+
+// The law's units.
+void set_root_law(cube2_ctx *ctx) {
     const double bpp = ctx->cfg.b_pp, bf = ctx->cfg.b_fine;
     // the largest odd e0 at least 3 octaves below (b_pp/2)^2 and at most -13 (the table
     // holds the octaves up from there, and s0 moves s across a power of two, where FP32
@@ -1009,24 +1056,11 @@ void build_root_tables(cube2_ctx *ctx) {
     const int top = ctx->pp_halo == 1 ? 6 : 7;           // s < 2^top
     ctx->pp_clamp = top - e0 > (kSRows >> kSMant);
     ctx->pp_unit = 1.0f;
-    ctx->pp_srows.assign((size_t)kSRows * 4, 0.0f);
-    ctx->pp_arows.assign((size_t)kSRowsAdj * 4, 0.0f);
     ctx->pp_bmax = ctx->pp_bmax_adj = 0x40000000u;       // the row of s0
     if (bf * bf <= 0x1p-30) return;                      // no pair of different positions: zero rows
     // unit / 4 >= 1.05 g(0): L stays below the clamp
     const double g0 = 64.0 / 5 * (1.0 / (bpp * bpp * bpp) - 1.0 / (bf * bf * bf));
     ctx->pp_unit = (float)std::ldexp(4.0, (int)std::ceil(std::log2(1.05 * g0)));
-    // L at both ends and in the middle of the adjoint's rows, up to the cutoff
-    const double p2 = (double)ctx->pp_pscale * ctx->pp_pscale, s0 = kPairS0, last = bf * bf * p2 + s0;
-    std::vector<double> grid((size_t)2 * kSRowsAdj + 1, 0.0);
-    for (size_t i = 0; i < grid.size(); ++i) {
-        const double oct = std::ldexp(s0, (int)(i >> (kSMantAdj + 1)));
-        const double x = oct + std::ldexp(oct, -kSMantAdj - 1) * (i & ((2 << kSMantAdj) - 1));
-        if (x >= last) break;
-        grid[i] = pair_root(bpp, bf, (x - s0) / p2, ctx->pp_unit / 4);
-    }
-    fit_root_rows(ctx, kSMant, kSRows, grid, ctx->pp_srows);
-    fit_root_rows(ctx, kSMantAdj, kSRowsAdj, grid, ctx->pp_arows);
     // first bit pattern of the row after the one that holds the cutoff
     const float cut = (float)(bf * bf * ctx->pp_pscale * ctx->pp_pscale + kPairS0);
     uint32_t b;
@@ -1037,7 +1071,16 @@ void build_root_tables(cube2_ctx *ctx) {
 
 }  // namespace
 
-// The pair-law tables (see the comment above pair_accumulate).  Returns
+// The FP32 tables (see RootLaw).
+int launch_pair_tables(cube2_ctx *ctx, hipStream_t s) {
+    root_rows_kernel<<<(kSRows + kSRowsAdj + 63) / 64, 64, 0, s>>>(
+        root_law(ctx), reinterpret_cast<float4 *>(ctx->tables + ctx->pp_soff),
+        reinterpret_cast<float4 *>(ctx->tables + ctx->pp_aoff));
+    CUBE2_LAUNCH_CHECK();
+    return CUBE2_OK;
+}
+
+// The FP64 pair-law table and the FP32 law's units.  Returns
 // nonzero when no K <= kPairKMax puts b_pp/2, b_pp and b_f/2 on interval
 // edges (the pieces would then straddle a breakpoint of eq. 2).
 int build_pair_table(cube2_ctx *ctx) {
@@ -1058,7 +1101,6 @@ int build_pair_table(cube2_ctx *ctx) {
     if (K == 0) return 1;
     const double w = bf / K;
     ctx->pp_K = K;
-    ctx->pp_kinv = (float)(K / bf);
     ctx->pp_rows64.assign((size_t)(K + 1) * kPairRow, 0.0);
     for (int k = 0; k < K; ++k) {
         const double mid = (k + 0.5) * w, rl = k * w, rr = (k + 1) * w;
@@ -1099,7 +1141,7 @@ int build_pair_table(cube2_ctx *ctx) {
         row64[9] = ya;
         row64[10] = yb;
     }
-    build_root_tables(ctx);
+    set_root_law(ctx);
     return 0;
 }
 
@@ -1237,13 +1279,13 @@ bool pair_law_host(const cube2_ctx *ctx, bool adj, float dx, float dy, float dz,
     std::memcpy(&b, &s, 4);
     if (ctx->pp_clamp) b = std::min(b, adj ? ctx->pp_bmax_adj : ctx->pp_bmax);
     const int mant = adj ? kSMantAdj : kSMant;
-    const float *c = &(adj ? ctx->pp_arows : ctx->pp_srows)[(size_t)row_place(b, mant) * 4];
-    const float y = std::fmaf(s, kPairY, c[3]);
-    const float t = std::fmaf(c[2], y, c[1]);
-    const float l = std::fmin(std::fmax(std::fmaf(t, y, c[0]), 0.0f), 1.0f);
+    const float4 c = root_row(root_law(ctx), mant, (int)row_place(b, mant));
+    const float y = std::fmaf(s, kPairY, c.w);
+    const float t = std::fmaf(c.z, y, c.y);
+    const float l = std::fmin(std::fmax(std::fmaf(t, y, c.x), 0.0f), 1.0f);
     const float l2 = l * l, l4 = l2 * l2;
-    *g = (l4 * root_rest(t, y, c[0], l)) * ctx->pp_unit;
-    *gs2 = (l4 * std::fmaf(c[2], y, t)) * (ctx->pp_unit * ps * ps);
+    *g = (l4 * root_rest(t, y, c.x, l)) * ctx->pp_unit;
+    *gs2 = (l4 * std::fmaf(c.z, y, t)) * (ctx->pp_unit * ps * ps);
     return true;
 }
 
