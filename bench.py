@@ -55,15 +55,16 @@ WORKLOADS = {
 # Algorithmic FP32 flops (FMA = 2) of one in-cutoff PP pair, counted from
 # the arithmetic of the compiled inner loop: 3 differences, s = r^2 with its
 # offset (3 FMA, 6), the local variable (1 FMA, 2), the row's quadratic (2 FMA,
-# 4), its square, fourth and fifth power (3), 3 accumulating FMA (6).  The
-# table index (a bit field and an address) is integer work and is not counted.
-PP_FLOPS_PER_PAIR = 24
+# 4), the fifth factor with its rounding taken back (2 FMA, 4), square, fourth
+# power and product (3), 3 accumulating FMA (6).  The table index (a bit field
+# and an address) is integer work and is not counted.
+PP_FLOPS_PER_PAIR = 28
 
 
 # VALU instructions per candidate pair of the compiled forward PP inner loop
-# (gfx950 ISA: 70 per iteration of the four-pair unrolled loop), and the
+# (gfx950 ISA: 78 per iteration of the four-pair unrolled loop), and the
 # unpacked FP32 VALU issue rate (lane-ops per second).
-PP_VALU_PER_PAIR = 17.5
+PP_VALU_PER_PAIR = 19.5
 VALU_LANE_OPS = 256 * 4 * 16 * 2.4e9
 
 

@@ -789,18 +789,25 @@ __global__ __launch_bounds__(kOrderBlock) void order_tiles_kernel(
     }
     if (tid == 0) *queue = 0u;
     if (xcd_queue && tid < kXcdQueueWords) xcd_queue[tid] = 0u;
+    __shared__ uint32_t heavy_sh;
+    if (tid == 255) heavy_sh = key_start;
     __syncthreads();
+    const bool list = keys && heavy_sh != 0u;
 #pragma unroll
     for (int r = 0; r < PER; ++r)
         if (key[r] < 256u) {
             const uint32_t i = wcnt[w][key[r]] + place[r];
             order[i] = tile[r];
-            sv[i] = tile[r];
-            sk[i] = (uint8_t)key[r];
+            if (list) {
+                sv[i] = tile[r];
+                sk[i] = (uint8_t)key[r];
+            }
         }
-    if (!keys) return;
-    __shared__ uint32_t heavy_sh;
-    if (tid == 255) heavy_sh = counts[0] = key_start;
+    if (keys && tid == 0) counts[0] = heavy_sh;
+    if (!list) {
+        if (keys && tid == 0) counts[1] = counts[2] = 0u;
+        return;
+    }
     const float work = whole_work(tid < 255 ? (float)mine * work_of_key((uint32_t)tid) : 0.0f, sum_sh);
     list_parts(heavy_sh, work, pp, [&](uint32_t i) { return (uint32_t)sk[i]; }, [&](uint32_t i) { return sv[i]; },
                parts, counts, scan_sh);

@@ -6,17 +6,19 @@
 // for 2 < b_f <= 4 within two cells (125); the cell-sorted particle order is
 // the linked list of the paper (section 2.3).
 //
-// One workgroup per tile.  The particles of the tile and of its halo of H
-// cells (a (8 + 2H)^3 box of IOS cells) are staged in LDS as FP32 positions
-// relative to the tile origin in fine cells.  Offsets are multiples of 2^-15
-// below 2^5, so these floats and their differences are exact: the pair
-// separation is the exact integer one.  Each thread takes one particle of the
-// tile and loops over its neighbour cells, which in the staged box are
-// (2H + 1)^2 contiguous ranges (x-rows of 2H + 1 cells); neighbours in a
-// dense cell are read by all lanes of a wave at the same LDS address (a
-// broadcast).  Per range the pair sum is accumulated in FP32 and then added
-// to the total with Kahan compensation.  Boxes too large for LDS pass through
-// it in parts.
+// The particles of a tile and of its halo of H cells (a (8 + 2H)^3 box of IOS
+// cells; a light tile: of one or two of its layers of cells) are staged in LDS
+// as FP32 positions relative to the tile origin in fine cells.  Offsets are
+// multiples of 2^-15 below 2^5, so these floats and their differences are
+// exact: the pair separation is the exact integer one.  A thread takes one
+// particle (where tiles with much work are few, four threads share one) and
+// loops over its neighbour cells, which in the staged box are (2H + 1)^2
+// contiguous ranges (x-rows of 2H + 1 cells); neighbours in a dense cell are
+// read by all lanes of a wave at the same LDS address (a broadcast).  Per range
+// the pair sum is accumulated in FP32 and then added to the total with Kahan
+// compensation.  Whole workgroups take the heavy tiles, or listed parts of them,
+// single waves the light ones.  Boxes too large for LDS pass through it in
+// parts.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -142,7 +144,7 @@ __device__ __forceinline__ void kahan_add(float &s, float &c, float v) {
 
 __device__ __forceinline__ float unit_clamp(float x) { return __builtin_amdgcn_fmed3f(x, 0.0f, 1.0f); }
 
-// Place of the row of s (float bits b) in the forward table.
+// Place of the row of s (float bits b) in the table of 2^mant rows per octave.
 __host__ __device__ __forceinline__ uint32_t row_place(uint32_t b, int mant) {
     return (b >> (23 - mant)) & (uint32_t)((kSOctaves << mant) - 1);
 }
@@ -566,7 +568,7 @@ __device__ __forceinline__ void light_tiles(unsigned char *lds, const uint16_t *
 
 // ADJ = false: acc = G m sum_j g D (forward).  ADJ = true: out = G m sum_j
 // J(D) (abar_j - abar_i) for the cotangent abar (the adjoint), which stages
-// abar_j beside x_j and so holds half as many particles per chunk.
+// abar_j beside x_j.
 template <bool ADJ, int H, bool CLAMP>
 __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK), 4) void pp_kernel(const uint16_t *__restrict__ pos,
                                                      const uint32_t *__restrict__ cs, int n,
@@ -642,7 +644,7 @@ __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK), 4) void pp_kernel(const uin
         const int tx = t % nt, ty = (t / nt) % nt, tz = t / (nt * nt);
         const int c0x = tx * kTileIos, c0y = ty * kTileIos, c0z = tz * kTileIos;
 
-        // particle ranges of the 10^3 box of IOS cells [c0-1, c0+9)
+        // particle ranges of the (8 + 2H)^3 box of IOS cells [c0-H, c0+8+H)
         uint32_t cnt[kPSegPerThread], src[kPSegPerThread], pre_k[kPSegPerThread];
         uint32_t sum = 0, mx = 0;
 #pragma unroll
@@ -677,7 +679,7 @@ __global__ __launch_bounds__((PPGeo<ADJ, H>::BLOCK), 4) void pp_kernel(const uin
         }
         if (tid == 0) seg_pre[kPSegs] = total;
         __syncthreads();
-        // own cells (box segments with coordinates 1..8): their particle
+        // own cells (box segments with coordinates H..H+7): their particle
         // starts relative to the tile's first particle, from the box ranges
         // (the own cells' particles are one contiguous range)
         const uint32_t p0 = seg_pre[(H * kPB + H) * kPB + H] + seg_delta[(H * kPB + H) * 3 + 1];
