@@ -22,11 +22,90 @@ namespace {
 // candidate, read from HBM cell by cell, 118 us now.
 constexpr int kPP64Block = 512, kPP64List = 16;
 
+// Where a tile has only a few particles that work is all latency: the box's list, its
+// barriers and two workgroups on a CU for 13 particles of 512 threads.  So where the tiles
+// outnumber those workgroups and have at most kPP64Mean particles on average, the tiles
+// that have at most kPP64Few and no neighbour with more are one wave's, which reads its
+// neighbours from memory; the others, if any, are found and done by the workgroups of a
+// second launch.  us so and with the boxes alone, one-cell reach: 13 per tile, 256^3 mesh
+// 14 and 35, 512^3 60 and 276; 53 per tile 23 and 38, 103 and 294; 107 per tile (boxes alone) 53.
+constexpr int kPP64Few = 128, kPP64Grid = 512;
+constexpr int64_t kPP64Mean = 64;
+
+// particles of tile (x, y, z), periodic
+__device__ __forceinline__ uint32_t tile_count(const uint32_t *__restrict__ cs, int nt, int x, int y, int z) {
+    const int m = nt - 1;
+    const uint32_t key = (uint32_t)(((z & m) * nt + (y & m)) * nt + (x & m)) * kTileCells;
+    return cs[key + kTileCells] - cs[key];
+}
+
+// the pair law's g(r) of r^2 > 0 in fine cells, from its rows
+__device__ __forceinline__ double pair64(const double *__restrict__ rows, int K, double kinv, double r2) {
+    const double r = sqrt(r2);
+    const double t = r * kinv;
+    const int idx = min((int)t, K);
+    const double *q = rows + (int64_t)idx * kPairRow;
+    const double y = q[9] + q[10] * (t - floor(t));
+    double U = q[8];
+#pragma unroll
+    for (int e = 7; e >= 0; --e) U = q[e] + y * U;
+    return U / (r2 * r);
+}
+
+__global__ __launch_bounds__(64) void pp64_few_kernel(
+    const uint16_t *__restrict__ pos, const uint32_t *__restrict__ cs, int n, int nt,
+    const double *__restrict__ rows, int K, double kinv, double gm, double *__restrict__ acc,
+    int accumulate, int H) {
+    __shared__ uint32_t cst[kTileCells + 1];
+    int tx, ty, tz;
+    tile_of_block(blockIdx.x, nt, tx, ty, tz);
+    const int lane = threadIdx.x, n_ios = nt * kTileIos;
+    const bool many = lane < 27 && tile_count(cs, nt, tx + lane % 3 - 1, ty + lane / 3 % 3 - 1,
+                                              tz + lane / 9 - 1) > kPP64Few;
+    if (__any(many)) return;
+    stage_cell_starts<64>(cst, cs, (uint32_t)((tz * nt + ty) * nt + tx) * kTileCells);
+    __syncthreads();
+    for (uint32_t p = cst[0] + lane; p < cst[kTileCells]; p += 64) {
+        const int u = seg_search_n<kTileCells>(cst, p);
+        const int c[3] = {tx * kTileIos + (u & 7), ty * kTileIos + ((u >> 3) & 7), tz * kTileIos + (u >> 6)};
+        int oi[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) oi[d] = pos[(int64_t)d * n + p];
+        double a[3] = {0.0, 0.0, 0.0};
+        for (int dz = -H; dz <= H; ++dz)
+            for (int dy = -H; dy <= H; ++dy)
+#pragma unroll 5
+                for (int dx = -H; dx <= H; ++dx) {
+                    const uint32_t key = cell_key(wrapn(c[0] + dx, n_ios), wrapn(c[1] + dy, n_ios),
+                                                  wrapn(c[2] + dz, n_ios), nt);
+                    const uint32_t j1 = cs[key + 1];
+                    for (uint32_t j = cs[key]; j < j1; ++j) {
+                        // in units of 2^-15 fine cells, exact
+                        const int D[3] = {dx * 65536 + (int)pos[j] - oi[0],
+                                          dy * 65536 + (int)pos[(int64_t)n + j] - oi[1],
+                                          dz * 65536 + (int)pos[2 * (int64_t)n + j] - oi[2]};
+                        const double X = D[0] * 0x1p-15, Y = D[1] * 0x1p-15, Z = D[2] * 0x1p-15;
+                        const double r2 = X * X + Y * Y + Z * Z;
+                        if (r2 == 0.0) continue;       // the particle itself (or a coincident one)
+                        const double g = pair64(rows, K, kinv, r2);
+                        a[0] += g * X;
+                        a[1] += g * Y;
+                        a[2] += g * Z;
+                    }
+                }
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            double *dst = acc + (int64_t)d * n + p;
+            *dst = accumulate ? *dst + gm * a[d] : gm * a[d];
+        }
+    }
+}
+
 template <int H>
-__global__ __launch_bounds__(kPP64Block) void pp64_kernel(
+__device__ __forceinline__ void pp64_tile(
     const uint16_t *__restrict__ pos, const uint32_t *__restrict__ cs, int n, int nt,
     const double *__restrict__ rows, int K, double kinv, float cut, double gm,
-    double *__restrict__ acc, int accumulate) {
+    double *__restrict__ acc, int accumulate, int block) {
     constexpr int B = kTileIos + 2 * H, SEGS = B * B * B, W = 2 * H + 1;
     using List = BoxList<SEGS, kPP64Block>;
     __shared__ typename List::Shared lsh;
@@ -34,7 +113,7 @@ __global__ __launch_bounds__(kPP64Block) void pp64_kernel(
     __shared__ uint32_t pre[SEGS + 1], cst[kTileCells + 1];
     __shared__ uint16_t held_at[kPP64List][kPP64Block];
     int tx, ty, tz;
-    tile_of_block(blockIdx.x, nt, tx, ty, tz);
+    tile_of_block(block, nt, tx, ty, tz);
     const int tid = threadIdx.x, lane = tid & 63, wave = wave_id(), n_ios = nt * kTileIos;
     const uint32_t key0 = (uint32_t)((tz * nt + ty) * nt + tx) * kTileCells;
     const uint32_t p0 = cs[key0], own = cs[key0 + kTileCells] - p0;
@@ -100,15 +179,7 @@ __global__ __launch_bounds__(kPP64Block) void pp64_kernel(
                     const double X = (xs[0][v] - xi[0]) * 0x1p-15f, Y = (xs[1][v] - xi[1]) * 0x1p-15f,
                                  Z = (xs[2][v] - xi[2]) * 0x1p-15f;          // exact
                     const double r2 = X * X + Y * Y + Z * Z;
-                    const double r = sqrt(r2);
-                    const double t = r * kinv;
-                    const int idx = min((int)t, K);
-                    const double *q = rows + (int64_t)idx * kPairRow;
-                    const double y = q[9] + q[10] * (t - floor(t));
-                    double U = q[8];
-#pragma unroll
-                    for (int e = 7; e >= 0; --e) U = q[e] + y * U;
-                    const double g = U / (r2 * r);
+                    const double g = pair64(rows, K, kinv, r2);
                     a[0] += g * X;
                     a[1] += g * Y;
                     a[2] += g * Z;
@@ -145,6 +216,42 @@ __global__ __launch_bounds__(kPP64Block) void pp64_kernel(
     }
 }
 
+// FEW: the tiles that pp64_few_kernel leaves.
+template <int H, bool FEW>
+__global__ __launch_bounds__(kPP64Block) void pp64_kernel(
+    const uint16_t *__restrict__ pos, const uint32_t *__restrict__ cs, int n, int nt,
+    const double *__restrict__ rows, int K, double kinv, float cut, double gm,
+    double *__restrict__ acc, int accumulate) {
+    if constexpr (!FEW) {
+        pp64_tile<H>(pos, cs, n, nt, rows, K, kinv, cut, gm, acc, accumulate, (int)blockIdx.x);
+    } else {
+        __shared__ uint64_t left[kPP64Block / 64];
+        const int ntiles = nt * nt * nt, grid = (int)gridDim.x;
+        for (int b0 = (int)blockIdx.x; b0 < ntiles; b0 += grid * kPP64Block) {
+            // thread i looks at the workgroup's i-th tile from here
+            const int64_t b = b0 + (int64_t)threadIdx.x * grid;
+            bool many = false;
+            if (b < ntiles) {
+                int x, y, z;
+                tile_of_block((int)b, nt, x, y, z);
+#pragma unroll
+                for (int k = 0; k < 27; ++k)
+                    many |= tile_count(cs, nt, x + k % 3 - 1, y + k / 3 % 3 - 1, z + k / 9 - 1) > kPP64Few;
+            }
+            const uint64_t m = __ballot(many);
+            __syncthreads();
+            if ((threadIdx.x & 63) == 0) left[wave_id()] = m;
+            __syncthreads();
+            for (int w = 0; w < kPP64Block / 64; ++w)
+                for (uint64_t r = left[w]; r; r &= r - 1) {
+                    const int i = 64 * w + __ffsll((long long)r) - 1;
+                    pp64_tile<H>(pos, cs, n, nt, rows, K, kinv, cut, gm, acc, accumulate, b0 + i * grid);
+                    __syncthreads();
+                }
+        }
+    }
+}
+
 }  // namespace
 
 int launch_pp64(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t n, double *acc,
@@ -152,10 +259,18 @@ int launch_pp64(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, int64_t
     const double *rows = reinterpret_cast<const double *>(ctx->tables + ctx->pp64_off);
     const int nt = ctx->nt;
     const double bf = ctx->cfg.b_fine * 32768.0;     // in position units, at most 2^17
-    auto *k = ctx->pp_halo == 1 ? pp64_kernel<1> : pp64_kernel<2>;
-    k<<<(unsigned)(nt * nt * nt), kPP64Block, 0, s>>>(
-        pos, cs, (int)n, nt, rows, ctx->pp_K, (double)ctx->pp_K / ctx->cfg.b_fine,
-        (float)(bf * bf * (1 + 1e-5)), ctx->cfg.g_newton * ctx->cfg.m_p, acc, accumulate);
+    const double kinv = (double)ctx->pp_K / ctx->cfg.b_fine, gm = ctx->cfg.g_newton * ctx->cfg.m_p;
+    const int ntiles = nt * nt * nt;
+    const bool few = ntiles > kPP64Grid && n <= kPP64Mean * ntiles;
+    if (few) {
+        pp64_few_kernel<<<(unsigned)ntiles, 64, 0, s>>>(pos, cs, (int)n, nt, rows, ctx->pp_K, kinv, gm, acc,
+                                                        accumulate, ctx->pp_halo);
+        CUBE2_LAUNCH_CHECK();
+    }
+    auto *k = few ? (ctx->pp_halo == 1 ? pp64_kernel<1, true> : pp64_kernel<2, true>)
+                  : (ctx->pp_halo == 1 ? pp64_kernel<1, false> : pp64_kernel<2, false>);
+    k<<<(unsigned)(few ? kPP64Grid : ntiles), kPP64Block, 0, s>>>(
+        pos, cs, (int)n, nt, rows, ctx->pp_K, kinv, (float)(bf * bf * (1 + 1e-5)), gm, acc, accumulate);
     CUBE2_LAUNCH_CHECK();
     return CUBE2_OK;
 }
