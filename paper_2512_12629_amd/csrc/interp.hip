@@ -135,15 +135,19 @@ __device__ __forceinline__ void gather_field(const Vec4<T> *F, int S, const int 
 // TSC gather all 256 VGPRs and one wave per SIMD.  FINE = false gathers the
 // coarse level only (the tile+buffer mode computes the fine level per tile).
 // HS > 0 fixes log2 of the coarse ratio at compile time (the coarse tile's
-// LDS strides then fold into immediate offsets); HS = 0 reads it from hshift.
+// LDS strides then fold into immediate offsets); HS = 0 reads it from hshift.  HS = 1
+// takes the coarse potential's lines, the others its node forces (kLinesPerTile).
 template <bool TWO, int P, typename T, bool FINE, int HS, int BLOCK>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void interp_kernel(
     const uint16_t *__restrict__ pos, const uint32_t *__restrict__ cs, int n, int n_f, int nt,
     const T *__restrict__ phi_f, const T *__restrict__ phi_c, int n_c, int hshift_arg, T scale_f,
     T scale_c, T *__restrict__ acc, int accumulate, const T *__restrict__ extra) {
     constexpr int FS = InterpGeo<P>::FS, HLO = InterpGeo<P>::HLO, CSM = coarse_field_max<P, HS>();
+    constexpr bool LINES = TWO && HS == 1;
+    constexpr int CL = kTileFine / 2 + FS - kTileFine;      // the coarse potential's side then
     __shared__ T pf[FINE ? FS * FS * FS : 1];
-    __shared__ Vec4<T> pc[TWO ? CSM * CSM * CSM : 1];
+    __shared__ Vec4<T> pc[TWO && !LINES ? CSM * CSM * CSM : 1];
+    __shared__ T pl[LINES ? CL * CL * CL : 1];
     __shared__ uint32_t cst[kTileCells + 1];
 
     int tx, ty, tz;
@@ -155,7 +159,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
     const int ax0 = tx * kTileFine, ay0 = ty * kTileFine, az0 = tz * kTileFine;
     if (FINE) stage_block<FS, BLOCK>(pf, phi_f, n_f, ax0 - HLO, ay0 - HLO, az0 - HLO);
     const int CS = (kTileFine >> hshift) + 1 + 2 * coarse_field_lo<P>();
-    if (TWO) stage_coarse_field<P, BLOCK, T>(pc, phi_c, nullptr, n_c, hshift, ax0, ay0, az0);
+    if constexpr (LINES)
+        stage_block<CL, BLOCK>(pl, phi_c, n_c, (ax0 >> 1) - HLO, (ay0 >> 1) - HLO, (az0 >> 1) - HLO);
+    else if (TWO)
+        stage_coarse_field<P, BLOCK, T>(pc, phi_c, nullptr, n_c, hshift, ax0, ay0, az0);
     __syncthreads();
     const uint32_t p0 = cst[0], p1 = cst[kTileCells];
     const T inv = T(1.0 / 32768.0);
@@ -214,7 +221,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
                 }
                 if (TWO) {
                     T c[3];
-                    gather_field<3, T>(pc, CS, jc, wc, c);
+                    if constexpr (LINES)
+                        gather3(pl, CL, jc[0] + HLO, jc[1] + HLO, jc[2] + HLO, wc[0], wc[1], wc[2], c[0], c[1],
+                                c[2]);
+                    else
+                        gather_field<3, T>(pc, CS, jc, wc, c);
                     a[0] += scale_c * c[0];
                     a[1] += scale_c * c[1];
                     a[2] += scale_c * c[2];
@@ -245,7 +256,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
                 }
                 if (TWO) {
                     T c[3];
-                    gather_field<2, T>(pc, CS, jc, wc, c);
+                    if constexpr (LINES)
+                        gather(pl, CL, jc[0] + HLO, jc[1] + HLO, jc[2] + HLO, wc[0], wc[1], wc[2], c[0], c[1],
+                               c[2]);
+                    else
+                        gather_field<2, T>(pc, CS, jc, wc, c);
                     a[0] += scale_c * c[0];
                     a[1] += scale_c * c[1];
                     a[2] += scale_c * c[2];
@@ -263,28 +278,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
 
 }  // namespace
 
-template <int P, typename T, int BLOCK>
-void launch_interp_block(cube2_ctx *ctx, unsigned blocks, const uint16_t *pos, const uint32_t *cs,
-                         int64_t n, const T *phi_f, const T *phi_c, double gm, T *acc,
-                         int accumulate, const T *extra, bool fine, bool coarse, hipStream_t s) {
-    const int nt = ctx->nt;
-    if (coarse && !fine) {
-        const Level &C = ctx->lv[1];
-        interp_kernel<true, P, T, false, 0, BLOCK><<<blocks, BLOCK, 0, s>>>(
-            pos, cs, (int)n, ctx->n_f, nt, nullptr, phi_c, C.n, C.hshift, T(0),
-            (T)(gm / ((double)C.H * C.H)), acc, accumulate, extra);
-    } else if (coarse) {
-        const Level &C = ctx->lv[1];
-        auto *k = C.hshift == 2 ? interp_kernel<true, P, T, true, 2, BLOCK>
-                                : interp_kernel<true, P, T, true, 0, BLOCK>;
-        k<<<blocks, BLOCK, 0, s>>>(pos, cs, (int)n, ctx->n_f, nt, phi_f, phi_c, C.n, C.hshift,
-                                   (T)gm, (T)(gm / ((double)C.H * C.H)), acc, accumulate, extra);
-    } else {
-        interp_kernel<false, P, T, true, 0, BLOCK><<<blocks, BLOCK, 0, s>>>(
-            pos, cs, (int)n, ctx->n_f, nt, phi_f, nullptr, 1, 0, (T)gm, T(0), acc, accumulate, extra);
-    }
-}
-
 // Threads per workgroup.  512 where few workgroups are resident in any case and a tile
 // is the latency of its staging and of one wave's particles: up to two tiles per CU
 // (64 tiles: 7.7 us at 256 threads, 5.8 at 512), and the TSC tiles in single precision,
@@ -293,6 +286,39 @@ void launch_interp_block(cube2_ctx *ctx, unsigned blocks, const uint16_t *pos, c
 // (1024^3 CIC: 3.72 ms at 256, 4.45 at 512, 6.58 at 1024; FP64 CIC, 256^3: 93 us, 115
 // and 114).
 constexpr int kSmallTiles = 512;
+
+// Ratio 2 (HS = 1): up to so many particles per tile the coarse potential is staged and its
+// lines read as the fine level's.  The node forces are 9^3 nodes of 12 scattered loads
+// each, for few particles per node.  us as lines and as node forces: CIC on a 512^3 mesh,
+// 109 particles per tile 377 and 470, 512 471 and 543, 1117 731 and 768, on 256^3 4096 232
+// and 222; TSC, 512 984 and 1090, 4096 620 and 520.
+constexpr int64_t kLinesPerTile = 2048;
+
+template <int P, typename T, int BLOCK>
+void launch_interp_block(cube2_ctx *ctx, unsigned blocks, const uint16_t *pos, const uint32_t *cs,
+                         int64_t n, const T *phi_f, const T *phi_c, double gm, T *acc,
+                         int accumulate, const T *extra, bool fine, bool coarse, hipStream_t s) {
+    const int nt = ctx->nt;
+    const bool lines = coarse && ctx->lv[1].hshift == 1 && n <= kLinesPerTile * (int64_t)blocks;
+    if (coarse && !fine) {
+        const Level &C = ctx->lv[1];
+        auto *k = lines ? interp_kernel<true, P, T, false, 1, BLOCK>
+                        : interp_kernel<true, P, T, false, 0, BLOCK>;
+        k<<<blocks, BLOCK, 0, s>>>(
+            pos, cs, (int)n, ctx->n_f, nt, nullptr, phi_c, C.n, C.hshift, T(0),
+            (T)(gm / ((double)C.H * C.H)), acc, accumulate, extra);
+    } else if (coarse) {
+        const Level &C = ctx->lv[1];
+        auto *k = C.hshift == 2 ? interp_kernel<true, P, T, true, 2, BLOCK>
+                  : lines ? interp_kernel<true, P, T, true, 1, BLOCK>
+                          : interp_kernel<true, P, T, true, 0, BLOCK>;
+        k<<<blocks, BLOCK, 0, s>>>(pos, cs, (int)n, ctx->n_f, nt, phi_f, phi_c, C.n, C.hshift,
+                                   (T)gm, (T)(gm / ((double)C.H * C.H)), acc, accumulate, extra);
+    } else {
+        interp_kernel<false, P, T, true, 0, BLOCK><<<blocks, BLOCK, 0, s>>>(
+            pos, cs, (int)n, ctx->n_f, nt, phi_f, nullptr, 1, 0, (T)gm, T(0), acc, accumulate, extra);
+    }
+}
 
 // levels: bit 0 the fine level, bit 1 the coarse level (if the context has one)
 template <int P, typename T>
