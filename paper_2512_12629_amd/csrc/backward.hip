@@ -507,8 +507,8 @@ constexpr int kGatherBlock = 512;
 
 // HS > 0 fixes log2 of the coarse ratio at compile time (the coarse tiles'
 // LDS strides then fold into immediate offsets); HS = 0 reads it from hshift.
-template <bool WITH_E, bool TWO, int P, int HS = 0>
-__global__ __launch_bounds__(kGatherBlock) void xbar_gather_kernel(
+template <bool WITH_E, bool TWO, int P, int HS = 0, int BLOCK = kGatherBlock>
+__global__ __launch_bounds__(BLOCK) void xbar_gather_kernel(
     const uint16_t *__restrict__ pos, const uint32_t *__restrict__ cs,
     const float *__restrict__ abar, int n, int n_f, int nt, const float *__restrict__ phi_f,
     const float *__restrict__ rb_f, float c_f, const float *__restrict__ phi_c,
@@ -517,28 +517,35 @@ __global__ __launch_bounds__(kGatherBlock) void xbar_gather_kernel(
     const int hshift = HS > 0 ? HS : hshift_arg;
     using G = GatherGeo<P>;
     constexpr int kFS = G::FS, kRS = G::RS, kCMax = coarse_field_max<P, HS>();
+    constexpr bool COARSE = TWO && !WITH_E;   // the coarse level's density alone
     __shared__ float pf[WITH_E ? kFS * kFS * kFS : 1];
-    __shared__ float rf[kRS * kRS * kRS];
-    __shared__ Vec4<float> pc[TWO ? kCMax * kCMax * kCMax : 1];
+    __shared__ float rf[COARSE ? kCMax * kCMax * kCMax : kRS * kRS * kRS];
+    __shared__ Vec4<float> pc[TWO && WITH_E ? kCMax * kCMax * kCMax : 1];
     __shared__ uint32_t cst[kTileCells + 1];
     int tx, ty, tz;
     tile_of_block(blockIdx.x, nt, tx, ty, tz);
     const int tid = threadIdx.x;
     const uint32_t key0 = (uint32_t)((tz * nt + ty) * nt + tx) * kTileCells;
-    stage_cell_starts<kGatherBlock>(cst, cs, key0);
+    stage_cell_starts<BLOCK>(cst, cs, key0);
     const int a0x = tx * kTileFine, a0y = ty * kTileFine, a0z = tz * kTileFine;
-    if (WITH_E) stage_block<kFS, kGatherBlock>(pf, phi_f, n_f, a0x - G::PLO, a0y - G::PLO, a0z - G::PLO);
-    if (rb_f) {
-        stage_block<kRS, kGatherBlock>(rf, rb_f, n_f, a0x - G::RLO, a0y - G::RLO, a0z - G::RLO);
-    } else {
-        for (int i = tid; i < kRS * kRS * kRS; i += kGatherBlock) rf[i] = 0.0f;
-    }
+    if (WITH_E) stage_block<kFS, BLOCK>(pf, phi_f, n_f, a0x - G::PLO, a0y - G::PLO, a0z - G::PLO);
     const int CS = (kTileFine >> hshift) + 1 + 2 * coarse_field_lo<P>();
-    if (TWO)
-        stage_coarse_field<P, kGatherBlock, float>(pc, WITH_E ? phi_c : nullptr, rb_c, n_c, hshift, a0x,
-                                                   a0y, a0z);
+    if constexpr (COARSE) {
+        // (as floats: with the force's four words per node, and the fine level's nodes all
+        // zero, the TSC workgroups were two to a CU; 512^3 mesh, ratio 2, 512 per tile,
+        // 785 us, now 195, CIC 196 and 133)
+        const int m = n_c - 1, LO = coarse_field_lo<P>();
+        for (int i = tid; i < CS * CS * CS; i += BLOCK) {
+            const int x = (a0x >> hshift) - LO + i % CS, y = (a0y >> hshift) - LO + (i / CS) % CS,
+                      z = (a0z >> hshift) - LO + i / (CS * CS);
+            rf[i] = rb_c[((int64_t)(z & m) * n_c + (y & m)) * n_c + (x & m)];
+        }
+    } else {
+        stage_block<kRS, BLOCK>(rf, rb_f, n_f, a0x - G::RLO, a0y - G::RLO, a0z - G::RLO);
+        if (TWO) stage_coarse_field<P, BLOCK, float>(pc, phi_c, rb_c, n_c, hshift, a0x, a0y, a0z);
+    }
     __syncthreads();
-    for (uint32_t p = cst[0] + tid; p < cst[kTileCells]; p += kGatherBlock) {
+    for (uint32_t p = cst[0] + tid; p < cst[kTileCells]; p += BLOCK) {
         const int u = seg_search_n<kTileCells>(cst, p);
         const int uc[3] = {u & 7, (u >> 3) & 7, u >> 6};
         int jf[3], jc[3];
@@ -556,9 +563,12 @@ __global__ __launch_bounds__(kGatherBlock) void xbar_gather_kernel(
             }
         }
         float xb[3] = {0.f, 0.f, 0.f};
-        level_gather<WITH_E, P>(pf, kFS, rf, kRS, jf, wf, dwf, ab, c_f, 1.0f, xb);
-        if (TWO)
-            field_gather<P>(pc, CS, jc, wc, dwc, ab, c_c, 1.0f / (float)(1 << hshift), xb);
+        const float invH = 1.0f / (float)(1 << hshift);
+        if constexpr (COARSE)
+            level_gather<false, P>(nullptr, 0, rf, CS, jc, wc, dwc, ab, 0.0f, invH, xb);
+        else
+            level_gather<WITH_E, P>(pf, kFS, rf, kRS, jf, wf, dwf, ab, c_f, 1.0f, xb);
+        if (TWO && !COARSE) field_gather<P>(pc, CS, jc, wc, dwc, ab, c_c, invH, xb);
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
             float *dst = xbar + (int64_t)d * n + p;
@@ -583,7 +593,6 @@ void launch_deposit_backward_p(cube2_ctx *ctx, const uint16_t *pos, const uint32
             pos, cs, nullptr, (int)n, ctx->n_f, nt, nullptr, rho_bar, 0.f, nullptr, nullptr, 0.f, 1,
             0, x_bar, accumulate, nullptr);
     } else {
-        // coarse only: a zero fine rhobar contributes nothing
         const Level &C = ctx->lv[1];
         xbar_gather_kernel<false, true, P><<<blocks, kGatherBlock, 0, s>>>(
             pos, cs, nullptr, (int)n, ctx->n_f, nt, nullptr, nullptr, 0.f, nullptr, rho_bar, 0.f,
