@@ -505,6 +505,11 @@ __device__ __forceinline__ int axis_footprint(int j, int f, float (&w)[P], float
 // 7.72 ms at 256 threads, 6.40 at 512, 9.71 at 1024; one level, 256^3: 74.5, 62.3, 60.3 us).
 constexpr int kGatherBlock = 512;
 
+// The deposit's adjoint (WITH_E = false) stages far less, so that more workgroups fit a CU:
+// 256 threads, but 512 with few tiles or many particles in each.  us at 256 and 512: 512^3
+// mesh, 109 per tile 194 and 203, 512 235 and 247; 256^3, 4096 110 and 104, TSC 159 and 145.
+constexpr int64_t kDepositTiles = 512, kDepositPerTile = 2048;
+
 // HS > 0 fixes log2 of the coarse ratio at compile time (the coarse tiles'
 // LDS strides then fold into immediate offsets); HS = 0 reads it from hshift.
 template <bool WITH_E, bool TWO, int P, int HS = 0, int BLOCK = kGatherBlock>
@@ -588,13 +593,16 @@ void launch_deposit_backward_p(cube2_ctx *ctx, const uint16_t *pos, const uint32
                                hipStream_t s) {
     const int nt = ctx->nt;
     const unsigned blocks = (unsigned)(nt * nt * nt);
+    const bool wide = blocks <= kDepositTiles || n > kDepositPerTile * (int64_t)blocks;
     if (level == 0) {
-        xbar_gather_kernel<false, false, P><<<blocks, kGatherBlock, 0, s>>>(
+        auto *k = wide ? xbar_gather_kernel<false, false, P> : xbar_gather_kernel<false, false, P, 0, kBlock>;
+        k<<<blocks, wide ? kGatherBlock : kBlock, 0, s>>>(
             pos, cs, nullptr, (int)n, ctx->n_f, nt, nullptr, rho_bar, 0.f, nullptr, nullptr, 0.f, 1,
             0, x_bar, accumulate, nullptr);
     } else {
         const Level &C = ctx->lv[1];
-        xbar_gather_kernel<false, true, P><<<blocks, kGatherBlock, 0, s>>>(
+        auto *k = wide ? xbar_gather_kernel<false, true, P> : xbar_gather_kernel<false, true, P, 0, kBlock>;
+        k<<<blocks, wide ? kGatherBlock : kBlock, 0, s>>>(
             pos, cs, nullptr, (int)n, ctx->n_f, nt, nullptr, nullptr, 0.f, nullptr, rho_bar, 0.f,
             C.n, C.hshift, x_bar, accumulate, nullptr);
     }
