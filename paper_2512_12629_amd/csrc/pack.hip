@@ -848,8 +848,10 @@ int radix_pass(const uint32_t *kin, const uint32_t *vin, uint32_t *kout, uint32_
 }
 
 // How the particles are sorted: by tile in `passes` digits of `bits` bits from
-// key bit `shift` on and then by cell within the tiles, or (few particles per
-// tile, or one tile) by the whole key, 8 bits a pass.
+// key bit `shift` on and then by cell within the tiles, or (one tile) by the whole
+// key, 8 bits a pass.  (By the whole key also where a tile has less than 64 particles, pack
+// took, us, on a 64^3 mesh with 729 particles 44 and not 24, 256^3 with 8000 123 and 53, with
+// 54872 86 and 59, 512^3 with 64000 131 and 109; with 0.44 million 109 and not 115.)
 struct SortPlan {
     bool by_tile;
     int bits, shift, passes;
@@ -859,8 +861,7 @@ SortPlan sort_plan(const cube2_ctx *ctx, int64_t n) {
     int bits = 0;
     while (((int64_t)kTileCells << bits) < ctx->n_cells) ++bits;
     SortPlan p;
-    // a workgroup per tile: 64 particles and more pay for it
-    p.by_tile = bits > 0 && n >= 64 * ntiles;
+    p.by_tile = bits > 0;
     p.shift = p.by_tile ? 9 : 0;
     const int all = p.by_tile ? bits : bits + 9;
     p.bits = p.by_tile && (all == 9 || all > 16) ? 9 : 8;   // 18 bits in two passes
