@@ -514,9 +514,11 @@ __global__ void kd_backward(const int32_t *__restrict__ perm, const float *__res
 
 }  // namespace
 
-// The local re-sort has a workgroup per tile in both passes; with only a few
-// particles per tile the radix sort costs less.
-constexpr int64_t kLocalPerTile = 32;
+// The local re-sort has a workgroup per tile in both passes; with only a few particles
+// per tile the radix sort costs less.  us, local and radix: 34 per tile 254 and 166 on a
+// 512^3 mesh, 43 and 33 on 128^3; 109 per tile 301 and 243, 43 and 34; 181 per tile, local,
+// 350 (sorts of the whole key 395); 512 per tile 521 (869).
+constexpr int64_t kLocalPerTile = 128;
 
 int launch_kick_drift(cube2_ctx *ctx, const uint16_t *pos_in, const uint32_t *cs_in,
                       const float *vel_in, const float *acc, int64_t n64, double kick,
@@ -528,7 +530,12 @@ int launch_kick_drift(cube2_ctx *ctx, const uint16_t *pos_in, const uint32_t *cs
     const int ntiles = nt * nt * nt;
     uint32_t *run = nullptr;
     HeavySlices heavy{};
-    if (n64 >= kLocalPerTile * (int64_t)ntiles) {
+    // Where neither a heavy tile nor, with at most two tiles per axis, a far particle is
+    // possible, the radix sort's kernels are not launched: 16^3 mesh, 512 particles 47 us
+    // with them, 22 without; so that also with a few particles per tile the local re-sort
+    // is the faster there.  One heavy tile is left to the radix sort from the start.
+    const bool heavies = n > (int)kHeavyTile, sure = nt <= 2 && !heavies;
+    if (n > 0 && (sure || (n64 >= kLocalPerTile * (int64_t)ntiles && !(heavies && ntiles == 1)))) {
         // the groups and the tiles' tables take the places of the sort's
         // buffers and of the fine mesh
         Moved m;
@@ -558,6 +565,7 @@ int launch_kick_drift(cube2_ctx *ctx, const uint16_t *pos_in, const uint32_t *cs
         local_merge<<<(unsigned)ntiles, kBlock, 0, s>>>(cs_in, n, nt, m, pre, starts, sums, fars, nblocks,
                                                         far, pos_out, cs_out, vel_out, perm_out, run);
         CUBE2_LAUNCH_CHECK();
+        if (sure) return CUBE2_OK;
     }
     if (n > 0) {
         kick_drift_kernel<<<(unsigned)(run ? std::min(ntiles, 2048) : ntiles), kBlock, 0, s>>>(
