@@ -165,14 +165,18 @@ __device__ __forceinline__ float vel_step(unsigned int dmax_bits) {
 
 // Per tile: q = rint((v - v_bulk) / s) (ENCODE: reads vel_in and amax,
 // writes vq_out and v_scale_out) or v = v_bulk + s q (decode: reads vq_in and
-// v_scale, writes vel_out).
+// v_scale, writes vel_out).  The tile's bulk velocities are staged, but from few particles
+// (kStagedPerTile) read where they are: at ratio 2 they are 6 kB a tile.  Decode, us, staged
+// and not: 512^3 mesh, ratio 2, 13 per tile 54 and 27, 109 82 and 40, 512 133 and 146; ratio 4,
+// 13 per tile 29 and 27.
+constexpr int64_t kStagedPerTile = 128;
 template <bool ENCODE>
 __global__ __launch_bounds__(kBlock) void vel_code_kernel(
     const uint32_t *__restrict__ cs, int n, int nt, int shift, int nb,
     const float *__restrict__ v_bulk, const unsigned int *__restrict__ amax,
     const float *__restrict__ vel_in, int16_t *__restrict__ vq_out, float *__restrict__ v_scale_out,
     const float *__restrict__ v_scale, const int16_t *__restrict__ vq_in,
-    float *__restrict__ vel_out) {
+    float *__restrict__ vel_out, bool staged) {
     __shared__ uint32_t cst[kTileCells + 1];
     __shared__ float vb[3][kTileCells];
     int tx, ty, tz;
@@ -181,11 +185,12 @@ __global__ __launch_bounds__(kBlock) void vel_code_kernel(
     const int ct = kTileFine >> shift;
     const uint32_t key0 = (uint32_t)((tz * nt + ty) * nt + tx) * kTileCells;
     const int64_t m3 = (int64_t)nb * nb * nb;
-    for (int i = tid; i < ct * ct * ct; i += kBlock) {
-        const int64_t g = bulk_index(tx, ty, tz, i, ct, nb);
+    if (staged)
+        for (int i = tid; i < ct * ct * ct; i += kBlock) {
+            const int64_t g = bulk_index(tx, ty, tz, i, ct, nb);
 #pragma unroll
-        for (int d = 0; d < 3; ++d) vb[d][i] = v_bulk[d * m3 + g];
-    }
+            for (int d = 0; d < 3; ++d) vb[d][i] = v_bulk[d * m3 + g];
+        }
     stage_cell_starts<kBlock>(cst, cs, key0);
     __syncthreads();
     const float s = ENCODE ? vel_step(amax[1]) : v_scale[0];
@@ -206,9 +211,10 @@ __global__ __launch_bounds__(kBlock) void vel_code_kernel(
             const uint32_t p = c0 + k * kBlock;
             if (p >= p1) continue;
             const int lc = bulk_cell(seg_search_n<kTileCells>(cst, p), shift, ct);
+            const int64_t g = bulk_index(tx, ty, tz, lc, ct, nb);
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
-                const float b = vb[d][lc];
+                const float b = staged ? vb[d][lc] : v_bulk[d * m3 + g];
                 if (ENCODE) {
                     const float r = rintf(__fdiv_rn(__fsub_rn(v[k][d], b), s));
                     vq_out[(int64_t)d * n + p] = (int16_t)fminf(fmaxf(r, -32767.0f), 32767.0f);
@@ -284,7 +290,8 @@ int launch_vel_encode(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, i
     if (r) return r;
     (void)pos;
     vel_code_kernel<true><<<blocks, kBlock, 0, s>>>(cs, (int)n, nt, shift, nb, v_bulk, amax,
-                                                    vel, vq, v_scale, nullptr, nullptr, nullptr);
+                                                    vel, vq, v_scale, nullptr, nullptr, nullptr,
+                                                    n >= kStagedPerTile * (int64_t)blocks);
     CUBE2_LAUNCH_CHECK();
     return CUBE2_OK;
 }
@@ -298,7 +305,8 @@ int launch_vel_decode(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, i
     const int shift = bulk_shift(ctx), nb = ctx->n_f >> shift;
     (void)pos;
     vel_code_kernel<false><<<blocks, kBlock, 0, s>>>(cs, (int)n, nt, shift, nb, v_bulk, nullptr,
-                                                     nullptr, nullptr, nullptr, v_scale, vq, vel);
+                                                     nullptr, nullptr, nullptr, v_scale, vq, vel,
+                                                     n >= kStagedPerTile * (int64_t)blocks);
     CUBE2_LAUNCH_CHECK();
     return CUBE2_OK;
 }
