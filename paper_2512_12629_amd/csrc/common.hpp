@@ -255,10 +255,6 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *s
     return off + x - v;
 }
 
-// A tile of more particles than this is sorted, and drifted, in chunks of so many by
-// several workgroups: one takes 5 ns a particle to sort and 9 to drift.
-constexpr uint32_t kHeavyTile = 8192;
-
 // Stable sort by cell of one tile's `total` elements, the first of which comes to
 // particle `start` (all kBlock threads call it): each wave takes a contiguous part of
 // them; the cells' counts per wave give the starts of the cells (written to

@@ -44,11 +44,17 @@ __device__ __forceinline__ void drifted(const uint16_t *__restrict__ pos, const 
     }
 }
 
-// Tiles of more than kHeavyTile particles that the local re-sort left: the entries {tile,
-// slice} of all their slices of so many.
+// Tiles of more than `limit` particles, with which a step is the radix sort's: the entries
+// {tile, slice} of all their slices of kHeavySlice.  One workgroup of the local re-sort
+// takes ~15 ns a particle, the radix sort in its place ~15 ns per thousand of all: a limit
+// of 4096 up to a million particles, 8192 above.  us, local and radix: 133 thousand, one tile
+// of 7026 109 and 79; 8.5 million, one of 8063 372 and 484 (sorts of the whole key 98, 486).
+constexpr uint32_t kHeavySlice = 2048;
+uint32_t heavy_limit(int64_t n) { return n > (1 << 20) ? 8192u : 4096u; }
 struct HeavySlices {
     uint32_t *count;
     uint2 *list;
+    uint32_t limit;
 };
 
 __global__ __launch_bounds__(kBlock) void kick_drift_kernel(
@@ -77,9 +83,9 @@ __global__ __launch_bounds__(kBlock) void kick_drift_kernel(
         stage_cell_starts<kBlock>(cst, cs, key0);
         __syncthreads();
         uint32_t p0 = cst[0], p1 = cst[kTileCells];
-        if (run && p1 - p0 > kHeavyTile) {
-            p0 = b < ntiles ? p1 : p0 + slice * kHeavyTile;
-            p1 = min(p1, p0 + kHeavyTile);
+        if (run && p1 - p0 > heavy.limit) {
+            p0 = b < ntiles ? p1 : p0 + slice * kHeavySlice;
+            p1 = min(p1, p0 + kHeavySlice);
         }
         for (uint32_t p = p0 + tid; p < p1; p += kBlock) {
             const int u = seg_search_n<kTileCells>(cst, p);
@@ -160,13 +166,44 @@ __global__ void far_clear(uint32_t *count, uint32_t *heavy) {
     *heavy = 0u;
 }
 
+// The heavy tiles' slices listed; if there are any the count of far particles is past its
+// list, so that the local kernels end at once.  (Heavy tiles found by local_split itself let
+// the tiles before them do their work in vain, a quarter of the step.)  A single workgroup
+// (alone) also clears the counts; on a 512^3 mesh one took 75 us for the cell
+// starts of 32768 tiles, each in a page of its own.
+constexpr int kListBlock = 512;
+__global__ __launch_bounds__(kListBlock) void list_heavy(const uint32_t *__restrict__ cs, int ntiles,
+                                                         uint32_t *__restrict__ far_count,
+                                                         HeavySlices heavy, bool alone) {
+    __shared__ uint32_t found, base;
+    const int t = (int)blockIdx.x * kListBlock + (int)threadIdx.x;
+    if (threadIdx.x == 0) found = 0u;
+    __syncthreads();
+    const uint32_t cnt = t < ntiles ? cs[(size_t)(t + 1) * kTileCells] - cs[(size_t)t * kTileCells] : 0u;
+    const uint32_t slices = cnt > heavy.limit ? (cnt + kHeavySlice - 1) / kHeavySlice : 0u;
+    const uint32_t at = slices ? atomicAdd(&found, slices) : 0u;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        base = 0u;
+        if (alone) {
+            *heavy.count = found;
+            *far_count = found ? kFarMax + 1u : 0u;
+        } else if (found) {
+            base = atomicAdd(heavy.count, found);
+            atomicMax(far_count, kFarMax + 1u);
+        }
+    }
+    __syncthreads();
+    for (uint32_t k = 0; k < slices; ++k) heavy.list[base + at + k] = make_uint2((uint32_t)t, k);
+}
+
 // pre[t * 28 + d]: first particle of group d (kFarDir: the far ones) relative to the
 // tile's first.
 __global__ __launch_bounds__(kBlock) void local_split(
     const uint16_t *__restrict__ pos, const uint32_t *__restrict__ cs,
     const float *__restrict__ vel, const float *__restrict__ acc, int n, int nt, int n_f,
     double kick, double drift, Moved out, uint32_t *__restrict__ pre, Far far,
-    HeavySlices heavy, uint32_t *__restrict__ status) {
+    uint32_t *__restrict__ status) {
     __shared__ uint32_t cst[kTileCells + 1];
     __shared__ uint32_t cnt[kDirs + 1][kGroups + 1];   // per group of 64 particles, then before it
     __shared__ uint32_t base[kDirs + 1];               // next slot of each direction
@@ -180,16 +217,6 @@ __global__ __launch_bounds__(kBlock) void local_split(
     if (tid <= kDirs) base[tid] = 0u;
     __syncthreads();
     const uint32_t p0 = cst[0], p1 = cst[kTileCells];
-    if (p1 - p0 > kHeavyTile) {        // listed for the radix sort's drift
-        const uint32_t slices = (p1 - p0 + kHeavyTile - 1) / kHeavyTile;
-        if (tid == 0) {
-            base[0] = atomicAdd(heavy.count, slices);
-            atomicAdd(far.count, kFarMax + 1u);
-        }
-        __syncthreads();
-        for (uint32_t k = tid; k < slices; k += kBlock) heavy.list[base[0] + k] = make_uint2(t, k);
-        return;
-    }
     if (far_sh > kFarMax) return;      // the radix sort does it
     const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     bool bad = false;
@@ -529,12 +556,12 @@ int launch_kick_drift(cube2_ctx *ctx, const uint16_t *pos_in, const uint32_t *cs
     const int nt = ctx->nt;
     const int ntiles = nt * nt * nt;
     uint32_t *run = nullptr;
-    HeavySlices heavy{};
+    HeavySlices heavy{nullptr, nullptr, heavy_limit(n64)};
     // Where neither a heavy tile nor, with at most two tiles per axis, a far particle is
     // possible, the radix sort's kernels are not launched: 16^3 mesh, 512 particles 47 us
     // with them, 22 without; so that also with a few particles per tile the local re-sort
     // is the faster there.  One heavy tile is left to the radix sort from the start.
-    const bool heavies = n > (int)kHeavyTile, sure = nt <= 2 && !heavies;
+    const bool heavies = n64 > (int64_t)heavy.limit, sure = nt <= 2 && !heavies;
     if (n > 0 && (sure || (n64 >= kLocalPerTile * (int64_t)ntiles && !(heavies && ntiles == 1)))) {
         // the groups and the tiles' tables take the places of the sort's
         // buffers and of the fine mesh
@@ -552,12 +579,19 @@ int launch_kick_drift(cube2_ctx *ctx, const uint16_t *pos_in, const uint32_t *cs
         far.count = run + 1;
         heavy.count = run + 2;
         far.list = reinterpret_cast<uint2 *>(run + 4);
-        heavy.list = reinterpret_cast<uint2 *>(work + L.keys2);   // at most n / 4096 entries
+        heavy.list = reinterpret_cast<uint2 *>(work + L.keys2);   // at most 3 n / 4096 entries
         const int nblocks = (ntiles + kStartTiles - 1) / kStartTiles;
-        far_clear<<<1, 1, 0, s>>>(far.count, heavy.count);
-        CUBE2_LAUNCH_CHECK();
+        const int lists = heavies ? (ntiles + kListBlock - 1) / kListBlock : 0;
+        if (lists != 1) {
+            far_clear<<<1, 1, 0, s>>>(far.count, heavy.count);
+            CUBE2_LAUNCH_CHECK();
+        }
+        if (lists) {
+            list_heavy<<<(unsigned)lists, kListBlock, 0, s>>>(cs_in, ntiles, far.count, heavy, lists == 1);
+            CUBE2_LAUNCH_CHECK();
+        }
         local_split<<<(unsigned)ntiles, kBlock, 0, s>>>(pos_in, cs_in, vel_in, acc, n, nt, ctx->n_f,
-                                                        kick, drift, m, pre, far, heavy,
+                                                        kick, drift, m, pre, far,
                                                         status_word(ctx));
         CUBE2_LAUNCH_CHECK();
         local_starts<<<(unsigned)nblocks, kStartTiles, 0, s>>>(pre, far, nt, starts, sums, fars);

@@ -293,9 +293,13 @@ __device__ __forceinline__ void put_particle(const ushort4 *__restrict__ offs, i
         }
 }
 
-// Tiles of more than kHeavyTile particles: the entries {tile, chunk} of all their chunks,
-// a tile's in order, and each entry's counts of the cells.  A tile of T has at most 2 T /
-// kHeavyTile chunks, so that n / 4096 entries and n / 8 counts hold any input.
+// Tiles of more than kSortHeavy particles: the entries {tile, chunk} of all their chunks, a
+// tile's in order, and each entry's counts of the cells.  A tile of T has at most 3 T / 4096
+// chunks, so that 3 n / 4096 entries and 3 n / 8 counts hold any input.  (A chunk is the
+// work of one workgroup, 39 us for 8192, but reads the counts of all chunks of its tile:
+// from 65537 on they are larger.)
+constexpr uint32_t kSortHeavy = 4096;
+__device__ __forceinline__ uint32_t heavy_chunk(uint32_t total) { return total <= 65536u ? 2048u : 8192u; }
 struct HeavyTiles {
     uint32_t *count;
     uint2 *list;
@@ -324,8 +328,8 @@ __global__ __launch_bounds__(kBlock) void tile_sort_kernel(
         const uint32_t start = tstart[t], total = tstart[t + 1] - start;
         auto cell_of = [&](uint32_t e) -> uint32_t { return keys[start + e] % kTileCells; };
         auto put = [&](uint32_t p, uint32_t i) { put_particle(offs, n, pos, perm, vel, acc, kick, vout, p, i); };
-        if (heavy.count && total > kHeavyTile) {
-            const uint32_t chunks = (total + kHeavyTile - 1) / kHeavyTile;
+        if (heavy.count && total > kSortHeavy) {
+            const uint32_t per = heavy_chunk(total), chunks = (total + per - 1) / per;
             if (threadIdx.x == 0) at_sh = atomicAdd(heavy.count, chunks);
             __syncthreads();
             for (uint32_t k = threadIdx.x; k < chunks; k += kBlock) heavy.list[at_sh + k] = make_uint2((uint32_t)t, k);
@@ -350,8 +354,8 @@ __global__ __launch_bounds__(kBlock) void tile_sort_kernel(
 // The chunks of the heavy tiles: each chunk's counts of the cells; then each chunk to its
 // place, which the counts of the tile's chunks before it and of its cells before give.
 // (131072 of 2.1 million particles in one tile: one workgroup per tile 890 us, with the
-// chunks 165; the radix sort of the whole key 209.  Where there is none the two launches
-// cost 5 to 10 us.)
+// chunks 165; the radix sort of the whole key 209.  8682 of 133 thousand: 83 in chunks of
+// 8192, 55 of 2048, whole key 67.  Where there is none the two launches cost 5 to 10 us.)
 __global__ __launch_bounds__(kBlock) void heavy_count_kernel(const uint32_t *__restrict__ keys,
                                                              const uint32_t *__restrict__ tstart,
                                                              HeavyTiles heavy,
@@ -361,7 +365,8 @@ __global__ __launch_bounds__(kBlock) void heavy_count_kernel(const uint32_t *__r
     const uint32_t entries = *heavy.count;
     for (uint32_t i = blockIdx.x; i < entries; i += gridDim.x) {
         const uint2 c = heavy.list[i];
-        const uint32_t e0 = tstart[c.x] + c.y * kHeavyTile, e1 = min(e0 + kHeavyTile, tstart[c.x + 1]);
+        const uint32_t start = tstart[c.x], end = tstart[c.x + 1], per = heavy_chunk(end - start);
+        const uint32_t e0 = start + c.y * per, e1 = min(e0 + per, end);
         for (int k = threadIdx.x; k < kTileCells; k += kBlock) h[k] = 0u;
         __syncthreads();
 #pragma unroll 8
@@ -387,8 +392,8 @@ __global__ __launch_bounds__(kBlock) void heavy_sort_kernel(
     for (uint32_t i = blockIdx.x; i < entries; i += gridDim.x) {
         const uint2 c = heavy.list[i];
         const uint32_t start = tstart[c.x], total = tstart[c.x + 1] - start;
-        const uint32_t chunks = (total + kHeavyTile - 1) / kHeavyTile, e0 = c.y * kHeavyTile,
-                       cnt = min(kHeavyTile, total - e0);
+        const uint32_t per = heavy_chunk(total), chunks = (total + per - 1) / per, e0 = c.y * per,
+                       cnt = min(per, total - e0);
         // thread tid: cells 2 tid, 2 tid + 1
         uint2 all = make_uint2(0u, 0u), before = all;
         const uint2 *h = reinterpret_cast<const uint2 *>(heavy.hist + (size_t)(i - c.y) * kTileCells) + tid;
@@ -963,7 +968,7 @@ int launch_sort_by_cell(cube2_ctx *ctx, int64_t n64, uint16_t *pos, uint32_t *ce
         uint32_t *tstart = reinterpret_cast<uint32_t *>(work + L.tile_order);
         // (in the buffers that the sorted keys and values are not in)
         HeavyTiles heavy{};
-        if (n > (int)kHeavyTile) {
+        if (n > (int)kSortHeavy) {
             heavy.count = tmp;
             heavy.list = reinterpret_cast<uint2 *>(v1);
             heavy.hist = k1;
@@ -976,7 +981,7 @@ int launch_sort_by_cell(cube2_ctx *ctx, int64_t n64, uint16_t *pos, uint32_t *ce
                                                                  vel_out, heavy, run);
         CUBE2_LAUNCH_CHECK();
         if (heavy.count) {
-            const unsigned blocks = (unsigned)std::min(2048, n / 4096);
+            const unsigned blocks = (unsigned)std::min(2048, n / 2048);
             heavy_count_kernel<<<blocks, kBlock, 0, s>>>(k0, tstart, heavy, run);
             CUBE2_LAUNCH_CHECK();
             heavy_sort_kernel<<<blocks, kBlock, 0, s>>>(k0, v0, tstart, offs, n, pos, cell_start, perm, vel,
