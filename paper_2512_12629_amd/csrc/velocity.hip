@@ -167,25 +167,25 @@ __device__ __forceinline__ float vel_step(unsigned int dmax_bits) {
 // writes vq_out and v_scale_out) or v = v_bulk + s q (decode: reads vq_in and
 // v_scale, writes vel_out).  The tile's bulk velocities are staged, but from few particles
 // (kStagedPerTile) read where they are: at ratio 2 they are 6 kB a tile.  Decode, us, staged
-// and not: 512^3 mesh, ratio 2, 13 per tile 54 and 27, 109 82 and 40, 512 133 and 146; ratio 4,
-// 13 per tile 29 and 27.
+// and not: 512^3 mesh, ratio 2, 13 per tile 54 and 24, 109 82 and 40, 512 133 and 146; ratio 4,
+// 13 per tile 29 and 24.
 constexpr int64_t kStagedPerTile = 128;
-template <bool ENCODE>
+template <bool ENCODE, bool STAGED>
 __global__ __launch_bounds__(kBlock) void vel_code_kernel(
     const uint32_t *__restrict__ cs, int n, int nt, int shift, int nb,
     const float *__restrict__ v_bulk, const unsigned int *__restrict__ amax,
     const float *__restrict__ vel_in, int16_t *__restrict__ vq_out, float *__restrict__ v_scale_out,
     const float *__restrict__ v_scale, const int16_t *__restrict__ vq_in,
-    float *__restrict__ vel_out, bool staged) {
+    float *__restrict__ vel_out) {
     __shared__ uint32_t cst[kTileCells + 1];
-    __shared__ float vb[3][kTileCells];
+    __shared__ float vb[3][STAGED ? kTileCells : 1];
     int tx, ty, tz;
     tile_of_block(blockIdx.x, nt, tx, ty, tz);
     const int tid = threadIdx.x;
     const int ct = kTileFine >> shift;
     const uint32_t key0 = (uint32_t)((tz * nt + ty) * nt + tx) * kTileCells;
     const int64_t m3 = (int64_t)nb * nb * nb;
-    if (staged)
+    if constexpr (STAGED)
         for (int i = tid; i < ct * ct * ct; i += kBlock) {
             const int64_t g = bulk_index(tx, ty, tz, i, ct, nb);
 #pragma unroll
@@ -211,10 +211,10 @@ __global__ __launch_bounds__(kBlock) void vel_code_kernel(
             const uint32_t p = c0 + k * kBlock;
             if (p >= p1) continue;
             const int lc = bulk_cell(seg_search_n<kTileCells>(cst, p), shift, ct);
-            const int64_t g = bulk_index(tx, ty, tz, lc, ct, nb);
+            const int64_t g = STAGED ? 0 : bulk_index(tx, ty, tz, lc, ct, nb);
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
-                const float b = staged ? vb[d][lc] : v_bulk[d * m3 + g];
+                const float b = STAGED ? vb[d][lc] : v_bulk[d * m3 + g];
                 if (ENCODE) {
                     const float r = rintf(__fdiv_rn(__fsub_rn(v[k][d], b), s));
                     vq_out[(int64_t)d * n + p] = (int16_t)fminf(fmaxf(r, -32767.0f), 32767.0f);
@@ -289,9 +289,10 @@ int launch_vel_encode(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, i
     const int r = launch_absmax(tmax, (int64_t)blocks, amax + 1, s);
     if (r) return r;
     (void)pos;
-    vel_code_kernel<true><<<blocks, kBlock, 0, s>>>(cs, (int)n, nt, shift, nb, v_bulk, amax,
-                                                    vel, vq, v_scale, nullptr, nullptr, nullptr,
-                                                    n >= kStagedPerTile * (int64_t)blocks);
+    auto *code = n >= kStagedPerTile * (int64_t)blocks ? vel_code_kernel<true, true>
+                                                       : vel_code_kernel<true, false>;
+    code<<<blocks, kBlock, 0, s>>>(cs, (int)n, nt, shift, nb, v_bulk, amax, vel, vq, v_scale, nullptr,
+                                   nullptr, nullptr);
     CUBE2_LAUNCH_CHECK();
     return CUBE2_OK;
 }
@@ -304,9 +305,10 @@ int launch_vel_decode(cube2_ctx *ctx, const uint16_t *pos, const uint32_t *cs, i
     const unsigned blocks = (unsigned)(nt * nt * nt);
     const int shift = bulk_shift(ctx), nb = ctx->n_f >> shift;
     (void)pos;
-    vel_code_kernel<false><<<blocks, kBlock, 0, s>>>(cs, (int)n, nt, shift, nb, v_bulk, nullptr,
-                                                     nullptr, nullptr, nullptr, v_scale, vq, vel,
-                                                     n >= kStagedPerTile * (int64_t)blocks);
+    auto *code = n >= kStagedPerTile * (int64_t)blocks ? vel_code_kernel<false, true>
+                                                       : vel_code_kernel<false, false>;
+    code<<<blocks, kBlock, 0, s>>>(cs, (int)n, nt, shift, nb, v_bulk, nullptr, nullptr, nullptr, nullptr,
+                                   v_scale, vq, vel);
     CUBE2_LAUNCH_CHECK();
     return CUBE2_OK;
 }
