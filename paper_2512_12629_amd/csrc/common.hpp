@@ -255,6 +255,10 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *s
     return off + x - v;
 }
 
+// A tile of more particles than this, of n in all, is more than one workgroup's in the
+// sorts and in the drift: one workgroup is the longer the fewer there are in all.
+inline uint32_t heavy_limit(int64_t n) { return n > (1 << 20) ? 8192u : 4096u; }
+
 // Stable sort by cell of one tile's `total` elements, the first of which comes to
 // particle `start` (all kBlock threads call it): each wave takes a contiguous part of
 // them; the cells' counts per wave give the starts of the cells (written to

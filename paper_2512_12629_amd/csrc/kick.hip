@@ -46,11 +46,10 @@ __device__ __forceinline__ void drifted(const uint16_t *__restrict__ pos, const 
 
 // Tiles of more than `limit` particles, with which a step is the radix sort's: the entries
 // {tile, slice} of all their slices of kHeavySlice.  One workgroup of the local re-sort
-// takes ~15 ns a particle, the radix sort in its place ~15 ns per thousand of all: a limit
-// of 4096 up to a million particles, 8192 above.  us, local and radix: 133 thousand, one tile
-// of 7026 109 and 79; 8.5 million, one of 8063 372 and 484 (sorts of the whole key 98, 486).
+// takes ~15 ns a particle, the radix sort in its place ~15 ns per thousand of all
+// (heavy_limit).  us, local and radix: 133 thousand, one tile of 7026 109 and 79; 8.5 million,
+// one of 8063 372 and 484 (sorts of the whole key 98, 486).
 constexpr uint32_t kHeavySlice = 2048;
-uint32_t heavy_limit(int64_t n) { return n > (1 << 20) ? 8192u : 4096u; }
 struct HeavySlices {
     uint32_t *count;
     uint2 *list;

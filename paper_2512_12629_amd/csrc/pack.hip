@@ -293,17 +293,17 @@ __device__ __forceinline__ void put_particle(const ushort4 *__restrict__ offs, i
         }
 }
 
-// Tiles of more than kSortHeavy particles: the entries {tile, chunk} of all their chunks, a
+// Tiles of more than `limit` particles: the entries {tile, chunk} of all their chunks, a
 // tile's in order, and each entry's counts of the cells.  A tile of T has at most 3 T / 4096
 // chunks, so that 3 n / 4096 entries and 3 n / 8 counts hold any input.  (A chunk is the
 // work of one workgroup, 39 us for 8192, but reads the counts of all chunks of its tile:
 // from 65537 on they are larger.)
-constexpr uint32_t kSortHeavy = 4096;
 __device__ __forceinline__ uint32_t heavy_chunk(uint32_t total) { return total <= 65536u ? 2048u : 8192u; }
 struct HeavyTiles {
     uint32_t *count;
     uint2 *list;
     uint32_t *hist;
+    uint32_t limit;      // heavy_limit, at least 4096
 };
 
 // The particles of each tile (keys and vals sorted by tile) sorted by cell, with
@@ -328,7 +328,7 @@ __global__ __launch_bounds__(kBlock) void tile_sort_kernel(
         const uint32_t start = tstart[t], total = tstart[t + 1] - start;
         auto cell_of = [&](uint32_t e) -> uint32_t { return keys[start + e] % kTileCells; };
         auto put = [&](uint32_t p, uint32_t i) { put_particle(offs, n, pos, perm, vel, acc, kick, vout, p, i); };
-        if (heavy.count && total > kSortHeavy) {
+        if (heavy.count && total > heavy.limit) {
             const uint32_t per = heavy_chunk(total), chunks = (total + per - 1) / per;
             if (threadIdx.x == 0) at_sh = atomicAdd(heavy.count, chunks);
             __syncthreads();
@@ -355,7 +355,8 @@ __global__ __launch_bounds__(kBlock) void tile_sort_kernel(
 // place, which the counts of the tile's chunks before it and of its cells before give.
 // (131072 of 2.1 million particles in one tile: one workgroup per tile 890 us, with the
 // chunks 165; the radix sort of the whole key 209.  8682 of 133 thousand: 83 in chunks of
-// 8192, 55 of 2048, whole key 67.  Where there is none the two launches cost 5 to 10 us.)
+// 8192, 55 of 2048, whole key 67.  27 million with 1000 halos, tiles from 4097 on: 813, from
+// 8193 on 797.  Where there is none the two launches cost 5 to 10 us.)
 __global__ __launch_bounds__(kBlock) void heavy_count_kernel(const uint32_t *__restrict__ keys,
                                                              const uint32_t *__restrict__ tstart,
                                                              HeavyTiles heavy,
@@ -967,8 +968,8 @@ int launch_sort_by_cell(cube2_ctx *ctx, int64_t n64, uint16_t *pos, uint32_t *ce
         const int ntiles = ctx->nt * ctx->nt * ctx->nt;
         uint32_t *tstart = reinterpret_cast<uint32_t *>(work + L.tile_order);
         // (in the buffers that the sorted keys and values are not in)
-        HeavyTiles heavy{};
-        if (n > (int)kSortHeavy) {
+        HeavyTiles heavy{nullptr, nullptr, nullptr, heavy_limit(n)};
+        if (n > (int)heavy.limit) {
             heavy.count = tmp;
             heavy.list = reinterpret_cast<uint2 *>(v1);
             heavy.hist = k1;
