@@ -1,7 +1,8 @@
 // fp64.hip -- the piece of the FP64 plain form that has no FP32 twin: the PP force
 // (eq. 4d) in FP64, one thread per particle looping over its neighbour IOS cells
 // (27, or 125 for b_f > 2), with the pair law of eq. (2) evaluated from the exact
-// piecewise-polynomial table in FP64.
+// piecewise-polynomial table in FP64.  One workgroup per tile, one wave where
+// tiles hold few particles.
 // It favours plainness over speed: it is the yardstick the FP32 path is
 // compared against at sizes the host oracle cannot reach.
 #include "common.hpp"

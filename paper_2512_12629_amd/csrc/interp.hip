@@ -5,7 +5,8 @@
 // One workgroup per tile (8^3 IOS cells = 16^3 fine cells).  It stages in LDS
 // the fine potential on the tile plus a halo (2 nodes for the stencil below,
 // 3 above: the CIC upper node plus the stencil), and the coarse level's force on
-// the tile's coarse footprint (stage_coarse_field).  Each particle then reads
+// the tile's coarse footprint (stage_coarse_field; at ratio 2 with few particles per
+// tile the coarse potential, like the fine one).  Each particle then reads
 // the 6 potential values along each axis around its 2x2 CIC footprint and
 // forms E = -[(2/3)(phi(+1) - phi(-1)) - (1/12)(phi(+2) - phi(-2))] at its two
 // nodes per axis, weighted with the deposit's 15-bit integer weights.

@@ -10,8 +10,8 @@
 // staged in LDS in digit order and written out in runs.  It sorts by the tile
 // only (two passes of up to 9 bits); one workgroup per tile then sorts the
 // tile's particles by cell in LDS, which also gives cell_start, and gathers
-// them; a tile of very many is left to several workgroups, by chunks.  With few particles per tile it sorts by the whole key instead and
-// reads cell_start off the sorted keys.  Ties keep their input order, so the
+// them; a tile of very many is left to several workgroups, by chunks.  One tile alone
+// is sorted by the whole key and cell_start read off the sorted keys.  Ties keep their input order, so the
 // result equals a stable argsort.  No global atomics.
 #include <algorithm>
 
