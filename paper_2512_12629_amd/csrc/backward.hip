@@ -560,7 +560,7 @@ __global__ __launch_bounds__(BLOCK) void xbar_gather_kernel(
             const uint32_t o = pos[(int64_t)d * n + p];
             jf[d] = axis_footprint<P>(2 * uc[d] + (int)(o >> 15), (int)(o & 0x7FFFu), wf[d], dwf[d]);
             ab[d] = WITH_E ? abar[(int64_t)d * n + p] : 0.0f;
-            eb[d] = extra ? extra[(int64_t)d * n + p] : 0.0f;
+            eb[d] = WITH_E && extra ? extra[(int64_t)d * n + p] : 0.0f;
             if (TWO) {
                 const uint32_t q = ((uint32_t)uc[d] << 16) + o;
                 jc[d] = axis_footprint<P>((int)(q >> (kFracBits + hshift)), (int)((q >> hshift) & 0x7FFFu),
@@ -578,7 +578,7 @@ __global__ __launch_bounds__(BLOCK) void xbar_gather_kernel(
         for (int d = 0; d < 3; ++d) {
             float *dst = xbar + (int64_t)d * n + p;
             const float v = accumulate ? *dst + xb[d] : xb[d];
-            *dst = extra ? v + eb[d] : v;
+            *dst = WITH_E && extra ? v + eb[d] : v;
         }
     }
 }
